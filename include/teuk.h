@@ -209,17 +209,20 @@ double teuk_get_dt(const teuk_grid* g);
 int teuk_set_tile(teuk_grid* g, int32_t rows_per_tile, int32_t waves_per_block);
 int teuk_get_tile(const teuk_grid* g, int32_t* rows_per_tile, int32_t* waves_per_block);
 
-/* Steps per pass over the state: 1 or 2 (default).  With 2, teuk_step_n
- * advances pairs of steps in one kernel pass (temporal blocking: the
- * intermediate state stays in registers, halving the state traffic per
- * step) and an odd last step alone; the per-point arithmetic is that of
- * single steps, so results are identical.  teuk_step_n_store keeps the
- * intermediate state of a pass in its window slot; its first step runs
- * alone (it also copies its input).  Runs whose extraction points share a
- * tile of the two-step kernel run one step per pass.  The tile rows of
- * teuk_set_tile apply; at most 4 wavefronts per workgroup are used.  Where
- * the small-grid block pass is on (teuk_set_block_launch), teuk_step_n takes
- * it instead of these passes.  TEUK_E_INVALID_ARG for other values. */
+/* Steps per pass over the state: 1, or 2 (default) for several.  With 2,
+ * teuk_step_n takes three steps in one kernel pass, and two at a call's end,
+ * with user coefficients, a source term, fewer than three rows or the in-loop
+ * finite check (temporal blocking: the intermediate states stay in registers,
+ * so the state is read and written once per pass), and an odd last step
+ * alone; the per-point arithmetic is that of single steps, so results are
+ * identical.  teuk_step_n_store takes two and keeps the intermediate state of
+ * a pass in its window slot; its first step runs alone (it also copies its
+ * input).  A pass whose extraction points share one of its tiles is not taken.
+ * The tile rows of teuk_set_tile apply (until it is called, the three-step
+ * pass takes a height of its own); at most 4 wavefronts per workgroup are
+ * used.  Where the small-grid block pass is on (teuk_set_block_launch),
+ * teuk_step_n takes it instead of these passes.  TEUK_E_INVALID_ARG for other
+ * values. */
 int teuk_set_steps_per_pass(teuk_grid* g, int32_t steps_per_pass);
 int teuk_get_steps_per_pass(const teuk_grid* g, int32_t* steps_per_pass);
 

@@ -753,214 +753,15 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))
 // One Lax-Wendroff step, u^{m+1} = A u^m, that also writes the derivative of
 // the step with respect to the spin at fixed input, T_m = (dA/da) u^m: the
 // spin gradient is then dL/da = sum_m Re <lambda^{m+1}, T_m>, a dot product
-// the reverse sweep forms from the cotangents it computes anyway.  With
-// stage 1 h = ubar - dt/2 [D delta/dr - S(ubar)] at the halves and stage 2
-// u' = u - dt [D dh/dr - S(hbar)],
-//   dh = -dt/2 [D' delta/dr - S'(ubar)]                       (halves)
-//   T  = -dt [D' dh/dr + D d(dh)/dr - S'(hbar) - S(d(h)bar)]   (columns)
-// with D', S' the operators of the a-derivatives of the coefficients (the
-// Phi row of S' vanishes) and T = 0 on the radial boundary columns.  The
-// sweep is that of the one-step forward kernel (64-column strips numbered
-// strip-fastest, theta rows in order, the same expressions, so u^{m+1} equals
-// its result bit for bit); each lane holds the radial factors of its column
-// and half point in registers for the whole tile and their a-derivatives in
-// its own part of the wavefront's LDS slice (written and read by the same
-// lane: no barrier).
-
-struct TanRow {
-    cd p, q;      // u^m at (i, t)
-    cd ubp;       // stage-1 average of Phi at the half point i+1/2
-    cd hbp, dhp;  // mean and difference of stage-1 Phi at i-1/2, i+1/2
-    cd x;         // stage-1 Pi at i+1/2 except its row-(t+1) term: h_Pi = x + wp ubp(t+1)
-    double wp;
-    cd tbp, tdp;  // the same mean and difference of the a-derivative of stage-1 Phi
-    cd tx;        // a-derivative of x
-    double twp;   // a-derivative of wp
-    Ang g;        // angular factors of row t (wavefront-uniform)
-};
-
+// the reverse sweep forms from the cotangents it computes anyway.
 template <int KEEP>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8)))
     lw_tangent_kernel(const double2* __restrict__ u_in, double2* __restrict__ u_out, double2* __restrict__ t_out,
                       const double* __restrict__ rad, const double* __restrict__ rad_da,
                       const double* __restrict__ ang, AdjScalars A) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wpb = blockDim.x / kWave;
-    const int tile = __builtin_amdgcn_readfirstlane(blockIdx.x * wpb + (threadIdx.x / kWave));
-    const int strip = tile % A.n_strips;
-    const int chunk = tile / A.n_strips;
-    if (chunk >= A.n_chunks) return;  // tiles beyond the last
-    const int nr = A.nr, nth = A.nth, P = A.pitch;
-    const int col = strip * kStripCols - 1 + lane;
-    // Lanes outside the grid read the clamped edge column; their values
-    // reach only the radial boundary columns of both outputs, which are zero.
-    const int ci = min(max(col, 0), nr - 1);
-    const int hi = min(max(col, 0), nr - 2);
-    // radial factors of this lane's column and half point; their
-    // a-derivatives go to the wavefront's LDS slice [integer/half][field][lane]
-    const Rad Vi = load_rad(rad, P, 0, ci), Vh = load_rad(rad, P, 1, hi);
     extern __shared__ double rad_s[];
-    double* ds = rad_s + (threadIdx.x / kWave) * 2 * kNumRad * kWave + lane;
-#pragma unroll
-    for (int f = 0; f < kNumRad; ++f) {
-        ds[f * kWave] = rad_da[((size_t)f * 2 + 0) * P + ci];
-        ds[(kNumRad + f) * kWave] = rad_da[((size_t)f * 2 + 1) * P + hi];
-    }
-    lds_cptr rdi = (lds_cptr)ds, rdh = (lds_cptr)(ds + kNumRad * kWave);
-
-    const bool store_ok = (lane >= 1) && (lane <= kWave - 2) && (col < nr);
-    const bool boundary = (col == 0) || (col == nr - 1);
-    const int j0 = chunk * A.rows;
-    const int j1 = min(j0 + A.rows, nth);
-    const double sg = (double)A.sigma;
-    const int last = (j1 < nth) ? j1 : nth - 1;  // last row this tile reads
-
-    auto ang_row = [&](int t) -> Ang { return load_ang(ang, nth, min(t, nth - 1)); };
-
-    // Arrival of row t: stage-1 pieces (the forward kernel's expressions)
-    // and their a-derivatives.  A halo row needs only ubp, hbp and tbp.
-    auto fresh = [&](int t, cd p, cd q, cd ubp_prev, const Ang& G) -> TanRow {
-        TanRow R;
-        R.p = p;
-        R.q = q;
-        R.g = G;
-        const Sig sh = kerr_sigma(Vh, G);
-        const Coef kh = kerr_coef(Vh, G, sh);
-        const Coef dkh = kerr_coef_da_reg(Vh, rad_from_lds(rdh, t & A.zero), G, sh, kh);
-        const cd pr = from_right(p), qr = from_right(q);
-        R.ubp = cavg(p, pr);
-        const cd ubq = cavg(q, qr);
-        const cd dp = csub(pr, p);
-        const double tb = A.hdt_dr * kh.b;
-        const cd hp = {fma(-tb, dp.re, fma(A.hdt, ubq.re, R.ubp.re)), fma(-tb, dp.im, fma(A.hdt, ubq.im, R.ubp.im))};
-        const cd hpl = from_left(hp);
-        R.hbp = cavg(hp, hpl);
-        R.dhp = csub(hp, hpl);
-        // d/da h_Phi = -dt/2 db delta_Phi / dr
-        const double ttb = A.hdt_dr * dkh.b;
-        const cd thp = {-ttb * dp.re, -ttb * dp.im};
-        const cd thpl = from_left(thp);
-        R.tbp = cavg(thp, thpl);
-        R.tdp = csub(thp, thpl);
-        const cd dq = csub(qr, q);
-        const cd um = (t == 0) ? cscale(sg, R.ubp) : ubp_prev;
-        const cd dq1 = d_pi(kh, dp, dq);
-        const cd s1 = s_pi(kh, um, R.ubp, cd{0.0, 0.0}, ubq);
-        R.x = {fma(A.hdt, s1.re, fma(-A.hdt_dr, dq1.re, ubq.re)), fma(A.hdt, s1.im, fma(-A.hdt_dr, dq1.im, ubq.im))};
-        R.wp = A.hdt * (kh.a2s + kh.a1s);
-        // d/da h_Pi = -dt/2 [ (dc delta_Phi - db delta_Pi)/dr - S'(ubar) ]
-        const cd tq1 = d_pi(dkh, dp, dq);
-        const cd ts1 = s_pi(dkh, um, R.ubp, cd{0.0, 0.0}, ubq);
-        R.tx = {fma(A.hdt, ts1.re, -A.hdt_dr * tq1.re), fma(A.hdt, ts1.im, -A.hdt_dr * tq1.im)};
-        R.twp = A.hdt * (dkh.a2s + dkh.a1s);
-        return R;
-    };
-
-    // ---- prologue: rows j0-1 (halo or ghost) and j0 ---------------------
-    cd hbp_m, tbp_m;  // hbar_Phi and its a-derivative at row t-1
-    TanRow cur;
-    {
-        cd ubp_prev = {0.0, 0.0};
-        if (j0 > 0) {
-            const size_t o = (size_t)(j0 - 1) * P + ci;
-            const TanRow rm = fresh(j0 - 1, ld(u_in, o), ld(u_in, o + A.plane), ubp_prev, ang_row(j0 - 1));
-            ubp_prev = rm.ubp;
-            hbp_m = rm.hbp;
-            tbp_m = rm.tbp;
-        }
-        const size_t o = (size_t)j0 * P + ci;
-        cur = fresh(j0, ld(u_in, o), ld(u_in, o + A.plane), ubp_prev, ang_row(j0));
-        if (j0 == 0) {
-            hbp_m = cscale(sg, cur.hbp);
-            tbp_m = cscale(sg, cur.tbp);
-        }
-    }
-    Ang g_next = ang_row(j0 + 1);  // angular factors one row ahead
-    cd bp[2], bq[2];               // rows j0+1, j0+2 in flight
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const size_t o = (size_t)min(j0 + 1 + k, last) * P + ci;
-        bp[k] = ld(u_in, o);
-        bq[k] = ld(u_in, o + A.plane);
-    }
-
-    // Row t is in cur; row t+1 arrives into nxt (roles alternate from row to
-    // row, so no row state is copied); rp, rq: ring slot of row t+1, refilled
-    // with row t+3.
-    auto finish_row = [&](int t, TanRow& cur, TanRow& nxt, cd& rp, cd& rq) {
-        cd ubp_p, hbp_p, tbp_p;
-        const Ang g1 = g_next;
-        g_next = ang_row(t + 2);
-        if (t + 1 < nth) {
-            nxt = fresh(t + 1, rp, rq, cur.ubp, g1);
-            ubp_p = nxt.ubp;
-            hbp_p = nxt.hbp;
-            tbp_p = nxt.tbp;
-        } else {  // pole ghost row
-            ubp_p = cscale(sg, cur.ubp);
-            hbp_p = cscale(sg, cur.hbp);
-            tbp_p = cscale(sg, cur.tbp);
-            nxt = cur;  // unused: the sweep ends with this row
-        }
-        {
-            const size_t o = (size_t)min(t + 3, last) * P + ci;
-            rp = ld(u_in, o);
-            rq = ld(u_in, o + A.plane);
-        }
-        const Sig si = kerr_sigma(Vi, cur.g);
-        const Coef ki = kerr_coef(Vi, cur.g, si);
-        const Coef dki = kerr_coef_da_reg(Vi, rad_from_lds(rdi, t & A.zero), cur.g, si, ki);
-
-        // stage 1, Pi component at the halves, and its a-derivative
-        const cd hq = {fma(cur.wp, ubp_p.re, cur.x.re), fma(cur.wp, ubp_p.im, cur.x.im)};
-        const cd hql = from_left(hq);
-        const cd hbq = cavg(hq, hql);
-        const cd dhq = csub(hq, hql);
-        const cd thq = {fma(cur.twp, ubp_p.re, cur.tx.re), fma(cur.twp, ubp_p.im, cur.tx.im)};
-        const cd thql = from_left(thq);
-        const cd tbq = cavg(thq, thql);
-        const cd tdq = csub(thq, thql);
-
-        // stage 2 (the forward kernel's expressions)
-        const double tb = A.dt_dr * ki.b;
-        cd np = {fma(-tb, cur.dhp.re, fma(A.dt, hbq.re, cur.p.re)), fma(-tb, cur.dhp.im, fma(A.dt, hbq.im, cur.p.im))};
-        const cd dq2 = d_pi(ki, cur.dhp, dhq);
-        const cd s2 = s_pi(ki, hbp_m, cur.hbp, hbp_p, hbq);
-        cd nq = {fma(A.dt, s2.re, fma(-A.dt_dr, dq2.re, cur.q.re)), fma(A.dt, s2.im, fma(-A.dt_dr, dq2.im, cur.q.im))};
-        // T_Phi = -dt/dr (db dh_Phi + b d(dh)_Phi) + dt d(h)bar_Pi
-        cd tp = {fma(-A.dt_dr, fma(dki.b, cur.dhp.re, ki.b * cur.tdp.re), A.dt * tbq.re),
-                 fma(-A.dt_dr, fma(dki.b, cur.dhp.im, ki.b * cur.tdp.im), A.dt * tbq.im)};
-        // T_Pi = -dt/dr [D'(dh) + D(d(dh))]_Pi + dt [S'(hbar) + S(d(h)bar)]
-        const cd e1 = d_pi(dki, cur.dhp, dhq), e2 = d_pi(ki, cur.tdp, tdq);
-        const cd f1 = s_pi(dki, hbp_m, cur.hbp, hbp_p, hbq), f2 = s_pi(ki, tbp_m, cur.tbp, tbp_p, tbq);
-        cd tq = {fma(A.dt, f1.re + f2.re, -A.dt_dr * (e1.re + e2.re)),
-                 fma(A.dt, f1.im + f2.im, -A.dt_dr * (e1.im + e2.im))};
-        if (boundary) {
-            np = {0.0, 0.0};
-            nq = {0.0, 0.0};
-            tp = {0.0, 0.0};
-            tq = {0.0, 0.0};
-        }
-        if (store_ok) {
-            const size_t so = (size_t)t * P + col;
-            st_state<KEEP>(u_out, so, np);
-            st_state<KEEP>(u_out, so + A.plane, nq);
-            st(t_out, so, tp);
-            st(t_out, so + A.plane, tq);
-        }
-        hbp_m = cur.hbp;
-        tbp_m = cur.tbp;
-    };
-
-    TanRow other;
-    int t0 = j0;
-    for (; t0 + 2 <= j1; t0 += 2) {
-        finish_row(t0, cur, other, bp[0], bq[0]);
-        finish_row(t0 + 1, other, cur, bp[1], bq[1]);
-    }
-    if (t0 < j1) finish_row(t0, cur, other, bp[0], bq[0]);
+    tangent_tile<false, KEEP>(u_in, nullptr, u_out, t_out, rad, rad_da, ang, nullptr, nullptr, nullptr, A, rad_s);
 }
-
 
 // lam_Phi += E^T g for every extraction point, in point order (one thread).
 __global__ void extract_adjoint_kernel(double2* __restrict__ lam, int pitch, const ExtPoint* __restrict__ pts, int n,
@@ -1046,14 +847,13 @@ hipError_t launch_adjoint2(const AdjArgs& a, const double* gsample_b, const doub
 
 hipError_t launch_tangent(const double2* u_in, double2* u_out, double2* t_out, const AdjArgs& a, int waves_per_block,
                           hipStream_t s) {
-    const int64_t tiles = (int64_t)a.k.n_strips * a.k.n_chunks;
-    const dim3 block(kWave * waves_per_block), grid((unsigned)((tiles + waves_per_block - 1) / waves_per_block));
-    const size_t lds = (size_t)waves_per_block * 2 * kNumRad * kWave * sizeof(double);
+    dim3 grid, block;
+    size_t lds;
+    adjoint_launch_shape(a.k, waves_per_block, 4 * kNumSRad, &grid, &block, &lds, kTanSlots * sizeof(double2));
     hipLaunchKernelGGL(a.k.keep ? lw_tangent_kernel<1> : lw_tangent_kernel<0>, grid, block, lds, s, u_in, u_out, t_out,
-                       a.rad, a.rad_da, a.ang, a.k);
+                       a.srad, a.srad_da, a.ang, a.k);
     return hipGetLastError();
 }
-
 
 hipError_t launch_extract_adjoint(double2* lam, int pitch, const ExtPoint* pts, int n, const double2* g,
                                   hipStream_t s) {

@@ -22,17 +22,6 @@ __device__ __forceinline__ cd cavg(cd a, cd b) { return {0.5 * (a.re + b.re), 0.
 // as two 32-bit DPP wavefront shifts (wave_shl:1 / wave_shr:1).  The edge
 // lanes (63 and 0) receive 0; their results are never stored.
 constexpr int kDppWaveShl1 = 0x130;
-// Rows of input loaded ahead of the row being finished, and the minimum
-// wavefronts per SIMD the register allocation must allow (build-time tuning).
-#ifndef TEUK_ROWS_IN_FLIGHT
-#define TEUK_ROWS_IN_FLIGHT 3
-#endif
-#ifndef TEUK_WAVES_PER_SIMD
-#define TEUK_WAVES_PER_SIMD 2
-#endif
-constexpr int kRowsInFlight = TEUK_ROWS_IN_FLIGHT;
-// The same for the two-step pass, whose row loop takes rows in pairs.
-constexpr int kRowsInFlight2 = 2;
 constexpr int kDppWaveShr1 = 0x138;
 
 // bound_ctrl: a lane whose source lane does not exist reads 0, so the
@@ -178,22 +167,6 @@ __device__ __forceinline__ Coef kerr_coef(const Rad& R, const Ang& G, Sig s) {
     return c;
 }
 
-__device__ __forceinline__ Coef user_coef(ctab_t u, int nth, int pitch, int j, int pos, double inv_dth2,
-                                          double inv_2dth) {
-    auto f = [&](int k) { return u[((size_t)k * nth + j) * pitch + pos]; };
-    Coef c;
-    c.b = f(U_B);
-    c.cre = f(U_CRE);
-    c.cim = f(U_CIM);
-    c.ctr = f(U_CTRE);
-    c.cti = f(U_CTIM);
-    c.a2s = f(U_A2) * inv_dth2;
-    c.a1s = f(U_A1) * inv_2dth;
-    c.v0r = f(U_V0RE);
-    c.v0i = f(U_V0IM);
-    return c;
-}
-
 // Pi row of S:  -Ct q + A2 (f_{j+1} - 2 f_j + f_{j-1})/dth^2
 //               + A1 (f_{j+1} - f_{j-1})/(2 dth) - V0 f_j
 __device__ __forceinline__ cd s_pi(const Coef& k, cd fm, cd f0, cd fp, cd q) {
@@ -327,6 +300,155 @@ __device__ __forceinline__ void st_row(__amdgpu_buffer_rsrc_t r, uint32_t off, c
     w.x = v.re;
     w.y = v.im;
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, w), r, off, 0, KEEP ? 0 : 2);
+}
+
+template <int V>
+struct Const {
+    static constexpr int value = V;
+};
+
+// ---- the two stages of a step -------------------------------------------
+//
+// Coefficients of one stage at one (position, row) with the step's factors
+// folded in.  Stage 1 works on sums over the two columns of a half point,
+// stage 2 on sums over the two halves of a column, so no average is halved:
+// with U, V the sums of Phi, Pi, H = 2 h_Phi and HQ = 2 h_Pi,
+//   half points:      b, c by dt/dr;   ct, a2, a1, v0 by dt/2
+//   integer columns:  b, c by dt/2dr;  ct, a2, a1, v0 by dt/4
+// wp, wm = a2 +- a1 are the weights of the theta differences to the next and
+// from the previous row, A2 f'' + A1 f' = wp (f_{t+1} - f_t) - wm (f_t - f_{t-1}).
+struct Stage {
+    double b, cr, ci, tr, ti, wm, wp, vr, vi;
+};
+
+struct SRad {
+    double rho2, a2d, b, k0, k1, k2, k3, tr, ti0, ti1, dl2, vr, vi;
+};
+
+template <class F>
+__device__ __forceinline__ SRad srad_of(F f) {
+    SRad R;
+    R.rho2 = f(S_RHO2);
+    R.a2d = f(S_A2D);
+    R.b = f(S_B);
+    R.k0 = f(S_K0);
+    R.k1 = f(S_K1);
+    R.k2 = f(S_K2);
+    R.k3 = f(S_K3);
+    R.tr = f(S_TR);
+    R.ti0 = f(S_TI0);
+    R.ti1 = f(S_TI1);
+    R.dl2 = f(S_DL2);
+    R.vr = f(S_VR);
+    R.vi = f(S_VI);
+    return R;
+}
+
+// 1/Sigma and 1/Sigma^2: the hardware reciprocal square root (about 23
+// correct bits) and one cubic step, y <- y + y e (1/2 + 3/8 e) with e = 1 - x
+// y^2, whose error is 5/16 e^3.
+__device__ __forceinline__ Sig ssigma(const SRad& R, const Ang& G) {
+    const double x = fma(-R.a2d, G.sn2, R.rho2);
+    const double y = __builtin_amdgcn_rsq(x);
+    const double t = x * y;
+    const double e = fma(-t, y, 1.0);
+    const double ye = y * e;
+    const double z = fma(ye, fma(0.375, e, 0.5), y);
+    return {z, z * z};
+}
+
+// kap: 1 over the factor of ct (c has the imaginary part -b ct_i).
+__device__ __forceinline__ Stage stage_coef(const SRad& R, const Ang& G, Sig s, double kap) {
+    Stage k;
+    k.b = R.b * s.isig;
+    k.tr = R.tr * s.inv;
+    k.ti = fma(R.ti1, G.cs, R.ti0) * s.inv;
+    const double c1 = fma(-R.k2, G.sn2, R.k1);
+    const double c0 = fma(-R.k3, s.isig, fma(-c1, s.inv, R.k0));
+    k.cr = c0 * s.inv;
+    const double bt = k.b * k.ti;
+    k.ci = -kap * bt;
+    const double a2 = R.dl2 * s.inv;
+    k.wp = fma(a2, G.cotp, a2);
+    k.wm = fma(-a2, G.cotp, a2);
+    k.vr = fma(R.dl2, G.pd, R.vr) * s.inv;
+    k.vi = R.vi * s.inv;
+    return k;
+}
+
+// sd, st: the factors of (b, c) and of the rest.
+__device__ __forceinline__ Stage user_stage(ctab_t u, int nth, int pitch, int j, int pos, double inv_dth2,
+                                            double inv_2dth, double sd, double st) {
+    auto f = [&](int k) { return u[((size_t)k * nth + j) * pitch + pos]; };
+    Stage k;
+    k.b = f(U_B) * sd;
+    k.cr = f(U_CRE) * sd;
+    k.ci = f(U_CIM) * sd;
+    k.tr = f(U_CTRE) * st;
+    k.ti = f(U_CTIM) * st;
+    const double a2 = f(U_A2) * inv_dth2 * st, a1 = f(U_A1) * inv_2dth * st;
+    k.wp = a2 + a1;
+    k.wm = a2 - a1;
+    k.vr = f(U_V0RE) * st;
+    k.vi = f(U_V0IM) * st;
+    return k;
+}
+
+// H = 2 h_Phi = U + dt/2 V - b dp.
+__device__ __forceinline__ cd stage1_phi(double b, double hdt, cd U, cd V, cd dp) {
+    return {fma(-b, dp.re, fma(hdt, V.re, U.re)), fma(-b, dp.im, fma(hdt, V.im, U.im))};
+}
+
+// The increment of 2 h_Pi over V but for its term of the next row:
+// -c dp + b dq - ct V - v0 U - wm (U_t - U_{t-1}).  Increments are summed on
+// their own and added to the value once, so that they round at their own size.
+__device__ __forceinline__ cd stage1_inc(const Stage& k, cd U, cd V, cd dp, cd dq, cd dU) {
+    double r = k.b * dq.re, i = k.b * dq.im;
+    r = fma(-k.cr, dp.re, r);
+    i = fma(-k.cr, dp.im, i);
+    r = fma(k.ci, dp.im, r);
+    i = fma(-k.ci, dp.re, i);
+    r = fma(-k.tr, V.re, r);
+    i = fma(-k.tr, V.im, i);
+    r = fma(k.ti, V.im, r);
+    i = fma(-k.ti, V.re, i);
+    r = fma(-k.vr, U.re, r);
+    i = fma(-k.vr, U.im, i);
+    r = fma(k.vi, U.im, r);
+    i = fma(-k.vi, U.re, i);
+    r = fma(-k.wm, dU.re, r);
+    i = fma(-k.wm, dU.im, i);
+    return {r, i};
+}
+
+__device__ __forceinline__ cd fma_real(double w, cd x, cd y) { return {fma(w, x.re, y.re), fma(w, x.im, y.im)}; }
+
+// The part of stage 2's Pi increment known when a row arrives: -c D - v0 S -
+// wm (S_t - S_{t-1}), with S, D the sum and difference of H at the two halves.
+__device__ __forceinline__ cd stage2_early(const Stage& k, cd S, cd D, cd dS) {
+    double r = -k.cr * D.re, i = -k.cr * D.im;
+    r = fma(k.ci, D.im, r);
+    i = fma(-k.ci, D.re, i);
+    r = fma(-k.vr, S.re, r);
+    i = fma(-k.vr, S.im, i);
+    r = fma(k.vi, S.im, r);
+    i = fma(-k.vi, S.re, i);
+    r = fma(-k.wm, dS.re, r);
+    i = fma(-k.wm, dS.im, i);
+    return {r, i};
+}
+
+// The rest, once the next row is there: b DQ - ct SQ + wp (S_{t+1} - S_t),
+// with SQ, DQ the sum and difference of HQ at the two halves.
+__device__ __forceinline__ cd stage2_late(double b, double tr, double ti, double wp, cd SQ, cd DQ, cd dSn) {
+    double r = b * DQ.re, i = b * DQ.im;
+    r = fma(-tr, SQ.re, r);
+    i = fma(-tr, SQ.im, i);
+    r = fma(ti, SQ.im, r);
+    i = fma(-ti, SQ.re, i);
+    r = fma(wp, dSn.re, r);
+    i = fma(wp, dSn.im, i);
+    return {r, i};
 }
 
 // All pointers are distinct allocations (restrict): the uniform reads of

@@ -121,6 +121,32 @@ void radial_fields(T a, int s, int m, T x, double dth, T out[kNumRad]) {
     out[R_V0I] = -T(2.0 * s * m) * a * rm1;
 }
 
+// The radial factors of SRadField at one position; d, t: the stage's factors.
+template <class T>
+void stage_fields(T a, int s, int m, T x, double dth, double d, double t, T out[kNumSRad]) {
+    using std::sqrt;
+    const T q = sqrt(T(1.0) - a * a);
+    const T r = T(1.0) + q + x;
+    const T delta = x * (x + T(2.0) * q);
+    const T rho = r * r + a * a;
+    const T rm1 = r - T(1.0);
+    const T ct = T(2.0 * s) * (r * delta - (r * r - a * a));
+    out[S_RHO2] = rho * rho;
+    out[S_A2D] = a * a * delta;
+    out[S_B] = T(d) * rho;
+    out[S_K0] = -(T(d) * rho * (T(6.0) * delta / r + T(2.0 * s) * rm1));
+    out[S_K1] = T(d) * (T(2.0) * r * rho * rho * delta);
+    out[S_K2] = T(d) * (a * a * rm1 * rho * delta);
+    out[S_K3] = T(d) * (rho * ct);
+    out[S_TR] = T(t) * ct;
+    out[S_TI0] = T(t) * (T(4.0 * m) * a * r);
+    out[S_TI1] = T(t) * (T(2.0 * s) * a * delta);
+    out[S_DL2] = T(t) * (delta / T(dth * dth));
+    out[S_VR] = T(t) * (-T(double(m) * m) * a * a -
+                        T(6.0) * delta * (T(s + 2.0) * r * r - T(s + 3.0) * r + a * a) / (r * r));
+    out[S_VI] = T(t) * (-T(2.0 * s * m) * a * rm1);
+}
+
 // The angular factors of AngField at row j (theta_j = (j + 1/2) dth).
 inline void angular_fields(int s, int m, int j, double dth, double out[kNumAng]) {
     const double th = (j + 0.5) * dth;

@@ -19,6 +19,9 @@ constexpr int kStripCols = kWave - 2;
 // first step's results one column further out on each side, so lanes 2..61
 // hold the output columns c0 .. c0+59 of a strip whose lanes hold c0-2 .. c0+61.
 constexpr int kStripCols2 = kWave - 4;
+// A pass of k steps has strips of 64 - 2k columns.
+constexpr int kMaxPassSteps = 3;
+constexpr int strip_cols(int k) { return kWave - 2 * k; }
 
 // Radial table fields, each a row of `pitch` doubles, first for the integer
 // positions r*_i then for the half positions r*_{i+1/2}.  With r, Delta,
@@ -38,6 +41,26 @@ enum RadField : int {
     R_V0R,      // -m^2 a^2 - 6 Delta ((s+2) r^2 - (s+3) r + a^2) / r^2
     R_V0I,      // -2 s m a (r - 1)              Im V0 = V0I / Sigma^2
     kNumRad
+};
+
+// Radial factors of the forward step's stage coefficients (stage_coef): row
+// f * 2 + kind (kind 0: the columns, 1: the half points), each with the
+// factors of its stage (d on b and c, t on the rest, see Stage).
+enum SRadField : int {
+    S_RHO2 = 0,  // rho^2
+    S_A2D,       // a^2 Delta                 Sigma^2 = rho^2 - a^2 Delta sin^2
+    S_B,         // d rho                     b = B / Sigma
+    S_K0,        // -d rho (6 Delta/r + 2 s (r - 1))
+    S_K1,        // d 2 r rho^2 Delta         Re c = (K0 - (K1 - K2 sin^2)/Sigma^2 - K3/Sigma)/Sigma^2
+    S_K2,        // d a^2 (r - 1) rho Delta
+    S_K3,        // d 2 s rho (r Delta - (r^2 - a^2))
+    S_TR,        // t 2 s (r Delta - (r^2 - a^2))
+    S_TI0,       // t 4 a m r                 Im Ct = (TI0 + TI1 cos)/Sigma^2
+    S_TI1,       // t 2 s a Delta
+    S_DL2,       // t Delta / dth^2
+    S_VR,        // t (-m^2 a^2 - 6 Delta ((s+2) r^2 - (s+3) r + a^2) / r^2)
+    S_VI,        // -t 2 s m a (r - 1)
+    kNumSRad
 };
 
 // Angular table fields, stored row by row: [ntheta][kNumAng] doubles, so
@@ -73,32 +96,33 @@ struct StepScalars {
     int64_t row0;               // block pass: series row of the launch's first input state (-1: not sampled)
     int64_t plane;              // nth * pitch: offset of the Pi plane in a state
     double dt, hdt, dt_dr, hdt_dr;
+    double qdt;                 // dt / 4
+    double kap_h, kap_i;        // 1 over the factor of ct: 2 / dt (half points), 4 / dt (columns)
     double inv_dth2, inv_2dth;  // USER mode scalings
-    // source term (inhomogeneous variant): time factors of the pass's steps,
-    // sf[4s .. 4s+3] = f(t_n), f(t_n + dt/2) (re, im) of its step s = 0, 1
-    double sf[8];
+    // source term (inhomogeneous variant): time factors of the pass's steps
+    // times dt, sf[4s .. 4s+3] = dt f(t_n), dt f(t_n + dt/2) (re, im) of its step s
+    double sf[4 * kMaxPassSteps];
 };
 
-// Tile order of the single-grid two-step pass.  Dispatch: tile = workgroup
+// Tile order of the single-grid passes of two and three steps.  Dispatch: tile = workgroup
 // x waves + wave, strips fastest; workgroups go round-robin over the 8 XCDs.
 // XCD strips: each XCD takes one contiguous run of strips (its 1/8) in every
 // theta chunk, so neighbouring strips (which share halo columns and 128-byte
 // lines) and the chunks of a strip (which share the radial tables) meet in
-// one L2; strips fastest (kTileOrderXcdStrip) or chunks fastest
-// (kTileOrderXcdChunk) within the XCD.
-constexpr int kTileOrderDispatch = 0, kTileOrderXcdStrip = 1, kTileOrderXcdChunk = 2;
+// one L2; strips fastest within the XCD.
+constexpr int kTileOrderDispatch = 0, kTileOrderXcdStrip = 1;
 
 struct StepArgs {
     const double2* u_in;     // state: [Phi, Pi][nth][pitch]
     double2* u_out;
-    const double* rad;       // [kNumRad][2][pitch] (KERR)
+    const double* rad;       // [kNumSRad][2][pitch] (KERR)
     const double* ang;       // [nth][kNumAng]      (KERR)
     const double* uci;       // [kNumUser][nth][pitch] (USER, integer positions)
     const double* uch;       // [kNumUser][nth][pitch] (USER, half positions)
     const ExtPoint* ext;     // [n_ext]
     double2* series;         // n_ext samples of the input Phi, or nullptr
-    double2* win;            // copy of the input state (two-step kernel: the intermediate state), or nullptr
-    double2* series_mid;     // two-step kernel: samples of Phi after the first step, or nullptr
+    double2* win;            // one-step pass: copy of the input state; two steps: the intermediate state; or nullptr
+    double2* series_mid;     // passes of more steps: samples of Phi after the first step (then the second), or nullptr
     const double2* src_i;    // source profile at the integer positions, [nth][pitch], or nullptr
     const double2* src_h;    // source profile at the half positions, [nth][pitch]
     StepScalars k;
@@ -110,10 +134,8 @@ struct BatchMember {
     const double* rad;       // its radial and angular tables (KERR)
     const double* ang;
     StepScalars k;           // its launch scalars (rows shared by all members)
-    int32_t tile_begin;      // first tile of this member in the work list
-    int32_t tile_begin2;     // the same in the two-step work list
-    int32_t n_strips2;       // its strips of the two-step kernel
-    int32_t pad;
+    int32_t tile_begin[kMaxPassSteps];  // its first tile in the work list of the passes of 1, 2, 3 steps
+    int32_t strips[kMaxPassSteps];      // its strips in these passes
 };
 
 // One extraction point of a batched evolution: the member's two state
@@ -142,6 +164,7 @@ struct AdjScalars {
     int32_t keep;                            // 1: lam_out and the tangent step's state with ordinary stores
                                              // (selects the kernel instance)
     double dt, hdt, dt_dr, hdt_dr;
+    double qdt, kap_h, kap_i;                // as in StepScalars
 };
 
 struct AdjArgs {
@@ -150,6 +173,8 @@ struct AdjArgs {
     double2* lam_out;        // lambda^m
     const double* rad;       // [kNumRad][2][pitch]
     const double* rad_da;    // d/da of rad
+    const double* srad;      // [kNumSRad][2][pitch]
+    const double* srad_da;   // d/da of srad
     const double* ang;       // [nth][kNumAng]
     double* slots;           // [n_strips * n_chunks] spin-gradient partial sums (accumulated)
     const ExtPoint* ext;     // [n_ext] extraction points
@@ -159,9 +184,9 @@ struct AdjArgs {
 
 // Launchers (lw_kernels.hip, adjoint_kernels.hip).  All return the
 // hipError_t of the launch.
-hipError_t launch_step(const StepArgs& a, bool kerr, int waves_per_block, hipStream_t s);
-// Two steps in one pass (k.n_strips counted in kStripCols2-column strips).
-hipError_t launch_step2(const StepArgs& a, bool kerr, int waves_per_block, hipStream_t s);
+// 1, 2 or (Kerr coefficients, no source) 3 steps in one pass; k.n_strips
+// counted in strip_cols(steps)-column strips.
+hipError_t launch_pass(const StepArgs& a, int steps, bool kerr, int waves_per_block, hipStream_t s);
 // Small grids (ntheta <= kMaxBlockRows, Kerr coefficients): k.bsteps steps in
 // one launch, each workgroup holding k.bcols columns x all rows in LDS
 // (a.series: samples of the launch's input states, rows k.row0 + s).
@@ -171,10 +196,10 @@ constexpr int kMaxBlockSteps = 31;  // (64 columns - 2) / 2
 hipError_t launch_block(const StepArgs& a, hipStream_t s);
 // Zero n ints (a fill kernel: usable where a memset node is not).
 hipError_t launch_zero_ints(int* p, int n, hipStream_t s);
-// two = true: two steps per launch (work list of tile_begin2 / n_strips2).
+// steps per launch: 1, 2 or 3 (the work list of tile_begin[steps - 1]).
 // keep: the members' next states with ordinary stores (StepScalars::keep).
 hipError_t launch_batch(const BatchMember* members, int n_members, int total_tiles, int parity, int n_blocks,
-                        int waves_per_block, bool two, bool keep, hipStream_t s);
+                        int waves_per_block, int steps, bool keep, hipStream_t s);
 hipError_t launch_import(const double2* src, double2* u, int f, int nr, int nth, int pitch, hipStream_t s);
 hipError_t launch_export(const double2* u, double2* dst, int f, int nr, int nth, int pitch, hipStream_t s);
 hipError_t launch_extract(const double2* u, int pitch, const ExtPoint* pts, int n, double2* out, hipStream_t s);

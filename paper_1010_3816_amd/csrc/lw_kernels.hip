@@ -1,29 +1,39 @@
 // gfx950 kernels for the two-step Lax-Wendroff evolution of the homogeneous
 // (2+1)D Teukolsky equation (arXiv:1010.3816, Sec. 3, Eqs. (lw1)-(lw2)).
 //
-// Fused step kernel.  One wavefront owns a tile of 64 consecutive r*
-// columns (62 output columns plus one halo column on each side) and a chunk
-// of theta rows, which it sweeps row by row:
+// The sweeps.  A pass takes K = 1, 2 or 3 steps over a tile: one wavefront
+// owns 64 consecutive r* columns (64 - 2K output columns plus K halo columns
+// on each side) and a chunk of theta rows, which it sweeps row by row:
 //   * stage 1 (Eq. lw1) is evaluated once per half point and row: lane L
-//     averages its column with the column of lane L+1 (the averaging of the
+//     combines its column with the column of lane L+1 (the averaging of the
 //     printed kernel_average1) and forms u^{n+1/2}_{i+1/2};
 //   * stage 2 (Eq. lw2) at column i combines the stage-1 values of lanes
 //     L-1 and L; both neighbour exchanges are cross-lane moves, so the
 //     stage-1 field never leaves registers;
-//   * the theta stencil of S (2nd-order centred differences) needs rows
-//     j-1, j, j+1 of the averaged fields; a three-row register window slides
-//     along theta, and the pole ghost rows (mirror for even |m|, anti-mirror
-//     for odd |m|) are formed in registers by a wavefront-uniform branch;
-//   * Phi = Pi = 0 is written on the radial boundary columns.
-// Every input point is read once per tile (plus a 2-column and 2-row halo),
-// every output point written once; the coefficients of Eq. (1) are rebuilt
-// per point from 1-D radial tables (per lane, held in registers) and 1-D
-// angular tables (per row, wavefront-uniform), so no 2-D coefficient array
-// is streamed from HBM.
+//   * the theta stencil of S needs the differences of the averaged fields to
+//     the neighbour rows; the sweep carries the last row's sums, and the pole
+//     ghost rows (mirror for even |m|, anti-mirror for odd |m|) are formed in
+//     registers;
+//   * a completed row goes on to the next step of the pass in registers;
+//   * Phi = Pi = 0 is set on the radial boundary columns.
+// Every input point is read once per tile (plus the halo), every output point
+// written once; the coefficients of Eq. (1) are rebuilt once per point and
+// pass from 1-D radial tables and 1-D angular tables, so no 2-D coefficient
+// array is streamed from HBM.
+//
+// What bounds it, and why three steps.  A pass moves 64 bytes a point however
+// many steps it takes, and rebuilding a point's coefficients costs about as
+// much as half a step, also once per pass; more steps divide both.  Per point
+// and step the main loops issue 150 (K = 1), 110 (K = 2) and 102 (K = 3)
+// vector instructions (the two-step pass before the stage coefficients and
+// theta differences of device_common.hpp: 180).  K = 3 is the most whose rows
+// and coefficients fit the registers of two wavefronts per SIMD (244 of 256).
+// 25600 x 512, us per step (the same box in turn): two steps, before, 95; two
+// steps 84-88, bound by memory; three steps 66-68 = 4.2 TB/s, bound by the
+// issue of its wavefronts as much as by memory.  6400 x 256: 15.1, 13.9, 12.3.
 //
 // Extraction is fused: the wavefront whose tile contains the bilinear
-// stencil of an extraction point accumulates Phi of the INPUT state while
-// it streams the rows, and writes the sample at the end of its sweep.
+// stencil of an extraction point samples Phi of the INPUT of every step.
 #include "device_common.hpp"
 
 namespace teuk {
@@ -35,353 +45,144 @@ __device__ __forceinline__ cd source(gin_t g, size_t o, double fr, double fi) {
     return {fma(fr, v.re, -fi * v.im), fma(fr, v.im, fi * v.re)};
 }
 
-// Row-sweep of one tile.  Per row t the sweep keeps:
-//   p, q      Phi, Pi at (i, t)
-//   ubp       stage-1 average of Phi at the half point i+1/2
-//   hbp, dhp  mean and difference of the stage-1 Phi values at i-1/2, i+1/2
-//   x, wp     the stage-1 Pi value at (i+1/2, t) except for its row-(t+1)
-//             term: h_Pi(t) = x + wp * ubp(t+1); the theta stencil is the only
-//             part of Eq. (lw1) that needs the next row.
+typedef __attribute__((address_space(3))) double* lds_t;
+typedef __attribute__((address_space(3))) v2d* cd_lds_t;
+
+// LDS of one wavefront of a sweep: its radial factors, [column/half][field][lane]
+// (13 KB), the slots of a sample's values, and a slot per lane for values not
+// sampled.
+constexpr int kSampleSlots = 4 * kMaxPassSteps;
+constexpr int kSliceDoubles = 2 * kNumSRad * kWave + 2 * (kSampleSlots + kWave);
+constexpr size_t kRadSliceBytes = kSliceDoubles * sizeof(double);
+
+// One row of one step between its arrival and its completion (the next
+// row's arrival): the new Phi but for its SQ term, the new Pi but for
+// stage2_late, 2 h_Pi but for its next-row term, and the row's sums of Phi
+// and of H, from which the next row's theta differences are formed.
 struct Row {
-    cd p, q, ubp, hbp, dhp, x;
-    double wp;
-    Ang g;  // angular factors of row t (wavefront-uniform, KERR)
+    cd P, Q, X, U, S;
 };
 
-// One tile (strip of 64 columns x theta chunk) of one grid.  Inlined into
-// the single-grid kernel and into the batched kernel.
-// KEEP: the cache policy of the new state's stores (0 streaming, 1 keeping).
-template <bool KERR, bool SRC, int KEEP>
-__device__ __forceinline__ void sweep_tile(gin_t __restrict__ u_in, gout_t __restrict__ u_out, ctab_t rad, ctab_t ang,
-                                           ctab_t uci, ctab_t uch, cext_t ext, double2* __restrict__ series,
-                                           gout_t __restrict__ win, const StepScalars& A, int strip, int chunk,
-                                           int lane, gin_t __restrict__ src_i = nullptr,
-                                           gin_t __restrict__ src_h = nullptr) {
+// Stage coefficients of one row: at the half point and at the column.
+struct RowCoef {
+    Stage h, i;
+};
+
+// sched_barrier mask: all classes the scheduler may move across, scalar
+// memory not among them.
+constexpr int kAllButScalarLoads = 0x3FF;
+
+// K Lax-Wendroff steps in one pass over a tile of 64 - 2K columns by A.rows
+// rows (temporal blocking: only the pass's input is read and its output
+// written).  Iteration r of the row loop takes input row r from memory; step
+// 0 of the pass completes row r - 1, which goes from registers to step 1 as
+// its row r - 1, and so on: step j takes row r - j and completes row r - j -
+// 1, and row r - K of the output is written.  Each step consumes one column
+// at each edge of the wavefront and one row at each end of the tile.
+//
+// A row's coefficients are the same for all steps and are built once, when
+// its input row arrives (from the lane's radial factors in the wavefront's
+// LDS slice rs, [column/half][field][lane], and the angular row, scalar),
+// and kept in registers until the last step has passed it: a ring of K + 1
+// rows.  The row loop is unrolled over the ring, so nothing is copied.
+//
+// Poles: the ghost rows are sigma times the first and last row, in the input
+// and in the stage-1 values alike, so at row 0 the difference to the
+// previous row is U - sigma U, and after the last row a step takes the ghost
+// as its next one.  A tile starts at row 0 or K rows above its first one,
+// where the first rows of each step hold values formed from rows that were
+// not read; the rows they complete are not used by the next step.
+//
+// The main loop is for rows away from the last pole, of strips without a
+// radial boundary column and tiles that sample or keep nothing; the loop
+// after it checks for all of these.
+template <int K, bool KERR, bool SRC, int KEEP>
+__device__ __forceinline__ void sweep(gin_t __restrict__ u_in, gout_t __restrict__ u_out, ctab_t rad, ctab_t ang,
+                                      ctab_t uci, ctab_t uch, cext_t ext, double2* __restrict__ series_in,
+                                      double2* __restrict__ series_mid, gout_t __restrict__ win, lds_t rs,
+                                      const StepScalars& A, int strip, int chunk, int lane,
+                                      gin_t __restrict__ src_i, gin_t __restrict__ src_h) {
+    constexpr int kRing = K + 1;               // coefficient rows held
+    constexpr int kAhead = (K == 3) ? 2 : kRing;  // input rows in flight (divides the unrolled rows)
+    constexpr int kCols = strip_cols(K);
     const int nr = A.nr, nth = A.nth, P = A.pitch;
-    const int col = strip * kStripCols - 1 + lane;
-    // Lanes outside the grid read the clamped edge column.  Their values
-    // reach only the radial boundary columns of the output, which are set to
-    // zero, so they need no masking.
-    const int ci = min(max(col, 0), nr - 1);  // clamped integer column
-    const int hi = min(max(col, 0), nr - 2);  // clamped half point col + 1/2
-
-    // radial factors of this lane's column and half point, held in registers
-    Rad Ri, Rh;
-    if constexpr (KERR) {
-        Ri = load_rad(rad, P, 0, ci);
-        Rh = load_rad(rad, P, 1, hi);
-    }
-
-    const bool store_ok = (lane >= 1) && (lane <= kWave - 2) && (col < nr);
+    const int col = strip * kCols - K + lane;
+    // Lanes outside the grid read the clamped edge column; what they hold
+    // reaches only the radial boundary columns, which every step sets to zero.
+    const int ci = min(max(col, 0), nr - 1);
+    const int hi = min(max(col, 0), nr - 2);
+    const bool store_ok = (lane >= K) && (lane < kWave - K) && (col < nr);
     const bool boundary = (col == 0) || (col == nr - 1);
     const int j0 = chunk * A.rows;
     const int j1 = min(j0 + A.rows, nth);
+    const int rs0 = max(j0 - K, 0);  // first input row
+    const int rE = j1 - 1 + K;       // last iteration
     const double sg = (double)A.sigma;
-    const int last = (j1 < nth) ? j1 : nth - 1;  // last row this tile reads
 
-    // The prologue's rows (j0-1, or row 0 again for the first tile, and j0)
-    // and the ring's first rows, loaded right after the radial factors so
-    // that the latencies overlap at the start of the tile.
-    cd hp[2], hq[2];
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const size_t o = (size_t)max(j0 - 1 + k, 0) * P + ci;
-        hp[k] = ld(u_in, o);
-        hq[k] = ld(u_in, o + A.plane);
-    }
-    // Ring of D row buffers: buffer u holds row t+1 when row t (t - j0 = u
-    // mod D) is finished, and is refilled with row t+1+D right after.  The
-    // loop is unrolled by D so that loaded registers are never copied (a copy
-    // would have to wait for the load), keeping D rows in flight.
-    cd bp[kRowsInFlight], bq[kRowsInFlight];
-#pragma unroll
-    for (int u = 0; u < kRowsInFlight; ++u) {
-        const size_t o = (size_t)min(j0 + 1 + u, last) * P + ci;
-        bp[u] = ld(u_in, o);
-        bq[u] = ld(u_in, o + A.plane);
-    }
+    const int32_t row_bytes = P * (int32_t)sizeof(v2d);
+    const uint32_t ld_off = (uint32_t)ci * sizeof(v2d);
+    const uint32_t st_off = store_ok ? (uint32_t)col * sizeof(v2d) : kOffNone;
+    auto load_row = [&](int t, cd& p, cd& q) {
+        const gin_t b = u_in + (size_t)min(max(t, 0), nth - 1) * P;
+        p = ld_row(row_rsrc(b, row_bytes), ld_off);
+        q = ld_row(row_rsrc(b + A.plane, row_bytes), ld_off);
+    };
+    // rows the tile does not own are dropped (an empty resource)
+    auto put_row = [&](gout_t base, int t, cd vp, cd vq, auto keep) {
+        const int32_t bytes = (t >= j0 && t < j1) ? row_bytes : 0;
+        const gout_t b = base + (size_t)max(t, 0) * P;
+        st_row<decltype(keep)::value>(row_rsrc(b, bytes), st_off, vp);
+        st_row<decltype(keep)::value>(row_rsrc(b + A.plane, bytes), st_off, vq);
+    };
 
-    // the (at most one) extraction point of this tile, in scalar registers
-    int e_id = -1, e_lane = 0, e_ra = -1, e_rb = -1;
-    double e_wr = 0.0, e_wa = 0.0, e_wb = 0.0;
-    for (int e = 0; e < A.n_ext; ++e) {
-        const ExtPoint E = {ext[e].col, ext[e].rowa, ext[e].rowb, 0, ext[e].wr, ext[e].wa, ext[e].wb, 0.0};
-        const int es = E.col / kStripCols;
-        if (es == strip && E.rowa / A.rows == chunk) {
-            e_id = e;
-            e_lane = E.col - es * kStripCols + 1;
-            e_ra = E.rowa;
-            e_rb = E.rowb;
-            e_wr = E.wr;
-            e_wa = E.wa;
-            e_wb = E.wb;
+    // the radial factors of this lane's column and half point, loaded
+    // with the first rows (so that the latencies overlap) and then written to the wavefront's slice
+    // (lane-private: written and read by the same lane, no barrier)
+    double tv[2 * kNumSRad];
+    if constexpr (KERR) {
+#pragma unroll
+        for (int f = 0; f < kNumSRad; ++f) {
+            tv[f] = rad[((size_t)f * 2 + 0) * P + ci];
+            tv[kNumSRad + f] = rad[((size_t)f * 2 + 1) * P + hi];
         }
     }
-    cd acc = {0.0, 0.0};
+    cd bp[kAhead], bq[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) load_row(rs0 + u, bp[u], bq[u]);
+    if constexpr (KERR) {
+#pragma unroll
+        for (int f = 0; f < 2 * kNumSRad; ++f) rs[f * kWave + lane] = tv[f];
+    }
 
-    // angular factors of row t (clamped to the grid: rows past the last
-    // are loaded ahead but never used)
     auto ang_row = [&](int t) -> Ang {
         Ang G{};
         if constexpr (KERR) G = load_ang(ang, nth, min(t, nth - 1));
         return G;
     };
-    auto half_coef = [&](int t, const Ang& G, double& b) -> Coef {
-        Coef k;
+    // the row-dependent zero offset keeps the LDS reads next to their use
+    auto coefs = [&](int t, const Ang& G, RowCoef& c) {
         if constexpr (KERR) {
-            k = kerr_coef(Rh, G, kerr_sigma(Rh, G));
+            const __attribute__((address_space(3))) double* r = rs + lane + (t & A.zero);
+            const SRad Ri = srad_of([&](int f) { return r[f * kWave]; });
+            c.i = stage_coef(Ri, G, ssigma(Ri, G), A.kap_i);
+            const SRad Rh = srad_of([&](int f) { return r[(kNumSRad + f) * kWave]; });
+            c.h = stage_coef(Rh, G, ssigma(Rh, G), A.kap_h);
         } else {
-            k = user_coef(uch, nth, P, t, hi, A.inv_dth2, A.inv_2dth);
-        }
-        b = k.b;
-        return k;
-    };
-    auto half_b = [&](int t, const Ang& G) -> double {
-        if constexpr (KERR) {
-            return Rh.rho * kerr_sigma(Rh, G).isig;
-        } else {
-            return uch[((size_t)U_B * nth + t) * P + hi];
+            const int tc = min(t, nth - 1);
+            c.i = user_stage(uci, nth, P, tc, ci, A.inv_dth2, A.inv_2dth, A.hdt_dr, A.qdt);
+            c.h = user_stage(uch, nth, P, tc, hi, A.inv_dth2, A.inv_2dth, A.dt_dr, A.hdt);
         }
     };
 
-    // Stage-1 pieces of row t from u(t) of this lane and of lane L+1.
-    // FULL: also the Pi part x, wp (needs ubp(t-1): `ubp_prev`, or the ghost
-    // row when t == 0).  Halo rows only need ubp and hbp.
-    auto fresh = [&](int t, cd p, cd q, cd ubp_prev, bool full, const Ang& G) -> Row {
-        Row R;
-        R.p = p;
-        R.q = q;
-        R.g = G;
-        const cd pr = from_right(p), qr = from_right(q);
-        R.ubp = cavg(p, pr);
-        const cd ubq = cavg(q, qr);
-        const cd dp = csub(pr, p);
-        double bh;
-        Coef kh;
-        if (full)
-            kh = half_coef(t, G, bh);
-        else
-            bh = half_b(t, G);
-        // h_Phi = ubar_Phi - dt/2 (b delta_Phi / dr - ubar_Pi)
-        const double tb = A.hdt_dr * bh;
-        const cd hp = {fma(-tb, dp.re, fma(A.hdt, ubq.re, R.ubp.re)), fma(-tb, dp.im, fma(A.hdt, ubq.im, R.ubp.im))};
-        const cd hpl = from_left(hp);
-        R.hbp = cavg(hp, hpl);
-        R.dhp = csub(hp, hpl);
-        if (full) {
-            // h_Pi = ubar_Pi - dt/2 [ (c delta_Phi - b delta_Pi)/dr - S_Pi(ubar) ], with
-            // S_Pi(ubar) = -Ct ubar_Pi + A2 lap + A1 grad - V0 ubar_Phi split as
-            // (everything but the row-(t+1) term) + (A2/dth^2 + A1/(2 dth)) ubar_Phi(t+1)
-            const cd dq = csub(qr, q);
-            const cd um = (t == 0) ? cscale(sg, R.ubp) : ubp_prev;
-            const cd dq1 = d_pi(kh, dp, dq);
-            cd s1 = s_pi(kh, um, R.ubp, cd{0.0, 0.0}, ubq);
-            if constexpr (SRC) s1 = cadd(s1, source(src_h, (size_t)t * P + hi, A.sf[0], A.sf[1]));
-            R.x = {fma(A.hdt, s1.re, fma(-A.hdt_dr, dq1.re, ubq.re)), fma(A.hdt, s1.im, fma(-A.hdt_dr, dq1.im, ubq.im))};
-            R.wp = A.hdt * (kh.a2s + kh.a1s);
-        }
-        if (t == e_ra || t == e_rb) {  // wavefront-uniform
-            const double w = (t == e_ra) ? e_wa : e_wb;
-            acc.re = fma(w, fma(e_wr, pr.re - p.re, p.re), acc.re);
-            acc.im = fma(w, fma(e_wr, pr.im - p.im, p.im), acc.im);
-        }
-        return R;
-    };
-
-    // ---- prologue: rows j0-1 (halo or ghost) and j0 ----------------------
-    cd hbp_m;  // hbar_Phi at row t-1
-    Row cur;
-    {
-        cd ubp_m = {0.0, 0.0};
-        if (j0 > 0) {
-            const Row rm = fresh(j0 - 1, hp[0], hq[0], ubp_m, false, ang_row(j0 - 1));
-            ubp_m = rm.ubp;
-            hbp_m = rm.hbp;
-        }
-        cur = fresh(j0, hp[1], hq[1], ubp_m, true, ang_row(j0));
-        if (j0 == 0) hbp_m = cscale(sg, cur.hbp);
-    }
-    // angular factors of the row after the next one to be finished, loaded
-    // one row ahead so that their scalar loads are complete when needed
-    Ang g_next = ang_row(j0 + 1);
-
-    auto finish_row = [&](int t, cd& rp, cd& rq) {
-        // row t+1: streamed, or the pole ghost row
-        Row nxt;
-        cd ubp_p, hbp_p;
-        const Ang g1 = g_next;
-        g_next = ang_row(t + 2);
-        if (t + 1 < nth) {
-            nxt = fresh(t + 1, rp, rq, cur.ubp, true, g1);
-            ubp_p = nxt.ubp;
-            hbp_p = nxt.hbp;
-        } else {
-            ubp_p = cscale(sg, cur.ubp);
-            hbp_p = cscale(sg, cur.hbp);
-            nxt = cur;  // unused: the sweep ends with this row
-        }
-        {
-            const size_t o = (size_t)min(t + 1 + kRowsInFlight, last) * P + ci;
-            rp = ld(u_in, o);
-            rq = ld(u_in, o + A.plane);
-        }
-
-        // stage 1, Pi component at (i+1/2, t), and its neighbour at i-1/2
-        const cd hq = {fma(cur.wp, ubp_p.re, cur.x.re), fma(cur.wp, ubp_p.im, cur.x.im)};
-        const cd hql = from_left(hq);
-        const cd hbq = cavg(hq, hql);
-        const cd dhq = csub(hq, hql);
-
-        // stage 2 at (i, t)
-        //   Phi' = Phi - dt [ b dh_Phi / dr - hbar_Pi ]
-        //   Pi'  = Pi  - dt [ (c dh_Phi - b dh_Pi)/dr - S_Pi(hbar) ]
-        Coef ki;
-        if constexpr (KERR) {
-            ki = kerr_coef(Ri, cur.g, kerr_sigma(Ri, cur.g));
-        } else {
-            ki = user_coef(uci, nth, P, t, ci, A.inv_dth2, A.inv_2dth);
-        }
-        const double tb = A.dt_dr * ki.b;
-        cd np = {fma(-tb, cur.dhp.re, fma(A.dt, hbq.re, cur.p.re)), fma(-tb, cur.dhp.im, fma(A.dt, hbq.im, cur.p.im))};
-        const cd dq2 = d_pi(ki, cur.dhp, dhq);
-        cd s2 = s_pi(ki, hbp_m, cur.hbp, hbp_p, hbq);
-        if constexpr (SRC) s2 = cadd(s2, source(src_i, (size_t)t * P + ci, A.sf[2], A.sf[3]));
-        cd nq = {fma(A.dt, s2.re, fma(-A.dt_dr, dq2.re, cur.q.re)), fma(A.dt, s2.im, fma(-A.dt_dr, dq2.im, cur.q.im))};
-        if (boundary) {
-            np = {0.0, 0.0};
-            nq = {0.0, 0.0};
-        }
-        if (store_ok) {
-            const size_t o = (size_t)t * P + col;
-            st_state<KEEP>(u_out, o, np);
-            st_state<KEEP>(u_out, o + A.plane, nq);
-            if (win != nullptr) {  // keep the input state (for the adjoint)
-                st(win, o, cur.p);
-                st(win, o + A.plane, cur.q);
-            }
-        }
-
-        hbp_m = cur.hbp;
-        cur = nxt;
-    };
-
-    // whole groups of kRowsInFlight rows, then the ragged tail
-    int t0 = j0;
-    for (; t0 + kRowsInFlight <= j1; t0 += kRowsInFlight) {
-#pragma unroll
-        for (int u = 0; u < kRowsInFlight; ++u) finish_row(t0 + u, bp[u], bq[u]);
-    }
-#pragma unroll
-    for (int u = 0; u < kRowsInFlight; ++u)
-        if (t0 + u < j1) finish_row(t0 + u, bp[u], bq[u]);
-
-    if (e_id >= 0 && lane == e_lane && series != nullptr) {
-        double2 w;
-        w.x = acc.re;
-        w.y = acc.im;
-        series[e_id] = w;
-    }
-}
-
-// Two Lax-Wendroff steps in one pass over a tile (temporal blocking): the
-// first step's result never leaves registers.  Step A sweeps the input rows
-// exactly as sweep_tile does; each row it completes, u^{n+1}(r), is fed as
-// the next input row of a second sweep, step B, which completes row r-1 of
-// u^{n+2}.  Per tile, A covers the rows j0-1 .. j1 that B needs (reading
-// j0-2 .. j1+1) and B writes j0 .. j1-1.  Across lanes, A's results are
-// valid on lanes 1..62 and B's on lanes 2..61, hence 60-column strips.
-// Boundary rules are those of one step: A's radial boundary columns are
-// zero before B reads them, and both sweeps use the pole ghost rows.
-// Both steps need the same coefficients at the same points: B takes those A
-// built one row earlier (the half-point set of row r, the integer-point set
-// of row r-1) instead of rebuilding them.  The wavefront's radial factors
-// live in its own LDS slice (rs: [integer/half][field][lane]), which frees
-// the registers the carried coefficients need.
-// Extraction is fused for both states a pass samples: the input (sample of
-// step n-1) and the intermediate state (sample of step n).
-typedef __attribute__((address_space(3))) double* lds_t;
-
-template <bool KERR, bool SRC, int KEEP>
-__device__ __forceinline__ void sweep_tile2(gin_t __restrict__ u_in, gout_t __restrict__ u_out, ctab_t rad,
-                                            ctab_t ang, ctab_t uci, ctab_t uch, cext_t ext,
-                                            double2* __restrict__ series_in, double2* __restrict__ series_mid,
-                                            gout_t __restrict__ u_mid, lds_t rs, const StepScalars& A, int strip,
-                                            int chunk, int lane, gin_t __restrict__ src_i = nullptr,
-                                            gin_t __restrict__ src_h = nullptr) {
-    const int nr = A.nr, nth = A.nth, P = A.pitch;
-    const int col = strip * kStripCols2 - 2 + lane;
-    // Lanes outside the grid need no masking (as in sweep_tile): what they
-    // hold reaches only the radial boundary columns of step A's and step B's
-    // outputs, which both steps set to zero.
-    const int ci = min(max(col, 0), nr - 1);
-    const int hi = min(max(col, 0), nr - 2);
-
-    // This lane's radial factors (kind 0: its column, kind 1: its half
-    // point), loaded here and written to the wavefront's LDS slice once the
-    // loads of the first rows are in flight too, so that the two latencies
-    // overlap at the start of the tile.
-    double tv[2 * kNumRad];
-    if constexpr (KERR) {
-#pragma unroll
-        for (int f = 0; f < kNumRad; ++f) {
-            tv[f] = rad[((size_t)f * 2 + 0) * P + ci];
-            tv[kNumRad + f] = rad[((size_t)f * 2 + 1) * P + hi];
-        }
-    }
-    // radial factors of this lane's column (kind 0) or half point (kind 1);
-    // the row-dependent zero offset keeps the reads next to their use
-    auto rad_lds = [&](int kind, int t) -> Rad {
-        const __attribute__((address_space(3))) double* r = rs + kind * kNumRad * kWave + lane + (t & A.zero);
-        Rad R;
-        R.rho = r[R_RHO * kWave];
-        R.rho2 = r[R_RHO2 * kWave];
-        R.a2d = r[R_A2D * kWave];
-        R.rb1 = r[R_RB1 * kWave];
-        R.rb2 = r[R_RB2 * kWave];
-        R.rb3 = r[R_RB3 * kWave];
-        R.ctr = r[R_CTR * kWave];
-        R.cti0 = r[R_CTI0 * kWave];
-        R.cti1 = r[R_CTI1 * kWave];
-        R.b1n = r[R_B1N * kWave];
-        R.dl2 = r[R_DL2 * kWave];
-        R.v0r = r[R_V0R * kWave];
-        R.v0i = r[R_V0I * kWave];
-        return R;
-    };
-    auto coef_h = [&](int t, const Ang& G) -> Coef {
-        if constexpr (KERR) {
-            const Rad R = rad_lds(1, t);
-            return kerr_coef(R, G, kerr_sigma(R, G));
-        } else {
-            return user_coef(uch, nth, P, t, hi, A.inv_dth2, A.inv_2dth);
-        }
-    };
-    auto coef_i = [&](int t, const Ang& G) -> Coef {
-        if constexpr (KERR) {
-            const Rad R = rad_lds(0, t);
-            return kerr_coef(R, G, kerr_sigma(R, G));
-        } else {
-            return user_coef(uci, nth, P, t, ci, A.inv_dth2, A.inv_2dth);
-        }
-    };
-
-    const bool store_ok = (lane >= 2) && (lane <= kWave - 3) && (col < nr);
-    const bool boundary = (col == 0) || (col == nr - 1);
-    const int j0 = chunk * A.rows;
-    const int j1 = min(j0 + A.rows, nth);
-    const int aE = min(j1, nth - 1);         // last row step A completes
-    const int lastA = min(aE + 1, nth - 1);  // last input row read
-    const double sg = (double)A.sigma;
-
-    // the (at most one) extraction point of this tile
+    // the (at most one) extraction point of this tile, in scalar registers
     int e_id = -1, e_lane = 0, e_ra = -1, e_rb = -1;
     double e_wr = 0.0, e_wa = 0.0, e_wb = 0.0;
     for (int e = 0; e < A.n_ext; ++e) {
         const int ecol = ext[e].col, era = ext[e].rowa;
-        const int es = ecol / kStripCols2;
+        const int es = ecol / kCols;
         if (es == strip && era / A.rows == chunk) {
             e_id = e;
-            e_lane = ecol - es * kStripCols2 + 2;
+            e_lane = ecol - es * kCols + K;
             e_ra = era;
             e_rb = ext[e].rowb;
             e_wr = ext[e].wr;
@@ -389,271 +190,149 @@ __device__ __forceinline__ void sweep_tile2(gin_t __restrict__ u_in, gout_t __re
             e_wb = ext[e].wb;
         }
     }
-    cd acc_in = {0.0, 0.0}, acc_mid = {0.0, 0.0};
-    // bilinear sample of a Phi row into acc
-    auto sample = [&](int t, cd p, cd& acc) {
-        if (t == e_ra || t == e_rb) {  // wavefront-uniform
-            const double w = (t == e_ra) ? e_wa : e_wb;
-            const cd pr = from_right(p);
-            acc.re = fma(w, fma(e_wr, pr.re - p.re, p.re), acc.re);
-            acc.im = fma(w, fma(e_wr, pr.im - p.im, p.im), acc.im);
-        }
-    };
+    // The values of Phi a sample is formed from go to the wavefront's LDS
+    // slots [step][row a, b][column, next column] as the rows pass; every
+    // other value goes to a slot of the lane's own, so no branch is taken.
+    cd_lds_t smp = (cd_lds_t)(rs + 2 * kNumSRad * kWave);
+    auto pick = [](bool c, cd a, cd b) -> cd { return {c ? a.re : b.re, c ? a.im : b.im}; };
 
-    auto ang_row = [&](int t) -> Ang {
-        Ang G{};
-        if constexpr (KERR) G = load_ang(ang, nth, min(t, nth - 1));
-        return G;
-    };
+    // last iteration of the main loop (none: -1)
+    const int c0 = strip * kCols - K;
+    const int plain = (int)(c0 > 0) & (int)(c0 + kWave - 1 < nr - 1) & (int)(e_id < 0) & (int)(win == nullptr);
+    const int rM = plain * (min(rE, nth - 1) + 1) - 1;
 
-    // Stage-1 pieces of row t (as in sweep_tile) with the half-point
-    // coefficients kh of the row.  FULL = false: only the averages needed
-    // from a halo row.
-    // stp: the step of the pass (0: sweep A, 1: sweep B), for the source term
-    auto fresh = [&](int t, cd p, cd q, cd ubp_prev, bool full, const Ang& G, const Coef& kh, int stp) -> Row {
-        Row R;
-        R.p = p;
-        R.q = q;
-        R.g = G;
-        const cd pr = from_right(p), qr = from_right(q);
-        R.ubp = cavg(p, pr);
-        const cd ubq = cavg(q, qr);
-        const cd dp = csub(pr, p);
-        const double tb = A.hdt_dr * kh.b;
-        const cd hp = {fma(-tb, dp.re, fma(A.hdt, ubq.re, R.ubp.re)), fma(-tb, dp.im, fma(A.hdt, ubq.im, R.ubp.im))};
-        const cd hpl = from_left(hp);
-        R.hbp = cavg(hp, hpl);
-        R.dhp = csub(hp, hpl);
-        if (full) {
-            const cd dq = csub(qr, q);
-            const cd um = (t == 0) ? cscale(sg, R.ubp) : ubp_prev;
-            const cd dq1 = d_pi(kh, dp, dq);
-            cd s1 = s_pi(kh, um, R.ubp, cd{0.0, 0.0}, ubq);
-            if constexpr (SRC) s1 = cadd(s1, source(src_h, (size_t)t * P + hi, A.sf[4 * stp], A.sf[4 * stp + 1]));
-            R.x = {fma(A.hdt, s1.re, fma(-A.hdt_dr, dq1.re, ubq.re)), fma(A.hdt, s1.im, fma(-A.hdt_dr, dq1.im, ubq.im))};
-            R.wp = A.hdt * (kh.a2s + kh.a1s);
-        }
-        return R;
-    };
+    Row st[K] = {};
+    RowCoef C[kRing] = {};
+    Ang g_next = ang_row(rs0);
 
-    // Stage 2 at (i, t) with the integer-point coefficients ki of row t: the
-    // new (Phi, Pi) of row t from its stage-1 state c, hbar_Phi of row t-1
-    // and (ubar_Phi, hbar_Phi) of row t+1.
-    auto out_row = [&](int t, const Row& c, const Coef& ki, cd hbp_m, cd ubp_p, cd hbp_p, cd& np, cd& nq, int stp) {
-        const cd hq = {fma(c.wp, ubp_p.re, c.x.re), fma(c.wp, ubp_p.im, c.x.im)};
-        const cd hql = from_left(hq);
-        const cd hbq = cavg(hq, hql);
-        const cd dhq = csub(hq, hql);
-        const double tb = A.dt_dr * ki.b;
-        np = {fma(-tb, c.dhp.re, fma(A.dt, hbq.re, c.p.re)), fma(-tb, c.dhp.im, fma(A.dt, hbq.im, c.p.im))};
-        const cd dq2 = d_pi(ki, c.dhp, dhq);
-        cd s2 = s_pi(ki, hbp_m, c.hbp, hbp_p, hbq);
-        if constexpr (SRC) s2 = cadd(s2, source(src_i, (size_t)t * P + ci, A.sf[4 * stp + 2], A.sf[4 * stp + 3]));
-        nq = {fma(A.dt, s2.re, fma(-A.dt_dr, dq2.re, c.q.re)), fma(A.dt, s2.im, fma(-A.dt_dr, dq2.im, c.q.im))};
-        if (boundary) {
-            np = {0.0, 0.0};
-            nq = {0.0, 0.0};
-        }
-    };
-
-    // Rows are read and written through row resources (device_common.hpp):
-    // lane byte offsets of the clamped column (loads) and of the owned
-    // column, or none (stores).
-    const int32_t row_bytes = P * (int32_t)sizeof(v2d);
-    const uint32_t ld_off = (uint32_t)ci * sizeof(v2d);
-    const uint32_t st_off = store_ok ? (uint32_t)col * sizeof(v2d) : kOffNone;
-    auto put_row = [&](gout_t base, int t, cd vp, cd vq, auto keep) {
-        const gout_t b = base + (size_t)t * P;
-        st_row<decltype(keep)::value>(row_rsrc(b, row_bytes), st_off, vp);
-        st_row<decltype(keep)::value>(row_rsrc(b + A.plane, row_bytes), st_off, vq);
-    };
-
-    // the intermediate state, kept for the adjoint (owned rows and columns)
-    auto store_mid = [&](int t, cd vp, cd vq) {
-        if (u_mid != nullptr && t >= j0 && t < j1) put_row(u_mid, t, vp, vq, std::integral_constant<int, 0>{});
-    };
-
-    auto load_row = [&](int t, cd& p, cd& q) {
-        const gin_t b = u_in + (size_t)min(max(t, 0), lastA) * P;
-        p = ld_row(row_rsrc(b, row_bytes), ld_off);
-        q = ld_row(row_rsrc(b + A.plane, row_bytes), ld_off);
-    };
-
-    // ---- prologue: step A completes rows j0-1 (if j0 > 0) and j0; step B
-    // takes them as its halo row and its first row ------------------------
-    // Carried between the sweeps: kh_a = half-point coefficients of A's
-    // current row (step B's next row), ki_b = integer-point coefficients of
-    // the row step B completes next.
-    Row a_cur, b_cur;
-    Coef kh_a, ki_b;
-    cd a_hbp_m, b_hbp_m;
-    // The rows the prologue starts from (step A's rows aS-1 .. aS+2, i.e.
-    // j0-2 .. j0+1) and the first two of the main sweep's ring, all loaded
-    // before the radial factors are written to LDS.
-    const int aS = max(j0 - 1, 0);
-    cd pp[4], pq[4];
+    // Iteration r.  PH: the ring slot of row r's coefficients; STEPS: the
+    // steps that take a row (fewer while a tile starts); CHECK: the row may
+    // be a pole's, a boundary column's, sampled or kept.
+    auto iteration = [&](int r, cd& rp, cd& rq, auto ph, auto steps, auto check) {
+        constexpr int PH = decltype(ph)::value, STEPS = decltype(steps)::value;
+        constexpr bool CHECK = decltype(check)::value != 0, FIRST = decltype(check)::value == 2;
+        const Ang G = g_next;
+        coefs(r, G, C[PH]);
+        if constexpr (CHECK) __builtin_amdgcn_sched_barrier(0);
+        cd p = rp, q = rq;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) load_row(aS - 1 + u, pp[u], pq[u]);
-    cd bp[kRowsInFlight2], bq[kRowsInFlight2];
-#pragma unroll
-    for (int u = 0; u < kRowsInFlight2; ++u) load_row(j0 + 2 + u, bp[u], bq[u]);
-    if constexpr (KERR) {
-        // this wavefront's slice: lane-private values, written and read by
-        // the same lane, so no barrier is needed
-#pragma unroll
-        for (int f = 0; f < 2 * kNumRad; ++f) rs[f * kWave + lane] = tv[f];
-    }
-    {
-        // step A's rows j0-2 (halo) .. j0+1
-        cd ubp_m = {0.0, 0.0};
-        if (aS > 0) {
-            const Ang G = ang_row(aS - 1);
-            const Row h = fresh(aS - 1, pp[0], pq[0], ubp_m, false, G, coef_h(aS - 1, G), 0);
-            sample(aS - 1, h.p, acc_in);
-            ubp_m = h.ubp;
-            a_hbp_m = h.hbp;
-        }
-        {
-            const Ang G = ang_row(aS);
-            kh_a = coef_h(aS, G);
-            a_cur = fresh(aS, pp[1], pq[1], ubp_m, true, G, kh_a, 0);
-        }
-        sample(aS, a_cur.p, acc_in);
-        if (aS == 0) a_hbp_m = cscale(sg, a_cur.hbp);
-        cd b_ubp_m = {0.0, 0.0};
-        // A completes row r with row r+1 = (p1, q1) arriving; B takes row r
-        auto prologue_row = [&](int r, cd p1, cd q1) {
-            Row a_nxt;
-            Coef kh_n;
-            cd ubp_p, hbp_p;
-            if (r + 1 < nth) {
-                const Ang G = ang_row(r + 1);
-                kh_n = coef_h(r + 1, G);
-                a_nxt = fresh(r + 1, p1, q1, a_cur.ubp, true, G, kh_n, 0);
-                sample(r + 1, a_nxt.p, acc_in);
-                ubp_p = a_nxt.ubp;
-                hbp_p = a_nxt.hbp;
-            } else {
-                ubp_p = cscale(sg, a_cur.ubp);
-                hbp_p = cscale(sg, a_cur.hbp);
-                a_nxt = a_cur;
-                kh_n = kh_a;
+        for (int j = 0; j < STEPS; ++j) {
+            const RowCoef& c = C[(PH + kRing - j) % kRing];      // of the arriving row
+            const RowCoef& d = C[(PH + kRing - j - 1) % kRing];  // of the row completed
+            const int t = r - j;
+            Row& s = st[j];
+            cd um = s.U, sm = s.S;
+            Row n;
+            if constexpr (CHECK) {
+                if constexpr (K <= 2)
+                    if (j == K - 1) put_row(win, win != nullptr ? t : -1, p, q, Const<0>{});
+                // lanes e_lane, e_lane + 1 of a sampled row (1 << 20: none)
+                const int rel = lane - ((t == e_ra || t == e_rb) ? e_lane : 1 << 20);
+                smp[(rel & ~1) == 0 ? rel + 4 * j + (t == e_rb ? 2 : 0) : kSampleSlots + lane] = v2d{p.re, p.im};
             }
-            ki_b = coef_i(r, a_cur.g);
-            cd vp, vq;
-            out_row(r, a_cur, ki_b, a_hbp_m, ubp_p, hbp_p, vp, vq, 0);
-            store_mid(r, vp, vq);
-            const Ang gr = a_cur.g;
-            a_hbp_m = a_cur.hbp;
-            a_cur = a_nxt;
-            if (r < j0) {  // step B's halo row j0-1
-                const Row h = fresh(r, vp, vq, b_ubp_m, false, gr, kh_a, 1);
-                sample(r, h.p, acc_mid);
-                b_ubp_m = h.ubp;
-                b_hbp_m = h.hbp;
-            } else {
-                b_cur = fresh(r, vp, vq, b_ubp_m, true, gr, kh_a, 1);
-                sample(r, b_cur.p, acc_mid);
-                if (r == 0) b_hbp_m = cscale(sg, b_cur.hbp);
+            const cd pr = from_right(p), qr = from_right(q);
+            n.U = cadd(p, pr);
+            const cd V = cadd(q, qr), dp = csub(pr, p), dq = csub(qr, q);
+            const cd H = stage1_phi(c.h.b, A.hdt, n.U, V, dp), Hl = from_left(H);
+            n.S = cadd(H, Hl);
+            const cd D = csub(H, Hl);
+            if constexpr (FIRST) {
+                // the step's first row: at the pole its previous one is its
+                // ghost; elsewhere nothing formed from the previous one is used
+                if (j == STEPS - 1) {
+                    um = cscale(sg, n.U);
+                    sm = cscale(sg, n.S);
+                }
+            } else if constexpr (CHECK) {  // the last row's next one is its ghost
+                n.U = pick(t == nth, cscale(sg, um), n.U);
+                n.S = pick(t == nth, cscale(sg, sm), n.S);
             }
-            kh_a = kh_n;
-        };
-        prologue_row(aS, pp[2], pq[2]);                    // one or two rows,
-        if (j0 > aS) prologue_row(aS + 1, pp[3], pq[3]);  // wavefront-uniform
-    }
-
-    // ---- main sweep: A completes row r (reading row r+1 from the ring), B
-    // completes row r-1 --------------------------------------------------
-    Ang g_next = ang_row(j0 + 2);
-
-    // Step A completes row r (reading row r+1 from the ring), step B row
-    // r-1.  The row states (A's and B's rows, the carried coefficient sets)
-    // live in two copies that swap roles from row to row: ac/bc/khc/kic
-    // hold row r's, the next row's arrive in an/bn/khn/kin.
-    static_assert(kRowsInFlight2 == 2, "the row loop takes rows in pairs");
-    // POLE: row r may be the grid's last (so may the pair loop's second row, in the last chunk)
-    auto step_row = [&](int r, cd& rp, cd& rq, Row& ac, Row& an, Row& bc, Row& bn, Coef& khc, Coef& khn, Coef& kic,
-                        Coef& kin, bool pole) {
-        cd ubp_p, hbp_p;
-        const Ang g1 = g_next;
-        g_next = ang_row(r + 2);
-        if (!pole || r + 1 < nth) {
-            khn = coef_h(r + 1, g1);
-            an = fresh(r + 1, rp, rq, ac.ubp, true, g1, khn, 0);
-            sample(r + 1, an.p, acc_in);
-            ubp_p = an.ubp;
-            hbp_p = an.hbp;
-        } else {
-            ubp_p = cscale(sg, ac.ubp);
-            hbp_p = cscale(sg, ac.hbp);
-            an = ac;  // unused: the sweep ends with this row
-            khn = khc;
+            const cd dU = csub(n.U, um), dS = csub(n.S, sm);
+            // row t - 1 is complete
+            const cd HQ = fma_real(d.h.wp, dU, s.X), HQl = from_left(HQ);
+            const cd SQ = cadd(HQ, HQl), DQ = csub(HQ, HQl);
+            cd np = fma_real(A.qdt, SQ, s.P);
+            cd nq = cadd(s.Q, stage2_late(d.i.b, d.i.tr, d.i.ti, d.i.wp, SQ, DQ, dS));
+            // row t, up to its next-row terms
+            cd e1 = stage1_inc(c.h, n.U, V, dp, dq, dU);
+            cd e2 = stage2_early(c.i, n.S, D, dS);
+            if constexpr (SRC) {
+                const size_t o = (size_t)min(max(t, 0), nth - 1) * P;
+                e1 = cadd(e1, source(src_h, o + hi, A.sf[4 * j], A.sf[4 * j + 1]));
+                e2 = cadd(e2, source(src_i, o + ci, A.sf[4 * j + 2], A.sf[4 * j + 3]));
+            }
+            n.X = cadd(V, e1);
+            n.P = fma_real(-c.i.b, D, p);
+            n.Q = cadd(q, e2);
+            s = n;
+            if constexpr (CHECK) {
+                np = pick(boundary, cd{0.0, 0.0}, np);
+                nq = pick(boundary, cd{0.0, 0.0}, nq);
+            }
+            p = np;
+            q = nq;
+            if (j == 0) {
+                // The next row's scalar loads, after this row's LDS reads:
+                // the two share a counter and return out of order, so a wait
+                // for LDS reads with a scalar load outstanding waits for both.
+                __builtin_amdgcn_sched_barrier(kAllButScalarLoads);
+                g_next = ang_row(r + 1);
+            }
         }
-        load_row(r + 1 + kRowsInFlight2, rp, rq);
-        kin = coef_i(r, ac.g);
-        cd vp, vq;
-        out_row(r, ac, kin, a_hbp_m, ubp_p, hbp_p, vp, vq, 0);
-        store_mid(r, vp, vq);
-        a_hbp_m = ac.hbp;
-
-        bn = fresh(r, vp, vq, bc.ubp, true, ac.g, khc, 1);
-        sample(r, bn.p, acc_mid);
-        cd wp, wq;
-        out_row(r - 1, bc, kic, b_hbp_m, bn.ubp, bn.hbp, wp, wq, 1);
-        put_row(u_out, r - 1, wp, wq, std::integral_constant<int, KEEP>{});
-        b_hbp_m = bc.hbp;
-    };
-    // the grid's last row: step B with the pole ghost row
-    auto last_row = [&](const Row& bc, const Coef& kic) {
-        cd wp, wq;
-        out_row(nth - 1, bc, kic, b_hbp_m, cscale(sg, bc.ubp), cscale(sg, bc.hbp), wp, wq, 1);
-        put_row(u_out, nth - 1, wp, wq, std::integral_constant<int, KEEP>{});
+        load_row(r + kAhead, rp, rq);
+        if constexpr (STEPS == K) put_row(u_out, r - K, p, q, Const<KEEP>{});
+        __builtin_amdgcn_sched_barrier(0);  // rows stay apart: scheduled across them, they need more registers
     };
 
-    Row a_oth, b_oth;
-    Coef kh_oth, ki_oth;
-    int r0 = j0 + 1;
-    // Enter the row loop as each of its iterations ends: the ring's first
-    // row loaded, its second still in flight.  The compiler's waits at the
-    // loop head must suit both ways in; without this they drain the ring in
-    // every iteration.  (Unconditional: a wait under the loop's own guard is
-    // not seen as one by the compiler.)
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(2));
-    for (; r0 + 1 <= aE; r0 += 2) {
-        step_row(r0, bp[0], bq[0], a_cur, a_oth, b_cur, b_oth, kh_a, kh_oth, ki_b, ki_oth, true);
-        step_row(r0 + 1, bp[1], bq[1], a_oth, a_cur, b_oth, b_cur, kh_oth, kh_a, ki_oth, ki_b, true);
-    }
-    // at most two rows left, the last of them possibly the pole row
-    if (r0 <= aE) {
-        step_row(r0, bp[0], bq[0], a_cur, a_oth, b_cur, b_oth, kh_a, kh_oth, ki_b, ki_oth, true);
-        if (r0 + 1 <= aE) {
-            step_row(r0 + 1, bp[1], bq[1], a_oth, a_cur, b_oth, b_cur, kh_oth, kh_a, ki_oth, ki_b, true);
-            if (j1 == nth) last_row(b_cur, ki_b);
-        } else if (j1 == nth) {
-            last_row(b_oth, ki_oth);
+    // the first K rows: one step more takes its first row each time
+    int r = rs0;
+    auto head = [&](auto self, auto i) {
+        constexpr int I = decltype(i)::value;
+        if constexpr (I < K) {
+            iteration(r, bp[I % kAhead], bq[I % kAhead], Const<I % kRing>{}, Const<I + 1>{}, Const<2>{});
+            ++r;
+            self(self, Const<I + 1>{});
         }
-    } else if (j1 == nth) {
-        last_row(b_cur, ki_b);
-    }
+    };
+    head(head, Const<0>{});
+    auto rows = [&](auto self, auto u, auto check) {
+        constexpr int I = decltype(u)::value + K;
+        if constexpr (I < K + kRing) {
+            iteration(r, bp[I % kAhead], bq[I % kAhead], Const<I % kRing>{}, Const<K>{}, check);
+            ++r;
+            self(self, Const<I - K + 1>{}, check);
+        }
+    };
+    while (r + kRing - 1 <= rM) rows(rows, Const<0>{}, Const<0>{});
+    while (r <= rE) rows(rows, Const<0>{}, Const<1>{});
 
-    if (e_id >= 0 && lane == e_lane) {
-        if (series_in != nullptr) series_in[e_id] = double2{acc_in.re, acc_in.im};
-        if (series_mid != nullptr) series_mid[e_id] = double2{acc_mid.re, acc_mid.im};
+    if (e_id >= 0 && lane < K) {
+        // lane j: the sample of step j's input
+        double2* out = lane == 0 ? series_in : series_mid ? series_mid + (size_t)(lane - 1) * A.n_ext : nullptr;
+        if (out != nullptr) {
+            cd w = {0.0, 0.0};
+            auto add = [&](double wt, v2d a, v2d b) {
+                w.re = fma(wt, fma(e_wr, b.x - a.x, a.x), w.re);
+                w.im = fma(wt, fma(e_wr, b.y - a.y, a.y), w.im);
+            };
+            add(e_wa, smp[4 * lane], smp[4 * lane + 1]);
+            if (e_rb >= 0) add(e_wb, smp[4 * lane + 2], smp[4 * lane + 3]);
+            out[e_id] = double2{w.re, w.im};
+        }
     }
 }
 
-// LDS for the radial factors of the two-step kernels: one slice of
-// 2 x kNumRad x 64 doubles (13 KB) per wavefront, sized at launch.
-constexpr size_t kRadSliceBytes = 2 * kNumRad * kWave * sizeof(double);
 
-// SRC: the inhomogeneous variant (source profile src_i, src_h; time factors in A.sf).
-template <bool KERR, bool SRC, int KEEP>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4)))
-    lw_step2_kernel(const double2* __restrict__ u_in, double2* __restrict__ u_out, const double* __restrict__ rad,
-                    const double* __restrict__ ang, const double* __restrict__ uci, const double* __restrict__ uch,
-                    const ExtPoint* __restrict__ ext, double2* __restrict__ series_in,
-                    double2* __restrict__ series_mid, double2* __restrict__ u_mid, const double2* __restrict__ src_i,
-                    const double2* __restrict__ src_h, StepScalars A) {
+// A tile of a single-grid launch.  SRC: the inhomogeneous variant (source
+// profile src_i, src_h; time factors in A.sf).
+template <int K, bool KERR, bool SRC, int KEEP>
+__device__ __forceinline__ void pass_tile(const double2* __restrict__ u_in, double2* __restrict__ u_out,
+                                          const double* __restrict__ rad, const double* __restrict__ ang,
+                                          const double* __restrict__ uci, const double* __restrict__ uch,
+                                          const ExtPoint* __restrict__ ext, double2* __restrict__ series_in,
+                                          double2* __restrict__ series_mid, double2* __restrict__ win,
+                                          const double2* __restrict__ src_i, const double2* __restrict__ src_h,
+                                          const StepScalars& A, double* rad_s) {
     const int lane = threadIdx.x & (kWave - 1);
     const int wpb = blockDim.x / kWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -666,22 +345,32 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4))
         const int x = blockIdx.x % 8, q = (blockIdx.x / 8) * wpb + wave;
         const int s_lo = x * A.n_strips / 8, n_x = (x + 1) * A.n_strips / 8 - s_lo;
         if (n_x == 0) return;  // fewer strips than XCDs
-        if (A.order == kTileOrderXcdStrip) {
-            strip = s_lo + q % n_x;
-            chunk = q / n_x;
-        } else {
-            strip = s_lo + q / A.n_chunks;
-            chunk = q % A.n_chunks;
-            if (strip >= s_lo + n_x) return;
-        }
+        strip = s_lo + q % n_x;
+        chunk = q / n_x;
     }
-    extern __shared__ double rad_s[];
     if (chunk >= A.n_chunks) return;  // tiles beyond the last
-    sweep_tile2<KERR, SRC, KEEP>((gin_t)u_in, (gout_t)u_out, (ctab_t)rad, (ctab_t)ang, (ctab_t)uci, (ctab_t)uch,
-                           (cext_t)ext, series_in, series_mid, (gout_t)u_mid,
-                           (lds_t)(rad_s + (threadIdx.x / kWave) * 2 * kNumRad * kWave), A, strip, chunk, lane,
-                           (gin_t)src_i, (gin_t)src_h);
+    sweep<K, KERR, SRC, KEEP>((gin_t)u_in, (gout_t)u_out, (ctab_t)rad, (ctab_t)ang, (ctab_t)uci, (ctab_t)uch,
+                              (cext_t)ext, series_in, series_mid, (gout_t)win,
+                              (lds_t)(rad_s + (threadIdx.x / kWave) * kSliceDoubles), A, strip, chunk, lane,
+                              (gin_t)src_i, (gin_t)src_h);
 }
+
+#define TEUK_PASS_KERNEL(NAME, K)                                                                                     \
+    template <bool KERR, bool SRC, int KEEP>                                                                          \
+    __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4)))                                \
+        NAME(const double2* __restrict__ u_in, double2* __restrict__ u_out, const double* __restrict__ rad,           \
+             const double* __restrict__ ang, const double* __restrict__ uci, const double* __restrict__ uch,          \
+             const ExtPoint* __restrict__ ext, double2* __restrict__ series_in, double2* __restrict__ series_mid,     \
+             double2* __restrict__ win, const double2* __restrict__ src_i, const double2* __restrict__ src_h,         \
+             StepScalars A) {                                                                                         \
+        extern __shared__ double rad_s[];                                                                             \
+        pass_tile<K, KERR, SRC, KEEP>(u_in, u_out, rad, ang, uci, uch, ext, series_in, series_mid, win, src_i, src_h, \
+                                      A, rad_s);                                                                      \
+    }
+TEUK_PASS_KERNEL(lw_step_kernel, 1)
+TEUK_PASS_KERNEL(lw_step2_kernel, 2)
+TEUK_PASS_KERNEL(lw_step3_kernel, 3)
+#undef TEUK_PASS_KERNEL
 
 // Small grids: k = A.bsteps steps in one launch.  A workgroup holds
 // A.bcols = W + 2k consecutive columns by all ntheta rows in LDS, one point
@@ -727,9 +416,10 @@ __global__ void __launch_bounds__(1024)
 
     cd p = ld(u_in, (size_t)t * P + ci), q = ld(u_in, (size_t)t * P + ci + A.plane);
     const Ang G = load_ang(ang, nth, t);
-    const Rad Rh = load_rad(rad, P, 1, hi), Ri = load_rad(rad, P, 0, ci);
-    const Coef kh = kerr_coef(Rh, G, kerr_sigma(Rh, G));
-    const Coef ki = kerr_coef(Ri, G, kerr_sigma(Ri, G));
+    const SRad Rh = srad_of([&](int f) { return rad[((size_t)f * 2 + 1) * P + hi]; });
+    const SRad Ri = srad_of([&](int f) { return rad[((size_t)f * 2 + 0) * P + ci]; });
+    const Stage kh = stage_coef(Rh, G, ssigma(Rh, G), A.kap_h);
+    const Stage ki = stage_coef(Ri, G, ssigma(Ri, G), A.kap_i);
     sp[me] = p;
     sq[me] = q;
     if ((int)threadIdx.x < A.n_ext) sx[threadIdx.x] = ext[threadIdx.x];
@@ -750,26 +440,19 @@ __global__ void __launch_bounds__(1024)
         // half-step, with the Phi averages of rows t -/+ 1 (or the pole
         // ghost rows) formed here from the state; samples
         const cd pr = sp[t * B + jr], qr = sq[t * B + jr];
-        const cd ubp = cavg(p, pr);
-        const cd ubq = cavg(q, qr);
-        const cd dp = csub(pr, p);
-        const double tb = A.hdt_dr * kh.b;
-        const cd hp = {fma(-tb, dp.re, fma(A.hdt, ubq.re, ubp.re)), fma(-tb, dp.im, fma(A.hdt, ubq.im, ubp.im))};
-        const cd dq = csub(qr, q);
-        sh[me] = hp;
+        const cd U = cadd(p, pr), V = cadd(q, qr), dp = csub(pr, p), dq = csub(qr, q);
+        const cd H = stage1_phi(kh.b, A.hdt, U, V, dp);
+        sh[me] = H;
         for (unsigned d = duty; d != 0; d &= d - 1) {
             const int b = __builtin_ctz(d);
             const double wr = sx[b >> 1].wr;
             se[b] = {fma(wr, pr.re - p.re, p.re), fma(wr, pr.im - p.im, p.im)};
         }
-        const cd um = (t == 0) ? cscale(sg, ubp) : cavg(sp[me - B], sp[(t - 1) * B + jr]);
-        const cd ubp_p = (t == nth - 1) ? cscale(sg, ubp) : cavg(sp[me + B], sp[(t + 1) * B + jr]);
-        const cd dq1 = d_pi(kh, dp, dq);
-        const cd s1 = s_pi(kh, um, ubp, cd{0.0, 0.0}, ubq);
-        const cd x = {fma(A.hdt, s1.re, fma(-A.hdt_dr, dq1.re, ubq.re)), fma(A.hdt, s1.im, fma(-A.hdt_dr, dq1.im, ubq.im))};
-        const double wp = A.hdt * (kh.a2s + kh.a1s);
-        const cd hq = {fma(wp, ubp_p.re, x.re), fma(wp, ubp_p.im, x.im)};
-        shq[me] = hq;
+        const cd Um = (t == 0) ? cscale(sg, U) : cadd(sp[me - B], sp[(t - 1) * B + jr]);
+        const cd Up = (t == nth - 1) ? cscale(sg, U) : cadd(sp[me + B], sp[(t + 1) * B + jr]);
+        const cd X = cadd(V, stage1_inc(kh, U, V, dp, dq, csub(U, Um)));
+        const cd HQ = fma_real(kh.wp, csub(Up, U), X);
+        shq[me] = HQ;
         __syncthreads();
 
         // stage 2 at (i, t); one thread per point forms its sample
@@ -785,19 +468,15 @@ __global__ void __launch_bounds__(1024)
                 sbuf[s * kMaxBlockExt + threadIdx.x] = acc;
             }
         }
-        const cd hpl = sh[t * B + jl];
-        const cd hbp = cavg(hp, hpl);
-        const cd dhp = csub(hp, hpl);
-        const cd hbp_m = (t == 0) ? cscale(sg, hbp) : cavg(sh[me - B], sh[(t - 1) * B + jl]);
-        const cd hbp_p = (t == nth - 1) ? cscale(sg, hbp) : cavg(sh[me + B], sh[(t + 1) * B + jl]);
-        const cd hql = shq[t * B + jl];
-        const cd hbq = cavg(hq, hql);
-        const cd dhq = csub(hq, hql);
-        const double tb2 = A.dt_dr * ki.b;
-        cd np = {fma(-tb2, dhp.re, fma(A.dt, hbq.re, p.re)), fma(-tb2, dhp.im, fma(A.dt, hbq.im, p.im))};
-        const cd dq2 = d_pi(ki, dhp, dhq);
-        const cd s2 = s_pi(ki, hbp_m, hbp, hbp_p, hbq);
-        cd nq = {fma(A.dt, s2.re, fma(-A.dt_dr, dq2.re, q.re)), fma(A.dt, s2.im, fma(-A.dt_dr, dq2.im, q.im))};
+        const cd Hl = sh[t * B + jl];
+        const cd S = cadd(H, Hl), D = csub(H, Hl);
+        const cd Sm = (t == 0) ? cscale(sg, S) : cadd(sh[me - B], sh[(t - 1) * B + jl]);
+        const cd Sp = (t == nth - 1) ? cscale(sg, S) : cadd(sh[me + B], sh[(t + 1) * B + jl]);
+        const cd HQl = shq[t * B + jl];
+        const cd SQ = cadd(HQ, HQl), DQ = csub(HQ, HQl);
+        cd np = fma_real(A.qdt, SQ, fma_real(-ki.b, D, p));
+        cd nq = cadd(cadd(q, stage2_early(ki, S, D, csub(S, Sm))),
+                     stage2_late(ki.b, ki.tr, ki.ti, ki.wp, SQ, DQ, csub(Sp, S)));
         if (boundary) {
             np = {0.0, 0.0};
             nq = {0.0, 0.0};
@@ -830,39 +509,16 @@ __global__ void zero_ints_kernel(int* p, int n) {
     if (i < n) p[i] = 0;
 }
 
-template <bool KERR, bool SRC, int KEEP>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(TEUK_WAVES_PER_SIMD, 8)))
-    lw_step_kernel(const double2* __restrict__ u_in, double2* __restrict__ u_out, const double* __restrict__ rad,
-                   const double* __restrict__ ang, const double* __restrict__ uci, const double* __restrict__ uch,
-                   const ExtPoint* __restrict__ ext, double2* __restrict__ series, double2* __restrict__ win,
-                   const double2* __restrict__ src_i, const double2* __restrict__ src_h, StepScalars A) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wpb = blockDim.x / kWave;
-    // Tiles are numbered strip-fastest, so the wavefronts of a workgroup take
-    // neighbouring strips of one theta chunk (their halo columns overlap).
-    // Workgroups are left in dispatch order, which deals them round-robin
-    // over the XCDs: measured faster for these streaming passes than giving
-    // each XCD a contiguous range (whose last, short theta chunk then falls
-    // on one XCD).  The tile index is made explicitly wavefront-uniform so
-    // that everything derived from it (rows, table reads, loop control) is
-    // scalar.
-    const int tile = __builtin_amdgcn_readfirstlane(blockIdx.x * wpb + (threadIdx.x / kWave));
-    const int strip = tile % A.n_strips;
-    const int chunk = tile / A.n_strips;
-    if (chunk >= A.n_chunks) return;  // tiles beyond the last
-    sweep_tile<KERR, SRC, KEEP>((gin_t)u_in, (gout_t)u_out, (ctab_t)rad, (ctab_t)ang, (ctab_t)uci, (ctab_t)uch,
-                          (cext_t)ext, series, (gout_t)win, A, strip, chunk, lane, (gin_t)src_i, (gin_t)src_h);
-}
-
 // Many grids in one persistent launch: the tiles of all members form one
 // work list (member k owns tiles [tile_begin_k, tile_begin_{k+1})); each
 // wavefront walks the list with a grid-wide stride.  All tiles have the
-// same shape (62 columns x `rows` rows, ragged only at a member's edges),
+// same shape (64 - 2K columns x `rows` rows, ragged only at a member's edges),
 // so the static stride balances uneven members.  `parity` selects which of
 // each member's two state buffers is the input.
-template <int KEEP>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(TEUK_WAVES_PER_SIMD, 8)))
-    lw_batch_kernel(const BatchMember* __restrict__ members, int n_members, int total_tiles, int parity) {
+template <int K, int KEEP>
+__device__ __forceinline__ void batch_tiles(const BatchMember* __restrict__ members, int n_members, int total_tiles,
+                                            int parity, double* rad_s) {
+    const lds_t rs = (lds_t)(rad_s + (threadIdx.x / kWave) * kSliceDoubles);
     const int lane = threadIdx.x & (kWave - 1);
     const int wpb = blockDim.x / kWave;
     const int nwaves = gridDim.x * wpb;
@@ -871,50 +527,34 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(TEUK_W
         int lo = 0, hi = n_members - 1;  // last member with tile_begin <= tile
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
-            if (members[mid].tile_begin <= tile)
+            if (members[mid].tile_begin[K - 1] <= tile)
                 lo = mid;
             else
                 hi = mid - 1;
         }
         const BatchMember& M = members[lo];
-        const int local = tile - M.tile_begin;
-        const int strip = local % M.k.n_strips;
-        const int chunk = local / M.k.n_strips;
-        sweep_tile<true, false, KEEP>((gin_t)M.u[parity], (gout_t)M.u[1 - parity], (ctab_t)M.rad, (ctab_t)M.ang, nullptr,
-                         nullptr, nullptr, nullptr, nullptr, M.k, strip, chunk, lane);
+        const int local = tile - M.tile_begin[K - 1];
+        StepScalars k = M.k;
+        k.n_strips = M.strips[K - 1];
+        const int strip = local % k.n_strips;
+        const int chunk = local / k.n_strips;
+        sweep<K, true, false, KEEP>((gin_t)M.u[parity], (gout_t)M.u[1 - parity], (ctab_t)M.rad, (ctab_t)M.ang, nullptr,
+                                    nullptr, nullptr, nullptr, nullptr, nullptr, rs, k, strip, chunk, lane, nullptr,
+                                    nullptr);
     }
 }
 
-// The batched launch of the two-step pass: as lw_batch_kernel, over the
-// members' two-step tiles.
-template <int KEEP>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4)))
-    lw_batch2_kernel(const BatchMember* __restrict__ members, int n_members, int total_tiles, int parity) {
-    extern __shared__ double rad_s[];
-    const lds_t rs = (lds_t)(rad_s + (threadIdx.x / kWave) * 2 * kNumRad * kWave);
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wpb = blockDim.x / kWave;
-    const int nwaves = gridDim.x * wpb;
-    const int w0 = __builtin_amdgcn_readfirstlane(blockIdx.x * wpb + (threadIdx.x / kWave));
-    for (int tile = w0; tile < total_tiles; tile += nwaves) {
-        int lo = 0, hi = n_members - 1;  // last member with tile_begin2 <= tile
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (members[mid].tile_begin2 <= tile)
-                lo = mid;
-            else
-                hi = mid - 1;
-        }
-        const BatchMember& M = members[lo];
-        const int local = tile - M.tile_begin2;
-        StepScalars k = M.k;
-        k.n_strips = M.n_strips2;
-        const int strip = local % k.n_strips;
-        const int chunk = local / k.n_strips;
-        sweep_tile2<true, false, KEEP>((gin_t)M.u[parity], (gout_t)M.u[1 - parity], (ctab_t)M.rad, (ctab_t)M.ang, nullptr,
-                          nullptr, nullptr, nullptr, nullptr, nullptr, rs, k, strip, chunk, lane);
+#define TEUK_BATCH_KERNEL(NAME, K)                                                              \
+    template <int KEEP>                                                                         \
+    __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4)))          \
+        NAME(const BatchMember* __restrict__ members, int n_members, int total_tiles, int parity) { \
+        extern __shared__ double rad_s[];                                                       \
+        batch_tiles<K, KEEP>(members, n_members, total_tiles, parity, rad_s);                   \
     }
-}
+TEUK_BATCH_KERNEL(lw_batch_kernel, 1)
+TEUK_BATCH_KERNEL(lw_batch2_kernel, 2)
+TEUK_BATCH_KERNEL(lw_batch3_kernel, 3)
+#undef TEUK_BATCH_KERNEL
 
 // The state is stored as two planes in one buffer: u[f * nth * pitch + j *
 // pitch + i], f = 0 for Phi and 1 for Pi.
@@ -1037,19 +677,46 @@ __global__ void pitch_copy_kernel(const double* __restrict__ src, double* __rest
 
 }  // namespace
 
-hipError_t launch_step(const StepArgs& a, bool kerr, int waves_per_block, hipStream_t s) {
-    const int nb = (a.k.n_strips * a.k.n_chunks + waves_per_block - 1) / waves_per_block;
+template <int K>
+static hipError_t launch_pass_k(const StepArgs& a, bool kerr, int waves_per_block, hipStream_t s) {
+    // XCD orders: 8 equal shares of workgroups, each covering the tiles of
+    // the largest XCD run of strips
+    const int per_xcd = (a.k.n_strips + 7) / 8 * a.k.n_chunks;
+    const int nb = a.k.order == kTileOrderDispatch
+                       ? (a.k.n_strips * a.k.n_chunks + waves_per_block - 1) / waves_per_block
+                       : 8 * ((per_xcd + waves_per_block - 1) / waves_per_block);
     const dim3 block(kWave * waves_per_block), grid(nb);
     const bool src = a.src_i != nullptr;
-    const int keep = a.k.keep ? 1 : 0;
-    auto pick = [&](auto k0, auto k1) { return keep ? k1 : k0; };
-    auto kern = kerr ? (src ? pick(lw_step_kernel<true, true, 0>, lw_step_kernel<true, true, 1>)
-                            : pick(lw_step_kernel<true, false, 0>, lw_step_kernel<true, false, 1>))
-                     : (src ? pick(lw_step_kernel<false, true, 0>, lw_step_kernel<false, true, 1>)
-                            : pick(lw_step_kernel<false, false, 0>, lw_step_kernel<false, false, 1>));
-    hipLaunchKernelGGL(kern, grid, block, 0, s, a.u_in, a.u_out, a.rad, a.ang, a.uci, a.uch,
-                       a.ext, a.series, a.win, a.src_i, a.src_h, a.k);
-    return hipGetLastError();
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, block, waves_per_block * kRadSliceBytes, s, a.u_in, a.u_out, a.rad,
+                           a.ang, a.uci, a.uch, a.ext, a.series, a.series_mid, a.win, a.src_i, a.src_h, a.k);
+        return hipGetLastError();
+    };
+    auto pick = [&](auto k0, auto k1) { return go(a.k.keep ? k1 : k0); };
+#define TEUK_PICK(KERR, SRC)                                                                       \
+    if constexpr (K == 1) return pick(lw_step_kernel<KERR, SRC, 0>, lw_step_kernel<KERR, SRC, 1>); \
+    if constexpr (K == 2) return pick(lw_step2_kernel<KERR, SRC, 0>, lw_step2_kernel<KERR, SRC, 1>); \
+    if constexpr (K == 3) return pick(lw_step3_kernel<KERR, SRC, 0>, lw_step3_kernel<KERR, SRC, 1>);
+    if constexpr (K < 3) {
+        if (src) {
+            if (kerr) {
+                TEUK_PICK(true, true)
+            }
+            TEUK_PICK(false, true)
+        }
+        if (!kerr) {
+            TEUK_PICK(false, false)
+        }
+    }
+    TEUK_PICK(true, false)
+#undef TEUK_PICK
+}
+
+hipError_t launch_pass(const StepArgs& a, int steps, bool kerr, int waves_per_block, hipStream_t s) {
+    if (steps == 3 && kerr && a.src_i == nullptr) return launch_pass_k<3>(a, kerr, waves_per_block, s);
+    if (steps == 2) return launch_pass_k<2>(a, kerr, waves_per_block, s);
+    if (steps == 1) return launch_pass_k<1>(a, kerr, waves_per_block, s);
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_block(const StepArgs& a, hipStream_t s) {
@@ -1065,42 +732,22 @@ hipError_t launch_block(const StepArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_step2(const StepArgs& a, bool kerr, int waves_per_block, hipStream_t s) {
-    // XCD orders: 8 equal shares of workgroups, each covering the tiles of
-    // the largest XCD run of strips
-    const int per_xcd = (a.k.n_strips + 7) / 8 * a.k.n_chunks;
-    const int nb = a.k.order == kTileOrderDispatch
-                       ? (a.k.n_strips * a.k.n_chunks + waves_per_block - 1) / waves_per_block
-                       : 8 * ((per_xcd + waves_per_block - 1) / waves_per_block);
-    const dim3 block(kWave * waves_per_block), grid(nb);
-    const bool src = a.src_i != nullptr;
-    const int keep = a.k.keep ? 1 : 0;
-    auto pick = [&](auto k0, auto k1) { return keep ? k1 : k0; };
-    auto kern = kerr ? (src ? pick(lw_step2_kernel<true, true, 0>, lw_step2_kernel<true, true, 1>)
-                            : pick(lw_step2_kernel<true, false, 0>, lw_step2_kernel<true, false, 1>))
-                     : (src ? pick(lw_step2_kernel<false, true, 0>, lw_step2_kernel<false, true, 1>)
-                            : pick(lw_step2_kernel<false, false, 0>, lw_step2_kernel<false, false, 1>));
-    hipLaunchKernelGGL(kern, grid, block, kerr ? waves_per_block * kRadSliceBytes : 0, s, a.u_in, a.u_out, a.rad, a.ang,
-                       a.uci, a.uch, a.ext, a.series, a.series_mid, a.win, a.src_i, a.src_h, a.k);
-    return hipGetLastError();
-}
-
 hipError_t launch_zero_ints(int* p, int n, hipStream_t s) {
     hipLaunchKernelGGL(zero_ints_kernel, dim3((n + 255) / 256), dim3(256), 0, s, p, n);
     return hipGetLastError();
 }
 
 hipError_t launch_batch(const BatchMember* members, int n_members, int total_tiles, int parity, int n_blocks,
-                        int waves_per_block, bool two, bool keep, hipStream_t s) {
-    if (two) {
-        const int w = waves_per_block < 4 ? waves_per_block : 4;
-        hipLaunchKernelGGL(keep ? lw_batch2_kernel<1> : lw_batch2_kernel<0>, dim3(n_blocks), dim3(kWave * w),
-                           w * kRadSliceBytes, s, members, n_members, total_tiles, parity);
-    } else {
-        hipLaunchKernelGGL(keep ? lw_batch_kernel<1> : lw_batch_kernel<0>, dim3(n_blocks),
-                           dim3(kWave * waves_per_block), 0, s, members, n_members, total_tiles, parity);
-    }
-    return hipGetLastError();
+                        int waves_per_block, int steps, bool keep, hipStream_t s) {
+    const int w = waves_per_block < 4 ? waves_per_block : 4;
+    auto go = [&](auto k0, auto k1) {
+        hipLaunchKernelGGL(keep ? k1 : k0, dim3(n_blocks), dim3(kWave * w), w * kRadSliceBytes, s, members, n_members,
+                           total_tiles, parity);
+        return hipGetLastError();
+    };
+    if (steps == 3) return go(lw_batch3_kernel<0>, lw_batch3_kernel<1>);
+    if (steps == 2) return go(lw_batch2_kernel<0>, lw_batch2_kernel<1>);
+    return go(lw_batch_kernel<0>, lw_batch_kernel<1>);
 }
 
 hipError_t launch_import(const double2* src, double2* u, int f, int nr, int nth, int pitch, hipStream_t s) {

@@ -52,7 +52,7 @@ struct Layout {
     int pitch = 0;
     size_t state = 0;                 // bytes of one state [Phi, Pi][nth][pitch]
     size_t off_u[2]{};                // ping-pong state
-    size_t off_rad = 0, off_ang = 0;  // KERR tables
+    size_t off_rad = 0, off_srad = 0, off_ang = 0;  // KERR tables
     size_t off_uci = 0, off_uch = 0;  // USER tables
     size_t off_ext = 0, off_ext2 = 0, off_flag = 0;
     size_t total = 0;
@@ -100,6 +100,8 @@ Layout make_layout(const teuk_params* p) {
     }
     L.off_rad = o;
     o += align_up((size_t)kNumRad * 2 * L.pitch * sizeof(double));
+    L.off_srad = o;
+    o += align_up((size_t)kNumSRad * 2 * L.pitch * sizeof(double));
     L.off_ang = o;
     o += align_up((size_t)kNumAng * nth * sizeof(double));
     if (p->coef_mode == TEUK_COEF_USER) {
@@ -202,9 +204,9 @@ struct teuk_grid {
     int64_t steps = 0;
     int rows = 64;        // theta rows per wavefront tile
     int wpb = 4;          // wavefronts per workgroup
-    bool fused_ext = true;
-    int steps_per_pass = 2;  // 2: pairs of steps in one pass (temporal blocking)
-    bool fused_ext2 = true;  // extraction fusable with the two-step strips
+    int rows3 = 64, wpb3 = 4;  // the same of the three-step pass (teuk_set_tile sets both)
+    int steps_per_pass = 2;  // 2: several steps in one pass (temporal blocking)
+    bool fused[kMaxPassSteps] = {true, true, true};  // extraction fusable with the strips of passes of 1, 2, 3 steps
     int block_steps = 0;     // teuk_set_block_launch: steps per launch of the block pass (0: off)
     int block_cols = 0;      // columns a block-pass workgroup holds (0: not set)
     int64_t check_every = 0;  // teuk_set_finite_check: steps between device checks of the state (0: off)
@@ -212,7 +214,7 @@ struct teuk_grid {
     bool coef_set = false;
     // adjoint (teuk_enable_adjoint)
     char* aws = nullptr;      // adjoint workspace
-    size_t aoff_lam[2]{}, aoff_da = 0, aoff_slots = 0, aoff_sum = 0;
+    size_t aoff_lam[2]{}, aoff_da = 0, aoff_sda = 0, aoff_slots = 0, aoff_sum = 0;
     int adj_rows = 32, adj_wpb = 4, adj_chunks = 0, adj_strips = 0;  // spin-gradient and one-step kernels
     int adj2_rows = 32, adj2_chunks = 0;                              // two-step cotangent kernel
     int tan_rows = 32, tan_chunks = 0;                                // step-with-tangent kernel
@@ -243,8 +245,8 @@ bool fused_extraction_ok(const teuk_grid* g, int strip_cols = kStripCols, int ro
 }
 
 void update_fusion(teuk_grid* g) {
-    g->fused_ext = fused_extraction_ok(g);
-    g->fused_ext2 = fused_extraction_ok(g, kStripCols2);
+    for (int k = 1; k <= kMaxPassSteps; ++k)
+        g->fused[k - 1] = fused_extraction_ok(g, strip_cols(k), k == 3 ? g->rows3 : g->rows);
 }
 
 // Two states (a pass's input and output) up to this size stay in the
@@ -266,24 +268,40 @@ StepArgs step_args(const teuk_grid* g) {
     k.pitch = g->L.pitch;
     k.sigma = g->sigma;
     k.rows = g->rows;
-    k.n_strips = (k.nr + kStripCols - 1) / kStripCols;
     k.n_chunks = (k.nth + g->rows - 1) / g->rows;
     k.dt = g->p.dt;
     k.hdt = 0.5 * g->p.dt;
+    k.qdt = 0.25 * g->p.dt;
+    k.kap_h = 1.0 / k.hdt;
+    k.kap_i = 1.0 / k.qdt;
     k.dt_dr = g->p.dt / g->dr;
     k.hdt_dr = 0.5 * g->p.dt / g->dr;
     k.inv_dth2 = 1.0 / (g->dth * g->dth);
     k.inv_2dth = 1.0 / (2.0 * g->dth);
     k.plane = (int64_t)k.nth * k.pitch;
-    a.rad = g->at<double>(g->L.off_rad);
+    a.rad = g->at<double>(g->L.off_srad);
     a.ang = g->at<double>(g->L.off_ang);
     if (g->p.coef_mode == TEUK_COEF_USER) {
         a.uci = g->at<double>(g->L.off_uci);
         a.uch = g->at<double>(g->L.off_uch);
     }
     a.ext = g->at<ExtPoint>(g->L.off_ext);
-    k.n_ext = g->fused_ext ? g->p.n_extract : 0;
     k.keep = keeps_states(g) ? 1 : 0;
+    return a;
+}
+
+// Launch arguments of a pass of `steps` steps.  XCD runs of strips where each
+// XCD gets at least 8 (measured: 0.6-0.8 % faster on 25600 x 512 at 32-64 row
+// tiles, neutral on 6400 x 256).
+StepArgs pass_args(const teuk_grid* g, int steps) {
+    StepArgs a = step_args(g);
+    a.k.n_strips = (a.k.nr + strip_cols(steps) - 1) / strip_cols(steps);
+    if (steps == 3) {
+        a.k.rows = g->rows3;
+        a.k.n_chunks = (a.k.nth + g->rows3 - 1) / g->rows3;
+    }
+    a.k.n_ext = g->fused[steps - 1] ? g->p.n_extract : 0;
+    a.k.order = steps > 1 && a.k.n_strips >= 64 ? kTileOrderXcdStrip : kTileOrderDispatch;
     return a;
 }
 
@@ -324,6 +342,44 @@ void default_tile(int nr, int nth, int cus, int* rows, int* wpb) {
     const int64_t tiles = strips2 * ((nth + r - 1) / r);
     *rows = (int)r;
     *wpb = tiles < (int64_t)cus * 4 ? 1 : 4;
+}
+
+// Default tile of the K-step pass, K = 3.  A wavefront walks its tile's rows one after the other: K
+// rows to fill the steps, then the tile's rows and K more in groups of K + 1
+// (the unrolled rows), after a start worth about two rows (tables and first
+// rows).  Two wavefronts fit a SIMD, where they share its issue: a row takes
+// two units of time beside another wavefront and 1.3 alone.  Tiles beyond one
+// round of wavefronts wait for a slot; with several rounds the last, partly
+// filled one counts for less.  The height with the lowest such time is taken,
+// at most 128 rows (a shorter last tile wastes part of that).  Measured with
+// it (three steps, us per step, units in brackets): 6400 x 256 at 15 / 17 / 29
+// rows 13.3 (50) / 12.2 (50) / 12.3 (48), at 14 rows (a second round) 14.7;
+// 5003 x 197 at 9 / 10 / 13 rows 9.6 (34) / 10.9 (42) / 10.1 (42); 1600 x 128
+// at 2 / 4 / 8 rows 7.0 (26) / 5.1 (17) / 5.9 (22); 25600 x 512 at 57 / 103
+// rows 68 / 86.  Grids with fewer tiles than SIMDs take one wavefront per
+// workgroup, to spread over the CUs.
+void default_pass_tile(int nr, int nth, int cus, int K, int* rows, int* wpb) {
+    const int64_t strips = (nr + strip_cols(K) - 1) / strip_cols(K);
+    double best = 0.0;
+    int64_t best_tiles = 0;
+    for (int r = 1; r <= std::min(nth, 128); ++r) {
+        const int64_t tiles = strips * ((nth + r - 1) / r);
+        const double x = (double)tiles / (4.0 * cus);  // tiles per SIMD
+        const int its = 2 + K + (r + K + K) / (K + 1) * (K + 1);
+        double f = 1.3;  // one wavefront per SIMD
+        if (x > 1.0) {
+            const double rounds = std::ceil(0.5 * x), over = x - 2.0 * (rounds - 1.0);
+            const double whole = 2.0 * (rounds - 1.0) + (over > 1.0 ? 2.0 : 1.3);
+            f = x + (whole - x) / std::max(1.0, rounds - 1.0);
+        }
+        const double t = its * f;
+        if (r == 1 || t < best || (t == best && tiles < best_tiles)) {
+            best = t;
+            best_tiles = tiles;
+            *rows = r;
+        }
+    }
+    *wpb = best_tiles < (int64_t)cus * 4 ? 1 : 4;
 }
 
 // Default tile height of an adjoint kernel: the shortest tiles of which
@@ -450,9 +506,10 @@ int teuk_init_grid(const teuk_params* p, void* hip_stream, void* d_workspace, si
 
     // 1-D tables on the host; x at each position is kept for the
     // a-derivative tables (teuk_enable_adjoint)
-    std::vector<double> rad, ang((size_t)kNumAng * nth), xs;
+    std::vector<double> rad, srad, ang((size_t)kNumAng * nth), xs;
     if (p->coef_mode == TEUK_COEF_KERR) {
         rad.assign((size_t)kNumRad * 2 * L.pitch, 0.0);
+        srad.assign((size_t)kNumSRad * 2 * L.pitch, 0.0);
         xs.assign((size_t)2 * nr, 0.0);
         for (int kind = 0; kind < 2; ++kind) {
             const int npos = kind == 0 ? nr : nr - 1;
@@ -465,6 +522,10 @@ int teuk_init_grid(const teuk_params* p, void* hip_stream, void* d_workspace, si
                 double R[kNumRad];
                 radial_fields<double>(p->a, p->s, p->m, x, dth, R);
                 for (int f = 0; f < kNumRad; ++f) rad[((size_t)f * 2 + kind) * L.pitch + i] = R[f];
+                double S[kNumSRad];
+                const double d = (kind == 0 ? 0.5 : 1.0) * dt / dr, t = (kind == 0 ? 0.25 : 0.5) * dt;
+                stage_fields<double>(p->a, p->s, p->m, x, dth, d, t, S);
+                for (int f = 0; f < kNumSRad; ++f) srad[((size_t)f * 2 + kind) * L.pitch + i] = S[f];
             }
         }
     }
@@ -491,6 +552,7 @@ int teuk_init_grid(const teuk_params* p, void* hip_stream, void* d_workspace, si
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
             cus = 256;
         default_tile(nr, nth, cus, &g->rows, &g->wpb);
+        default_pass_tile(nr, nth, cus, 3, &g->rows3, &g->wpb3);
     }
     // The block pass: one thread per point of (columns x all rows).  Default
     // launch: over workgroups of up to 256, 512 or 1024 threads (at most 64
@@ -548,6 +610,8 @@ int teuk_init_grid(const teuk_params* p, void* hip_stream, void* d_workspace, si
     if (e == hipSuccess) e = hipMemsetAsync(g->ws + L.off_flag, 0, kAlign, s);  // status flags
     if (e == hipSuccess && !rad.empty())
         e = hipMemcpyAsync(g->ws + L.off_rad, rad.data(), rad.size() * sizeof(double), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess && !srad.empty())
+        e = hipMemcpyAsync(g->ws + L.off_srad, srad.data(), srad.size() * sizeof(double), hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
         e = hipMemcpyAsync(g->ws + L.off_ang, ang.data(), ang.size() * sizeof(double), hipMemcpyHostToDevice, s);
     if (e == hipSuccess && !g->ext.empty())
@@ -636,16 +700,16 @@ int step_n_impl(teuk_grid* g, int64_t n, void* d_series, void* d_window, const d
     if (int rc = set_device(g)) return rc;
     const int ne = g->p.n_extract;
     double2* series = (ne > 0) ? static_cast<double2*>(d_series) : nullptr;
-    StepArgs a = step_args(g);
-    if (h_f) {
-        a.src_i = reinterpret_cast<const double2*>(g->sws);
-        a.src_h = reinterpret_cast<const double2*>(g->sws + source_plane_bytes(g));
-    }
-    auto set_f = [&](StepScalars& k, int64_t step, int nsteps) {
-        if (h_f)
-            for (int j = 0; j < 4 * nsteps; ++j) k.sf[j] = h_f[4 * step + j];
-    };
     const bool kerr = g->p.coef_mode == TEUK_COEF_KERR;
+    StepArgs args[kMaxPassSteps];
+    for (int m = 1; m <= kMaxPassSteps; ++m) {
+        StepArgs& a = args[m - 1];
+        a = pass_args(g, m);
+        if (h_f) {
+            a.src_i = reinterpret_cast<const double2*>(g->sws);
+            a.src_h = reinterpret_cast<const double2*>(g->sws + source_plane_bytes(g));
+        }
+    }
     const ExtPoint* ext = g->at<ExtPoint>(g->L.off_ext);
     char* win = static_cast<char*>(d_window);
     auto window_state = [&](int64_t k) { return reinterpret_cast<double2*>(win + (size_t)k * g->L.state); };
@@ -664,20 +728,25 @@ int step_n_impl(teuk_grid* g, int64_t n, void* d_series, void* d_window, const d
         if (!win) cur = 1 - cur;
         in = out;
     };
-    // Pairs of steps run as one two-step pass (not the first step of a
-    // window run, which also copies its input).
-    const bool two = g->steps_per_pass == 2 && (ne == 0 || g->fused_ext2);
-    StepArgs a2 = a;
-    a2.k.n_strips = (a2.k.nr + kStripCols2 - 1) / kStripCols2;
-    a2.k.n_ext = ne;
-    // XCD runs of strips when each XCD gets at least 8 (measured: 0.6-0.8 %
-    // faster on 25600 x 512 at 32-64 row tiles, neutral on 6400 x 256)
-    a2.k.order = a2.k.n_strips >= 64 ? kTileOrderXcdStrip : kTileOrderDispatch;
-    const int wpb2 = std::min(g->wpb, 4);
+    // Steps run several to a pass: three where the pass has a kernel for it
+    // (Kerr coefficients, no source, no window, three rows or more) and no
+    // check falls between them, two otherwise.  A call's last
+    // four steps run as two and two rather than three and one, and the first
+    // step of a window run, which also copies its input, runs alone.
+    const bool multi = g->steps_per_pass == 2;
+    const bool fuse2 = multi && (!series || g->fused[1]);
+    const bool fuse3 = fuse2 && kerr && !h_f && !win && g->p.ntheta >= 3 && g->check_every == 0 &&
+                       (!series || g->fused[2]);
+    auto pass_steps = [&](int64_t k) -> int {
+        const int64_t left = n - k;
+        if (win && k == 0) return 1;
+        if (fuse3 && left >= 3 && left != 4) return 3;
+        return fuse2 && left >= 2 ? 2 : 1;
+    };
     // Sample of state j (after step j) goes to series row j-1.  Launches
-    // with fused extraction sample their input (and a pass its intermediate
-    // state); otherwise a separate pass samples each new state.
-    const bool fused = g->fused_ext;
+    // with fused extraction sample their input and a pass its intermediate
+    // states; otherwise a separate pass samples each new state.
+    const bool fused = g->fused[0];
     int64_t sampled = 0;
     InLoopCheck chk(g);
     auto extract_state = [&](const double2* u, int64_t j) -> int {
@@ -692,7 +761,7 @@ int step_n_impl(teuk_grid* g, int64_t n, void* d_series, void* d_window, const d
         if (block) {
             const int m = (int)std::min<int64_t>(g->block_steps, n - k);
             double2* out = next_buffer(k + m);
-            StepArgs ab = a;
+            StepArgs ab = step_args(g);
             ab.u_in = in;
             ab.u_out = out;
             ab.k.bsteps = m;
@@ -708,38 +777,29 @@ int step_n_impl(teuk_grid* g, int64_t n, void* d_series, void* d_window, const d
             if (int rc = chk.maybe(in)) return rc;
             continue;
         }
-        if (two && k + 2 <= n && !(win && k == 0)) {
-            double2* out = next_buffer(k + 2);
-            a2.u_in = in;
-            a2.u_out = out;
-            a2.win = win ? window_state(k + 1) : nullptr;
-            a2.series = (series && k > 0) ? series + (k - 1) * ne : nullptr;
-            a2.series_mid = series ? series + k * ne : nullptr;
-            set_f(a2.k, k, 2);
-            HIP_TRY(launch_step2(a2, kerr, wpb2, g->stream));
-            if (series) sampled = k + 1;
-            advance(out);
-            k += 2;
-            g->steps += 2;
-            if (int rc = chk.maybe(in)) return rc;
-        } else {
-            if (series && !fused && k > sampled)
-                if (int rc = extract_state(in, k)) return rc;
-            double2* out = next_buffer(k + 1);
-            a.u_in = in;
-            a.u_out = out;
-            a.win = (win && k == 0) ? window_state(0) : nullptr;
-            a.series = (series && fused && k > 0) ? series + (k - 1) * ne : nullptr;
-            set_f(a.k, k, 1);
-            HIP_TRY(launch_step(a, kerr, g->wpb, g->stream));
-            if (series && fused && k > 0) sampled = k;
-            advance(out);
-            k += 1;
-            g->steps += 1;
-            if (series && !fused)
-                if (int rc = extract_state(out, k)) return rc;
-            if (int rc = chk.maybe(in)) return rc;
-        }
+        const int m = pass_steps(k);
+        // a one-step launch that cannot sample leaves each new state to a
+        // separate pass
+        const bool sample = series && (m > 1 || fused);
+        if (series && !sample && k > sampled)
+            if (int rc = extract_state(in, k)) return rc;
+        double2* out = next_buffer(k + m);
+        StepArgs& a = args[m - 1];
+        a.u_in = in;
+        a.u_out = out;
+        a.win = !win ? nullptr : m == 1 ? (k == 0 ? window_state(0) : nullptr) : window_state(k + 1);
+        a.series = (sample && k > 0) ? series + (k - 1) * ne : nullptr;
+        a.series_mid = sample ? series + k * ne : nullptr;
+        if (h_f)
+            for (int j = 0; j < 4 * m; ++j) a.k.sf[j] = g->p.dt * h_f[4 * k + j];
+        HIP_TRY(launch_pass(a, m, kerr, std::min(m == 3 ? g->wpb3 : g->wpb, 4), g->stream));
+        if (sample) sampled = k + m - 1;
+        advance(out);
+        k += m;
+        g->steps += m;
+        if (series && !sample)
+            if (int rc = extract_state(out, k)) return rc;
+        if (int rc = chk.maybe(in)) return rc;
     }
     if (series && sampled < n)
         if (int rc = extract_state(in, n)) return rc;
@@ -920,8 +980,8 @@ int teuk_set_tile(teuk_grid* g, int32_t rows_per_tile, int32_t waves_per_block) 
         return fail(TEUK_E_INVALID_ARG, "rows_per_tile=%d outside [1, ntheta]", rows_per_tile);
     if (waves_per_block != 1 && waves_per_block != 2 && waves_per_block != 4 && waves_per_block != 8)
         return fail(TEUK_E_INVALID_ARG, "waves_per_block=%d not in {1, 2, 4, 8}", waves_per_block);
-    g->rows = rows_per_tile;
-    g->wpb = waves_per_block;
+    g->rows = g->rows3 = rows_per_tile;
+    g->wpb = g->wpb3 = waves_per_block;
     update_fusion(g);
     return TEUK_OK;
 }
@@ -1018,6 +1078,8 @@ void adjoint_layout(teuk_grid* g, size_t* total) {
     }
     g->aoff_da = o;
     o += align_up((size_t)kNumRad * 2 * g->L.pitch * sizeof(double));
+    g->aoff_sda = o;
+    o += align_up((size_t)kNumSRad * 2 * g->L.pitch * sizeof(double));
     g->aoff_slots = o;
     // one slot per tile of either adjoint tiling, for any tile rows
     const size_t strips2 = ((size_t)g->p.nr + kStripCols2 - 1) / kStripCols2;
@@ -1052,7 +1114,7 @@ int teuk_enable_adjoint(teuk_grid* g, void* d_adj_workspace, size_t bytes) {
     // the tortoise inversion and every radial factor), from the x that
     // teuk_init_grid solved for at each position
     const int nr = (int)g->p.nr;
-    std::vector<double> da((size_t)kNumRad * 2 * g->L.pitch, 0.0);
+    std::vector<double> da((size_t)kNumRad * 2 * g->L.pitch, 0.0), sda((size_t)kNumSRad * 2 * g->L.pitch, 0.0);
     for (int kind = 0; kind < 2; ++kind) {
         const int npos = kind == 0 ? nr : nr - 1;
         for (int i = 0; i < npos; ++i) {
@@ -1060,12 +1122,19 @@ int teuk_enable_adjoint(teuk_grid* g, void* d_adj_workspace, size_t bytes) {
             Dual R[kNumRad];
             radial_fields<Dual>(Dual(g->p.a, 1.0), g->p.s, g->p.m, x, g->dth, R);
             for (int f = 0; f < kNumRad; ++f) da[((size_t)f * 2 + kind) * g->L.pitch + i] = R[f].d;
+            Dual S[kNumSRad];
+            const double dt = g->p.dt;
+            const double d = (kind == 0 ? 0.5 : 1.0) * dt / g->dr, t = (kind == 0 ? 0.25 : 0.5) * dt;
+            stage_fields<Dual>(Dual(g->p.a, 1.0), g->p.s, g->p.m, x, g->dth, d, t, S);
+            for (int f = 0; f < kNumSRad; ++f) sda[((size_t)f * 2 + kind) * g->L.pitch + i] = S[f].d;
         }
     }
     if (int rc = set_device(g)) return rc;
     g->aws = static_cast<char*>(d_adj_workspace);
     HIP_TRY(hipMemsetAsync(g->aws, 0, total, g->stream));
     HIP_TRY(hipMemcpyAsync(g->aws + g->aoff_da, da.data(), da.size() * sizeof(double), hipMemcpyHostToDevice,
+                           g->stream));
+    HIP_TRY(hipMemcpyAsync(g->aws + g->aoff_sda, sda.data(), sda.size() * sizeof(double), hipMemcpyHostToDevice,
                            g->stream));
     HIP_TRY(hipStreamSynchronize(g->stream));
     return TEUK_OK;
@@ -1094,6 +1163,11 @@ AdjArgs adjoint_args(const teuk_grid* g) {
     a.k.hdt_dr = 0.5 * g->p.dt / g->dr;
     a.rad = g->at<double>(g->L.off_rad);
     a.rad_da = reinterpret_cast<const double*>(g->aws + g->aoff_da);
+    a.srad = g->at<double>(g->L.off_srad);
+    a.srad_da = reinterpret_cast<const double*>(g->aws + g->aoff_sda);
+    a.k.qdt = 0.25 * g->p.dt;
+    a.k.kap_h = 1.0 / (0.5 * g->p.dt);
+    a.k.kap_i = 1.0 / a.k.qdt;
     a.ang = g->at<double>(g->L.off_ang);
     a.ext = g->at<ExtPoint>(g->L.off_ext);
     return a;
@@ -1348,7 +1422,7 @@ struct teuk_batch {
     hipStream_t stream = nullptr;
     int device = 0;
     int rows = 64, wpb = 4, n_blocks = 0;  // default launch: 64-row tiles, four wavefronts per SIMD
-    int total_tiles = 0, total_tiles2 = 0;  // single-step and two-step work lists
+    int total_tiles[kMaxPassSteps] = {};   // work lists of the passes of 1, 2, 3 steps
     int steps_per_pass = 2;
     int parity = 0;                 // which state buffer of every member is the input
     bool keep = false;              // next states with cache-keeping stores (set by batch_upload)
@@ -1386,7 +1460,7 @@ void batch_drop_graph(teuk_batch* b) {
 // Descriptor table for the current tile rows; uploaded synchronously.
 int batch_upload(teuk_batch* b) {
     std::vector<BatchMember> d(b->members.size());
-    int tiles = 0, tiles2 = 0;
+    int tiles[kMaxPassSteps] = {};
     // one launch advances every member: their states share the cache
     size_t states = 0;
     for (const teuk_grid* g : b->members) states += 2 * g->L.state;
@@ -1404,36 +1478,43 @@ int batch_upload(teuk_batch* b) {
         M.k = a.k;
         M.k.n_ext = 0;
         M.k.keep = keep;
-        M.tile_begin = tiles;
-        tiles += a.k.n_strips * a.k.n_chunks;
-        M.n_strips2 = (a.k.nr + kStripCols2 - 1) / kStripCols2;
-        M.tile_begin2 = tiles2;
-        tiles2 += M.n_strips2 * a.k.n_chunks;
+        for (int m = 0; m < kMaxPassSteps; ++m) {
+            M.strips[m] = (a.k.nr + strip_cols(m + 1) - 1) / strip_cols(m + 1);
+            M.tile_begin[m] = tiles[m];
+            tiles[m] += M.strips[m] * a.k.n_chunks;
+        }
     }
-    b->total_tiles = tiles;
-    b->total_tiles2 = tiles2;
+    for (int m = 0; m < kMaxPassSteps; ++m) b->total_tiles[m] = tiles[m];
     HIP_TRY(hipMemcpyAsync(b->ws + b->desc_off, d.data(), d.size() * sizeof(BatchMember), hipMemcpyHostToDevice,
                            b->stream));
     HIP_TRY(hipStreamSynchronize(b->stream));
     return TEUK_OK;
 }
 
-int batch_launch(teuk_batch* b, int parity, bool two, hipStream_t s) {
+int batch_launch(teuk_batch* b, int parity, int steps, hipStream_t s) {
     const hipError_t e =
         launch_batch(reinterpret_cast<const BatchMember*>(b->ws + b->desc_off), (int)b->members.size(),
-                     two ? b->total_tiles2 : b->total_tiles, parity, b->n_blocks, b->wpb, two, b->keep, s);
+                     b->total_tiles[steps - 1], parity, b->n_blocks, b->wpb, steps, b->keep, s);
     return e == hipSuccess ? TEUK_OK : fail(TEUK_E_HIP, "batched step launch failed: %s", hipGetErrorString(e));
 }
 
-// Capture two launches (parity 0, then 1; two or four steps) into a graph.  The capture runs on a
+// Most steps of a launch: 1, or with several steps a pass, 3 (2 if a member
+// has fewer than the three rows that pass needs).
+int batch_pass_steps(const teuk_batch* b) {
+    if (b->steps_per_pass == 1) return 1;
+    for (const teuk_grid* g : b->members)
+        if (g->p.ntheta < 3) return 2;
+    return 3;
+}
+
+// Capture two launches (parity 0, then 1) into a graph.  The capture runs on a
 // private stream (capturing the caller's stream may not be allowed, e.g. the
 // legacy default stream); the graph is launched on the caller's stream.
 int batch_capture(teuk_batch* b) {
     if (!b->cap) HIP_TRY(hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking));
     HIP_TRY(hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal));
-    const bool two = b->steps_per_pass == 2;
-    const int rc0 = batch_launch(b, 0, two, b->cap);
-    const int rc1 = batch_launch(b, 1, two, b->cap);
+    const int rc0 = batch_launch(b, 0, batch_pass_steps(b), b->cap);
+    const int rc1 = batch_launch(b, 1, batch_pass_steps(b), b->cap);
     hipGraph_t graph = nullptr;
     const hipError_t e = hipStreamEndCapture(b->cap, &graph);
     if (rc0 || rc1 || e != hipSuccess || !graph) {
@@ -1554,21 +1635,22 @@ int teuk_batch_step_n(teuk_batch* b, int64_t n) {
     if (n < 0) return fail(TEUK_E_INVALID_ARG, "n=%lld < 0", (long long)n);
     if (n == 0) return TEUK_OK;
     if (int rc = set_device(b->members[0])) return rc;
-    // launches of `per` steps each flip the parity; whole graphs (two
-    // launches) start from parity 0; an odd last step runs alone
-    const int per = b->steps_per_pass;
+    // every launch flips the parity; whole graphs (two launches) start from
+    // parity 0; the last steps run as in step_n_impl
+    const int most = batch_pass_steps(b);
     int64_t left = n;
     while (left > 0) {
-        if (b->parity == 0 && left >= 2 * per) {
+        if (b->parity == 0 && left >= 2 * most && !(most == 3 && left == 7)) {
             if (!b->exec)  // captured once per launch configuration
                 if (int rc = batch_capture(b)) return rc;
-            for (; left >= 2 * per; left -= 2 * per) HIP_TRY(hipGraphLaunch(b->exec, b->stream));
+            HIP_TRY(hipGraphLaunch(b->exec, b->stream));
+            left -= 2 * most;
             continue;
         }
-        const bool two = left >= per && per == 2;
-        if (int rc = batch_launch(b, b->parity, two, b->stream)) return rc;
+        const int m = most == 3 && left >= 3 && left != 4 ? 3 : (int)std::min<int64_t>(left, std::min(most, 2));
+        if (int rc = batch_launch(b, b->parity, m, b->stream)) return rc;
         b->parity = 1 - b->parity;
-        left -= two ? 2 : 1;
+        left -= m;
     }
     b->steps += n;
     for (teuk_grid* g : b->members) {
