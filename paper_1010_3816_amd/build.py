@@ -5,7 +5,8 @@ import subprocess
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libteuk.so")
-SOURCES = ["lw_kernels.hip", "adjoint_kernels.hip", "spin_tangent.hip", "teuk_api.cpp"]
+SOURCES = ["lw_kernels.hip", "adjoint_kernels.hip", "spin_tangent.hip", "tables.hip",
+           "teuk_api.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # -packed-fp32-ops: no packed FP32 instructions are generated (all arithmetic

@@ -13,50 +13,8 @@ namespace {
 // `o` is a row-dependent offset that is 0 at run time (row & zero): it keeps
 // the reads inside the row loop instead of in (scarce) registers.
 typedef const __attribute__((address_space(3))) double* lds_cptr;
-
-__device__ __forceinline__ Rad rad_from_lds(lds_cptr rs, int o) {
-    Rad R;
-    R.rho = rs[o + R_RHO * kWave];
-    R.rho2 = rs[o + R_RHO2 * kWave];
-    R.a2d = rs[o + R_A2D * kWave];
-    R.rb1 = rs[o + R_RB1 * kWave];
-    R.rb2 = rs[o + R_RB2 * kWave];
-    R.rb3 = rs[o + R_RB3 * kWave];
-    R.ctr = rs[o + R_CTR * kWave];
-    R.cti0 = rs[o + R_CTI0 * kWave];
-    R.cti1 = rs[o + R_CTI1 * kWave];
-    R.b1n = rs[o + R_B1N * kWave];
-    R.dl2 = rs[o + R_DL2 * kWave];
-    R.v0r = rs[o + R_V0R * kWave];
-    R.v0i = rs[o + R_V0I * kWave];
-    return R;
-}
-
-// d/da of kerr_coef at one position from the radial factors V and their
-// a-derivatives D (as kerr_coef_da).
-__device__ __forceinline__ Coef kerr_coef_da_reg(const Rad& V, const Rad& D, const Ang& G, Sig s, const Coef& c) {
-    const double w = s.inv * fma(-D.a2d, G.sn2, D.rho2);
-    const double hw = 0.5 * w;
-    Coef r;
-    r.b = fma(s.isig, D.rho, -c.b * hw);
-    const double T = fma(-V.rb3, G.sn2, V.rb2);
-    const double dT = fma(-D.rb3, G.sn2, D.rb2);
-    const double Q = fma(-T, s.inv, V.rb1);
-    const double dQ = fma(-s.inv, fma(-T, w, dT), D.rb1);
-    const double bp = s.isig * Q;
-    const double dbp = s.isig * fma(-Q, hw, dQ);
-    r.ctr = fma(s.inv, D.ctr, -c.ctr * w);
-    r.cti = fma(s.inv, fma(D.cti1, G.cs, D.cti0), -c.cti * w);
-    const double b1 = V.b1n * s.inv;
-    const double db1 = fma(s.inv, D.b1n, -b1 * w);
-    r.cre = fma(r.b, bp - c.ctr, c.b * (dbp - r.ctr)) - db1;
-    r.cim = -fma(r.b, c.cti, c.b * r.cti);
-    r.a2s = fma(s.inv, D.dl2, -c.a2s * w);
-    r.a1s = r.a2s * G.cotp;
-    r.v0r = fma(s.inv, fma(D.dl2, G.pd, D.v0r), -c.v0r * w);
-    r.v0i = fma(s.inv, D.v0i, -c.v0i * w);
-    return r;
-}
+typedef __attribute__((address_space(3))) double* lds_t;
+typedef __attribute__((address_space(3))) v2d* cd_lds_t;
 
 // Tile of a wavefront.  Tiles are numbered strip-major (the theta chunks of
 // a strip consecutive) and workgroup b takes tiles b*wpb .. b*wpb + wpb - 1,
@@ -155,6 +113,14 @@ struct TanRow {
 // rvi, rvh, rdi, rdh: the lane's radial factors and their a-derivatives at
 // its column and half point, in LDS, read row by row.  smp: this wavefront's
 // sample slots.  T_m is streamed; the next states follow KEEP.
+//
+// What bounds it: 328 vector instructions per point and step with v (498
+// before), half of the cycles of its two wavefronts per SIMD; 36 % of a
+// wavefront's time it waits, for its 52 LDS reads a row in turn (more of them
+// at once would need registers; 240 of 256 are used) and for memory (210 MB a
+// step on 6400 x 256, 25 us at the rate of a copy within the last-level
+// cache).  us per step, before and now: 6400 x 256 48.6 -> 43-45 with v, 35.8
+// -> 33.5 without; 3200 x 128 19.4 -> 17.4, 13.7 -> 15.0.
 template <bool V, int KEEP>
 __device__ __forceinline__ void tangent_sweep(gin_t u_in, gin_t v_in, gout_t u_out, gout_t v_out, ctab_t ang,
                                               const ExtPoint* __restrict__ ext, double2* __restrict__ series_u,
@@ -361,17 +327,30 @@ __device__ __forceinline__ void tangent_sweep(gin_t u_in, gin_t v_in, gout_t u_o
 // LDS of a wavefront's sample slots: u, v x row a, b x two columns, and a slot per lane.
 constexpr int kTanSlots = 8 + kWave;
 
-// The workgroup's radial tables and their a-derivatives in LDS,
-// [strip][value/derivative][column/half][field][lane].
+// The radial tables (kTables = 2: and their a-derivatives) of the workgroup's
+// strips of K-step tiles, in LDS: [strip][table][column/half][field][lane].
+// A wavefront loads 13 rows at once before it writes them: one by one, each
+// load's latency is waited for in turn (26 rows a wavefront, a third of the
+// spin-tangent step on 6400 x 256).
+template <int K, int kTables>
 __device__ __forceinline__ void fill_tables(const TileOf& T, const double* __restrict__ rad,
                                             const double* __restrict__ rad_da, double* rad_s, int nr, int P, int wave,
                                             int wpb, int lane) {
-    constexpr int kF = 4 * kNumSRad;
-    for (int f = wave; f < T.n_slices * kF; f += wpb) {
-        const int g = f % kF, deriv = g / (2 * kNumSRad), kind = (g / kNumSRad) % 2, field = g % kNumSRad;
-        const int c = min(max((T.s0 + f / kF) * kStripCols - 1 + lane, 0), nr - 1);
-        const double* src = deriv ? rad_da : rad;
-        rad_s[f * kWave + lane] = src[((size_t)field * 2 + kind) * P + (kind == 0 ? c : min(c, nr - 2))];
+    constexpr int kF = kTables * 2 * kNumSRad, kBatch = kNumSRad;
+    const int n = T.n_slices * kF;
+    for (int f0 = wave; f0 < n; f0 += kBatch * wpb) {
+        double v[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const int f = min(f0 + u * wpb, n - 1);
+            const int g = f % kF, deriv = g / (2 * kNumSRad), kind = (g / kNumSRad) % 2, field = g % kNumSRad;
+            const int c = min(max((T.s0 + f / kF) * strip_cols(K) - K + lane, 0), nr - 1);
+            const double* src = deriv ? rad_da : rad;
+            v[u] = src[((size_t)field * 2 + kind) * P + (kind == 0 ? c : min(c, nr - 2))];
+        }
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u)
+            if (f0 + u * wpb < n) rad_s[(f0 + u * wpb) * kWave + lane] = v[u];
     }
     __syncthreads();
 }
@@ -386,7 +365,7 @@ __device__ __forceinline__ void tangent_tile(const double2* u_in, const double2*
     const int wpb = blockDim.x / kWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const TileOf T = tile_of(xcd_block(blockIdx.x, gridDim.x), wpb, wave, A.n_strips, A.n_chunks);
-    fill_tables(T, rad, rad_da, rad_s, A.nr, A.pitch, wave, wpb, lane);
+    fill_tables<1, 2>(T, rad, rad_da, rad_s, A.nr, A.pitch, wave, wpb, lane);
     if (!T.valid) return;  // wavefront-uniform
     constexpr int kF = 4 * kNumSRad;
     const double* slice = rad_s + T.slice * kF * kWave + lane;

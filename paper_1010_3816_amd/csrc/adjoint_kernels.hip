@@ -3,60 +3,30 @@
 // gradient contribution Re <lambda^{m+1}, (dA/da) u^m>.
 //
 // The step is complex-linear, so its adjoint for a real loss (gradient
-// convention dL/dRe + i dL/dIm) is the conjugate transpose.  The kernel is
-// the gather form of the transposed step and sweeps the same tiles as the
-// forward kernel (64 r* columns per wavefront, theta rows in order):
-//   * stage 2 transposed at integer points: nu = lambda^{m+1} with the
-//     radial boundary columns zeroed gives the cotangents of hbar and dh;
-//     the theta stencil of S becomes a stencil over the cotangents of rows
-//     t-1, t, t+1 (each row emits an "up", "mid" and "down" part);
-//   * hbar/dh transposed to the half points: lane L adds lane L+1's share;
-//   * stage 1 transposed at half points, again with a row stencil;
-//   * averaging/difference transposed back to integer points: lane L adds
-//     lane L-1's share; plus the direct term nu.
-// The spin gradient needs the forward intermediates of step m (ubar, delta,
-// hbar, dh), which are recomputed from u^m exactly as in the forward
-// kernel, and the a-derivatives of the coefficients, obtained by forward
-// differentiation of their reconstruction from the radial tables and their
-// a-derivative tables (held in LDS for the workgroup's strip).
+// convention dL/dRe + i dL/dIm) is the conjugate transpose.  The sweep is the
+// gather form of the transposed step over the forward passes' tiles (64 r*
+// columns per wavefront, theta rows in order, K steps a pass); with n =
+// lambda^{m+1}, zeroed on the radial boundary columns:
+//   * stage 2 transposed at the columns: the cotangents of SQ, DQ, D and S
+//     (the sums and differences of the stage-1 values), the last with the
+//     theta weights' shares of rows t-1, t, t+1;
+//   * sum and difference transposed to the half points: lane L adds lane
+//     L+1's share, giving the cotangents of H and HQ;
+//   * stage 1 transposed at the half points, with its own theta shares;
+//   * sum and difference transposed back to the columns: lane L adds lane
+//     L-1's share; plus the direct term n.
+//
+// What bounds it.  With the stage coefficients of the forward passes, built
+// once per row and pass, a two-step sweep issues 133 vector instructions per
+// point and step (195 before); on 6400 x 256 (states in the last-level cache)
+// it is bound by the latency and issue of one round of wavefronts, two per
+// SIMD: us per step, before and now, cotangents 16.9 -> 15.0, with the dot
+// products 22.4 -> 23.0, spin gradient from states 48 -> 46; 3200 x 128 8.3 ->
+// 7.8, 10.0 -> 9.7, 20.3 -> 18.9.
 #include "adjoint_common.hpp"
 
 namespace teuk {
 namespace {
-
-
-// d/da of kerr_coef at one position from the a-derivative tables rd, four
-// value fields (rv), the angular factors, s = (1/Sigma, 1/Sigma^2) and the
-// coefficient values c.  With w = d(Sigma^2)/Sigma^2, a coefficient
-// X/Sigma^2 has derivative dX/Sigma^2 - c w and rho/Sigma has
-// drho/Sigma - c w/2, so most value fields are not needed again.
-__device__ __forceinline__ Coef kerr_coef_da(lds_cptr rv, lds_cptr rd, int o, const Ang& G, Sig s, const Coef& c) {
-    auto d = [&](int f) { return rd[o + f * kWave]; };
-    auto v = [&](int f) { return rv[o + f * kWave]; };
-    const double w = s.inv * fma(-d(R_A2D), G.sn2, d(R_RHO2));
-    const double hw = 0.5 * w;
-    Coef r;
-    r.b = fma(s.isig, d(R_RHO), -c.b * hw);
-    const double T = fma(-v(R_RB3), G.sn2, v(R_RB2));
-    const double dT = fma(-d(R_RB3), G.sn2, d(R_RB2));
-    const double Q = fma(-T, s.inv, v(R_RB1));
-    const double dQ = fma(-s.inv, fma(-T, w, dT), d(R_RB1));
-    const double bp = s.isig * Q;
-    const double dbp = s.isig * fma(-Q, hw, dQ);
-    r.ctr = fma(s.inv, d(R_CTR), -c.ctr * w);
-    r.cti = fma(s.inv, fma(d(R_CTI1), G.cs, d(R_CTI0)), -c.cti * w);
-    const double b1 = v(R_B1N) * s.inv;
-    const double db1 = fma(s.inv, d(R_B1N), -b1 * w);
-    r.cre = fma(r.b, bp - c.ctr, c.b * (dbp - r.ctr)) - db1;
-    r.cim = -fma(r.b, c.cti, c.b * r.cti);
-    r.a2s = fma(s.inv, d(R_DL2), -c.a2s * w);
-    r.a1s = r.a2s * G.cotp;
-    r.v0r = fma(s.inv, fma(d(R_DL2), G.pd, d(R_V0R)), -c.v0r * w);
-    r.v0i = fma(s.inv, d(R_V0I), -c.v0i * w);
-    return r;
-}
-
-
 
 // Extraction points (of the first n) whose bilinear stencil touches output
 // rows r_lo .. r_hi of a tile and the columns c0 .. c0 + 63 of its lanes, as
@@ -71,66 +41,341 @@ __device__ __forceinline__ unsigned ext_mask(const ExtPoint* __restrict__ ext, i
     return m;
 }
 
-// complex helpers for the transposed operators
-__device__ __forceinline__ cd cadd3(cd a, cd b, cd c) { return {a.re + b.re + c.re, a.im + b.im + c.im}; }
-// (x + i y) * (re + i im)
-__device__ __forceinline__ cd cmul(double x, double y, cd v) {
-    return {fma(x, v.re, -y * v.im), fma(x, v.im, y * v.re)};
+// x - conj(re + i im) v
+__device__ __forceinline__ cd sub_conj(double re, double im, cd v, cd x) {
+    return {fma(-im, v.im, fma(-re, v.re, x.re)), fma(im, v.re, fma(-re, v.im, x.im))};
 }
 
-// Rows of input loaded ahead of the row being finished.  One keeps the
-// kernel within the registers of two wavefronts per SIMD.
-#ifndef TEUK_ADJ_ROWS_IN_FLIGHT
-#define TEUK_ADJ_ROWS_IN_FLIGHT 1
-#endif
-constexpr int kAdjRowsInFlight = TEUK_ADJ_ROWS_IN_FLIGHT;
-// The cotangent-only kernel holds far fewer values per row.
-#ifndef TEUK_ADJ_ROWS_IN_FLIGHT_NOSPIN
-#define TEUK_ADJ_ROWS_IN_FLIGHT_NOSPIN 2
-#endif
-static_assert(TEUK_ADJ_ROWS_IN_FLIGHT == 1 || TEUK_ADJ_ROWS_IN_FLIGHT == 2, "the row loop takes rows in pairs");
-static_assert(TEUK_ADJ_ROWS_IN_FLIGHT_NOSPIN == 1 || TEUK_ADJ_ROWS_IN_FLIGHT_NOSPIN == 2,
-              "the row loop takes rows in pairs");
-
-// Per-row state carried from the row's arrival to its completion.  The
-// forward recompute is needed for the spin gradient only.
-template <bool SPIN>
-struct AdjFwd {
-    cd ubp, ubq, dp, dq;  // half point i+1/2
-    cd hbp, dhp;          // integer point i
-    cd x;                 // stage-1 Pi value at the half, minus its row-(t+1) term
-    double wp;
-};
-template <>
-struct AdjFwd<false> {};
-
-// Tangent rows of the spin gradient's dot product (DOT kernels only).
-template <bool DOT>
-struct AdjTan {
-    cd tp, tq;            // T_m = (dA/da) u^m at (i, t)
-};
-template <>
-struct AdjTan<false> {};
-
-template <bool SPIN, bool DOT = false>
+// One row of one step between its arrival and its completion, which adds
+// the next row's theta shares (the cotangents of S and U lack them).
 struct AdjRow {
-    AdjFwd<SPIN> f;       // forward recompute of step m at this row
-    AdjTan<DOT> tan;      // tangent row, for the dot product with nu
-    // adjoint
-    cd np, nq;            // nu at (i, t), radial boundary columns zeroed
-    cd lhq;               // cotangent of the stage-1 Pi value at the half
-    cd up, dn;            // stage-2 theta-stencil pieces to rows t+1, t-1
-    cd uph, dnh;          // stage-1 theta-stencil pieces to rows t+1, t-1
-    Sig si, sh;           // 1/Sigma, 1/Sigma^2 at the integer and half point
-    Ang g;                // angular factors of the row (wavefront-uniform)
+    cd np, nq;    // n plus the part of the output known at the arrival
+    cd lp, lq;    // the same of the share for the next column
+    cd lS, lD;    // cotangents of S and D at the column
+    cd up, uph;   // theta shares to the next row: stage 2 (column), stage 1 (half point)
+    double bh;    // b at the half point
 };
 
-// SPIN = false: the cotangents only.  The step is linear in the state, so
-// they do not need u^m: no state rows are read, nothing of the forward step
-// is recomputed and no spin gradient is accumulated.
-// DOT (with SPIN = false): u_in holds T_m = (dA/da) u^m (lw_tangent_kernel)
-// instead of u^m, and the spin gradient's term of this step is the dot
-// product Re <lambda^{m+1}, T_m> over the owned points.
+// LDS of a wavefront for the points of a row: two steps' weights per lane and gradients.
+constexpr int kHitDoubles = 2 * kRowHits * (kWave + 2);
+
+// What the adjoint's sweeps accumulate beside the cotangents: nothing, the
+// dot products with stored tangents, or the spin gradient from the states.
+enum SpinPart { kNone, kDot, kStates };
+
+// K adjoint steps in one pass over a tile of 64 - 2K columns: step j takes
+// row r - j in iteration r and completes row r - j - 1, as in the forward
+// passes (sweep in the forward kernels' source), with the same row loops: the
+// second one checks for the last pole, boundary columns and extraction.  A
+// row's coefficients are built once and serve all steps.  gs[j]: the gradient
+// of the sample of step j's output state, or nullptr.
+//   kDot:    tan[j] holds T = (dA/da) u of step j; Re <n, T> is summed over the owned points;
+//   kStates: (K = 1) tan[0] holds u^m; T_m is formed on the way (tangent_sweep's
+//            expressions) and its dot product with n summed.
+// Returns this lane's sum.
+template <int K, SpinPart SP, int KEEP>
+__device__ __forceinline__ double adjoint_sweep(const double2* __restrict__ nu_in, double2* __restrict__ lam_out,
+                                                const double* __restrict__ ang, const ExtPoint* __restrict__ ext,
+                                                const double* const (&gs)[K], const double2* const (&tan)[K],
+                                                lds_cptr rvi, lds_cptr rvh, lds_cptr rdi, lds_cptr rdh, lds_t hits,
+                                                const AdjScalars& A, int strip, int chunk, int lane) {
+    static_assert(SP != kStates || K == 1, "the spin gradient from states is a one-step sweep");
+    // rows in flight (and rows the loop is unrolled by); coefficient rows: K
+    constexpr int kRing = (SP == kStates) ? 1 : (K == 1) ? 2 : K;
+    constexpr int kCols = strip_cols(K);
+    const int nr = A.nr, nth = A.nth, P = A.pitch;
+    const int col = strip * kCols - K + lane;
+    const int ci = min(max(col, 0), nr - 1);
+    const bool own = (lane >= K) && (lane < kWave - K) && (col < nr);
+    const bool interior = (col >= 1) && (col < nr - 1);
+    const int j0 = chunk * A.rows;
+    const int j1 = min(j0 + A.rows, nth);
+    const int rs0 = max(j0 - K, 0), rE = j1 - 1 + K;
+    const double sg = (double)A.sigma;
+    const int c0 = strip * kCols - K;
+    bool any_g = false;
+#pragma unroll
+    for (int j = 0; j < K; ++j) any_g = any_g || gs[j] != nullptr;
+    const unsigned emask = ext_mask(ext, any_g ? A.n_ext : 0, j0 - K + 1, j1 + K - 2, c0);
+
+    const int32_t row_bytes = P * (int32_t)sizeof(v2d);
+    const uint32_t ld_off = (uint32_t)ci * sizeof(v2d);
+    const uint32_t st_off = own ? (uint32_t)col * sizeof(v2d) : kOffNone;
+    auto load_from = [&](const double2* base, int t, cd& p, cd& q) {
+        const double2* b = base + (size_t)min(max(t, 0), nth - 1) * P;
+        p = ld_row(row_rsrc(b, row_bytes), ld_off);
+        q = ld_row(row_rsrc(b + A.plane, row_bytes), ld_off);
+    };
+    auto pick = [](bool c, cd a, cd b) -> cd { return {c ? a.re : b.re, c ? a.im : b.im}; };
+    const cd zero = {0.0, 0.0};
+
+    cd bp[kRing], bq[kRing];
+#pragma unroll
+    for (int u = 0; u < kRing; ++u) load_from(nu_in, rs0 + u, bp[u], bq[u]);
+    // rows of the tangents (or states): step j's row r - j, one row ahead
+    constexpr int kT = SP == kNone ? 1 : K;
+    cd tp[kT], tq[kT];
+    if constexpr (SP != kNone) {
+#pragma unroll
+        for (int j = 0; j < K; ++j) load_from(tan[j], rs0 - j, tp[j], tq[j]);
+    }
+    const int plain = (int)(c0 > 0) & (int)(c0 + kWave - 1 < nr - 1) & (int)(emask == 0);
+    const int rM = plain * (min(rE, nth - 1) + 1) - 1;
+
+    double acc = 0.0;
+    AdjRow st[K] = {};
+    Stage Ch[K] = {}, Ci[K] = {};
+    TanRow tr = {};  // kStates: the row of the tangent
+    cd n_prev_p = zero, n_prev_q = zero;
+    Ang g_next = load_ang(ang, nth, rs0);
+
+    // Transposed extraction of the sample of step j's output state: each
+    // stencil point of an extraction point receives its bilinear weight times
+    // the sample's gradient (gs, re/im interleaved).  The weights and
+    // gradients of the rows an iteration completes go to the wavefront's LDS
+    // beforehand (zeros where there are none), so that the row itself takes
+    // no branch; the host sees to it that a row of a tile has at most
+    // kRowHits points.
+    lds_t hit_w = (lds_t)hits + lane;
+    cd_lds_t hit_g = (cd_lds_t)((lds_t)hits + K * kRowHits * kWave);
+    auto put_hit = [&](int slot, double w, double re, double im) {
+        hit_w[slot * kWave] = w;
+        hit_g[slot] = v2d{re, im};
+    };
+    bool hit_set = true;  // slots to be cleared
+    auto set_hits = [&](int r) {
+        if (hit_set) {
+            for (int k = 0; k < K * kRowHits; ++k) put_hit(k, 0.0, 0.0, 0.0);
+            hit_set = false;
+        }
+        if (emask == 0) return;
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            if (gs[j] == nullptr) continue;
+            const int t = r - j - 1;
+            int h = 0;
+            for (int e = 0; e < A.n_ext; ++e) {
+                if (!((emask >> e) & 1u)) continue;
+                const ExtPoint E = ext[e];
+                if ((t != E.rowa && t != E.rowb) || h >= kRowHits) continue;  // wavefront-uniform
+                const double wrow = (t == E.rowa) ? E.wa : E.wb;
+                const double w = (col == E.col) ? wrow * (1.0 - E.wr) : (col == E.col + 1) ? wrow * E.wr : 0.0;
+                put_hit(j * kRowHits + h, w, gs[j][2 * e], gs[j][2 * e + 1]);
+                hit_set = true;
+                ++h;
+            }
+        }
+    };
+
+    auto iteration = [&](int r, cd& rp, cd& rq, auto ph, auto steps, auto check) {
+        constexpr int PH = decltype(ph)::value % K, STEPS = decltype(steps)::value, CHECK = decltype(check)::value;
+        if constexpr (CHECK) set_hits(r);
+        const Ang G = g_next;
+        const int z = r & A.zero;
+        Stage dh, di;
+        {
+            const SRad R = srad_of([&](int f) { return rvi[z + f * kWave]; });
+            const Sig s = ssigma(R, G);
+            Ci[PH] = stage_coef(R, G, s, A.kap_i);
+            if constexpr (SP == kStates) {
+                const SRad D = srad_of([&](int f) { return rdi[z + f * kWave]; });
+                di = stage_coef_da(R, D, G, s, A.kap_i, Ci[PH]);
+            }
+        }
+        {
+            const SRad R = srad_of([&](int f) { return rvh[z + f * kWave]; });
+            const Sig s = ssigma(R, G);
+            Ch[PH] = stage_coef(R, G, s, A.kap_h);
+            if constexpr (SP == kStates) {
+                const SRad D = srad_of([&](int f) { return rdh[z + f * kWave]; });
+                dh = stage_coef_da(R, D, G, s, A.kap_h, Ch[PH]);
+            }
+        }
+        cd p = rp, q = rq;
+#pragma unroll
+        for (int j = 0; j < STEPS; ++j) {
+            const Stage &kh = Ch[(PH + K - j) % K], &ki = Ci[(PH + K - j) % K];
+            const int t = r - j;
+            AdjRow& s = st[j];
+            if constexpr (CHECK) {
+                p = pick(interior, p, zero);
+                q = pick(interior, q, zero);
+            }
+            if constexpr (SP == kDot) {
+                double c = p.re * tp[j].re + p.im * tp[j].im;
+                c = fma(q.re, tq[j].re, fma(q.im, tq[j].im, c));
+                const bool in = own && t >= j0 && t < j1;
+                acc += in ? c : 0.0;
+                load_from(tan[j], t + 1, tp[j], tq[j]);
+            }
+            // stage 2 at the column
+            const cd lSQ = sub_conj(ki.tr, ki.ti, q, cd{A.qdt * p.re, A.qdt * p.im});
+            const cd lDQ = cscale(ki.b, q);
+            AdjRow n;
+            n.lD = sub_conj(ki.cr, ki.ci, q, cd{-ki.b * p.re, -ki.b * p.im});
+            n.up = cscale(ki.wp, q);
+            cd dn = cscale(ki.wm, q);
+            // stage 1 at the half point
+            const cd lHQ = cadd(cadd(lSQ, lDQ), from_right(csub(lSQ, lDQ)));
+            n.uph = cscale(kh.wp, lHQ);
+            cd dnh = cscale(kh.wm, lHQ);
+            cd up0 = s.up, uph0 = s.uph;  // shares of the previous row
+            if constexpr (CHECK == 2) {
+                // the step's first row: at the pole its previous one is its
+                // ghost; elsewhere nothing formed from it is used
+                if (j == STEPS - 1) {
+                    up0 = cscale(sg, dn);
+                    uph0 = cscale(sg, dnh);
+                }
+            }
+            n.lS = sub_conj(ki.vr, ki.vi, q, csub(csub(up0, n.up), dn));
+            const cd lU = sub_conj(kh.vr, kh.vi, lHQ, csub(csub(uph0, n.uph), dnh));
+            const cd lV = sub_conj(kh.tr, kh.ti, lHQ, lHQ);
+            const cd ldp = sub_conj(kh.cr, kh.ci, lHQ, zero), ldq = cscale(kh.b, lHQ);
+            n.np = cadd(p, csub(lU, ldp));
+            n.nq = cadd(q, csub(lV, ldq));
+            n.lp = cadd(lU, ldp);
+            n.lq = cadd(lV, ldq);
+            n.bh = kh.b;
+            if constexpr (CHECK == 1) {  // the last row's next one is its ghost
+                dn = pick(t == nth, cscale(sg, up0), dn);
+                dnh = pick(t == nth, cscale(sg, uph0), dnh);
+            }
+            // row t - 1 is complete
+            const cd lS = cadd(s.lS, dn);
+            const cd lH = cadd(cadd(lS, s.lD), from_right(csub(lS, s.lD)));
+            const cd a = cadd(lH, dnh);
+            cd op = cadd(s.np, cadd(fma_real(s.bh, lH, a), from_left(cadd(s.lp, fma_real(-s.bh, lH, a)))));
+            cd oq = cadd(s.nq, fma_real(A.hdt, lH, from_left(fma_real(A.hdt, lH, s.lq))));
+            if constexpr (SP == kStates) {
+                // T of row t - 1 (tangent_sweep's expressions without v) with n
+                const cd u = tp[0], w = tq[0], ur = from_right(u), wr = from_right(w);
+                TanRow m;
+                m.U = cadd(u, ur);
+                const cd W = cadd(w, wr), dp = csub(ur, u), dq = csub(wr, w);
+                const cd H = stage1_phi(kh.b, A.hdt, m.U, W, dp), Hl = from_left(H);
+                m.S = cadd(H, Hl);
+                const cd D = csub(H, Hl);
+                const cd tH = {-dh.b * dp.re, -dh.b * dp.im}, tHl = from_left(tH);
+                m.tS = cadd(tH, tHl);
+                const cd tD = csub(tH, tHl);
+                cd Um = tr.U, Sm = tr.S, tSm = tr.tS;
+                if constexpr (CHECK == 2) {
+                    Um = cscale(sg, m.U);
+                    Sm = cscale(sg, m.S);
+                    tSm = cscale(sg, m.tS);
+                } else if constexpr (CHECK == 1) {
+                    m.U = pick(t == nth, cscale(sg, Um), m.U);
+                    m.S = pick(t == nth, cscale(sg, Sm), m.S);
+                    m.tS = pick(t == nth, cscale(sg, tSm), m.tS);
+                }
+                const cd dU = csub(m.U, Um), dS = csub(m.S, Sm), tdS = csub(m.tS, tSm);
+                const cd HQ = fma_real(tr.k.wh, dU, tr.X), HQl = from_left(HQ);
+                const cd SQ = cadd(HQ, HQl), DQ = csub(HQ, HQl);
+                const cd tHQ = fma_real(tr.d.wh, dU, tr.tX), tHQl = from_left(tHQ);
+                const cd tSQ = cadd(tHQ, tHQl), tDQ = csub(tHQ, tHQl);
+                const cd vp = fma_real(A.qdt, tSQ, tr.tP);
+                const cd vq = cadd(tr.tQ, cadd(stage2_late(tr.d.b, tr.d.tr, tr.d.ti, tr.d.wp, SQ, DQ, dS),
+                                               stage2_late(tr.k.b, tr.k.tr, tr.k.ti, tr.k.wp, tSQ, tDQ, tdS)));
+                double c = n_prev_p.re * vp.re + n_prev_p.im * vp.im;
+                c = fma(n_prev_q.re, vq.re, fma(n_prev_q.im, vq.im, c));
+                const bool in = own && t - 1 >= j0 && t - 1 < j1;
+                acc += in ? c : 0.0;
+                m.X = cadd(W, stage1_inc(kh, m.U, W, dp, dq, dU));
+                m.tX = stage1_inc(dh, m.U, W, dp, dq, dU);
+                m.tP = fma_real(-di.b, D, cd{-ki.b * tD.re, -ki.b * tD.im});
+                m.tQ = cadd(stage2_early(di, m.S, D, dS), stage2_early(ki, m.tS, tD, tdS));
+                m.k = late_of(kh, ki);
+                m.d = late_of(dh, di);
+                tr = m;
+                n_prev_p = p;
+                n_prev_q = q;
+                load_from(tan[0], t + 1, tp[0], tq[0]);
+            }
+            s = n;
+            if constexpr (CHECK) {
+#pragma unroll
+                for (int h = 0; h < kRowHits; ++h) {
+                    const double w = hit_w[(j * kRowHits + h) * kWave];
+                    const v2d g = hit_g[j * kRowHits + h];
+                    op.re = fma(w, g.x, op.re);
+                    op.im = fma(w, g.y, op.im);
+                }
+            }
+            p = op;
+            q = oq;
+            if (j == 0) {
+                __builtin_amdgcn_sched_barrier(kAllButScalarLoads);
+                g_next = load_ang(ang, nth, min(r + 1, nth - 1));
+            }
+        }
+        load_from(nu_in, r + kRing, rp, rq);
+        if constexpr (STEPS == K) {
+            const int t = r - K;
+            const int32_t bytes = (t >= j0 && t < j1) ? row_bytes : 0;
+            const double2* b = lam_out + (size_t)max(t, 0) * P;
+            st_row<KEEP>(row_rsrc(b, bytes), st_off, p);
+            st_row<KEEP>(row_rsrc(b + A.plane, bytes), st_off, q);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    int r = rs0;
+    auto head = [&](auto self, auto i) {
+        constexpr int I = decltype(i)::value;
+        if constexpr (I < K) {
+            iteration(r, bp[I % kRing], bq[I % kRing], Const<I>{}, Const<I + 1>{}, Const<2>{});
+            ++r;
+            self(self, Const<I + 1>{});
+        }
+    };
+    head(head, Const<0>{});
+    auto rows = [&](auto self, auto u, auto check) {
+        constexpr int I = decltype(u)::value + K;
+        if constexpr (I < K + kRing) {
+            iteration(r, bp[I % kRing], bq[I % kRing], Const<I>{}, Const<K>{}, check);
+            ++r;
+            self(self, Const<I - K + 1>{}, check);
+        }
+    };
+    while (r + kRing - 1 <= rM) rows(rows, Const<0>{}, Const<0>{});
+    while (r <= rE) rows(rows, Const<0>{}, Const<1>{});
+    return acc;
+}
+
+// The workgroup's radial tables (with their a-derivatives for kStates) in
+// LDS, and its wavefront's tile of a K-step adjoint sweep; the sums of the
+// lanes go to the tile's slot, in a fixed order.
+template <int K, SpinPart SP, int KEEP>
+__device__ __forceinline__ void adjoint_tile(const double2* __restrict__ nu_in, double2* __restrict__ lam_out,
+                                             const double* __restrict__ rad, const double* __restrict__ rad_da,
+                                             const double* __restrict__ ang, const ExtPoint* __restrict__ ext,
+                                             const double* const (&gs)[K], const double2* const (&tan)[K],
+                                             double* __restrict__ dlda_slots, const AdjScalars& A, double* rad_s) {
+    constexpr int kTables = SP == kStates ? 2 : 1;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wpb = blockDim.x / kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const TileOf T = tile_of(xcd_block(blockIdx.x, gridDim.x), wpb, wave, A.n_strips, A.n_chunks);
+    fill_tables<K, kTables>(T, rad, rad_da, rad_s, A.nr, A.pitch, wave, wpb, lane);
+    if (!T.valid) return;  // wavefront-uniform
+    const double* slice = rad_s + T.slice * kTables * 2 * kNumSRad * kWave + lane;
+    const double* da = slice + (kTables - 1) * 2 * kNumSRad * kWave;
+    double acc = adjoint_sweep<K, SP, KEEP>(nu_in, lam_out, ang, ext, gs, tan, (lds_cptr)slice,
+                                            (lds_cptr)(slice + kNumSRad * kWave), (lds_cptr)da,
+                                            (lds_cptr)(da + kNumSRad * kWave),
+                                            (lds_t)(rad_s + T.n_slices * kTables * 2 * kNumSRad * kWave +
+                                                    wave * kHitDoubles),
+                                            A, T.strip, T.chunk, lane);
+    if constexpr (SP != kNone) {
+        for (int off = kWave / 2; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, kWave);
+        if (lane == 0) dlda_slots[(size_t)T.chunk * A.n_strips + T.strip] += acc;
+    }
+}
+
+// One adjoint step.  SPIN: with the spin gradient from u^m = u_in; DOT: from
+// the stored tangent T_m = u_in; neither: the cotangents only (linear in the
+// state, so they need no forward state).
 template <bool SPIN, bool DOT, int KEEP>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8)))
     lw_adjoint_kernel(const double2* __restrict__ nu_in, const double2* __restrict__ u_in,
@@ -138,616 +383,24 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))
                       const double* __restrict__ rad_da, const double* __restrict__ ang,
                       double* __restrict__ dlda_slots, const ExtPoint* __restrict__ ext,
                       const double* __restrict__ gsample, AdjScalars A) {
-    constexpr int kRIF = SPIN ? kAdjRowsInFlight : TEUK_ADJ_ROWS_IN_FLIGHT_NOSPIN;
-    static_assert(!(SPIN && DOT), "the stored-tangent dot product replaces the spin recompute");
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wpb = blockDim.x / kWave;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const TileOf T = tile_of(xcd_block(blockIdx.x, gridDim.x), wpb, wave, A.n_strips, A.n_chunks);
-    const int strip = T.strip, chunk = T.chunk;
-    const int nr = A.nr, nth = A.nth, P = A.pitch;
-    const int col = strip * kStripCols - 1 + lane;
-    const unsigned long long interior = ((col >= 1) && (col < nr - 1)) ? ~0ull : 0ull;
-    const int ci = min(max(col, 0), nr - 1);
-
-    // the radial tables of the workgroup's strips: [strip][value/derivative][integer/half][field][lane]
-    // (dynamic LDS, adjoint_lds_bytes)
-    constexpr int kF = (SPIN ? 4 : 2) * kNumRad;
     extern __shared__ double rad_s[];
-    for (int f = wave; f < T.n_slices * kF; f += wpb) {
-        const int g = f % kF, deriv = g / (2 * kNumRad), kind = (g / kNumRad) % 2, field = g % kNumRad;
-        const int c = min(max((T.s0 + f / kF) * kStripCols - 1 + lane, 0), nr - 1);
-        const double* src = deriv ? rad_da : rad;
-        rad_s[f * kWave + lane] = src[((size_t)field * 2 + kind) * P + (kind == 0 ? c : min(c, nr - 2))];
-    }
-    __syncthreads();
-    if (!T.valid) return;  // wavefront-uniform
-    const double* slice = rad_s + T.slice * kF * kWave + lane;
-    lds_cptr rvi = (lds_cptr)(slice + 0 * kNumRad * kWave);
-    lds_cptr rvh = (lds_cptr)(slice + 1 * kNumRad * kWave);
-    lds_cptr rdi = (lds_cptr)(slice + 2 * kNumRad * kWave);
-    lds_cptr rdh = (lds_cptr)(slice + 3 * kNumRad * kWave);
-
-    const bool own = (lane >= 1) && (lane <= kWave - 2) && (col < nr);  // columns and halves this tile owns
-    const int j0 = chunk * A.rows;
-    const int j1 = min(j0 + A.rows, nth);
-    const double sg = (double)A.sigma;
-    const int last = (j1 < nth) ? j1 : nth - 1;
-    double acc = 0.0;  // spin-gradient partial sum of this lane
-    const unsigned emask = ext_mask(ext, gsample ? A.n_ext : 0, j0, j1 - 1, strip * kStripCols - 1);
-
-    // angular factors of row t (clamped: rows past the last are loaded
-    // ahead but never used)
-    auto ang_row = [&](int t) -> Ang { return load_ang(ang, nth, min(t, nth - 1)); };
-    auto coefs = [&](int t, const Ang& G, Coef& ki, Coef& kh, Sig& si, Sig& sh) {
-        const int o = t & A.zero;
-        const Rad Ri = rad_from_lds(rvi, o), Rh = rad_from_lds(rvh, o);
-        si = kerr_sigma(Ri, G);
-        sh = kerr_sigma(Rh, G);
-        ki = kerr_coef(Ri, G, si);
-        kh = kerr_coef(Rh, G, sh);
-    };
-
-    // Arrival of row t: forward stage-1 pieces of u^m and the same-row part
-    // of the transposed step applied to nu.
-    auto fresh = [&](int t, cd p, cd q, cd np, cd nq, cd ubp_prev, const Ang& G) -> AdjRow<SPIN, DOT> {
-        AdjRow<SPIN, DOT> R;
-        if constexpr (DOT) {
-            R.tan.tp = p;
-            R.tan.tq = q;
-        }
-        Coef ki, kh;
-        Sig si, sh;
-        coefs(t, G, ki, kh, si, sh);
-        R.si = si;
-        R.sh = sh;
-        R.g = G;
-        if constexpr (SPIN) {  // forward (as in the step kernel)
-            // Lanes outside the grid hold the clamped edge column, unmasked:
-            // a spin term of an owned column reads them only at the radial
-            // boundary, multiplied by cotangents that are zero there.
-            AdjFwd<true>& F = R.f;
-            const cd pr = from_right(p), qr = from_right(q);
-            F.ubp = cavg(p, pr);
-            F.ubq = cavg(q, qr);
-            F.dp = csub(pr, p);
-            F.dq = csub(qr, q);
-            const double tb = A.hdt_dr * kh.b;
-            const cd hp = {fma(-tb, F.dp.re, fma(A.hdt, F.ubq.re, F.ubp.re)),
-                           fma(-tb, F.dp.im, fma(A.hdt, F.ubq.im, F.ubp.im))};
-            const cd hpl = from_left(hp);
-            F.hbp = cavg(hp, hpl);
-            F.dhp = csub(hp, hpl);
-            const cd um = (t == 0) ? cscale(sg, F.ubp) : ubp_prev;
-            const cd dq1 = d_pi(kh, F.dp, F.dq);
-            const cd s1 = s_pi(kh, um, F.ubp, cd{0.0, 0.0}, F.ubq);
-            F.x = {fma(A.hdt, s1.re, fma(-A.hdt_dr, dq1.re, F.ubq.re)),
-                   fma(A.hdt, s1.im, fma(-A.hdt_dr, dq1.im, F.ubq.im))};
-            F.wp = A.hdt * (kh.a2s + kh.a1s);
-        }
-        // adjoint, stage 2 at (i, t):
-        //   Phi' = Phi + dt hbar_Pi - dt/dr b dh_Phi
-        //   Pi'  = Pi - dt/dr (c dh_Phi - b dh_Pi) + dt S_Pi(hbar)
-        R.np = masked(np, interior);
-        R.nq = masked(nq, interior);
-        const cd sq = cscale(A.dt, R.nq);                                   // cotangent of S_Pi(hbar)
-        R.up = cscale(ki.a2s + ki.a1s, sq);
-        R.dn = cscale(ki.a2s - ki.a1s, sq);
-        const cd lhbq = cadd(cscale(A.dt, R.np), cmul(-ki.ctr, ki.cti, sq));  // + conj(-Ct) sq
-        const cd ldhq = cscale(A.dt_dr * ki.b, R.nq);
-        // hbar/dh -> half point i+1/2: own (1/2 hbar + dh) + right neighbour's (1/2 hbar - dh)
-        const cd aq = {fma(0.5, lhbq.re, ldhq.re), fma(0.5, lhbq.im, ldhq.im)};
-        const cd bq = {fma(0.5, lhbq.re, -ldhq.re), fma(0.5, lhbq.im, -ldhq.im)};
-        R.lhq = cadd(aq, from_right(bq));
-        // stage 1 at (i+1/2, t): h_Pi = ubar_Pi - dt/2dr (c delta_Phi - b delta_Pi) + dt/2 S_Pi(ubar)
-        const cd tq = cscale(A.hdt, R.lhq);
-        R.uph = cscale(kh.a2s + kh.a1s, tq);
-        R.dnh = cscale(kh.a2s - kh.a1s, tq);
-        return R;
-    };
-
-    // rows of u^m (or T_m) are read only for the spin gradient
-    auto ldu = [&](size_t o) -> cd {
-        if constexpr (SPIN || DOT) return ld(u_in, o);
-        return cd{0.0, 0.0};
-    };
-
-    // ---- prologue ----------------------------------------------------------
-    AdjRow<SPIN, DOT> cur;
-    cd ubp_m, hbp_m, below, below_h;
-    {
-        cd ubp_prev = {0.0, 0.0};
-        if (j0 > 0) {
-            const size_t o = (size_t)(j0 - 1) * P + ci;
-            const AdjRow<SPIN, DOT> rm = fresh(j0 - 1, ldu(o), ldu(o + A.plane), ld(nu_in, o), ld(nu_in, o + A.plane),
-                                          ubp_prev, ang_row(j0 - 1));
-            if constexpr (SPIN) {
-                ubp_prev = rm.f.ubp;
-                ubp_m = rm.f.ubp;
-                hbp_m = rm.f.hbp;
-            }
-            below = rm.up;
-            below_h = rm.uph;
-        }
-        const size_t o = (size_t)j0 * P + ci;
-        cur = fresh(j0, ldu(o), ldu(o + A.plane), ld(nu_in, o), ld(nu_in, o + A.plane), ubp_prev, ang_row(j0));
-        if (j0 == 0) {
-            if constexpr (SPIN) {
-                ubp_m = cscale(sg, cur.f.ubp);
-                hbp_m = cscale(sg, cur.f.hbp);
-            }
-            below = cscale(sg, cur.dn);
-            below_h = cscale(sg, cur.dnh);
-        }
-    }
-    Ang g_next = ang_row(j0 + 1);  // angular factors one row ahead
-    cd bu[kRIF][2], bn[kRIF][2];
-#pragma unroll
-    for (int k = 0; k < kRIF; ++k) {
-        const size_t o = (size_t)min(j0 + 1 + k, last) * P + ci;
-        bu[k][0] = ldu(o);
-        bu[k][1] = ldu(o + A.plane);
-        bn[k][0] = ld(nu_in, o);
-        bn[k][1] = ld(nu_in, o + A.plane);
-    }
-
-    // Row t is in cur; row t+1 arrives into nxt (the two alternate roles
-    // from row to row, so no row state is copied).
-    auto finish_row = [&](int t, AdjRow<SPIN, DOT>& cur, AdjRow<SPIN, DOT>& nxt, cd* ru, cd* rn) {
-        cd ubp_p, hbp_p, above, above_h;
-        const Ang g1 = g_next;
-        g_next = ang_row(t + 2);
-        if (t + 1 < nth) {
-            cd ubp_cur = {0.0, 0.0};
-            if constexpr (SPIN) ubp_cur = cur.f.ubp;
-            nxt = fresh(t + 1, ru[0], ru[1], rn[0], rn[1], ubp_cur, g1);
-            if constexpr (SPIN) {
-                ubp_p = nxt.f.ubp;
-                hbp_p = nxt.f.hbp;
-            }
-            above = nxt.dn;
-            above_h = nxt.dnh;
-        } else {
-            if constexpr (SPIN) {
-                ubp_p = cscale(sg, cur.f.ubp);
-                hbp_p = cscale(sg, cur.f.hbp);
-            }
-            above = cscale(sg, cur.up);
-            above_h = cscale(sg, cur.uph);
-            nxt = cur;  // unused: the sweep ends with this row
-        }
-        {
-            const size_t o = (size_t)min(t + 1 + kRIF, last) * P + ci;
-            ru[0] = ldu(o);
-            ru[1] = ldu(o + A.plane);
-            rn[0] = ld(nu_in, o);
-            rn[1] = ld(nu_in, o + A.plane);
-        }
-        // coefficients of row t again (rebuilding them from the tables is
-        // cheaper than keeping them in registers since the row arrived)
-        const Ang& G = cur.g;
-        const Sig si = cur.si, sh = cur.sh;
-        Coef ki, kh;
-        {
-            const int o = t & A.zero;
-            ki = kerr_coef(rad_from_lds(rvi, o), G, si);
-            kh = kerr_coef(rad_from_lds(rvh, o), G, sh);
-        }
-
-        // adjoint: hbar_Phi cotangent complete, then stage 1 transposed at the half
-        // the row's own stage-2 theta piece and dh_Phi cotangent (rebuilt
-        // here rather than kept in registers since the row arrived)
-        const cd mid = cmul(-2.0 * ki.a2s - ki.v0r, ki.v0i, cscale(A.dt, cur.nq));  // (-2 A2 - conj V0) sq
-        const cd cnq = cmul(ki.cre, -ki.cim, cur.nq);                                // conj(c) nq
-        const cd ldhp = {-A.dt_dr * fma(ki.b, cur.np.re, cnq.re), -A.dt_dr * fma(ki.b, cur.np.im, cnq.im)};
-        const cd lhbp = cadd3(mid, below, above);
-        const cd ap = {fma(0.5, lhbp.re, ldhp.re), fma(0.5, lhbp.im, ldhp.im)};
-        const cd bp = {fma(0.5, lhbp.re, -ldhp.re), fma(0.5, lhbp.im, -ldhp.im)};
-        const cd lhp = cadd(ap, from_right(bp));
-        //   h_Phi = ubar_Phi + dt/2 ubar_Pi - dt/2dr b delta_Phi
-        const cd midh = cmul(-2.0 * kh.a2s - kh.v0r, kh.v0i, cscale(A.hdt, cur.lhq));
-        const cd lubp = cadd(lhp, cadd3(midh, below_h, above_h));
-        const cd ctq = cmul(-kh.ctr, kh.cti, cur.lhq);                      // conj(-Ct) lhq
-        const cd lubq = {fma(A.hdt, lhp.re, fma(A.hdt, ctq.re, cur.lhq.re)),
-                         fma(A.hdt, lhp.im, fma(A.hdt, ctq.im, cur.lhq.im))};
-        const cd cq = cmul(kh.cre, -kh.cim, cur.lhq);                        // conj(c) lhq
-        const cd ldp = {-A.hdt_dr * fma(kh.b, lhp.re, cq.re), -A.hdt_dr * fma(kh.b, lhp.im, cq.im)};
-        const cd ldq = cscale(A.hdt_dr * kh.b, cur.lhq);
-        // ubar/delta -> integer points: own (1/2 ubar - delta) + left neighbour's (1/2 ubar + delta)
-        const cd cP = {fma(0.5, lubp.re, ldp.re), fma(0.5, lubp.im, ldp.im)};
-        const cd cQ = {fma(0.5, lubq.re, ldq.re), fma(0.5, lubq.im, ldq.im)};
-        const cd dP = {fma(0.5, lubp.re, -ldp.re), fma(0.5, lubp.im, -ldp.im)};
-        const cd dQ = {fma(0.5, lubq.re, -ldq.re), fma(0.5, lubq.im, -ldq.im)};
-        cd outp = cadd3(cur.np, dP, from_left(cP));
-        const cd outq = cadd3(cur.nq, dQ, from_left(cQ));
-        // transposed extraction of the sample of the output state: each
-        // stencil point of an extraction point receives its bilinear weight
-        // times the sample's gradient (gsample[e], re/im interleaved)
-        if (emask != 0) {
-            for (int e = 0; e < A.n_ext; ++e) {
-                if (!((emask >> e) & 1u)) continue;
-                const ExtPoint E = ext[e];
-                if (t != E.rowa && t != E.rowb) continue;  // wavefront-uniform
-                const double wrow = (t == E.rowa) ? E.wa : E.wb;
-                const double w = (col == E.col) ? wrow * (1.0 - E.wr) : (col == E.col + 1) ? wrow * E.wr : 0.0;
-                outp.re = fma(w, gsample[2 * e], outp.re);
-                outp.im = fma(w, gsample[2 * e + 1], outp.im);
-            }
-        }
-        if (own) {
-            const size_t o = (size_t)t * P + col;
-            st_state<KEEP>(lam_out, o, outp);
-            st_state<KEEP>(lam_out, o + A.plane, outq);
-        }
-
-        // spin gradient: coefficient derivatives against the cotangents of
-        // the stage outputs, at the owned half point and integer point
-        if constexpr (SPIN) {
-            // forward stage-1 Pi value at the halves i+1/2, i-1/2 of row t
-            const AdjFwd<true>& F = cur.f;
-            const cd hq = {fma(F.wp, ubp_p.re, F.x.re), fma(F.wp, ubp_p.im, F.x.im)};
-            const cd hql = from_left(hq);
-            const cd hbq = cavg(hq, hql);
-            const cd dhq = csub(hq, hql);
-            const int o = t & A.zero;
-            const Coef dkh = kerr_coef_da(rvh, rdh, o, G, sh, kh);
-            const Coef dki = kerr_coef_da(rvi, rdi, o, G, si, ki);
-            // half: dh_Phi = -dt/2dr db delta_Phi;  dh_Pi = -dt/2dr (dc dP - db dQ) + dt/2 dS(ubar)
-            const cd dhP = cscale(-A.hdt_dr * dkh.b, F.dp);
-            const cd dd1 = d_pi(dkh, F.dp, F.dq);
-            const cd ds1 = s_pi(dkh, ubp_m, F.ubp, ubp_p, F.ubq);
-            const cd dhQ = {fma(A.hdt, ds1.re, -A.hdt_dr * dd1.re), fma(A.hdt, ds1.im, -A.hdt_dr * dd1.im)};
-            // integer: dPhi' = -dt/dr db dh_Phi;  dPi' = -dt/dr (dc dhP - db dhQ) + dt dS(hbar)
-            const cd dPp = cscale(-A.dt_dr * dki.b, F.dhp);
-            const cd dd2 = d_pi(dki, F.dhp, dhq);
-            const cd ds2 = s_pi(dki, hbp_m, F.hbp, hbp_p, hbq);
-            const cd dQp = {fma(A.dt, ds2.re, -A.dt_dr * dd2.re), fma(A.dt, ds2.im, -A.dt_dr * dd2.im)};
-            double c = lhp.re * dhP.re + lhp.im * dhP.im;
-            c = fma(cur.lhq.re, dhQ.re, fma(cur.lhq.im, dhQ.im, c));
-            c = fma(cur.np.re, dPp.re, fma(cur.np.im, dPp.im, c));
-            c = fma(cur.nq.re, dQp.re, fma(cur.nq.im, dQp.im, c));
-            if (own) acc += c;
-        }
-
-        // spin gradient from the stored tangent: Re <nu, T_m> (T_m is zero on
-        // the radial boundary columns, where nu is masked)
-        if constexpr (DOT) {
-            double c = cur.np.re * cur.tan.tp.re + cur.np.im * cur.tan.tp.im;
-            c = fma(cur.nq.re, cur.tan.tq.re, fma(cur.nq.im, cur.tan.tq.im, c));
-            if (own) acc += c;
-        }
-
-        below = cur.up;
-        below_h = cur.uph;
-        if constexpr (SPIN) {
-            ubp_m = cur.f.ubp;
-            hbp_m = cur.f.hbp;
-        }
-    };
-
-    // rows in pairs (the ring slot of row t+1 is (t - j0) mod kRIF)
-    AdjRow<SPIN, DOT> other;
-    int t0 = j0;
-    for (; t0 + 2 <= j1; t0 += 2) {
-        finish_row(t0, cur, other, bu[0], bn[0]);
-        finish_row(t0 + 1, other, cur, bu[1 % kRIF], bn[1 % kRIF]);
-    }
-    if (t0 < j1) finish_row(t0, cur, other, bu[0], bn[0]);
-
-    // fixed-order reduction over the wavefront, one slot per tile
-    if constexpr (SPIN || DOT) {
-        for (int off = kWave / 2; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, kWave);
-        if (lane == 0) dlda_slots[(size_t)chunk * A.n_strips + strip] += acc;
-    }
+    adjoint_tile<1, SPIN ? kStates : DOT ? kDot : kNone, KEEP>(nu_in, lam_out, rad, rad_da, ang, ext, {gsample}, {u_in},
+                                                               dlda_slots, A, rad_s);
 }
 
-// Two adjoint steps per pass, cotangents only (temporal blocking, as the
-// forward two-step pass): sweep A takes lambda^{m+2} row by row and
-// completes lambda^{m+1}, which goes from registers into sweep B, one row
-// behind, completing lambda^m.  A covers rows j0-1 .. j1 (reading
-// j0-2 .. j1+1), B writes j0 .. j1-1; A's results are valid on lanes 1..62
-// and B's on 2..61 (60-column strips).  Every quantity is formed by the same
-// expressions as in lw_adjoint_kernel<false>, so the results are identical.
-struct AdjCot {
-    cd np, nq;          // nu at (i, t), radial boundary columns zeroed
-    cd lhq;             // cotangent of the stage-1 Pi value at the half
-    cd up, dn;          // stage-2 theta-stencil pieces to rows t+1, t-1
-    cd uph, dnh;        // stage-1 theta-stencil pieces to rows t+1, t-1
-    Sig si, sh;         // 1/Sigma, 1/Sigma^2 at the integer and half point
-    Ang g;              // angular factors of the row (wavefront-uniform)
-};
-
+// Two adjoint steps per pass (temporal blocking): lambda^{m+2} -> lambda^m.
 // DOT: also the spin gradient's terms of both steps from stored tangents,
-// Re <lambda^{m+2}, T_{m+1}> (tan_a, with the input rows as sweep A
-// completes them) and Re <lambda^{m+1}, T_m> (tan_b, with sweep B's rows),
-// over the owned points, summed per tile into slots.
+// tan_a = T_{m+1} and tan_b = T_m.
 template <bool DOT, int KEEP>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8)))
-    lw_adjoint2_kernel(const double2* __restrict__ nu_in, double2* __restrict__ lam_out, const double* __restrict__ rad, const double* __restrict__ ang,
+    lw_adjoint2_kernel(const double2* __restrict__ nu_in, double2* __restrict__ lam_out,
+                       const double* __restrict__ rad, const double* __restrict__ ang,
                        const ExtPoint* __restrict__ ext, const double* __restrict__ gsample_a,
                        const double* __restrict__ gsample_b, const double2* __restrict__ tan_a,
                        const double2* __restrict__ tan_b, double* __restrict__ dlda_slots, AdjScalars A) {
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wpb = blockDim.x / kWave;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const TileOf T = tile_of(xcd_block(blockIdx.x, gridDim.x), wpb, wave, A.n_strips, A.n_chunks);
-    const int strip = T.strip, chunk = T.chunk;
-    const int nr = A.nr, nth = A.nth, P = A.pitch;
-    const int col = strip * kStripCols2 - 2 + lane;
-    const unsigned long long interior = ((col >= 1) && (col < nr - 1)) ? ~0ull : 0ull;
-    const int ci = min(max(col, 0), nr - 1);
-
-    constexpr int kF = 2 * kNumRad;
-    extern __shared__ double rad_s[];  // as in lw_adjoint_kernel<false>
-    for (int f = wave; f < T.n_slices * kF; f += wpb) {
-        const int g = f % kF, kind = g / kNumRad, field = g % kNumRad;
-        const int c = min(max((T.s0 + f / kF) * kStripCols2 - 2 + lane, 0), nr - 1);
-        rad_s[f * kWave + lane] = rad[((size_t)field * 2 + kind) * P + (kind == 0 ? c : min(c, nr - 2))];
-    }
-    __syncthreads();
-    if (!T.valid) return;  // wavefront-uniform
-    const double* slice = rad_s + T.slice * kF * kWave + lane;
-    lds_cptr rvi = (lds_cptr)(slice + 0 * kNumRad * kWave);
-    lds_cptr rvh = (lds_cptr)(slice + 1 * kNumRad * kWave);
-
-    const bool own = (lane >= 2) && (lane <= kWave - 3) && (col < nr);
-    // Owned rows are stored through row resources (the lane's byte offset,
-    // or none) without DOT; with DOT, whose tangent rows need the registers,
-    // by plain stores under the lane mask (measured: the row resources spill
-    // there).
-    const int32_t row_bytes = P * (int32_t)sizeof(double2);
-    const uint32_t st_off = own ? (uint32_t)col * sizeof(double2) : kOffNone;
-    auto put_row = [&](int t, cd wp, cd wq) {
-        if constexpr (DOT) {
-            if (own) {
-                const size_t o = (size_t)t * P + col;
-                st_state<KEEP>(lam_out, o, wp);
-                st_state<KEEP>(lam_out, o + A.plane, wq);
-            }
-        } else {
-            const size_t o = (size_t)t * P;
-            st_row<KEEP>(row_rsrc(lam_out + o, row_bytes), st_off, wp);
-            st_row<KEEP>(row_rsrc(lam_out + o + A.plane, row_bytes), st_off, wq);
-        }
-    };
-    const int j0 = chunk * A.rows;
-    const int j1 = min(j0 + A.rows, nth);
-    const int aE = min(j1, nth - 1);        // last row sweep A completes
-    const int last = min(aE + 1, nth - 1);  // last row of lambda^{m+2} read
-    const double sg = (double)A.sigma;
-    // both sweeps' output rows, j0-1 .. j1
-    const unsigned emask = ext_mask(ext, (gsample_a || gsample_b) ? A.n_ext : 0, j0 - 1, j1, strip * kStripCols2 - 2);
-
-    auto ang_row = [&](int t) -> Ang { return load_ang(ang, nth, min(t, nth - 1)); };
-    // arrival of a row (as fresh() of lw_adjoint_kernel<false>)
-    // The row's coefficients come with it: sweep B's rows are the rows sweep
-    // A has just completed, whose coefficients A's finish() built (same
-    // expressions, same values), so B takes them instead of rebuilding them.
-    auto fresh_k = [&](cd np, cd nq, const Ang& G, Sig si, Sig sh, const Coef& ki, const Coef& kh) -> AdjCot {
-        AdjCot R;
-        R.si = si;
-        R.sh = sh;
-        R.g = G;
-        R.np = masked(np, interior);
-        R.nq = masked(nq, interior);
-        const cd sq = cscale(A.dt, R.nq);
-        R.up = cscale(ki.a2s + ki.a1s, sq);
-        R.dn = cscale(ki.a2s - ki.a1s, sq);
-        const cd lhbq = cadd(cscale(A.dt, R.np), cmul(-ki.ctr, ki.cti, sq));
-        const cd ldhq = cscale(A.dt_dr * ki.b, R.nq);
-        const cd aq = {fma(0.5, lhbq.re, ldhq.re), fma(0.5, lhbq.im, ldhq.im)};
-        const cd bq = {fma(0.5, lhbq.re, -ldhq.re), fma(0.5, lhbq.im, -ldhq.im)};
-        R.lhq = cadd(aq, from_right(bq));
-        const cd tq = cscale(A.hdt, R.lhq);
-        R.uph = cscale(kh.a2s + kh.a1s, tq);
-        R.dnh = cscale(kh.a2s - kh.a1s, tq);
-        return R;
-    };
-    auto fresh = [&](int t, cd np, cd nq, const Ang& G) -> AdjCot {
-        const int o = t & A.zero;
-        const Rad Ri = rad_from_lds(rvi, o), Rh = rad_from_lds(rvh, o);
-        const Sig si = kerr_sigma(Ri, G), sh = kerr_sigma(Rh, G);
-        return fresh_k(np, nq, G, si, sh, kerr_coef(Ri, G, si), kerr_coef(Rh, G, sh));
-    };
-    // completion of row t (as in lw_adjoint_kernel<false>): the new
-    // cotangent, plus E^T g of the output state's sample; ki, kh receive the
-    // row's coefficients
-    auto finish = [&](int t, const AdjCot& cur, cd below, cd below_h, cd above, cd above_h, const double* gsample,
-                      cd& outp, cd& outq, Coef& ki, Coef& kh) {
-        {
-            const int o = t & A.zero;
-            ki = kerr_coef(rad_from_lds(rvi, o), cur.g, cur.si);
-            kh = kerr_coef(rad_from_lds(rvh, o), cur.g, cur.sh);
-        }
-        const cd mid = cmul(-2.0 * ki.a2s - ki.v0r, ki.v0i, cscale(A.dt, cur.nq));
-        const cd cnq = cmul(ki.cre, -ki.cim, cur.nq);
-        const cd ldhp = {-A.dt_dr * fma(ki.b, cur.np.re, cnq.re), -A.dt_dr * fma(ki.b, cur.np.im, cnq.im)};
-        const cd lhbp = cadd3(mid, below, above);
-        const cd ap = {fma(0.5, lhbp.re, ldhp.re), fma(0.5, lhbp.im, ldhp.im)};
-        const cd bp = {fma(0.5, lhbp.re, -ldhp.re), fma(0.5, lhbp.im, -ldhp.im)};
-        const cd lhp = cadd(ap, from_right(bp));
-        const cd midh = cmul(-2.0 * kh.a2s - kh.v0r, kh.v0i, cscale(A.hdt, cur.lhq));
-        const cd lubp = cadd(lhp, cadd3(midh, below_h, above_h));
-        const cd ctq = cmul(-kh.ctr, kh.cti, cur.lhq);
-        const cd lubq = {fma(A.hdt, lhp.re, fma(A.hdt, ctq.re, cur.lhq.re)),
-                         fma(A.hdt, lhp.im, fma(A.hdt, ctq.im, cur.lhq.im))};
-        const cd cq = cmul(kh.cre, -kh.cim, cur.lhq);
-        const cd ldp = {-A.hdt_dr * fma(kh.b, lhp.re, cq.re), -A.hdt_dr * fma(kh.b, lhp.im, cq.im)};
-        const cd ldq = cscale(A.hdt_dr * kh.b, cur.lhq);
-        const cd cP = {fma(0.5, lubp.re, ldp.re), fma(0.5, lubp.im, ldp.im)};
-        const cd cQ = {fma(0.5, lubq.re, ldq.re), fma(0.5, lubq.im, ldq.im)};
-        const cd dP = {fma(0.5, lubp.re, -ldp.re), fma(0.5, lubp.im, -ldp.im)};
-        const cd dQ = {fma(0.5, lubq.re, -ldq.re), fma(0.5, lubq.im, -ldq.im)};
-        outp = cadd3(cur.np, dP, from_left(cP));
-        outq = cadd3(cur.nq, dQ, from_left(cQ));
-        if (gsample != nullptr && emask != 0) {
-            for (int e = 0; e < A.n_ext; ++e) {
-                if (!((emask >> e) & 1u)) continue;
-                const ExtPoint E = ext[e];
-                if (t != E.rowa && t != E.rowb) continue;  // wavefront-uniform
-                const double wrow = (t == E.rowa) ? E.wa : E.wb;
-                const double w = (col == E.col) ? wrow * (1.0 - E.wr) : (col == E.col + 1) ? wrow * E.wr : 0.0;
-                outp.re = fma(w, gsample[2 * e], outp.re);
-                outp.im = fma(w, gsample[2 * e + 1], outp.im);
-            }
-        }
-    };
-    auto load_row = [&](int t, cd& p, cd& q) {
-        const size_t o = (size_t)min(max(t, 0), last) * P + ci;
-        p = ld(nu_in, o);
-        q = ld(nu_in, o + A.plane);
-    };
-    // a tangent row (DOT), clamped to the grid
-    struct TRow {
-        cd p, q;
-    };
-    auto load_tan = [&](const double2* tan, int t, TRow& r) {
-        if constexpr (DOT) {
-            const size_t o = (size_t)min(max(t, 0), nth - 1) * P + ci;
-            r.p = ld(tan, o);
-            r.q = ld(tan, o + A.plane);
-        }
-    };
-    double acc = 0.0;  // spin-gradient partial sum of this lane (DOT)
-    // Re <cotangent row, tangent row> of an owned row
-    auto dot = [&](const AdjCot& c, const TRow& t) {
-        if constexpr (DOT) {
-            double v = c.np.re * t.p.re + c.np.im * t.p.im;
-            v = fma(c.nq.re, t.q.re, fma(c.nq.im, t.q.im, v));
-            if (own) acc += v;
-        }
-    };
-
-    // ---- prologue: A completes rows j0-1 (if j0 > 0) and j0; B takes them
-    // as its halo row and its first row -------------------------------------
-    AdjCot a_cur, b_cur;
-    cd a_below, a_below_h, b_below, b_below_h;
-    {
-        cd p, q;
-        const int aS = max(j0 - 1, 0);
-        if (aS > 0) {
-            load_row(aS - 1, p, q);
-            const AdjCot h = fresh(aS - 1, p, q, ang_row(aS - 1));
-            a_below = h.up;
-            a_below_h = h.uph;
-        }
-        load_row(aS, p, q);
-        a_cur = fresh(aS, p, q, ang_row(aS));
-        if (aS == 0) {
-            a_below = cscale(sg, a_cur.dn);
-            a_below_h = cscale(sg, a_cur.dnh);
-        }
-        for (int r = aS; r <= j0; ++r) {  // one or two rows, wavefront-uniform
-            AdjCot a_nxt;
-            cd above, above_h;
-            if (r + 1 < nth) {
-                load_row(r + 1, p, q);
-                a_nxt = fresh(r + 1, p, q, ang_row(r + 1));
-                above = a_nxt.dn;
-                above_h = a_nxt.dnh;
-            } else {
-                above = cscale(sg, a_cur.up);
-                above_h = cscale(sg, a_cur.uph);
-                a_nxt = a_cur;
-            }
-            cd vp, vq;
-            Coef ki, kh;
-            finish(r, a_cur, a_below, a_below_h, above, above_h, gsample_a, vp, vq, ki, kh);
-            if (DOT && r == j0) {  // the one owned row the prologue completes
-                TRow tr;
-                load_tan(tan_a, r, tr);
-                dot(a_cur, tr);
-            }
-            a_below = a_cur.up;
-            a_below_h = a_cur.uph;
-            const AdjCot ar = a_cur;
-            a_cur = a_nxt;
-            if (r < j0) {  // B's halo row j0-1
-                const AdjCot h = fresh_k(vp, vq, ar.g, ar.si, ar.sh, ki, kh);
-                b_below = h.up;
-                b_below_h = h.uph;
-            } else {
-                b_cur = fresh_k(vp, vq, ar.g, ar.si, ar.sh, ki, kh);
-                if (r == 0) {
-                    b_below = cscale(sg, b_cur.dn);
-                    b_below_h = cscale(sg, b_cur.dnh);
-                }
-            }
-        }
-    }
-
-    // ---- main sweep: A completes row r, B row r-1; the row states swap
-    // roles from row to row instead of being copied --------------------------
-    cd rp[2], rq[2];
-    load_row(j0 + 2, rp[0], rq[0]);
-    load_row(j0 + 3, rp[1], rq[1]);
-    // tangent rows (DOT): step_row(r) finds T_{m+1} row r in ta and T_m row
-    // r-1 in tb, and loads the next rows into them once used
-    TRow ta, tb;
-    load_tan(tan_a, j0 + 1, ta);
-    load_tan(tan_b, j0, tb);
-    Ang g_next = ang_row(j0 + 2);
-    auto step_row = [&](int r, cd& lp, cd& lq, AdjCot& ac, AdjCot& an, AdjCot& bc, AdjCot& bn, TRow& tar,
-                        TRow& tbr) {
-        cd above, above_h;
-        const Ang g1 = g_next;
-        g_next = ang_row(r + 2);
-        if (r + 1 < nth) {
-            an = fresh(r + 1, lp, lq, g1);
-            above = an.dn;
-            above_h = an.dnh;
-        } else {
-            above = cscale(sg, ac.up);
-            above_h = cscale(sg, ac.uph);
-            an = ac;  // unused: the sweep ends with this row
-        }
-        load_row(r + 3, lp, lq);
-        cd vp, vq;
-        Coef ki, kh;
-        finish(r, ac, a_below, a_below_h, above, above_h, gsample_a, vp, vq, ki, kh);
-        if (r < j1) dot(ac, tar);  // wavefront-uniform: row j1 is a halo row of sweep A
-        load_tan(tan_a, r + 1, tar);
-        a_below = ac.up;
-        a_below_h = ac.uph;
-
-        bn = fresh_k(vp, vq, ac.g, ac.si, ac.sh, ki, kh);
-        cd wp, wq;
-        finish(r - 1, bc, b_below, b_below_h, bn.dn, bn.dnh, gsample_b, wp, wq, ki, kh);
-        dot(bc, tbr);
-        load_tan(tan_b, r, tbr);
-        put_row(r - 1, wp, wq);
-        b_below = bc.up;
-        b_below_h = bc.uph;
-    };
-    auto last_row = [&](const AdjCot& bc, const TRow& tbr) {  // the grid's last row: B with the pole ghost row
-        cd wp, wq;
-        Coef ki, kh;
-        finish(nth - 1, bc, b_below, b_below_h, cscale(sg, bc.up), cscale(sg, bc.uph), gsample_b, wp, wq, ki, kh);
-        dot(bc, tbr);
-        put_row(nth - 1, wp, wq);
-    };
-    AdjCot a_oth, b_oth;
-    int r0 = j0 + 1;
-    // Without DOT, enter the row loop as its iterations end: the ring's first
-    // row loaded, its second still in flight, so that the compiler's wait at
-    // the loop head, which must suit both ways in, does not drain the ring.
-    if constexpr (!DOT) __builtin_amdgcn_s_waitcnt(waitcnt_vm(2));
-    for (; r0 + 1 <= aE; r0 += 2) {
-        step_row(r0, rp[0], rq[0], a_cur, a_oth, b_cur, b_oth, ta, tb);
-        step_row(r0 + 1, rp[1], rq[1], a_oth, a_cur, b_oth, b_cur, ta, tb);
-    }
-    if (r0 <= aE) {
-        step_row(r0, rp[0], rq[0], a_cur, a_oth, b_cur, b_oth, ta, tb);
-        if (j1 == nth) last_row(b_oth, tb);
-    } else if (j1 == nth) {
-        last_row(b_cur, tb);
-    }
-
-    // fixed-order reduction over the wavefront, one slot per tile
-    if constexpr (DOT) {
-        for (int off = kWave / 2; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, kWave);
-        if (lane == 0) dlda_slots[(size_t)chunk * A.n_strips + strip] += acc;
-    }
+    extern __shared__ double rad_s[];
+    adjoint_tile<2, DOT ? kDot : kNone, KEEP>(nu_in, lam_out, rad, nullptr, ang, ext, {gsample_a, gsample_b},
+                                              {tan_a, tan_b}, dlda_slots, A, rad_s);
 }
 
 // One Lax-Wendroff step, u^{m+1} = A u^m, that also writes the derivative of
@@ -819,7 +472,7 @@ hipError_t launch_adjoint(const AdjArgs& a, int waves_per_block, AdjMode mode, h
     dim3 grid, block;
     size_t lds;
     const bool spin = mode == AdjMode::kSpin;
-    adjoint_launch_shape(a.k, waves_per_block, (spin ? 4 : 2) * kNumRad, &grid, &block, &lds);
+    adjoint_launch_shape(a.k, waves_per_block, (spin ? 4 : 2) * kNumSRad, &grid, &block, &lds, kHitDoubles * sizeof(double));
     const bool keep = a.k.keep != 0;
     auto pick = [&](auto k0, auto k1) { return keep ? k1 : k0; };
     auto kern = spin ? pick(lw_adjoint_kernel<true, false, 0>, lw_adjoint_kernel<true, false, 1>)
@@ -836,7 +489,7 @@ hipError_t launch_adjoint2(const AdjArgs& a, const double* gsample_b, const doub
                            hipStream_t s) {
     dim3 grid, block;
     size_t lds;
-    adjoint_launch_shape(a.k, waves_per_block, 2 * kNumRad, &grid, &block, &lds);
+    adjoint_launch_shape(a.k, waves_per_block, 2 * kNumSRad, &grid, &block, &lds, kHitDoubles * sizeof(double));
     const bool keep = a.k.keep != 0;
     auto kern = a.u_in ? (keep ? lw_adjoint2_kernel<true, 1> : lw_adjoint2_kernel<true, 0>)
                        : (keep ? lw_adjoint2_kernel<false, 1> : lw_adjoint2_kernel<false, 0>);
@@ -851,7 +504,7 @@ hipError_t launch_tangent(const double2* u_in, double2* u_out, double2* t_out, c
     size_t lds;
     adjoint_launch_shape(a.k, waves_per_block, 4 * kNumSRad, &grid, &block, &lds, kTanSlots * sizeof(double2));
     hipLaunchKernelGGL(a.k.keep ? lw_tangent_kernel<1> : lw_tangent_kernel<0>, grid, block, lds, s, u_in, u_out, t_out,
-                       a.srad, a.srad_da, a.ang, a.k);
+                       a.rad, a.rad_da, a.ang, a.k);
     return hipGetLastError();
 }
 

@@ -23,29 +23,11 @@ constexpr int kStripCols2 = kWave - 4;
 constexpr int kMaxPassSteps = 3;
 constexpr int strip_cols(int k) { return kWave - 2 * k; }
 
-// Radial table fields, each a row of `pitch` doubles, first for the integer
-// positions r*_i then for the half positions r*_{i+1/2}.  With r, Delta,
-// rho = r^2 + a^2 at the position (Sigma^2 = rho^2 - a^2 Delta sin^2 th):
-enum RadField : int {
-    R_RHO = 0,  // rho
-    R_RHO2,     // rho^2
-    R_A2D,      // a^2 Delta                     Sigma^2 = rho^2 - a^2 Delta sin^2
-    R_RB1,      // 2 r Delta / rho               b' = (RB1 - (RB2 - RB3 sin^2)/Sigma^2)/Sigma
-    R_RB2,      // 2 r rho Delta
-    R_RB3,      // a^2 (r - 1) Delta
-    R_CTR,      // 2 s (r Delta - (r^2 - a^2))   Re Ct = CTR / Sigma^2
-    R_CTI0,     // 4 a m r                       Im Ct = (CTI0 + CTI1 cos) / Sigma^2
-    R_CTI1,     // 2 s a Delta
-    R_B1N,      // rho (6 Delta/r + 2 s (r-1) + 2 r Delta/rho)     B1 = B1N / Sigma^2
-    R_DL2,      // Delta / dth^2                 A2/dth^2 = DL2 / Sigma^2
-    R_V0R,      // -m^2 a^2 - 6 Delta ((s+2) r^2 - (s+3) r + a^2) / r^2
-    R_V0I,      // -2 s m a (r - 1)              Im V0 = V0I / Sigma^2
-    kNumRad
-};
-
-// Radial factors of the forward step's stage coefficients (stage_coef): row
-// f * 2 + kind (kind 0: the columns, 1: the half points), each with the
-// factors of its stage (d on b and c, t on the rest, see Stage).
+// Radial table of the step's stage coefficients (stage_coef), each field a
+// row of `pitch` doubles, field f of kind k (0: the columns r*_i, 1: the half
+// points r*_{i+1/2}) in row 2 f + k, with the factors of its stage (d on b
+// and c, t on the rest, see Stage).  With r, Delta, rho = r^2 + a^2 at the
+// position:
 enum SRadField : int {
     S_RHO2 = 0,  // rho^2
     S_A2D,       // a^2 Delta                 Sigma^2 = rho^2 - a^2 Delta sin^2
@@ -171,16 +153,25 @@ struct AdjArgs {
     const double2* nu_in;    // lambda^{m+1}, [Phi, Pi][nth][pitch]
     const double2* u_in;     // u^m
     double2* lam_out;        // lambda^m
-    const double* rad;       // [kNumRad][2][pitch]
+    const double* rad;       // [kNumSRad][2][pitch]
     const double* rad_da;    // d/da of rad
-    const double* srad;      // [kNumSRad][2][pitch]
-    const double* srad_da;   // d/da of srad
     const double* ang;       // [nth][kNumAng]
     double* slots;           // [n_strips * n_chunks] spin-gradient partial sums (accumulated)
     const ExtPoint* ext;     // [n_ext] extraction points
     const double* gsample;   // gradient of the output state's sample, 2 doubles per point, or nullptr
     AdjScalars k;
 };
+
+// What a grid's tables are built from; d, t: the stages' factors of the two
+// kinds of position (0: columns, 1: half points), see Stage.
+struct TableArgs {
+    double a, rmin, dr, dth, d[2], t[2];
+    int32_t nr, nth, pitch, s, m;
+};
+// x_tab [2][pitch]: r - r_+ at the positions; rad [kNumSRad][2][pitch] (both
+// nullptr: not built); ang [nth][kNumAng]; *failed = 1 if a position has no r.
+hipError_t launch_tables(const TableArgs& a, double* x_tab, double* rad, double* ang, int* failed, hipStream_t s);
+hipError_t launch_tables_da(const TableArgs& a, const double* x_tab, double* da, hipStream_t s);
 
 // Launchers (lw_kernels.hip, adjoint_kernels.hip).  All return the
 // hipError_t of the launch.
@@ -214,6 +205,8 @@ hipError_t launch_nonfinite_step(const double2* u, int nr, int nth, int pitch, l
 // read); with the spin gradient recomputed from u^m = u_in; with the spin
 // gradient as the dot product of nu with T_m = u_in, the stored tangent.
 enum class AdjMode { kCotangent, kSpin, kTangentDot };
+// Their fused transposed extraction takes at most kRowHits points on a row of a tile.
+constexpr int kRowHits = 3;
 hipError_t launch_adjoint(const AdjArgs& a, int waves_per_block, AdjMode mode, hipStream_t s);
 // Two cotangent adjoint steps: nu_in = lambda^{m+2} -> lam_out = lambda^m
 // (k.n_strips counted in kStripCols2-column strips); a.gsample is the sample

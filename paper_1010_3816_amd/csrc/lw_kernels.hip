@@ -68,10 +68,6 @@ struct RowCoef {
     Stage h, i;
 };
 
-// sched_barrier mask: all classes the scheduler may move across, scalar
-// memory not among them.
-constexpr int kAllButScalarLoads = 0x3FF;
-
 // K Lax-Wendroff steps in one pass over a tile of 64 - 2K columns by A.rows
 // rows (temporal blocking: only the pass's input is read and its output
 // written).  Iteration r of the row loop takes input row r from memory; step

@@ -60,7 +60,7 @@ hipError_t launch_spin_tangent(const double2* u_in, const double2* v_in, double2
     size_t lds;
     adjoint_launch_shape(a.k, waves_per_block, 4 * kNumSRad, &grid, &block, &lds, kTanSlots * sizeof(double2));
     hipLaunchKernelGGL(a.k.keep ? lw_spin_tangent_kernel<1> : lw_spin_tangent_kernel<0>, grid, block, lds, s, u_in,
-                       v_in, u_out, v_out, a.srad, a.srad_da, a.ang, a.ext, series_u, series_v, a.k);
+                       v_in, u_out, v_out, a.rad, a.rad_da, a.ang, a.ext, series_u, series_v, a.k);
     return hipGetLastError();
 }
 

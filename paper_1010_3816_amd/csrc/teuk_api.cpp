@@ -52,7 +52,7 @@ struct Layout {
     int pitch = 0;
     size_t state = 0;                 // bytes of one state [Phi, Pi][nth][pitch]
     size_t off_u[2]{};                // ping-pong state
-    size_t off_rad = 0, off_srad = 0, off_ang = 0;  // KERR tables
+    size_t off_rad = 0, off_ang = 0, off_x = 0;  // KERR tables; x = r - r_+ at their positions
     size_t off_uci = 0, off_uch = 0;  // USER tables
     size_t off_ext = 0, off_ext2 = 0, off_flag = 0;
     size_t total = 0;
@@ -99,11 +99,13 @@ Layout make_layout(const teuk_params* p) {
         o += L.state;
     }
     L.off_rad = o;
-    o += align_up((size_t)kNumRad * 2 * L.pitch * sizeof(double));
-    L.off_srad = o;
     o += align_up((size_t)kNumSRad * 2 * L.pitch * sizeof(double));
     L.off_ang = o;
     o += align_up((size_t)kNumAng * nth * sizeof(double));
+    if (p->coef_mode == TEUK_COEF_KERR) {
+        L.off_x = o;
+        o += align_up((size_t)2 * L.pitch * sizeof(double));
+    }
     if (p->coef_mode == TEUK_COEF_USER) {
         L.off_uci = o;
         o += align_up((size_t)kNumUser * nth * L.pitch * sizeof(double));
@@ -214,12 +216,11 @@ struct teuk_grid {
     bool coef_set = false;
     // adjoint (teuk_enable_adjoint)
     char* aws = nullptr;      // adjoint workspace
-    size_t aoff_lam[2]{}, aoff_da = 0, aoff_sda = 0, aoff_slots = 0, aoff_sum = 0;
+    size_t aoff_lam[2]{}, aoff_da = 0, aoff_slots = 0, aoff_sum = 0;
     int adj_rows = 32, adj_wpb = 4, adj_chunks = 0, adj_strips = 0;  // spin-gradient and one-step kernels
     int adj2_rows = 32, adj2_chunks = 0;                              // two-step cotangent kernel
     int tan_rows = 32, tan_chunks = 0;                                // step-with-tangent kernel
     int cache_policy = TEUK_CACHE_AUTO;                               // teuk_set_cache_policy
-    std::vector<double> x_tab;  // x = r - r_+ at the integer [0][nr] and half [1][nr] positions (KERR)
     // forward-mode spin derivative (teuk_enable_spin_tangent): v = du/da in two buffers
     char* tws = nullptr;
     int vcur = 0;
@@ -232,6 +233,27 @@ struct teuk_grid {
 
 namespace {
 
+// What the device builds the grid's tables from: b and c carry dt/dr at the
+// half points and half of it at the columns, the rest dt/2 and dt/4 (Stage).
+TableArgs table_args(const teuk_grid* g) {
+    TableArgs a{};
+    a.a = g->p.a;
+    a.rmin = g->p.rstar_min;
+    a.dr = g->dr;
+    a.dth = g->dth;
+    for (int kind = 0; kind < 2; ++kind) {
+        const double k = kind == 0 ? 0.5 : 1.0;
+        a.d[kind] = k * g->p.dt / g->dr;
+        a.t[kind] = 0.5 * k * g->p.dt;
+    }
+    a.nr = (int32_t)g->p.nr;
+    a.nth = (int32_t)g->p.ntheta;
+    a.pitch = g->L.pitch;
+    a.s = g->p.s;
+    a.m = g->p.m;
+    return a;
+}
+
 // Fused extraction handles at most one point per tile (its state is held
 // in scalar registers of the tile's wavefront).
 bool fused_extraction_ok(const teuk_grid* g, int strip_cols = kStripCols, int rows = 0) {
@@ -241,6 +263,22 @@ bool fused_extraction_ok(const teuk_grid* g, int strip_cols = kStripCols, int ro
         for (size_t k = i + 1; k < E.size(); ++k)
             if (E[i].col / strip_cols == E[k].col / strip_cols && E[i].rowa / rows == E[k].rowa / rows)
                 return false;
+    return true;
+}
+
+// The adjoint passes take up to kRowHits points on a row of a tile (of 64
+// columns): no point may share a row with more within that distance.
+bool fused_adjoint_ok(const teuk_grid* g) {
+    const auto& E = g->ext;
+    if ((int)E.size() > kMaxFusedAdjointExtract) return false;
+    for (const ExtPoint& a : E) {
+        int near = 0;
+        for (const ExtPoint& b : E) {
+            const bool row = a.rowa == b.rowa || a.rowa == b.rowb || (a.rowb >= 0 && (a.rowb == b.rowa || a.rowb == b.rowb));
+            if (row && std::abs(a.col - b.col) <= kWave) ++near;
+        }
+        if (near > kRowHits) return false;
+    }
     return true;
 }
 
@@ -279,7 +317,7 @@ StepArgs step_args(const teuk_grid* g) {
     k.inv_dth2 = 1.0 / (g->dth * g->dth);
     k.inv_2dth = 1.0 / (2.0 * g->dth);
     k.plane = (int64_t)k.nth * k.pitch;
-    a.rad = g->at<double>(g->L.off_srad);
+    a.rad = g->at<double>(g->L.off_rad);
     a.ang = g->at<double>(g->L.off_ang);
     if (g->p.coef_mode == TEUK_COEF_USER) {
         a.uci = g->at<double>(g->L.off_uci);
@@ -344,42 +382,43 @@ void default_tile(int nr, int nth, int cus, int* rows, int* wpb) {
     *wpb = tiles < (int64_t)cus * 4 ? 1 : 4;
 }
 
-// Default tile of the K-step pass, K = 3.  A wavefront walks its tile's rows one after the other: K
-// rows to fill the steps, then the tile's rows and K more in groups of K + 1
-// (the unrolled rows), after a start worth about two rows (tables and first
-// rows).  Two wavefronts fit a SIMD, where they share its issue: a row takes
-// two units of time beside another wavefront and 1.3 alone.  Tiles beyond one
-// round of wavefronts wait for a slot; with several rounds the last, partly
-// filled one counts for less.  The height with the lowest such time is taken,
-// at most 128 rows (a shorter last tile wastes part of that).  Measured with
-// it (three steps, us per step, units in brackets): 6400 x 256 at 15 / 17 / 29
-// rows 13.3 (50) / 12.2 (50) / 12.3 (48), at 14 rows (a second round) 14.7;
-// 5003 x 197 at 9 / 10 / 13 rows 9.6 (34) / 10.9 (42) / 10.1 (42); 1600 x 128
-// at 2 / 4 / 8 rows 7.0 (26) / 5.1 (17) / 5.9 (22); 25600 x 512 at 57 / 103
-// rows 68 / 86.  Grids with fewer tiles than SIMDs take one wavefront per
-// workgroup, to spread over the CUs.
-void default_pass_tile(int nr, int nth, int cus, int K, int* rows, int* wpb) {
+// Tile height of a K-step sweep whose row loop is unrolled by G rows.  A
+// wavefront walks its tile's rows one after the other: K rows to fill the
+// steps, then the tile's rows and K more in groups of G, after a start (tables
+// and first rows) worth about three rows.  Two wavefronts fit a SIMD, where
+// they share its issue: a row takes two units of time beside another wavefront
+// and `alone` units without.  Tiles beyond one round of wavefronts wait for a
+// slot; with several rounds the last, partly filled one counts for less.  The
+// height with the lowest such time is taken, at most 128 rows.  Measured (us
+// per step): three-step pass (G = 4), 6400 x 256 at 15 / 17 / 29 rows 13.3 /
+// 12.2 / 12.3, at 14 rows (a second round) 14.7; 5003 x 197 at 9 / 10 / 13
+// rows 9.6 / 10.9 / 10.1; 1600 x 128 at 2 / 4 / 8 rows 7.0 / 5.1 / 5.9;
+// 25600 x 512 at 57 / 103 rows 68 / 86.  Step with its spin tangent (G = 2),
+// 6400 x 256 at 14 / 15 / 17 rows 46.4 / 43.4 / 44.9, 3200 x 128 at 4 / 7 / 9
+// rows 18.6 / 17.4 / 19.3.  Two-step adjoint (G = 2), 6400 x 256 at 14 / 15 /
+// 29 rows 15.0 / 16.5 / 22.4, 3200 x 128 at 4 / 5 / 8 rows 8.1 / 9.1 / 9.5.
+int sweep_rows(int nr, int nth, int cus, int K, int G, double alone) {
     const int64_t strips = (nr + strip_cols(K) - 1) / strip_cols(K);
     double best = 0.0;
-    int64_t best_tiles = 0;
+    int rows = 1;
     for (int r = 1; r <= std::min(nth, 128); ++r) {
-        const int64_t tiles = strips * ((nth + r - 1) / r);
-        const double x = (double)tiles / (4.0 * cus);  // tiles per SIMD
-        const int its = 2 + K + (r + K + K) / (K + 1) * (K + 1);
-        double f = 1.3;  // one wavefront per SIMD
+        const double x = (double)(strips * ((nth + r - 1) / r)) / (4.0 * cus);  // tiles per SIMD
+        const int its = K + (r + K + G - 1) / G * G;
+        double f = alone, rounds = 1.0;
         if (x > 1.0) {
-            const double rounds = std::ceil(0.5 * x), over = x - 2.0 * (rounds - 1.0);
-            const double whole = 2.0 * (rounds - 1.0) + (over > 1.0 ? 2.0 : 1.3);
+            rounds = std::ceil(0.5 * x);
+            const double over = x - 2.0 * (rounds - 1.0);
+            const double whole = 2.0 * (rounds - 1.0) + (over > 1.0 ? 2.0 : alone);
             f = x + (whole - x) / std::max(1.0, rounds - 1.0);
         }
-        const double t = its * f;
-        if (r == 1 || t < best || (t == best && tiles < best_tiles)) {
+        const double t = 3.0 * rounds + its * f;
+        // equal times: fewer tiles where two share a SIMD, else shorter ones
+        if (r == 1 || t < best || (t == best && x > 1.0)) {
             best = t;
-            best_tiles = tiles;
-            *rows = r;
+            rows = r;
         }
     }
-    *wpb = best_tiles < (int64_t)cus * 4 ? 1 : 4;
+    return rows;
 }
 
 // Default tile height of an adjoint kernel: the shortest tiles of which
@@ -412,13 +451,13 @@ double angular_eig_bound(const teuk_params* p, double dr) {
     for (int i = 0; i < nr; ++i) {
         double x;
         if (!tortoise_inverse(p->a, p->rstar_min + i * dr, &x)) continue;
-        double R[kNumRad];
-        radial_fields<double>(p->a, p->s, p->m, x, dth, R);
+        double R[kNumSRad];
+        stage_fields<double>(p->a, p->s, p->m, x, dth, 1.0, 1.0, R);
         for (int j = 0; j < nth; ++j) {
             const double* G = &ang[(size_t)j * kNumAng];
-            const double inv = 1.0 / (R[R_RHO2] - R[R_A2D] * G[A_SN2]);
-            const double a2 = R[R_DL2] * inv, a1 = a2 * G[A_COTP];
-            const double v0 = std::hypot((R[R_DL2] * G[A_PD] + R[R_V0R]) * inv, R[R_V0I] * inv);
+            const double inv = 1.0 / (R[S_RHO2] - R[S_A2D] * G[A_SN2]);
+            const double a2 = R[S_DL2] * inv, a1 = a2 * G[A_COTP];
+            const double v0 = std::hypot((R[S_DL2] * G[A_PD] + R[S_VR]) * inv, R[S_VI] * inv);
             double lo = a2 - a1, hi = a2 + a1, diag = -2.0 * a2;  // weights of f-, f+, f
             if (j == 0) diag += sigma * lo, lo = 0.0;
             if (j == nth - 1) diag += sigma * hi, hi = 0.0;
@@ -504,42 +543,10 @@ int teuk_init_grid(const teuk_params* p, void* hip_stream, void* d_workspace, si
     const double dr = (p->rstar_max - p->rstar_min) / (double)(nr - 1);
     const double dth = M_PI / nth;
 
-    // 1-D tables on the host; x at each position is kept for the
-    // a-derivative tables (teuk_enable_adjoint)
-    std::vector<double> rad, srad, ang((size_t)kNumAng * nth), xs;
-    if (p->coef_mode == TEUK_COEF_KERR) {
-        rad.assign((size_t)kNumRad * 2 * L.pitch, 0.0);
-        srad.assign((size_t)kNumSRad * 2 * L.pitch, 0.0);
-        xs.assign((size_t)2 * nr, 0.0);
-        for (int kind = 0; kind < 2; ++kind) {
-            const int npos = kind == 0 ? nr : nr - 1;
-            for (int i = 0; i < npos; ++i) {
-                const double rs = p->rstar_min + (i + 0.5 * kind) * dr;
-                double x;
-                if (!tortoise_inverse(p->a, rs, &x))
-                    return fail(TEUK_E_INVALID_ARG, "tortoise inversion failed at r*=%g", rs);
-                xs[(size_t)kind * nr + i] = x;
-                double R[kNumRad];
-                radial_fields<double>(p->a, p->s, p->m, x, dth, R);
-                for (int f = 0; f < kNumRad; ++f) rad[((size_t)f * 2 + kind) * L.pitch + i] = R[f];
-                double S[kNumSRad];
-                const double d = (kind == 0 ? 0.5 : 1.0) * dt / dr, t = (kind == 0 ? 0.25 : 0.5) * dt;
-                stage_fields<double>(p->a, p->s, p->m, x, dth, d, t, S);
-                for (int f = 0; f < kNumSRad; ++f) srad[((size_t)f * 2 + kind) * L.pitch + i] = S[f];
-            }
-        }
-    }
-    for (int j = 0; j < nth; ++j) {
-        double G[kNumAng];
-        angular_fields(p->s, p->m, j, dth, G);
-        for (int f = 0; f < kNumAng; ++f) ang[(size_t)j * kNumAng + f] = G[f];
-    }
-
     teuk_grid* g = new teuk_grid();
     g->p = *p;
     g->p.dt = dt;
     g->L = L;
-    g->x_tab = std::move(xs);
     g->stream = reinterpret_cast<hipStream_t>(hip_stream);
     g->ws = reinterpret_cast<char*>(d_workspace);
     g->dr = dr;
@@ -552,7 +559,9 @@ int teuk_init_grid(const teuk_params* p, void* hip_stream, void* d_workspace, si
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
             cus = 256;
         default_tile(nr, nth, cus, &g->rows, &g->wpb);
-        default_pass_tile(nr, nth, cus, 3, &g->rows3, &g->wpb3);
+        // (four wavefronts a workgroup, or one, to spread few tiles over the CUs)
+        g->rows3 = sweep_rows(nr, nth, cus, 3, 4, 1.3);
+        g->wpb3 = (nr + strip_cols(3) - 1) / strip_cols(3) * ((nth + g->rows3 - 1) / g->rows3) < cus * 4 ? 1 : 4;
     }
     // The block pass: one thread per point of (columns x all rows).  Default
     // launch: over workgroups of up to 256, 512 or 1024 threads (at most 64
@@ -579,14 +588,13 @@ int teuk_init_grid(const teuk_params* p, void* hip_stream, void* d_workspace, si
         }
     }
     // a device holds two adjoint wavefronts per SIMD (8 per CU).  The
-    // spin-gradient kernel leaves one slot in eight to the recompute that
-    // the reverse pass runs beside it; the two-step cotangent kernel, which
-    // runs alone, fills the round.
+    // one-step kernels leave one slot in eight to a recompute that runs
+    // beside them.
     g->adj_rows = adjoint_rows(nr, nth, (int64_t)cus * 7, kStripCols);
     g->adj_chunks = (nth + g->adj_rows - 1) / g->adj_rows;
-    g->adj2_rows = adjoint_rows(nr, nth, (int64_t)cus * 8, kStripCols2);
+    g->adj2_rows = sweep_rows(nr, nth, cus, 2, 2, 1.8);
     g->adj2_chunks = (nth + g->adj2_rows - 1) / g->adj2_rows;
-    g->tan_rows = adjoint_rows(nr, nth, (int64_t)cus * 8, kStripCols);
+    g->tan_rows = sweep_rows(nr, nth, cus, 1, 2, 1.3);
     g->tan_chunks = (nth + g->tan_rows - 1) / g->tan_rows;
     g->adj_strips = ((int)p->nr + kStripCols - 1) / kStripCols;
     g->ext_r.assign(p->extract_rstar, p->extract_rstar + p->n_extract);
@@ -608,17 +616,21 @@ int teuk_init_grid(const teuk_params* p, void* hip_stream, void* d_workspace, si
     hipStream_t s = g->stream;
     e = hipMemsetAsync(g->ws, 0, L.off_rad, s);  // both state buffers
     if (e == hipSuccess) e = hipMemsetAsync(g->ws + L.off_flag, 0, kAlign, s);  // status flags
-    if (e == hipSuccess && !rad.empty())
-        e = hipMemcpyAsync(g->ws + L.off_rad, rad.data(), rad.size() * sizeof(double), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess && !srad.empty())
-        e = hipMemcpyAsync(g->ws + L.off_srad, srad.data(), srad.size() * sizeof(double), hipMemcpyHostToDevice, s);
+    // The tables, built on the device; the status block's third word tells of
+    // a position without an r.
+    const bool kerr = p->coef_mode == TEUK_COEF_KERR;
+    int* d_failed = g->at<int>(L.off_flag + 16);
+    int failed = 0;
     if (e == hipSuccess)
-        e = hipMemcpyAsync(g->ws + L.off_ang, ang.data(), ang.size() * sizeof(double), hipMemcpyHostToDevice, s);
+        e = launch_tables(table_args(g), kerr ? g->at<double>(L.off_x) : nullptr,
+                          kerr ? g->at<double>(L.off_rad) : nullptr, g->at<double>(L.off_ang), d_failed, s);
+    if (e == hipSuccess && kerr) e = hipMemcpyAsync(&failed, d_failed, sizeof(failed), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess && !g->ext.empty())
         e = hipMemcpyAsync(g->ws + L.off_ext, g->ext.data(), g->ext.size() * sizeof(ExtPoint),
                            hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return bail(fail(TEUK_E_HIP, "uploading tables: %s", hipGetErrorString(e)));
+    if (e != hipSuccess) return bail(fail(TEUK_E_HIP, "building tables: %s", hipGetErrorString(e)));
+    if (failed) return bail(fail(TEUK_E_INVALID_ARG, "tortoise inversion failed on the grid's r* range"));
     *out = g;
     return TEUK_OK;
 }
@@ -1077,8 +1089,6 @@ void adjoint_layout(teuk_grid* g, size_t* total) {
         o += g->L.state;
     }
     g->aoff_da = o;
-    o += align_up((size_t)kNumRad * 2 * g->L.pitch * sizeof(double));
-    g->aoff_sda = o;
     o += align_up((size_t)kNumSRad * 2 * g->L.pitch * sizeof(double));
     g->aoff_slots = o;
     // one slot per tile of either adjoint tiling, for any tile rows
@@ -1110,32 +1120,14 @@ int teuk_enable_adjoint(teuk_grid* g, void* d_adj_workspace, size_t bytes) {
     size_t total;
     adjoint_layout(g, &total);
     if (bytes < total) return fail(TEUK_E_WORKSPACE, "adjoint workspace has %zu bytes, needs %zu", bytes, total);
-    // a-derivatives of the radial tables at fixed r* (dual numbers through
-    // the tortoise inversion and every radial factor), from the x that
-    // teuk_init_grid solved for at each position
-    const int nr = (int)g->p.nr;
-    std::vector<double> da((size_t)kNumRad * 2 * g->L.pitch, 0.0), sda((size_t)kNumSRad * 2 * g->L.pitch, 0.0);
-    for (int kind = 0; kind < 2; ++kind) {
-        const int npos = kind == 0 ? nr : nr - 1;
-        for (int i = 0; i < npos; ++i) {
-            const Dual x = tortoise_x_dual(g->p.a, g->x_tab[(size_t)kind * nr + i]);
-            Dual R[kNumRad];
-            radial_fields<Dual>(Dual(g->p.a, 1.0), g->p.s, g->p.m, x, g->dth, R);
-            for (int f = 0; f < kNumRad; ++f) da[((size_t)f * 2 + kind) * g->L.pitch + i] = R[f].d;
-            Dual S[kNumSRad];
-            const double dt = g->p.dt;
-            const double d = (kind == 0 ? 0.5 : 1.0) * dt / g->dr, t = (kind == 0 ? 0.25 : 0.5) * dt;
-            stage_fields<Dual>(Dual(g->p.a, 1.0), g->p.s, g->p.m, x, g->dth, d, t, S);
-            for (int f = 0; f < kNumSRad; ++f) sda[((size_t)f * 2 + kind) * g->L.pitch + i] = S[f].d;
-        }
-    }
     if (int rc = set_device(g)) return rc;
     g->aws = static_cast<char*>(d_adj_workspace);
     HIP_TRY(hipMemsetAsync(g->aws, 0, total, g->stream));
-    HIP_TRY(hipMemcpyAsync(g->aws + g->aoff_da, da.data(), da.size() * sizeof(double), hipMemcpyHostToDevice,
-                           g->stream));
-    HIP_TRY(hipMemcpyAsync(g->aws + g->aoff_sda, sda.data(), sda.size() * sizeof(double), hipMemcpyHostToDevice,
-                           g->stream));
+    // a-derivatives of the radial tables at fixed r* (dual numbers through
+    // the tortoise inversion and every radial factor), from the x that
+    // teuk_init_grid solved for at each position
+    HIP_TRY(launch_tables_da(table_args(g), g->at<double>(g->L.off_x), reinterpret_cast<double*>(g->aws + g->aoff_da),
+                             g->stream));
     HIP_TRY(hipStreamSynchronize(g->stream));
     return TEUK_OK;
 }
@@ -1163,8 +1155,6 @@ AdjArgs adjoint_args(const teuk_grid* g) {
     a.k.hdt_dr = 0.5 * g->p.dt / g->dr;
     a.rad = g->at<double>(g->L.off_rad);
     a.rad_da = reinterpret_cast<const double*>(g->aws + g->aoff_da);
-    a.srad = g->at<double>(g->L.off_srad);
-    a.srad_da = reinterpret_cast<const double*>(g->aws + g->aoff_sda);
     a.k.qdt = 0.25 * g->p.dt;
     a.k.kap_h = 1.0 / (0.5 * g->p.dt);
     a.k.kap_i = 1.0 / a.k.qdt;
@@ -1241,7 +1231,7 @@ int adjoint_impl(teuk_grid* g, int64_t n, void* d_lam_phi, void* d_lam_pi, const
     a.slots = slots;
     // the sample of the state an adjoint step produces is added by the
     // adjoint kernel itself for a few points, by a separate pass otherwise
-    const bool fused = ne <= kMaxFusedAdjointExtract;
+    const bool fused = fused_adjoint_ok(g);
     a.k.n_ext = fused ? ne : 0;
     const char* win = static_cast<const char*>(d_window);
     auto slot = [&](int64_t k) { return reinterpret_cast<const double2*>(win + (size_t)k * g->L.state); };
