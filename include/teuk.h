@@ -242,7 +242,15 @@ int teuk_get_steps_per_pass(const teuk_grid* g, int32_t* steps_per_pass);
  * per compute unit, the pair scored by the per-step time measured on small
  * grids; off where none fits (400 x 32 on 256 compute units: 16 columns,
  * 7 steps; 6400 x 64: off).  TEUK_E_INVALID_ARG for values out of range or a
- * grid the pass does not take.  The getter reports cols = 0 when unset. */
+ * grid the pass does not take.  The getter reports cols = 0 when unset.
+ *
+ * With the tile (teuk_set_tile) and the block launch as teuk_init_grid chose
+ * them, several steps per pass and no in-loop check, a grid with Kerr
+ * coefficients may take the tile pass in their place (several steps per launch
+ * on register tiles, where that is estimated to be fastest: grids up to about
+ * 4 x 10^5 points), for series of up to 8 points; results are identical.  Any
+ * other tile or block launch set turns it off, as does steps = 0 here;
+ * teuk_set_tile with the default tile brings it back. */
 int teuk_set_block_launch(teuk_grid* g, int32_t steps, int32_t cols);
 int teuk_get_block_launch(const teuk_grid* g, int32_t* steps, int32_t* cols);
 

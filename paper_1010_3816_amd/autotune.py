@@ -117,8 +117,8 @@ def tune_grid(grid, rows=None, waves=GRID_WAVES, steps=20, use_cache=True, margi
     if use_cache:
         hit = _load_cache().get(key)
         if hit:
-            grid.set_tile(min(hit["rows"], grid.ntheta), hit["waves"])
             grid.set_block_launch(hit.get("block", 0), hit.get("cols", 0))
+            grid.set_tile(min(hit["rows"], grid.ntheta), hit["waves"])
             return dict(hit, cached=True)
     cus = torch.cuda.get_device_properties(grid.device).multi_processor_count
     if rows is None:
@@ -129,8 +129,8 @@ def tune_grid(grid, rows=None, waves=GRID_WAVES, steps=20, use_cache=True, margi
     table = []
 
     def timed(r, w, k, c):
+        grid.set_block_launch(k, c)  # first: the default tile brings the library's own choice back
         grid.set_tile(r, w)
-        grid.set_block_launch(k, c)
         ms = _time(torch, grid.stream, lambda n: binding.teuk_step_n(grid.handle, n, None), steps)
         table.append({"rows": r, "waves": w, "block": k, "cols": c, "ms": ms})
 
@@ -142,8 +142,8 @@ def tune_grid(grid, rows=None, waves=GRID_WAVES, steps=20, use_cache=True, margi
     dflt = next(e for e in table if (e["rows"], e["waves"], e["block"], e["cols"]) == default)
     if dflt["ms"] <= best["ms"] * (1.0 + margin):
         best = dflt
-    grid.set_tile(best["rows"], best["waves"])
     grid.set_block_launch(best["block"], best["cols"])
+    grid.set_tile(best["rows"], best["waves"])
     out = {k: best[k] for k in ("rows", "waves", "block", "cols", "ms")}
     if use_cache:
         _store_cache(key, dict(out))

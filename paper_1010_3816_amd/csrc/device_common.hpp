@@ -280,10 +280,12 @@ __device__ __forceinline__ cd stage1_phi(double b, double hdt, cd U, cd V, cd dp
     return {fma(-b, dp.re, fma(hdt, V.re, U.re)), fma(-b, dp.im, fma(hdt, V.im, U.im))};
 }
 
-// The increment of 2 h_Pi over V but for its term of the next row:
-// -c dp + b dq - ct V - v0 U - wm (U_t - U_{t-1}).  Increments are summed on
-// their own and added to the value once, so that they round at their own size.
-__device__ __forceinline__ cd stage1_inc(const Stage& k, cd U, cd V, cd dp, cd dq, cd dU) {
+__device__ __forceinline__ cd fma_real(double w, cd x, cd y) { return {fma(w, x.re, y.re), fma(w, x.im, y.im)}; }
+
+// The increment of 2 h_Pi over V but for its terms of the neighbour rows:
+// -c dp + b dq - ct V - v0 U.  Increments are summed on their own and added
+// to the value once, so that they round at their own size.
+__device__ __forceinline__ cd stage1_inc0(const Stage& k, cd U, cd V, cd dp, cd dq) {
     double r = k.b * dq.re, i = k.b * dq.im;
     r = fma(-k.cr, dp.re, r);
     i = fma(-k.cr, dp.im, i);
@@ -297,16 +299,17 @@ __device__ __forceinline__ cd stage1_inc(const Stage& k, cd U, cd V, cd dp, cd d
     i = fma(-k.vr, U.im, i);
     r = fma(k.vi, U.im, r);
     i = fma(-k.vi, U.re, i);
-    r = fma(-k.wm, dU.re, r);
-    i = fma(-k.wm, dU.im, i);
     return {r, i};
 }
 
-__device__ __forceinline__ cd fma_real(double w, cd x, cd y) { return {fma(w, x.re, y.re), fma(w, x.im, y.im)}; }
+// The same with the previous row's term, -wm (U_t - U_{t-1}).
+__device__ __forceinline__ cd stage1_inc(const Stage& k, cd U, cd V, cd dp, cd dq, cd dU) {
+    return fma_real(-k.wm, dU, stage1_inc0(k, U, V, dp, dq));
+}
 
-// The part of stage 2's Pi increment known when a row arrives: -c D - v0 S -
-// wm (S_t - S_{t-1}), with S, D the sum and difference of H at the two halves.
-__device__ __forceinline__ cd stage2_early(const Stage& k, cd S, cd D, cd dS) {
+// The part of stage 2's Pi increment of the row itself, -c D - v0 S, with S, D
+// the sum and difference of H at the two halves.
+__device__ __forceinline__ cd stage2_early0(const Stage& k, cd S, cd D) {
     double r = -k.cr * D.re, i = -k.cr * D.im;
     r = fma(k.ci, D.im, r);
     i = fma(-k.ci, D.re, i);
@@ -314,9 +317,12 @@ __device__ __forceinline__ cd stage2_early(const Stage& k, cd S, cd D, cd dS) {
     i = fma(-k.vr, S.im, i);
     r = fma(k.vi, S.im, r);
     i = fma(-k.vi, S.re, i);
-    r = fma(-k.wm, dS.re, r);
-    i = fma(-k.wm, dS.im, i);
     return {r, i};
+}
+
+// What is known when a row arrives: the same with -wm (S_t - S_{t-1}).
+__device__ __forceinline__ cd stage2_early(const Stage& k, cd S, cd D, cd dS) {
+    return fma_real(-k.wm, dS, stage2_early0(k, S, D));
 }
 
 // The rest, once the next row is there: b DQ - ct SQ + wp (S_{t+1} - S_t),

@@ -185,14 +185,26 @@ constexpr int kMaxBlockRows = 64;
 constexpr int kMaxBlockExt = 8;
 constexpr int kMaxBlockSteps = 31;  // (64 columns - 2) / 2
 hipError_t launch_block(const StepArgs& a, hipStream_t s);
+// Tile pass (Kerr coefficients): k.bsteps steps in one launch on register
+// tiles of `cols` (16, 32 or 64) columns, `rows` (1 to 3) rows a lane and
+// `waves` wavefronts a workgroup (at most 16, 12 or 8 for 1, 2 or 3 rows).  A
+// tile of one row a lane may hold all rows of the grid; otherwise the grid
+// has more rows than a tile and a tile more than 2 x bsteps.  a.series as for
+// launch_block, at most kMaxBlockExt points.
+struct TileShape {
+    int cols = 0, rows = 0, waves = 0;
+};
+hipError_t launch_tile(const StepArgs& a, const TileShape& t, hipStream_t s);
 // Zero n ints (a fill kernel: usable where a memset node is not).
 hipError_t launch_zero_ints(int* p, int n, hipStream_t s);
 // steps per launch: 1, 2 or 3 (the work list of tile_begin[steps - 1]).
 // keep: the members' next states with ordinary stores (StepScalars::keep).
 hipError_t launch_batch(const BatchMember* members, int n_members, int total_tiles, int parity, int n_blocks,
                         int waves_per_block, int steps, bool keep, hipStream_t s);
-hipError_t launch_import(const double2* src, double2* u, int f, int nr, int nth, int pitch, hipStream_t s);
-hipError_t launch_export(const double2* u, double2* dst, int f, int nr, int nth, int pitch, hipStream_t s);
+// Both planes of a state between the caller's arrays and the pitched layout.
+hipError_t launch_import(const double2* phi, const double2* pi, double2* u, int nr, int nth, int pitch,
+                         hipStream_t s);
+hipError_t launch_export(const double2* u, double2* phi, double2* pi, int nr, int nth, int pitch, hipStream_t s);
 hipError_t launch_extract(const double2* u, int pitch, const ExtPoint* pts, int n, double2* out, hipStream_t s);
 hipError_t launch_batch_extract(const BatchExtPoint* pts, int n, int parity, double2* out, hipStream_t s);
 hipError_t launch_assemble(const AssembleArgs& a, int64_t n_samples, const double2* samples, double2* psi,

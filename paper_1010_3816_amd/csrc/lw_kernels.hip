@@ -500,6 +500,196 @@ __global__ void __launch_bounds__(1024)
     }
 }
 
+// Small and medium grids: k = A.bsteps steps in one launch on tiles held in
+// registers.  A wavefront holds 64 / C groups of C consecutive columns by R
+// consecutive rows, one column a lane; a workgroup's groups are one below the
+// other, a tile of C columns by G R rows (G groups).  Every point's state and
+// coefficients stay in its lane's registers for the whole launch, so a step is
+// the stencil arithmetic alone: column neighbours by cross-lane moves, row
+// neighbours within the lane, and across groups through LDS, where each group
+// leaves the sums (of Phi, and of H) of its first and last row; one barrier a
+// step, with two buffers in turn.  Each step consumes one column at both edges
+// and one row at each end that is not a pole; the tile's own part, what is
+// left after k steps, is written back.  Tiles overlap by that much: redundant
+// work in place of any synchronisation between workgroups, and of passes over
+// memory.  The expressions are those of the sweeps, operand for operand.
+//
+// At a pole the group next to it takes its own row times sigma for the ghost.
+// The first tile starts at row 0 and the last one ends at the last row; with
+// R = 1 a tile may run past the last row of a grid it holds whole.
+//
+// Bound by the issue of about 94 vector instructions per point and step (three
+// rows a lane, two wavefronts a SIMD: 1.13 us a step, 1.07 by that count at
+// 2.1 GHz), and for one row a lane by the latency of a step's chain and its
+// barrier (0.54 us against 0.36).  What a launch costs besides, 5-7 us (2.5
+// between dependent launches, and the start of its workgroups), is spread over
+// its steps.  us per step, before and now: 400 x 32 1.60 -> 1.28 (the block
+// pass, then this), 200 x 16 1.18 -> 0.87, 1600 x 64 3.2 -> 2.2, 1600 x 128
+// 6.9 -> 3.0, 1200 x 100 5.2 (sweeps of three steps) -> 2.0, 3200 x 128 5.9 ->
+// 5.2; 5003 x 197 would take 11 against the sweeps' 9.
+//
+// T: most threads a workgroup may have (registers: 128, 160, 256 a lane for
+// one, two, three rows).
+template <int C, int R, int T, int KEEP>
+__global__ void __launch_bounds__(T)
+    lw_tile_kernel(const double2* __restrict__ u_in, double2* __restrict__ u_out, const double* __restrict__ rad,
+                   const double* __restrict__ ang, const ExtPoint* __restrict__ ext, double2* __restrict__ series,
+                   StepScalars A) {
+    constexpr int kEnds = R == 1 ? 1 : 2;
+    const int K = A.bsteps, W = C - 2 * K;
+    const int nr = A.nr, nth = A.nth, P = A.pitch;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int j = lane % C, G = blockDim.x / C;
+    const int g = threadIdx.x / C;
+    const int strip = blockIdx.x % A.n_strips, tt = blockIdx.x / A.n_strips, n_tt = A.n_chunks;
+    const int H = G * R;  // the tile's rows: its first, and its own
+    const int own0 = tt == 0 ? 0 : H - K + (tt - 1) * (H - 2 * K);
+    const int own1 = tt == n_tt - 1 ? nth : H - K + tt * (H - 2 * K);
+    const int row0 = tt == 0 ? 0 : tt == n_tt - 1 ? nth - H : own0 - K;
+    const int t0 = row0 + g * R;
+    const int c0 = strip * W;  // first column written
+    const int col = c0 - K + j;
+    const int ci = min(max(col, 0), nr - 1), hi = min(max(col, 0), nr - 2);
+    const bool boundary = (col == 0) || (col == nr - 1);
+    const bool edge = c0 - K <= 0 || c0 - K + C >= nr;  // uniform: the tile holds a boundary column
+    const double sg = (double)A.sigma;
+
+    extern __shared__ double2 lds2[];
+    // [buffer][first row, last row][U, S][group][column], then the samples' values
+    v2d* xch = reinterpret_cast<v2d*>(lds2);
+    const int plane = G * C, buf = kEnds * 2 * plane;
+    v2d* smp = xch + 2 * buf;  // [step][point][row a, b][column, next column]
+    const int me = g * C + j;
+    // where the rows before the first and after the last are, and their factor
+    const bool pole0 = t0 == 0, pole1 = t0 + R == nth;
+    const int i_up = pole0 || g == 0 ? me : (kEnds - 1) * 2 * plane + me - C;
+    const int i_dn = pole1 || g == G - 1 ? (kEnds - 1) * 2 * plane + me : me + C;
+    const double f_up = pole0 ? sg : 1.0, f_dn = pole1 ? sg : 1.0;
+
+    cd p[R], q[R];
+    Stage kh[R], ki[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const size_t o = (size_t)min(t0 + r, nth - 1) * P + ci;
+        p[r] = ld(u_in, o);
+        q[r] = ld(u_in, o + A.plane);
+    }
+    const SRad Rh = srad_of([&](int f) { return rad[((size_t)f * 2 + 1) * P + hi]; });
+    const SRad Ri = srad_of([&](int f) { return rad[((size_t)f * 2 + 0) * P + ci]; });
+    // this lane's part in the samples: bit 4 e + 2 (row b) + (next column) of
+    // its rows, for the points in the tile's own part
+    unsigned duty[R] = {};
+    unsigned any = 0;
+    for (int e = 0; e < A.n_ext; ++e) {
+        const ExtPoint E = ext[e];
+        if (E.col < c0 || E.col >= c0 + W || E.rowa < own0 || E.rowa >= own1) continue;
+        const int dc = col - E.col;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int t = t0 + r;
+            if ((dc == 0 || dc == 1) && (t == E.rowa || t == E.rowb))
+                duty[r] |= 1u << (4 * e + (t == E.rowa ? 0 : 2) + dc);
+            any |= duty[r];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const Ang ga = load_ang(ang, nth, min(t0 + r, nth - 1));
+        kh[r] = stage_coef(Rh, ga, ssigma(Rh, ga), A.kap_h);
+        ki[r] = stage_coef(Ri, ga, ssigma(Ri, ga), A.kap_i);
+    }
+
+    for (int s = 0; s < K; ++s) {
+        if (any != 0) {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                for (unsigned d = duty[r]; d != 0; d &= d - 1)
+                    smp[s * 4 * kMaxBlockExt + __builtin_ctz(d)] = v2d{p[r].re, p[r].im};
+        }
+        v2d* x = xch + (s & 1) * buf;
+        cd U[R], S[R], V[R], D[R], dp[R], dq[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const cd pr = from_right(p[r]), qr = from_right(q[r]);
+            U[r] = cadd(p[r], pr);
+            V[r] = cadd(q[r], qr);
+            dp[r] = csub(pr, p[r]);
+            dq[r] = csub(qr, q[r]);
+            const cd H = stage1_phi(kh[r].b, A.hdt, U[r], V[r], dp[r]), Hl = from_left(H);
+            S[r] = cadd(H, Hl);
+            D[r] = csub(H, Hl);
+            if (r == 0 || r == R - 1) {
+                const int o = (r == 0 ? 0 : 2 * plane) + me;
+                x[o] = v2d{U[r].re, U[r].im};
+                x[o + plane] = v2d{S[r].re, S[r].im};
+            }
+        }
+        __syncthreads();
+        // the neighbours' rows are read at once, and arrive while the terms of
+        // the rows themselves are formed
+        const v2d x0 = x[i_up], x1 = x[i_up + plane], x2 = x[i_dn], x3 = x[i_dn + plane];
+        __builtin_amdgcn_sched_barrier(0);
+        cd e1[R], e2[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            e1[r] = stage1_inc0(kh[r], U[r], V[r], dp[r], dq[r]);
+            e2[r] = stage2_early0(ki[r], S[r], D[r]);
+            p[r] = fma_real(-ki[r].b, D[r], p[r]);
+        }
+        const cd Uu = {f_up * x0.x, f_up * x0.y}, Su = {f_up * x1.x, f_up * x1.y};
+        const cd Ud = {f_dn * x2.x, f_dn * x2.y}, Sd = {f_dn * x3.x, f_dn * x3.y};
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const cd dU = csub(U[r], r == 0 ? Uu : U[r > 0 ? r - 1 : 0]);
+            const cd dS = csub(S[r], r == 0 ? Su : S[r > 0 ? r - 1 : 0]);
+            const cd dUn = csub(r == R - 1 ? Ud : U[r < R - 1 ? r + 1 : r], U[r]);
+            const cd dSn = csub(r == R - 1 ? Sd : S[r < R - 1 ? r + 1 : r], S[r]);
+            const cd X = cadd(V[r], fma_real(-kh[r].wm, dU, e1[r]));
+            const cd HQ = fma_real(kh[r].wp, dUn, X), HQl = from_left(HQ);
+            const cd SQ = cadd(HQ, HQl), DQ = csub(HQ, HQl);
+            p[r] = fma_real(A.qdt, SQ, p[r]);
+            q[r] = cadd(cadd(q[r], fma_real(-ki[r].wm, dS, e2[r])),
+                        stage2_late(ki[r].b, ki[r].tr, ki[r].ti, ki[r].wp, SQ, DQ, dSn));
+        }
+        if (edge) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                p[r] = {boundary ? 0.0 : p[r].re, boundary ? 0.0 : p[r].im};
+                q[r] = {boundary ? 0.0 : q[r].re, boundary ? 0.0 : q[r].im};
+            }
+        }
+    }
+    if (j >= K && j < K + W && col < nr) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int t = t0 + r;
+            if (t >= own0 && t < own1) {
+                st_state<KEEP>(u_out, (size_t)t * P + col, p[r]);
+                st_state<KEEP>(u_out, (size_t)t * P + col + A.plane, q[r]);
+            }
+        }
+    }
+    // the samples of the launch's input states (state row0 + s + 1 at series
+    // row row0 + s; none for the initial state), step by step and point by point
+    if (A.n_ext > 0) {
+        __syncthreads();
+        for (int i = threadIdx.x; i < K * A.n_ext; i += blockDim.x) {
+            const int s = i / A.n_ext, e = i % A.n_ext;
+            const ExtPoint E = ext[e];
+            if (A.row0 + s < 0 || E.col < c0 || E.col >= c0 + W || E.rowa < own0 || E.rowa >= own1) continue;
+            const v2d* v = smp + (s * kMaxBlockExt + e) * 4;
+            cd w = {0.0, 0.0};
+            auto add = [&](double wt, v2d a, v2d b) {
+                w.re = fma(wt, fma(E.wr, b.x - a.x, a.x), w.re);
+                w.im = fma(wt, fma(E.wr, b.y - a.y, a.y), w.im);
+            };
+            add(E.wa, v[0], v[1]);
+            if (E.rowb >= 0) add(E.wb, v[2], v[3]);
+            series[(size_t)(A.row0 + s) * A.n_ext + e] = double2{w.re, w.im};
+        }
+    }
+}
+
 __global__ void zero_ints_kernel(int* p, int n) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0;
@@ -559,9 +749,11 @@ TEUK_BATCH_KERNEL(lw_batch3_kernel, 3)
 // ...: a launch's y dimension is capped (kMaxGridY) while ntheta may reach 2^20.
 constexpr int kMaxGridY = 65535;
 
-__global__ void import_kernel(const double2* __restrict__ src, double2* __restrict__ u, int f, int nr, int nth,
-                              int pitch) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+// Both planes of a state in one launch (blockIdx.z: Phi, Pi).
+__global__ void import_kernel(const double2* __restrict__ phi, const double2* __restrict__ pi, double2* __restrict__ u,
+                              int nr, int nth, int pitch) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x, f = blockIdx.z;
+    const double2* src = f == 0 ? phi : pi;
     if (i >= pitch) return;
     for (int j = blockIdx.y; j < nth; j += gridDim.y) {
         double2 v;
@@ -572,9 +764,10 @@ __global__ void import_kernel(const double2* __restrict__ src, double2* __restri
     }
 }
 
-__global__ void export_kernel(const double2* __restrict__ u, double2* __restrict__ dst, int f, int nr, int nth,
-                              int pitch) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void export_kernel(const double2* __restrict__ u, double2* __restrict__ phi, double2* __restrict__ pi,
+                              int nr, int nth, int pitch) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x, f = blockIdx.z;
+    double2* dst = f == 0 ? phi : pi;
     if (i >= nr) return;
     for (int j = blockIdx.y; j < nth; j += gridDim.y)
         dst[(size_t)j * nr + i] = u[(size_t)f * nth * pitch + (size_t)j * pitch + i];
@@ -728,6 +921,42 @@ hipError_t launch_block(const StepArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+hipError_t launch_tile(const StepArgs& a, const TileShape& t, hipStream_t s) {
+    const int w = t.cols - 2 * a.k.bsteps, threads = t.waves * kWave, groups = threads / t.cols;
+    if (a.k.bsteps < 1 || w < 1 || a.k.n_ext > kMaxBlockExt || t.waves < 1) return hipErrorInvalidValue;
+    StepArgs b = a;
+    b.k.n_strips = (a.k.nr + w - 1) / w;
+    const int rows = groups * t.rows, nth = a.k.nth;
+    // theta tiles: the first holds rows - k of its own, the last ends at the
+    // last row, those between rows - 2 k
+    if (rows >= nth) {
+        if (rows > nth && t.rows != 1) return hipErrorInvalidValue;
+        b.k.n_chunks = 1;
+    } else {
+        const int k = a.k.bsteps, mid = rows - 2 * k;
+        if (mid < 1) return hipErrorInvalidValue;
+        b.k.n_chunks = 2 + std::max(0, (nth - 2 * (rows - k) + mid - 1) / mid);
+    }
+    const size_t lds = (size_t)(2 * (t.rows == 1 ? 1 : 2) * 2 * threads + (a.k.n_ext > 0 ? 4 * kMaxBlockExt * a.k.bsteps : 0)) *
+                       sizeof(double2);
+    const dim3 grid(b.k.n_strips * b.k.n_chunks), block(threads);
+    auto go = [&](auto k0, auto k1, int most) {
+        if (threads > most) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(a.k.keep ? k1 : k0, grid, block, lds, s, b.u_in, b.u_out, b.rad, b.ang, b.ext, b.series, b.k);
+        return hipGetLastError();
+    };
+#define TEUK_TILE(C, R, T) \
+    if (t.cols == C && t.rows == R) return go(lw_tile_kernel<C, R, T, 0>, lw_tile_kernel<C, R, T, 1>, T);
+    TEUK_TILE(16, 1, 1024)
+    TEUK_TILE(32, 1, 1024)
+    TEUK_TILE(64, 1, 1024)
+    TEUK_TILE(32, 2, 512)
+    TEUK_TILE(64, 2, 512)
+    TEUK_TILE(64, 3, 512)
+#undef TEUK_TILE
+    return hipErrorInvalidValue;
+}
+
 hipError_t launch_zero_ints(int* p, int n, hipStream_t s) {
     hipLaunchKernelGGL(zero_ints_kernel, dim3((n + 255) / 256), dim3(256), 0, s, p, n);
     return hipGetLastError();
@@ -746,15 +975,16 @@ hipError_t launch_batch(const BatchMember* members, int n_members, int total_til
     return go(lw_batch_kernel<0>, lw_batch_kernel<1>);
 }
 
-hipError_t launch_import(const double2* src, double2* u, int f, int nr, int nth, int pitch, hipStream_t s) {
-    const dim3 block(256), grid((pitch + 255) / 256, std::min(nth, kMaxGridY));
-    hipLaunchKernelGGL(import_kernel, grid, block, 0, s, src, u, f, nr, nth, pitch);
+hipError_t launch_import(const double2* phi, const double2* pi, double2* u, int nr, int nth, int pitch,
+                         hipStream_t s) {
+    const dim3 block(256), grid((pitch + 255) / 256, std::min(nth, kMaxGridY), 2);
+    hipLaunchKernelGGL(import_kernel, grid, block, 0, s, phi, pi, u, nr, nth, pitch);
     return hipGetLastError();
 }
 
-hipError_t launch_export(const double2* u, double2* dst, int f, int nr, int nth, int pitch, hipStream_t s) {
-    const dim3 block(256), grid((nr + 255) / 256, std::min(nth, kMaxGridY));
-    hipLaunchKernelGGL(export_kernel, grid, block, 0, s, u, dst, f, nr, nth, pitch);
+hipError_t launch_export(const double2* u, double2* phi, double2* pi, int nr, int nth, int pitch, hipStream_t s) {
+    const dim3 block(256), grid((nr + 255) / 256, std::min(nth, kMaxGridY), 2);
+    hipLaunchKernelGGL(export_kernel, grid, block, 0, s, u, phi, pi, nr, nth, pitch);
     return hipGetLastError();
 }
 

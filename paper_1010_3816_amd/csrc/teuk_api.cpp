@@ -211,6 +211,10 @@ struct teuk_grid {
     bool fused[kMaxPassSteps] = {true, true, true};  // extraction fusable with the strips of passes of 1, 2, 3 steps
     int block_steps = 0;     // teuk_set_block_launch: steps per launch of the block pass (0: off)
     int block_cols = 0;      // columns a block-pass workgroup holds (0: not set)
+    TileShape tile_shape;    // the tile pass's shape and steps per launch (0: off)
+    int tile_steps = 0;
+    bool default_launch = true;  // tile and block launch as teuk_init_grid chose them
+    int default_tile[2] = {0, 0}, default_block[2] = {0, 0}, default_rows3 = 0, default_wpb3 = 0;
     int64_t check_every = 0;  // teuk_set_finite_check: steps between device checks of the state (0: off)
     char* sws = nullptr;      // source profile (teuk_set_source): [integer, half][nth][pitch] complex128
     bool coef_set = false;
@@ -397,7 +401,7 @@ void default_tile(int nr, int nth, int cus, int* rows, int* wpb) {
 // 6400 x 256 at 14 / 15 / 17 rows 46.4 / 43.4 / 44.9, 3200 x 128 at 4 / 7 / 9
 // rows 18.6 / 17.4 / 19.3.  Two-step adjoint (G = 2), 6400 x 256 at 14 / 15 /
 // 29 rows 15.0 / 16.5 / 22.4, 3200 x 128 at 4 / 5 / 8 rows 8.1 / 9.1 / 9.5.
-int sweep_rows(int nr, int nth, int cus, int K, int G, double alone) {
+int sweep_rows(int nr, int nth, int cus, int K, int G, double alone, double* us = nullptr) {
     const int64_t strips = (nr + strip_cols(K) - 1) / strip_cols(K);
     double best = 0.0;
     int rows = 1;
@@ -416,9 +420,58 @@ int sweep_rows(int nr, int nth, int cus, int K, int G, double alone) {
         if (r == 1 || t < best || (t == best && x > 1.0)) {
             best = t;
             rows = r;
+            if (us) *us = (8.4 + (x > 1.0 ? 0.65 : 0.5) * its * f) / K;
         }
     }
     return rows;
+}
+
+// Shape and steps per launch of the tile pass with the lowest estimated time
+// per step, which is returned (us); 0 steps if no shape applies.  A launch
+// costs 2.5 us before its first workgroup; a workgroup starts (loads, builds
+// its coefficients) and takes its steps, and with more workgroups than the
+// device holds at once they run in rounds.  Measured: a step takes 0.54 us
+// with one row a lane and two wavefronts a SIMD, 0.87 with four, 1.13 with
+// three rows and two; a launch of 256 workgroups 5.7, 7.5 and 7.1 us besides.
+// Estimate and measurement (us per step): 400 x 32 1.28 and 1.27, 1600 x 128
+// 2.97 and 3.05, 3200 x 128 5.4 and 5.2, 1200 x 100 2.2 and 2.0.
+double best_tile(int nr, int nth, int cus, TileShape* shape, int* steps) {
+    struct Kind {
+        int cols, rows, most, per_cu;  // most wavefronts a workgroup and a CU
+        double us;                     // per row and wavefront of a SIMD
+    };
+    constexpr Kind kinds[] = {{16, 1, 16, 20, 0.155}, {32, 1, 16, 20, 0.155}, {64, 1, 16, 20, 0.155},
+                              {32, 2, 8, 8, 0.14},    {64, 2, 8, 8, 0.14},    {64, 3, 8, 8, 0.145}};
+    double best = 0.0;
+    *steps = 0;
+    for (const Kind& c : kinds)
+        for (int waves = 1; waves <= c.most; ++waves) {
+            const int per = kWave / c.cols, rows = waves * per * c.rows;
+            if (rows > nth && (c.rows != 1 || rows - per >= nth)) continue;
+            for (int k = 1; k <= (c.cols - 2) / 2; ++k) {
+                int chunks = 1;
+                if (rows < nth) {
+                    if (rows - 2 * k < 1) break;
+                    chunks = 2 + std::max(0, (nth - 2 * (rows - k) + rows - 2 * k - 1) / (rows - 2 * k));
+                }
+                const int w = c.cols - 2 * k;
+                const int64_t groups = (int64_t)((nr + w - 1) / w) * chunks;
+                const int64_t at_once = (groups + cus - 1) / cus;  // per CU
+                const int held = (int)std::min<int64_t>(at_once, std::max(1, c.per_cu / waves));
+                const double rounds = std::ceil((double)groups / ((double)cus * held));
+                const double load = c.rows * std::max(1.0, 0.25 * waves), all = c.rows * std::max(1.0, 0.25 * waves * held);
+                const double t = (2.5 + rounds * ((1.5 + 0.35 * load) * held + 1.3 * std::min(1.0, (double)groups / cus) +
+                                                  k * (0.25 + c.us * all))) / k;
+                if (*steps == 0 || t < best) {
+                    best = t;
+                    *steps = k;
+                    shape->cols = c.cols;
+                    shape->rows = c.rows;
+                    shape->waves = waves;
+                }
+            }
+        }
+    return best;
 }
 
 // Default tile height of an adjoint kernel: the shortest tiles of which
@@ -553,6 +606,7 @@ int teuk_init_grid(const teuk_params* p, void* hip_stream, void* d_workspace, si
     g->dth = dth;
     g->sigma = (std::abs(p->m) % 2 == 0) ? 1 : -1;
     int cus = 0;
+    double sweep_us = 0.0;  // estimated time of a step by the three-step pass
     {
         int dev = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
@@ -560,7 +614,7 @@ int teuk_init_grid(const teuk_params* p, void* hip_stream, void* d_workspace, si
             cus = 256;
         default_tile(nr, nth, cus, &g->rows, &g->wpb);
         // (four wavefronts a workgroup, or one, to spread few tiles over the CUs)
-        g->rows3 = sweep_rows(nr, nth, cus, 3, 4, 1.3);
+        g->rows3 = sweep_rows(nr, nth, cus, 3, 4, 1.3, &sweep_us);
         g->wpb3 = (nr + strip_cols(3) - 1) / strip_cols(3) * ((nth + g->rows3 - 1) / g->rows3) < cus * 4 ? 1 : 4;
     }
     // The block pass: one thread per point of (columns x all rows).  Default
@@ -587,6 +641,15 @@ int teuk_init_grid(const teuk_params* p, void* hip_stream, void* d_workspace, si
             }
         }
     }
+    // the tile pass where its estimate is below the sweeps'
+    if (p->coef_mode == TEUK_COEF_KERR && best_tile(nr, nth, cus, &g->tile_shape, &g->tile_steps) >= sweep_us)
+        g->tile_steps = 0;
+    g->default_tile[0] = g->rows;
+    g->default_tile[1] = g->wpb;
+    g->default_block[0] = g->block_steps;
+    g->default_block[1] = g->block_cols;
+    g->default_rows3 = g->rows3;
+    g->default_wpb3 = g->wpb3;
     // a device holds two adjoint wavefronts per SIMD (8 per CU).  The
     // one-step kernels leave one slot in eight to a recompute that runs
     // beside them.
@@ -652,8 +715,8 @@ int teuk_set_initial_data(teuk_grid* g, const void* d_phi, const void* d_pi) {
     if (!d_phi || !d_pi) return fail(TEUK_E_INVALID_ARG, "initial data pointers are NULL");
     if (int rc = set_device(g)) return rc;
     const int nr = (int)g->p.nr, nth = (int)g->p.ntheta;
-    HIP_TRY(launch_import(static_cast<const double2*>(d_phi), g->u(0), 0, nr, nth, g->L.pitch, g->stream));
-    HIP_TRY(launch_import(static_cast<const double2*>(d_pi), g->u(0), 1, nr, nth, g->L.pitch, g->stream));
+    HIP_TRY(launch_import(static_cast<const double2*>(d_phi), static_cast<const double2*>(d_pi), g->u(0),
+                          nr, nth, g->L.pitch, g->stream));
     g->cur = 0;
     g->steps = 0;
     return TEUK_OK;
@@ -769,7 +832,28 @@ int step_n_impl(teuk_grid* g, int64_t n, void* d_series, void* d_window, const d
     // Small grids: launches of the block pass (not with a window, a source
     // term or a series of more extraction points than it samples).
     const bool block = g->block_steps > 0 && kerr && !win && !h_f && (!series || ne <= kMaxBlockExt);
+    // The tile pass, in launches of about equal steps.
+    const bool tile = g->tile_steps > 0 && g->default_launch && g->steps_per_pass == 2 && kerr && !win && !h_f &&
+                      g->check_every == 0 && (!series || ne <= kMaxBlockExt);
     for (int64_t k = 0; k < n;) {
+        if (tile) {
+            const int64_t left = n - k, launches = (left + g->tile_steps - 1) / g->tile_steps;
+            const int m = (int)((left + launches - 1) / launches);
+            double2* out = next_buffer(k + m);
+            StepArgs at = step_args(g);
+            at.u_in = in;
+            at.u_out = out;
+            at.k.bsteps = m;
+            at.k.n_ext = series ? ne : 0;
+            at.k.row0 = k - 1;  // state k + s goes to series row k + s - 1
+            at.series = series;
+            HIP_TRY(launch_tile(at, g->tile_shape, g->stream));
+            if (series) sampled = k + m - 1;
+            advance(out);
+            k += m;
+            g->steps += m;
+            continue;
+        }
         if (block) {
             const int m = (int)std::min<int64_t>(g->block_steps, n - k);
             double2* out = next_buffer(k + m);
@@ -910,8 +994,7 @@ int teuk_get_window_slot(teuk_grid* g, const void* d_window, int64_t k, void* d_
     if (int rc = set_device(g)) return rc;
     const int nr = (int)g->p.nr, nth = (int)g->p.ntheta;
     const double2* u = reinterpret_cast<const double2*>(static_cast<const char*>(d_window) + (size_t)k * g->L.state);
-    HIP_TRY(launch_export(u, static_cast<double2*>(d_phi), 0, nr, nth, g->L.pitch, g->stream));
-    HIP_TRY(launch_export(u, static_cast<double2*>(d_pi), 1, nr, nth, g->L.pitch, g->stream));
+    HIP_TRY(launch_export(u, static_cast<double2*>(d_phi), static_cast<double2*>(d_pi), nr, nth, g->L.pitch, g->stream));
     return TEUK_OK;
 }
 
@@ -957,8 +1040,7 @@ int teuk_get_state(teuk_grid* g, void* d_phi, void* d_pi) {
     if (!d_phi || !d_pi) return fail(TEUK_E_INVALID_ARG, "output pointers are NULL");
     if (int rc = set_device(g)) return rc;
     const int nr = (int)g->p.nr, nth = (int)g->p.ntheta;
-    HIP_TRY(launch_export(g->u(g->cur), static_cast<double2*>(d_phi), 0, nr, nth, g->L.pitch, g->stream));
-    HIP_TRY(launch_export(g->u(g->cur), static_cast<double2*>(d_pi), 1, nr, nth, g->L.pitch, g->stream));
+    HIP_TRY(launch_export(g->u(g->cur), static_cast<double2*>(d_phi), static_cast<double2*>(d_pi), nr, nth, g->L.pitch, g->stream));
     return TEUK_OK;
 }
 
@@ -986,14 +1068,36 @@ int64_t teuk_steps_taken(const teuk_grid* g) { return g ? g->steps : -1; }
 
 double teuk_get_dt(const teuk_grid* g) { return g ? g->p.dt : 0.0; }
 
+namespace {
+
+// After a change of the tile or the block launch: with both as teuk_init_grid
+// chose them the grid's own choice among the passes is back (the three-step
+// pass's tile and the tile pass); otherwise the sweeps take the tile given.
+// off: the block pass was turned off, which leaves the sweeps.
+void select_launch(teuk_grid* g, bool off) {
+    const bool tile = g->rows == g->default_tile[0] && g->wpb == g->default_tile[1];
+    const bool block = g->block_steps == g->default_block[0] && g->block_cols == g->default_block[1];
+    g->default_launch = tile && block && !off;
+    if (!tile) {
+        g->rows3 = g->rows;
+        g->wpb3 = g->wpb;
+    } else {
+        g->rows3 = g->default_rows3;
+        g->wpb3 = g->default_wpb3;
+    }
+}
+
+}  // namespace
+
 int teuk_set_tile(teuk_grid* g, int32_t rows_per_tile, int32_t waves_per_block) {
     if (int rc = check_grid(g)) return rc;
     if (rows_per_tile < 1 || rows_per_tile > g->p.ntheta)
         return fail(TEUK_E_INVALID_ARG, "rows_per_tile=%d outside [1, ntheta]", rows_per_tile);
     if (waves_per_block != 1 && waves_per_block != 2 && waves_per_block != 4 && waves_per_block != 8)
         return fail(TEUK_E_INVALID_ARG, "waves_per_block=%d not in {1, 2, 4, 8}", waves_per_block);
-    g->rows = g->rows3 = rows_per_tile;
-    g->wpb = g->wpb3 = waves_per_block;
+    g->rows = rows_per_tile;
+    g->wpb = waves_per_block;
+    select_launch(g, false);
     update_fusion(g);
     return TEUK_OK;
 }
@@ -1016,6 +1120,7 @@ int teuk_set_block_launch(teuk_grid* g, int32_t steps, int32_t cols) {
     if (int rc = check_grid(g)) return rc;
     if (steps == 0) {
         g->block_steps = 0;
+        select_launch(g, true);
         return TEUK_OK;
     }
     const int nth = (int)g->p.ntheta;
@@ -1028,6 +1133,7 @@ int teuk_set_block_launch(teuk_grid* g, int32_t steps, int32_t cols) {
         return fail(TEUK_E_INVALID_ARG, "block steps=%d outside [0, %d] for %d columns", steps, (cols - 2) / 2, cols);
     g->block_steps = steps;
     g->block_cols = cols;
+    select_launch(g, false);
     return TEUK_OK;
 }
 
@@ -1219,8 +1325,8 @@ int adjoint_impl(teuk_grid* g, int64_t n, void* d_lam_phi, void* d_lam_pi, const
     const int nslots = std::max(g->adj_strips * g->adj_chunks, strips2 * g->adj2_chunks);
 
     int c = 0;
-    HIP_TRY(launch_import(static_cast<const double2*>(d_lam_phi), lam(c), 0, nr, nth, P, s));
-    HIP_TRY(launch_import(static_cast<const double2*>(d_lam_pi), lam(c), 1, nr, nth, P, s));
+    HIP_TRY(launch_import(static_cast<const double2*>(d_lam_phi), static_cast<const double2*>(d_lam_pi), lam(c),
+                          nr, nth, P, s));
     if (spin) {
         HIP_TRY(hipMemsetAsync(slots, 0, (size_t)nslots * sizeof(double), s));
         if (!d_dL_da_accum) HIP_TRY(hipMemsetAsync(sum, 0, sizeof(double), s));
@@ -1264,8 +1370,7 @@ int adjoint_impl(teuk_grid* g, int64_t n, void* d_lam_phi, void* d_lam_pi, const
         if (gs && k >= 1 && !fused) HIP_TRY(launch_extract_adjoint(lam(c), P, ext, ne, gs + (k - 1) * ne, s));
     }
     if (flags & TEUK_ADJ_PROJECT_INITIAL) HIP_TRY(launch_zero_radial_boundary(lam(c), nr, nth, P, s));
-    HIP_TRY(launch_export(lam(c), static_cast<double2*>(d_lam_phi), 0, nr, nth, P, s));
-    HIP_TRY(launch_export(lam(c), static_cast<double2*>(d_lam_pi), 1, nr, nth, P, s));
+    HIP_TRY(launch_export(lam(c), static_cast<double2*>(d_lam_phi), static_cast<double2*>(d_lam_pi), nr, nth, P, s));
     if (!spin) return TEUK_OK;  // asynchronous
     if (d_dL_da_accum) {         // asynchronous: added on the stream, in call order
         HIP_TRY(launch_reduce_slots(slots, nslots, d_dL_da_accum, s));
@@ -1328,8 +1433,8 @@ int teuk_set_spin_tangent(teuk_grid* g, const void* d_vphi, const void* d_vpi) {
         return TEUK_OK;
     }
     const int nr = (int)g->p.nr, nth = (int)g->p.ntheta;
-    HIP_TRY(launch_import(static_cast<const double2*>(d_vphi), g->v(0), 0, nr, nth, g->L.pitch, g->stream));
-    HIP_TRY(launch_import(static_cast<const double2*>(d_vpi), g->v(0), 1, nr, nth, g->L.pitch, g->stream));
+    HIP_TRY(launch_import(static_cast<const double2*>(d_vphi), static_cast<const double2*>(d_vpi), g->v(0),
+                          nr, nth, g->L.pitch, g->stream));
     return TEUK_OK;
 }
 
@@ -1339,8 +1444,7 @@ int teuk_get_spin_tangent(teuk_grid* g, void* d_vphi, void* d_vpi) {
     if (!d_vphi || !d_vpi) return fail(TEUK_E_INVALID_ARG, "output pointers are NULL");
     if (int rc = set_device(g)) return rc;
     const int nr = (int)g->p.nr, nth = (int)g->p.ntheta;
-    HIP_TRY(launch_export(g->v(g->vcur), static_cast<double2*>(d_vphi), 0, nr, nth, g->L.pitch, g->stream));
-    HIP_TRY(launch_export(g->v(g->vcur), static_cast<double2*>(d_vpi), 1, nr, nth, g->L.pitch, g->stream));
+    HIP_TRY(launch_export(g->v(g->vcur), static_cast<double2*>(d_vphi), static_cast<double2*>(d_vpi), nr, nth, g->L.pitch, g->stream));
     return TEUK_OK;
 }
 
@@ -1608,8 +1712,8 @@ int teuk_batch_set_initial_data(teuk_batch* b, int32_t member, const void* d_phi
     teuk_grid* g = b->members[member];
     if (int rc = set_device(g)) return rc;
     const int nr = (int)g->p.nr, nth = (int)g->p.ntheta;
-    HIP_TRY(launch_import(static_cast<const double2*>(d_phi), g->u(b->parity), 0, nr, nth, g->L.pitch, g->stream));
-    HIP_TRY(launch_import(static_cast<const double2*>(d_pi), g->u(b->parity), 1, nr, nth, g->L.pitch, g->stream));
+    HIP_TRY(launch_import(static_cast<const double2*>(d_phi), static_cast<const double2*>(d_pi), g->u(b->parity),
+                          nr, nth, g->L.pitch, g->stream));
     g->cur = b->parity;
     g->steps = 0;
     return TEUK_OK;
