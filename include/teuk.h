@@ -450,6 +450,16 @@ int teuk_batch_step_n(teuk_batch* b, int64_t n);
  * the order of its extract_rstar/extract_theta.  Asynchronous on the batch
  * stream.  TEUK_E_STATE if no member has extraction points. */
 int teuk_batch_extract(teuk_batch* b, void* d_out);
+
+/* n_samples times: advance every member by `every` >= 1 steps and sample as
+ * teuk_batch_extract, into row k of d_out (complex128
+ * [n_samples][teuk_batch_n_extract(b)]); the same states and samples as the
+ * two calls in turn.  The samples are taken inside the passes, which need not
+ * end at a sample (unless two different points of a member share a tile, or
+ * `every` exceeds 16).  Asynchronous on the batch stream.  TEUK_E_INVALID_ARG
+ * for n_samples < 0, every < 1 or a missing output; TEUK_E_STATE if no member
+ * has extraction points. */
+int teuk_batch_step_samples(teuk_batch* b, int64_t n_samples, int64_t every, void* d_out);
 int32_t teuk_batch_n_extract(const teuk_batch* b);
 
 /* The field from its azimuthal modes (Sec. 3.2: Psi = e^{i m phi} r^3 Phi

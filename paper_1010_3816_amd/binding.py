@@ -106,6 +106,7 @@ def _load():
         "teuk_batch_set_launch": (ctypes.c_int, [V, I32, I32, I32]),
         "teuk_batch_set_steps_per_pass": (ctypes.c_int, [V, I32]),
         "teuk_batch_extract": (ctypes.c_int, [V, V]),
+        "teuk_batch_step_samples": (ctypes.c_int, [V, I64, I64, V]),
         "teuk_batch_n_extract": (I32, [V]),
         "teuk_radius": (ctypes.c_int, [D, D, ctypes.POINTER(D)]),
         "teuk_assemble_modes": (ctypes.c_int, [I64, I32, ctypes.POINTER(I32), I32, ctypes.POINTER(D),
@@ -132,7 +133,7 @@ EXPORTED = ("teuk_workspace_bytes", "teuk_init_grid", "teuk_set_coefficients", "
             "teuk_batch_workspace_bytes", "teuk_batch_init",
             "teuk_batch_set_initial_data", "teuk_batch_get_state", "teuk_batch_step_n", "teuk_batch_set_launch",
             "teuk_batch_get_launch", "teuk_batch_total_points", "teuk_batch_free",
-            "teuk_batch_set_steps_per_pass", "teuk_batch_extract", "teuk_batch_n_extract", "teuk_radius",
+            "teuk_batch_set_steps_per_pass", "teuk_batch_extract", "teuk_batch_step_samples", "teuk_batch_n_extract", "teuk_radius",
             "teuk_assemble_modes", "teuk_set_finite_check", "teuk_extract_noalloc",
             "teuk_step_n_tangent", "teuk_get_window_slot", "teuk_source_workspace_bytes", "teuk_set_source",
             "teuk_step_n_source", "teuk_adjoint_step_n_async", "teuk_spin_tangent_workspace_bytes",
@@ -720,6 +721,13 @@ class TeukBatch:
         if out is None:
             out = self.torch.empty(self.n_extract(), dtype=self.torch.complex128, device=self.device)
         _check(_lib.teuk_batch_extract(self.handle, _dptr(out)))
+        return out
+
+    def step_samples(self, n_samples, every, out=None):
+        """n_samples times `every` steps and a sample of all points: complex128 (n_samples, n_extract())."""
+        if out is None:
+            out = self.torch.empty((int(n_samples), self.n_extract()), dtype=self.torch.complex128, device=self.device)
+        _check(_lib.teuk_batch_step_samples(self.handle, int(n_samples), int(every), _dptr(out)))
         return out
 
     def launch(self):

@@ -115,9 +115,17 @@ struct BatchMember {
     double2* u[2];           // the member's two state buffers
     const double* rad;       // its radial and angular tables (KERR)
     const double* ang;
+    const ExtPoint* ext;     // its extraction points (k.n_ext of them), and the index of the
+    int64_t ext_off;         // first among all members' points
     StepScalars k;           // its launch scalars (rows shared by all members)
     int32_t tile_begin[kMaxPassSteps];  // its first tile in the work list of the passes of 1, 2, 3 steps
     int32_t strips[kMaxPassSteps];      // its strips in these passes
+};
+
+// Where a batched launch of m steps puts the samples of the inputs of its
+// steps: a row of all members' points each, or nullptr.
+struct BatchSeries {
+    double2* row[kMaxPassSteps];
 };
 
 // One extraction point of a batched evolution: the member's two state
@@ -199,8 +207,9 @@ hipError_t launch_tile(const StepArgs& a, const TileShape& t, hipStream_t s);
 hipError_t launch_zero_ints(int* p, int n, hipStream_t s);
 // steps per launch: 1, 2 or 3 (the work list of tile_begin[steps - 1]).
 // keep: the members' next states with ordinary stores (StepScalars::keep).
+// series: rows to sample (one point of a member per tile).
 hipError_t launch_batch(const BatchMember* members, int n_members, int total_tiles, int parity, int n_blocks,
-                        int waves_per_block, int steps, bool keep, hipStream_t s);
+                        int waves_per_block, int steps, bool keep, const BatchSeries& series, hipStream_t s);
 // Both planes of a state between the caller's arrays and the pitched layout.
 hipError_t launch_import(const double2* phi, const double2* pi, double2* u, int nr, int nth, int pitch,
                          hipStream_t s);

@@ -89,13 +89,15 @@ struct RowCoef {
 // where the first rows of each step hold values formed from rows that were
 // not read; the rows they complete are not used by the next step.
 //
+// series0, 1, 2: where the samples of the inputs of the steps go, or nullptr.
+//
 // The main loop is for rows away from the last pole, of strips without a
 // radial boundary column and tiles that sample or keep nothing; the loop
 // after it checks for all of these.
 template <int K, bool KERR, bool SRC, int KEEP>
 __device__ __forceinline__ void sweep(gin_t __restrict__ u_in, gout_t __restrict__ u_out, ctab_t rad, ctab_t ang,
-                                      ctab_t uci, ctab_t uch, cext_t ext, double2* __restrict__ series_in,
-                                      double2* __restrict__ series_mid, gout_t __restrict__ win, lds_t rs,
+                                      ctab_t uci, ctab_t uch, cext_t ext, double2* series0, double2* series1,
+                                      double2* series2, gout_t __restrict__ win, lds_t rs,
                                       const StepScalars& A, int strip, int chunk, int lane,
                                       gin_t __restrict__ src_i, gin_t __restrict__ src_h) {
     constexpr int kRing = K + 1;               // coefficient rows held
@@ -170,7 +172,8 @@ __device__ __forceinline__ void sweep(gin_t __restrict__ u_in, gout_t __restrict
         }
     };
 
-    // the (at most one) extraction point of this tile, in scalar registers
+    // the (at most one, apart from equal ones) extraction point of this tile,
+    // in scalar registers
     int e_id = -1, e_lane = 0, e_ra = -1, e_rb = -1;
     double e_wr = 0.0, e_wa = 0.0, e_wb = 0.0;
     for (int e = 0; e < A.n_ext; ++e) {
@@ -304,7 +307,7 @@ __device__ __forceinline__ void sweep(gin_t __restrict__ u_in, gout_t __restrict
 
     if (e_id >= 0 && lane < K) {
         // lane j: the sample of step j's input
-        double2* out = lane == 0 ? series_in : series_mid ? series_mid + (size_t)(lane - 1) * A.n_ext : nullptr;
+        double2* out = lane == 0 ? series0 : lane == 1 ? series1 : series2;
         if (out != nullptr) {
             cd w = {0.0, 0.0};
             auto add = [&](double wt, v2d a, v2d b) {
@@ -313,7 +316,9 @@ __device__ __forceinline__ void sweep(gin_t __restrict__ u_in, gout_t __restrict
             };
             add(e_wa, smp[4 * lane], smp[4 * lane + 1]);
             if (e_rb >= 0) add(e_wb, smp[4 * lane + 2], smp[4 * lane + 3]);
-            out[e_id] = double2{w.re, w.im};
+            const int e_col = strip * kCols + e_lane - K;
+            for (int e = 0; e <= e_id; ++e)  // the point and those equal to it
+                if (ext[e].col == e_col && ext[e].rowa == e_ra) out[e] = double2{w.re, w.im};
         }
     }
 }
@@ -346,9 +351,8 @@ __device__ __forceinline__ void pass_tile(const double2* __restrict__ u_in, doub
     }
     if (chunk >= A.n_chunks) return;  // tiles beyond the last
     sweep<K, KERR, SRC, KEEP>((gin_t)u_in, (gout_t)u_out, (ctab_t)rad, (ctab_t)ang, (ctab_t)uci, (ctab_t)uch,
-                              (cext_t)ext, series_in, series_mid, (gout_t)win,
-                              (lds_t)(rad_s + (threadIdx.x / kWave) * kSliceDoubles), A, strip, chunk, lane,
-                              (gin_t)src_i, (gin_t)src_h);
+                              (cext_t)ext, series_in, series_mid, series_mid ? series_mid + A.n_ext : nullptr,
+                              (gout_t)win, (lds_t)(rad_s + (threadIdx.x / kWave) * kSliceDoubles), A, strip, chunk, lane, (gin_t)src_i, (gin_t)src_h);
 }
 
 #define TEUK_PASS_KERNEL(NAME, K)                                                                                     \
@@ -703,7 +707,7 @@ __global__ void zero_ints_kernel(int* p, int n) {
 // each member's two state buffers is the input.
 template <int K, int KEEP>
 __device__ __forceinline__ void batch_tiles(const BatchMember* __restrict__ members, int n_members, int total_tiles,
-                                            int parity, double* rad_s) {
+                                            int parity, const BatchSeries& S, double* rad_s) {
     const lds_t rs = (lds_t)(rad_s + (threadIdx.x / kWave) * kSliceDoubles);
     const int lane = threadIdx.x & (kWave - 1);
     const int wpb = blockDim.x / kWave;
@@ -724,8 +728,10 @@ __device__ __forceinline__ void batch_tiles(const BatchMember* __restrict__ memb
         k.n_strips = M.strips[K - 1];
         const int strip = local % k.n_strips;
         const int chunk = local / k.n_strips;
+        auto row = [&](int j) -> double2* { return j < K && S.row[j] ? S.row[j] + M.ext_off : nullptr; };
+        if (row(0) == nullptr && row(1) == nullptr && row(2) == nullptr) k.n_ext = 0;
         sweep<K, true, false, KEEP>((gin_t)M.u[parity], (gout_t)M.u[1 - parity], (ctab_t)M.rad, (ctab_t)M.ang, nullptr,
-                                    nullptr, nullptr, nullptr, nullptr, nullptr, rs, k, strip, chunk, lane, nullptr,
+                                    nullptr, (cext_t)M.ext, row(0), row(1), row(2), nullptr, rs, k, strip, chunk, lane, nullptr,
                                     nullptr);
     }
 }
@@ -733,9 +739,10 @@ __device__ __forceinline__ void batch_tiles(const BatchMember* __restrict__ memb
 #define TEUK_BATCH_KERNEL(NAME, K)                                                              \
     template <int KEEP>                                                                         \
     __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4)))          \
-        NAME(const BatchMember* __restrict__ members, int n_members, int total_tiles, int parity) { \
+        NAME(const BatchMember* __restrict__ members, int n_members, int total_tiles, int parity, \
+             BatchSeries S) {                                                                   \
         extern __shared__ double rad_s[];                                                       \
-        batch_tiles<K, KEEP>(members, n_members, total_tiles, parity, rad_s);                   \
+        batch_tiles<K, KEEP>(members, n_members, total_tiles, parity, S, rad_s);                \
     }
 TEUK_BATCH_KERNEL(lw_batch_kernel, 1)
 TEUK_BATCH_KERNEL(lw_batch2_kernel, 2)
@@ -963,11 +970,11 @@ hipError_t launch_zero_ints(int* p, int n, hipStream_t s) {
 }
 
 hipError_t launch_batch(const BatchMember* members, int n_members, int total_tiles, int parity, int n_blocks,
-                        int waves_per_block, int steps, bool keep, hipStream_t s) {
+                        int waves_per_block, int steps, bool keep, const BatchSeries& series, hipStream_t s) {
     const int w = waves_per_block < 4 ? waves_per_block : 4;
     auto go = [&](auto k0, auto k1) {
         hipLaunchKernelGGL(keep ? k1 : k0, dim3(n_blocks), dim3(kWave * w), w * kRadSliceBytes, s, members, n_members,
-                           total_tiles, parity);
+                           total_tiles, parity, series);
         return hipGetLastError();
     };
     if (steps == 3) return go(lw_batch3_kernel<0>, lw_batch3_kernel<1>);

@@ -259,13 +259,17 @@ TableArgs table_args(const teuk_grid* g) {
 }
 
 // Fused extraction handles at most one point per tile (its state is held
-// in scalar registers of the tile's wavefront).
-bool fused_extraction_ok(const teuk_grid* g, int strip_cols = kStripCols, int rows = 0) {
+// in scalar registers of the tile's wavefront); the forward passes also any
+// number of points equal to it (observers that differ in azimuth alone).
+bool fused_extraction_ok(const teuk_grid* g, int strip_cols, int rows, bool equal_ok) {
     const auto& E = g->ext;
-    if (rows <= 0) rows = g->rows;
+    auto same = [](const ExtPoint& a, const ExtPoint& b) {
+        return a.col == b.col && a.rowa == b.rowa && a.rowb == b.rowb && a.wr == b.wr && a.wa == b.wa && a.wb == b.wb;
+    };
     for (size_t i = 0; i < E.size(); ++i)
         for (size_t k = i + 1; k < E.size(); ++k)
-            if (E[i].col / strip_cols == E[k].col / strip_cols && E[i].rowa / rows == E[k].rowa / rows)
+            if (E[i].col / strip_cols == E[k].col / strip_cols && E[i].rowa / rows == E[k].rowa / rows &&
+                !(equal_ok && same(E[i], E[k])))
                 return false;
     return true;
 }
@@ -288,7 +292,7 @@ bool fused_adjoint_ok(const teuk_grid* g) {
 
 void update_fusion(teuk_grid* g) {
     for (int k = 1; k <= kMaxPassSteps; ++k)
-        g->fused[k - 1] = fused_extraction_ok(g, strip_cols(k), k == 3 ? g->rows3 : g->rows);
+        g->fused[k - 1] = fused_extraction_ok(g, strip_cols(k), k == 3 ? g->rows3 : g->rows, true);
 }
 
 // Two states (a pass's input and output) up to this size stay in the
@@ -1466,7 +1470,7 @@ int teuk_step_n_spin_tangent(teuk_grid* g, int64_t n, void* d_series, void* d_ts
     // the launches sample their input (row k-1 of a series: the state after
     // step k); the call's last state, or every state when two extraction
     // points share a tile, by a separate pass
-    const bool fused = fused_extraction_ok(g, kStripCols, g->tan_rows);
+    const bool fused = fused_extraction_ok(g, kStripCols, g->tan_rows, false);
     a.k.n_ext = fused ? ne : 0;
     auto extract = [&](int64_t j) -> int {
         if (series) HIP_TRY(launch_extract(g->u(g->cur), g->L.pitch, ext, ne, series + (j - 1) * ne, g->stream));
@@ -1520,6 +1524,7 @@ struct teuk_batch {
     int steps_per_pass = 2;
     int parity = 0;                 // which state buffer of every member is the input
     bool keep = false;              // next states with cache-keeping stores (set by batch_upload)
+    bool fused = true;              // the passes can sample every member's points (set by batch_upload)
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;  // two launches (parity 0 then 1)
     hipStream_t cap = nullptr;      // private stream the graph is captured on
@@ -1560,6 +1565,8 @@ int batch_upload(teuk_batch* b) {
     for (const teuk_grid* g : b->members) states += 2 * g->L.state;
     const int keep = states <= kKeepStatesBytes ? 1 : 0;
     b->keep = keep != 0;
+    b->fused = true;
+    int64_t points = 0;
     for (size_t k = 0; k < b->members.size(); ++k) {
         teuk_grid* g = b->members[k];
         g->rows = std::min<int>(b->rows, (int)g->p.ntheta);
@@ -1570,8 +1577,13 @@ int batch_upload(teuk_batch* b) {
         M.rad = a.rad;
         M.ang = a.ang;
         M.k = a.k;
-        M.k.n_ext = 0;
+        M.ext = a.ext;
+        M.ext_off = points;
+        points += g->p.n_extract;
+        M.k.n_ext = g->p.n_extract;
         M.k.keep = keep;
+        for (int m = 1; m <= kMaxPassSteps; ++m)
+            b->fused = b->fused && fused_extraction_ok(g, strip_cols(m), g->rows, true);
         for (int m = 0; m < kMaxPassSteps; ++m) {
             M.strips[m] = (a.k.nr + strip_cols(m + 1) - 1) / strip_cols(m + 1);
             M.tile_begin[m] = tiles[m];
@@ -1585,10 +1597,10 @@ int batch_upload(teuk_batch* b) {
     return TEUK_OK;
 }
 
-int batch_launch(teuk_batch* b, int parity, int steps, hipStream_t s) {
+int batch_launch(teuk_batch* b, int parity, int steps, hipStream_t s, const BatchSeries& series = {}) {
     const hipError_t e =
         launch_batch(reinterpret_cast<const BatchMember*>(b->ws + b->desc_off), (int)b->members.size(),
-                     b->total_tiles[steps - 1], parity, b->n_blocks, b->wpb, steps, b->keep, s);
+                     b->total_tiles[steps - 1], parity, b->n_blocks, b->wpb, steps, b->keep, series, s);
     return e == hipSuccess ? TEUK_OK : fail(TEUK_E_HIP, "batched step launch failed: %s", hipGetErrorString(e));
 }
 
@@ -1599,6 +1611,11 @@ int batch_pass_steps(const teuk_batch* b) {
     for (const teuk_grid* g : b->members)
         if (g->p.ntheta < 3) return 2;
     return 3;
+}
+
+// Steps of the next launch with `left` to take (the last as in step_n_impl).
+int batch_next_steps(int most, int64_t left) {
+    return most == 3 && left >= 3 && left != 4 ? 3 : (int)std::min<int64_t>(left, std::min(most, 2));
 }
 
 // Capture two launches (parity 0, then 1) into a graph.  The capture runs on a
@@ -1741,7 +1758,7 @@ int teuk_batch_step_n(teuk_batch* b, int64_t n) {
             left -= 2 * most;
             continue;
         }
-        const int m = most == 3 && left >= 3 && left != 4 ? 3 : (int)std::min<int64_t>(left, std::min(most, 2));
+        const int m = batch_next_steps(most, left);
         if (int rc = batch_launch(b, b->parity, m, b->stream)) return rc;
         b->parity = 1 - b->parity;
         left -= m;
@@ -1752,6 +1769,43 @@ int teuk_batch_step_n(teuk_batch* b, int64_t n) {
         g->steps += n;
     }
     return TEUK_OK;
+}
+
+int teuk_batch_step_samples(teuk_batch* b, int64_t n_samples, int64_t every, void* d_out) {
+    if (int rc = batch_check(b, 0)) return rc;
+    if (n_samples < 0 || every < 1) return fail(TEUK_E_INVALID_ARG, "need n_samples >= 0 and every >= 1");
+    if (b->n_points == 0) return fail(TEUK_E_STATE, "no member has extraction points");
+    if (n_samples > 0 && !d_out) return fail(TEUK_E_INVALID_ARG, "output pointer is NULL");
+    if (every > INT64_MAX / std::max<int64_t>(n_samples, 1))
+        return fail(TEUK_E_INVALID_ARG, "n_samples * every out of range");
+    double2* out = static_cast<double2*>(d_out);
+    if (!b->fused || every > 16) {  // points that share a tile, or samples too rare to cut the passes
+        for (int64_t k = 0; k < n_samples; ++k) {
+            if (int rc = teuk_batch_step_n(b, every)) return rc;
+            if (int rc = teuk_batch_extract(b, out + k * b->n_points)) return rc;
+        }
+        return TEUK_OK;
+    }
+    if (int rc = set_device(b->members[0])) return rc;
+    const int most = batch_pass_steps(b);
+    const int64_t n = n_samples * every;
+    for (int64_t k = 0; k < n;) {
+        const int m = batch_next_steps(most, n - k);
+        BatchSeries rows{};
+        for (int j = 0; j < m; ++j) {  // the state after k + j steps
+            const int64_t at = k + j;
+            rows.row[j] = at > 0 && at % every == 0 ? out + (at / every - 1) * b->n_points : nullptr;
+        }
+        if (int rc = batch_launch(b, b->parity, m, b->stream, rows)) return rc;
+        b->parity = 1 - b->parity;
+        k += m;
+    }
+    b->steps += n;
+    for (teuk_grid* g : b->members) {
+        g->cur = b->parity;
+        g->steps += n;
+    }
+    return n > 0 ? teuk_batch_extract(b, out + (n_samples - 1) * b->n_points) : TEUK_OK;
 }
 
 int teuk_batch_set_launch(teuk_batch* b, int32_t rows_per_tile, int32_t waves_per_block, int32_t n_blocks) {

@@ -5,8 +5,8 @@ Psi(t, r*, theta, phi) = sum_m e^{i m phi} r^3 Phi_m(t, r*, theta)
 Phi for each, and the modes evolve independently).
 
 Every mode is one member of a TeukBatch with the same grid, time step and
-observers; the batch is sampled after every `sample_every` steps with one
-extraction launch, and the mode sum runs in the library
+observers; the batch is sampled after every `sample_every` steps inside its
+passes, and the mode sum runs in the library
 (teuk_assemble_modes).  This module only moves tensors between the calls.
 """
 import numpy as np
@@ -42,6 +42,9 @@ class ModeSet:
         complex128 [n_samples][n_modes][n_obs], after every sample_every steps."""
         out = self.torch.empty((int(n_samples), len(self.m_values), len(self.observers)),
                                dtype=self.torch.complex128, device=self.batch.device)
+        if int(n_samples) > 0 and int(sample_every) > 0:
+            self.batch.step_samples(n_samples, sample_every, out)
+            return out
         for k in range(int(n_samples)):
             self.batch.step(sample_every)
             self.batch.extract(out[k].view(-1))

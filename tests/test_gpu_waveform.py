@@ -98,3 +98,36 @@ def test_assemble_modes_against_oracle(gpu, n_modes, n_obs, n_samples):
     torch.cuda.synchronize()
     ref = oracle.mode_sum(a, modes, rstar, phi, smp)
     assert rel_err(psi.cpu().numpy(), ref) <= TOL
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("every,n_samples,share", [(1, 7, False), (2, 5, False), (3, 4, True), (5, 3, False),
+                                                   (2, 4, True), (17, 2, False)])
+def test_samples_inside_the_passes(gpu, every, n_samples, share):
+    """Samples taken inside the batch's passes equal, bit for bit, those of
+    stepping and sampling in turn, for intervals on both sides of a pass's
+    steps, observers that differ in azimuth alone, uneven members, and points
+    that share a tile (share: sampled by launches of their own)."""
+    import torch
+
+    pts = [(20.0, 1.2), (20.0, 1.2), (-30.0, 0.01), (55.0, 3.1)] + ([(20.5, 1.21)] if share else [])
+    members = [dict(a=0.3 * k, s=-2, m=k - 1, nr=130 + 61 * k, ntheta=24 + 7 * k, rstar_min=-40.0, rstar_max=60.0,
+                    dt=0.01, extract_rstar=[p[0] for p in pts], extract_theta=[p[1] for p in pts]) for k in range(3)]
+    out = []
+    for route in range(2):
+        b = gpu.TeukBatch(members)
+        for k in range(3):
+            b.set_initial_data(k, *(torch.from_numpy(x).cuda() for x in inputs.random_state(130 + 61 * k, 24 + 7 * k, 5 + k)))
+        if route:
+            got = b.step_samples(n_samples, every)
+        else:
+            rows = []
+            for _ in range(n_samples):
+                b.step(every)
+                rows.append(b.extract())
+            got = torch.stack(rows)
+        out.append((got.cpu(), [[t.cpu() for t in b.state(k)] for k in range(3)]))
+        b.close()
+    assert torch.equal(out[0][0], out[1][0])
+    for x, y in zip(out[0][1], out[1][1]):
+        assert torch.equal(x[0], y[0]) and torch.equal(x[1], y[1])
