@@ -403,6 +403,170 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8))
                                               {tan_a, tan_b}, dlda_slots, A, rad_s);
 }
 
+// Adjoint steps on register tiles, for small and medium grids: the forward
+// tile pass (lw_tile_kernel) with the transposed step.  A group's last row
+// sends its theta shares (up, uph) to the row below and its first row (dn,
+// dnh) to the row above, through LDS, with one barrier a step; everything
+// else is in the lane or a cross-lane move.  K steps take lambda^{m+K} to
+// lambda^m; after step s the gradient of the sample of its output state, row
+// A.g_row - s of g (if that is not negative), is added at every stencil point
+// in the tile, own part or not.  Expressions and their order are those of
+// adjoint_sweep, so the cotangents are the same bit for bit.
+//
+// Bound as the forward tile pass, at about 110 vector instructions per point
+// and step.  us per step with three extraction points, the two-step sweep and
+// now: 1200 x 100 7.1 -> 2.5, 1600 x 128 8.6 -> 3.6, 3200 x 128 10.7 -> 6.1.
+template <int C, int R, int T, int KEEP>
+__global__ void __launch_bounds__(T)
+    lw_adjoint_tile_kernel(const double2* __restrict__ nu_in, double2* __restrict__ lam_out,
+                           const double* __restrict__ rad, const double* __restrict__ ang,
+                           const ExtPoint* __restrict__ ext, const double2* __restrict__ gser, AdjScalars A,
+                           AdjTileArgs B) {
+    const int K = B.steps, W = C - 2 * K;
+    const int nr = A.nr, nth = A.nth, P = A.pitch;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int j = lane % C, G = blockDim.x / C;
+    const int g = threadIdx.x / C;
+    const int strip = blockIdx.x % B.n_strips, tt = blockIdx.x / B.n_strips, n_tt = B.n_chunks;
+    const int H = G * R;  // the tile's rows: its first, and its own
+    const int own0 = tt == 0 ? 0 : H - K + (tt - 1) * (H - 2 * K);
+    const int own1 = tt == n_tt - 1 ? nth : H - K + tt * (H - 2 * K);
+    const int row0 = tt == 0 ? 0 : tt == n_tt - 1 ? nth - H : own0 - K;
+    const int t0 = row0 + g * R;
+    const int c0 = strip * W;
+    const int col = c0 - K + j;
+    const int ci = min(max(col, 0), nr - 1), hi = min(max(col, 0), nr - 2);
+    const bool interior = (col >= 1) && (col < nr - 1);
+    const bool edge = c0 - K <= 0 || c0 - K + C >= nr;
+    const double sg = (double)A.sigma;
+
+    extern __shared__ double rad_s[];
+    // [buffer][first row: dn, dnh; last row: up, uph][group][column]; then the
+    // points and the gradients of the launch's samples
+    v2d* xch = reinterpret_cast<v2d*>(rad_s);
+    const int plane = G * C, buf = 4 * plane;
+    v2d* sg_s = xch + 2 * buf;  // [step][point]
+    ExtPoint* sx = reinterpret_cast<ExtPoint*>(sg_s + K * kMaxBlockExt);
+    const int me = g * C + j;
+    const bool pole0 = t0 == 0, pole1 = t0 + R == nth;
+    const int i_up = pole0 || g == 0 ? me : 2 * plane + me - C;
+    const int i_dn = pole1 || g == G - 1 ? 2 * plane + me : me + C;
+    const double f_up = pole0 ? sg : 1.0, f_dn = pole1 ? sg : 1.0;
+
+    cd p[R], q[R];
+    Stage kh[R], ki[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const size_t o = (size_t)min(t0 + r, nth - 1) * P + ci;
+        p[r] = ld(nu_in, o);
+        q[r] = ld(nu_in, o + A.plane);
+    }
+    const SRad Rh = srad_of([&](int f) { return rad[((size_t)f * 2 + 1) * P + hi]; });
+    const SRad Ri = srad_of([&](int f) { return rad[((size_t)f * 2 + 0) * P + ci]; });
+    const int n_ext = gser != nullptr ? A.n_ext : 0;
+    for (int i = threadIdx.x; i < K * n_ext; i += blockDim.x) {
+        const int s = i / n_ext, e = i % n_ext;
+        const int64_t row = B.g_row - s;
+        const double2 v = row >= 0 ? gser[row * n_ext + e] : double2{0.0, 0.0};
+        sg_s[s * kMaxBlockExt + e] = v2d{v.x, v.y};
+    }
+    if ((int)threadIdx.x < n_ext) sx[threadIdx.x] = ext[threadIdx.x];
+    // stencil points this lane holds: bit e of its row r
+    unsigned duty[R] = {};
+    unsigned any = 0;
+    for (int e = 0; e < n_ext; ++e) {
+        const ExtPoint E = ext[e];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int t = t0 + r;
+            if ((col == E.col || col == E.col + 1) && (t == E.rowa || t == E.rowb)) duty[r] |= 1u << e;
+            any |= duty[r];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const Ang ga = load_ang(ang, nth, min(t0 + r, nth - 1));
+        kh[r] = stage_coef(Rh, ga, ssigma(Rh, ga), A.kap_h);
+        ki[r] = stage_coef(Ri, ga, ssigma(Ri, ga), A.kap_i);
+    }
+
+    for (int s = 0; s < K; ++s) {
+        v2d* x = xch + (s & 1) * buf;
+        if (edge) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                p[r] = {interior ? p[r].re : 0.0, interior ? p[r].im : 0.0};
+                q[r] = {interior ? q[r].re : 0.0, interior ? q[r].im : 0.0};
+            }
+        }
+        cd lD[R], up[R], dn[R], lHQ[R], uph[R], dnh[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const Stage &h = kh[r], &i = ki[r];
+            const cd lSQ = sub_conj(i.tr, i.ti, q[r], cd{A.qdt * p[r].re, A.qdt * p[r].im});
+            const cd lDQ = cscale(i.b, q[r]);
+            lD[r] = sub_conj(i.cr, i.ci, q[r], cd{-i.b * p[r].re, -i.b * p[r].im});
+            up[r] = cscale(i.wp, q[r]);
+            dn[r] = cscale(i.wm, q[r]);
+            lHQ[r] = cadd(cadd(lSQ, lDQ), from_right(csub(lSQ, lDQ)));
+            uph[r] = cscale(h.wp, lHQ[r]);
+            dnh[r] = cscale(h.wm, lHQ[r]);
+            if (r == 0) {
+                x[me] = v2d{dn[r].re, dn[r].im};
+                x[me + plane] = v2d{dnh[r].re, dnh[r].im};
+            }
+            if (r == R - 1) {
+                x[me + 2 * plane] = v2d{up[r].re, up[r].im};
+                x[me + 3 * plane] = v2d{uph[r].re, uph[r].im};
+            }
+        }
+        __syncthreads();
+        const v2d x0 = x[i_up], x1 = x[i_up + plane], x2 = x[i_dn], x3 = x[i_dn + plane];
+        __builtin_amdgcn_sched_barrier(0);
+        const cd Uu = {f_up * x0.x, f_up * x0.y}, Uh = {f_up * x1.x, f_up * x1.y};
+        const cd Du = {f_dn * x2.x, f_dn * x2.y}, Dh = {f_dn * x3.x, f_dn * x3.y};
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const Stage &h = kh[r], &i = ki[r];
+            const cd up0 = r == 0 ? Uu : up[r > 0 ? r - 1 : 0], uph0 = r == 0 ? Uh : uph[r > 0 ? r - 1 : 0];
+            const cd dnn = r == R - 1 ? Du : dn[r < R - 1 ? r + 1 : r], dnhn = r == R - 1 ? Dh : dnh[r < R - 1 ? r + 1 : r];
+            const cd lS = cadd(sub_conj(i.vr, i.vi, q[r], csub(csub(up0, up[r]), dn[r])), dnn);
+            const cd lU = sub_conj(h.vr, h.vi, lHQ[r], csub(csub(uph0, uph[r]), dnh[r]));
+            const cd lV = sub_conj(h.tr, h.ti, lHQ[r], lHQ[r]);
+            const cd ldp = sub_conj(h.cr, h.ci, lHQ[r], cd{0.0, 0.0}), ldq = cscale(h.b, lHQ[r]);
+            const cd np = cadd(p[r], csub(lU, ldp)), nq = cadd(q[r], csub(lV, ldq));
+            const cd lp = cadd(lU, ldp), lq = cadd(lV, ldq);
+            const cd lH = cadd(cadd(lS, lD[r]), from_right(csub(lS, lD[r])));
+            const cd a = cadd(lH, dnhn);
+            p[r] = cadd(np, cadd(fma_real(h.b, lH, a), from_left(cadd(lp, fma_real(-h.b, lH, a)))));
+            q[r] = cadd(nq, fma_real(A.hdt, lH, from_left(fma_real(A.hdt, lH, lq))));
+        }
+        if (any != 0 && B.g_row - s >= 0) {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                for (unsigned d = duty[r]; d != 0; d &= d - 1) {
+                    const int e = __builtin_ctz(d);
+                    const ExtPoint E = sx[e];
+                    const v2d gv = sg_s[s * kMaxBlockExt + e];
+                    const double wrow = (t0 + r == E.rowa) ? E.wa : E.wb;
+                    const double w = (col == E.col) ? wrow * (1.0 - E.wr) : wrow * E.wr;
+                    p[r].re = fma(w, gv.x, p[r].re);
+                    p[r].im = fma(w, gv.y, p[r].im);
+                }
+        }
+    }
+    if (j >= K && j < K + W && col < nr) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int t = t0 + r;
+            if (t >= own0 && t < own1) {
+                st_state<KEEP>(lam_out, (size_t)t * P + col, p[r]);
+                st_state<KEEP>(lam_out, (size_t)t * P + col + A.plane, q[r]);
+            }
+        }
+    }
+}
+
 // One Lax-Wendroff step, u^{m+1} = A u^m, that also writes the derivative of
 // the step with respect to the spin at fixed input, T_m = (dA/da) u^m: the
 // spin gradient is then dL/da = sum_m Re <lambda^{m+1}, T_m>, a dot product
@@ -496,6 +660,34 @@ hipError_t launch_adjoint2(const AdjArgs& a, const double* gsample_b, const doub
     hipLaunchKernelGGL(kern, grid, block, lds, s, a.nu_in, a.lam_out, a.rad, a.ang, a.ext, a.gsample, gsample_b,
                        a.u_in, tan_b, a.slots, a.k);
     return hipGetLastError();
+}
+
+hipError_t launch_adjoint_tile(const AdjArgs& a, const double2* gser, int64_t g_row, int steps, const TileShape& t,
+                               hipStream_t s) {
+    AdjTileArgs b{};
+    b.steps = steps;
+    b.g_row = g_row;
+    if (!tile_grid(t, a.k.nr, a.k.nth, steps, &b.n_strips, &b.n_chunks) || a.k.n_ext > kMaxBlockExt)
+        return hipErrorInvalidValue;
+    const int threads = t.waves * kWave;
+    const size_t lds = (size_t)(8 * threads + steps * kMaxBlockExt) * sizeof(double2) + kMaxBlockExt * sizeof(ExtPoint);
+    const dim3 grid(b.n_strips * b.n_chunks), block(threads);
+    auto go = [&](auto k0, auto k1, int most) {
+        if (threads > most) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(a.k.keep ? k1 : k0, grid, block, lds, s, a.nu_in, a.lam_out, a.rad, a.ang, a.ext, gser, a.k, b);
+        return hipGetLastError();
+    };
+#define TEUK_TILE(C, R, T) \
+    if (t.cols == C && t.rows == R) \
+        return go(lw_adjoint_tile_kernel<C, R, T, 0>, lw_adjoint_tile_kernel<C, R, T, 1>, T);
+    TEUK_TILE(16, 1, 1024)
+    TEUK_TILE(32, 1, 1024)
+    TEUK_TILE(64, 1, 1024)
+    TEUK_TILE(32, 2, 512)
+    TEUK_TILE(64, 2, 512)
+    TEUK_TILE(64, 3, 512)
+#undef TEUK_TILE
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_tangent(const double2* u_in, double2* u_out, double2* t_out, const AdjArgs& a, int waves_per_block,

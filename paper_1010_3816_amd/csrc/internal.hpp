@@ -203,6 +203,19 @@ struct TileShape {
     int cols = 0, rows = 0, waves = 0;
 };
 hipError_t launch_tile(const StepArgs& a, const TileShape& t, hipStream_t s);
+// Strips and theta tiles of a tile pass of `steps` steps; false if the shape
+// does not apply.
+bool tile_grid(const TileShape& t, int nr, int nth, int steps, int* n_strips, int* n_chunks);
+// The same for adjoint steps, cotangents only: a.nu_in = lambda^{m+steps} ->
+// a.lam_out = lambda^m, adding row g_row - s of gser ([rows][a.k.n_ext], or
+// nullptr) after step s.
+struct AdjTileArgs {
+    int32_t steps, n_strips, n_chunks, pad;
+    int64_t g_row;
+};
+struct AdjArgs;
+hipError_t launch_adjoint_tile(const AdjArgs& a, const double2* gser, int64_t g_row, int steps, const TileShape& t,
+                               hipStream_t s);
 // Zero n ints (a fill kernel: usable where a memset node is not).
 hipError_t launch_zero_ints(int* p, int n, hipStream_t s);
 // steps per launch: 1, 2 or 3 (the work list of tile_begin[steps - 1]).

@@ -928,22 +928,26 @@ hipError_t launch_block(const StepArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+bool tile_grid(const TileShape& t, int nr, int nth, int steps, int* n_strips, int* n_chunks) {
+    if (t.cols < 1 || t.waves < 1 || steps < 1) return false;
+    const int w = t.cols - 2 * steps, rows = t.waves * kWave / t.cols * t.rows;
+    if (w < 1) return false;
+    *n_strips = (nr + w - 1) / w;
+    *n_chunks = 1;
+    if (rows >= nth) return rows == nth || t.rows == 1;
+    // theta tiles: the first holds rows - steps of its own, the last ends at
+    // the last row, those between rows - 2 steps
+    const int mid = rows - 2 * steps;
+    if (mid < 1) return false;
+    *n_chunks = 2 + std::max(0, (nth - 2 * (rows - steps) + mid - 1) / mid);
+    return true;
+}
+
 hipError_t launch_tile(const StepArgs& a, const TileShape& t, hipStream_t s) {
-    const int w = t.cols - 2 * a.k.bsteps, threads = t.waves * kWave, groups = threads / t.cols;
-    if (a.k.bsteps < 1 || w < 1 || a.k.n_ext > kMaxBlockExt || t.waves < 1) return hipErrorInvalidValue;
     StepArgs b = a;
-    b.k.n_strips = (a.k.nr + w - 1) / w;
-    const int rows = groups * t.rows, nth = a.k.nth;
-    // theta tiles: the first holds rows - k of its own, the last ends at the
-    // last row, those between rows - 2 k
-    if (rows >= nth) {
-        if (rows > nth && t.rows != 1) return hipErrorInvalidValue;
-        b.k.n_chunks = 1;
-    } else {
-        const int k = a.k.bsteps, mid = rows - 2 * k;
-        if (mid < 1) return hipErrorInvalidValue;
-        b.k.n_chunks = 2 + std::max(0, (nth - 2 * (rows - k) + mid - 1) / mid);
-    }
+    if (!tile_grid(t, a.k.nr, a.k.nth, a.k.bsteps, &b.k.n_strips, &b.k.n_chunks) || a.k.n_ext > kMaxBlockExt)
+        return hipErrorInvalidValue;
+    const int threads = t.waves * kWave;
     const size_t lds = (size_t)(2 * (t.rows == 1 ? 1 : 2) * 2 * threads + (a.k.n_ext > 0 ? 4 * kMaxBlockExt * a.k.bsteps : 0)) *
                        sizeof(double2);
     const dim3 grid(b.k.n_strips * b.k.n_chunks), block(threads);

@@ -223,6 +223,9 @@ struct teuk_grid {
     size_t aoff_lam[2]{}, aoff_da = 0, aoff_slots = 0, aoff_sum = 0;
     int adj_rows = 32, adj_wpb = 4, adj_chunks = 0, adj_strips = 0;  // spin-gradient and one-step kernels
     int adj2_rows = 32, adj2_chunks = 0;                              // two-step cotangent kernel
+    TileShape adj_tile;       // adjoint tile pass: shape and steps per launch (0: off)
+    int adj_tile_steps = 0;
+    bool adj_default = true;  // teuk_set_adjoint_tile has not been called
     int tan_rows = 32, tan_chunks = 0;                                // step-with-tangent kernel
     int cache_policy = TEUK_CACHE_AUTO;                               // teuk_set_cache_policy
     // forward-mode spin derivative (teuk_enable_spin_tangent): v = du/da in two buffers
@@ -438,8 +441,10 @@ int sweep_rows(int nr, int nth, int cus, int K, int G, double alone, double* us 
 // with one row a lane and two wavefronts a SIMD, 0.87 with four, 1.13 with
 // three rows and two; a launch of 256 workgroups 5.7, 7.5 and 7.1 us besides.
 // Estimate and measurement (us per step): 400 x 32 1.28 and 1.27, 1600 x 128
-// 2.97 and 3.05, 3200 x 128 5.4 and 5.2, 1200 x 100 2.2 and 2.0.
-double best_tile(int nr, int nth, int cus, TileShape* shape, int* steps) {
+// 2.97 and 3.05, 3200 x 128 5.4 and 5.2, 1200 x 100 2.2 and 2.0; adjoint (three
+// points) 1200 x 100 2.5 and 2.5, 3200 x 128 5.6 and 6.1, 5003 x 197 13.1 and
+// 13.8 (sweeps: 7.1, 10.7, 16.7).  work: instructions per step, the forward's as 1.
+double best_tile(int nr, int nth, int cus, double work, TileShape* shape, int* steps) {
     struct Kind {
         int cols, rows, most, per_cu;  // most wavefronts a workgroup and a CU
         double us;                     // per row and wavefront of a SIMD
@@ -465,7 +470,7 @@ double best_tile(int nr, int nth, int cus, TileShape* shape, int* steps) {
                 const double rounds = std::ceil((double)groups / ((double)cus * held));
                 const double load = c.rows * std::max(1.0, 0.25 * waves), all = c.rows * std::max(1.0, 0.25 * waves * held);
                 const double t = (2.5 + rounds * ((1.5 + 0.35 * load) * held + 1.3 * std::min(1.0, (double)groups / cus) +
-                                                  k * (0.25 + c.us * all))) / k;
+                                                  k * (0.25 + work * c.us * all))) / k;
                 if (*steps == 0 || t < best) {
                     best = t;
                     *steps = k;
@@ -646,7 +651,7 @@ int teuk_init_grid(const teuk_params* p, void* hip_stream, void* d_workspace, si
         }
     }
     // the tile pass where its estimate is below the sweeps'
-    if (p->coef_mode == TEUK_COEF_KERR && best_tile(nr, nth, cus, &g->tile_shape, &g->tile_steps) >= sweep_us)
+    if (p->coef_mode == TEUK_COEF_KERR && best_tile(nr, nth, cus, 1.0, &g->tile_shape, &g->tile_steps) >= sweep_us)
         g->tile_steps = 0;
     g->default_tile[0] = g->rows;
     g->default_tile[1] = g->wpb;
@@ -659,7 +664,9 @@ int teuk_init_grid(const teuk_params* p, void* hip_stream, void* d_workspace, si
     // beside them.
     g->adj_rows = adjoint_rows(nr, nth, (int64_t)cus * 7, kStripCols);
     g->adj_chunks = (nth + g->adj_rows - 1) / g->adj_rows;
-    g->adj2_rows = sweep_rows(nr, nth, cus, 2, 2, 1.8);
+    g->adj2_rows = sweep_rows(nr, nth, cus, 2, 2, 1.8, &sweep_us);
+    // (the adjoint tile pass: 1.17 times the forward one's instructions)
+    if (best_tile(nr, nth, cus, 1.17, &g->adj_tile, &g->adj_tile_steps) >= 0.95 * sweep_us) g->adj_tile_steps = 0;
     g->adj2_chunks = (nth + g->adj2_rows - 1) / g->adj2_rows;
     g->tan_rows = sweep_rows(nr, nth, cus, 1, 2, 1.3);
     g->tan_chunks = (nth + g->tan_rows - 1) / g->tan_rows;
@@ -1179,6 +1186,7 @@ int teuk_set_adjoint_tile(teuk_grid* g, int32_t rows_per_tile, int32_t waves_per
     g->adj_rows = g->adj2_rows = g->tan_rows = rows_per_tile;
     g->adj_chunks = g->adj2_chunks = g->tan_chunks = (int)((g->p.ntheta + rows_per_tile - 1) / rows_per_tile);
     g->adj_wpb = waves_per_block;
+    g->adj_default = false;
     return TEUK_OK;
 }
 
@@ -1346,6 +1354,20 @@ int adjoint_impl(teuk_grid* g, int64_t n, void* d_lam_phi, void* d_lam_pi, const
     const char* win = static_cast<const char*>(d_window);
     auto slot = [&](int64_t k) { return reinterpret_cast<const double2*>(win + (size_t)k * g->L.state); };
     int64_t k = n - 1;
+    if (!spin && g->adj_tile_steps > 0 && g->adj_default && g->steps_per_pass == 2 && ne <= kMaxBlockExt) {
+        // cotangents on register tiles, in launches of about equal steps
+        AdjArgs at = a;
+        at.k.n_ext = ne;
+        for (; k >= 0;) {
+            const int64_t left = k + 1, launches = (left + g->adj_tile_steps - 1) / g->adj_tile_steps;
+            const int m = (int)((left + launches - 1) / launches);
+            at.nu_in = lam(c);
+            at.lam_out = lam(1 - c);
+            HIP_TRY(launch_adjoint_tile(at, gs, k - 1, m, g->adj_tile, s));
+            c = 1 - c;
+            k -= m;
+        }
+    }
     if ((!spin || tangent) && fused && g->steps_per_pass == 2) {
         // cotangents (and the tangents' dot products): two adjoint steps
         // (k, then k-1) per pass
