@@ -17,14 +17,8 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-ffp-contract=on",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
-# Per-source flags.  The forward-mode spin derivative carries two states'
-# row data (u and v = du/da); the machine scheduler's occupancy-first
-# strategy keeps them within the registers of two wavefronts per SIMD
-# without spilling (measured faster there; slower for the other kernels,
-# which keep the default).  Scheduling does not change results.
-SOURCE_FLAGS = {
-    "spin_tangent.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-maxocc"],
-}
+# Per-source flags (none at present).
+SOURCE_FLAGS = {}
 
 
 def _run(cmd):

@@ -115,12 +115,15 @@ struct TanRow {
 // sample slots.  T_m is streamed; the next states follow KEEP.
 //
 // What bounds it: 328 vector instructions per point and step with v (498
-// before), half of the cycles of its two wavefronts per SIMD; 36 % of a
-// wavefront's time it waits, for its 52 LDS reads a row in turn (more of them
-// at once would need registers; 240 of 256 are used) and for memory (210 MB a
-// step on 6400 x 256, 25 us at the rate of a copy within the last-level
-// cache).  us per step, before and now: 6400 x 256 48.6 -> 43-45 with v, 35.8
-// -> 33.5 without; 3200 x 128 19.4 -> 17.4, 13.7 -> 15.0.
+// before), half of the cycles of its two wavefronts per SIMD, and the waits for
+// its 52 LDS reads a row and for memory (210 MB a step on 6400 x 256, 25 us at
+// the rate of a copy within the last-level cache).  Stage 1 is finished, and
+// the previous row completed and stored, before the column's coefficients are
+// read: 200 registers instead of 240 with v, 162 instead of 218 without, so the
+// default instruction schedule, which has more loads in flight than one for
+// occupancy, does not spill.  us per step, before and now: 6400 x 256 48.6 ->
+// 38.7 with v, 35.8 -> 33.4 without; 3200 x 128 19.4 -> 16.4, 13.7 -> 15.1.
+// Three wavefronts per SIMD (168 registers) spill with v and take 51-60 us.
 template <bool V, int KEEP>
 __device__ __forceinline__ void tangent_sweep(gin_t u_in, gin_t v_in, gout_t u_out, gout_t v_out, ctab_t ang,
                                               const ExtPoint* __restrict__ ext, double2* __restrict__ series_u,
@@ -188,20 +191,15 @@ __device__ __forceinline__ void tangent_sweep(gin_t u_in, gin_t v_in, gout_t u_o
         constexpr int CHECK = decltype(check)::value;
         const Ang G = g_next;
         const int z = t & A.zero;
-        Stage kh, dh, ki, di;
+        // stage 1 with the half point's coefficients first, then stage 2 with
+        // the column's: both sets at once need more registers
+        Stage kh, dh;
         {
             const SRad R = srad_of([&](int f) { return rvh[z + f * kWave]; });
             const Sig sig = ssigma(R, G);
             kh = stage_coef(R, G, sig, A.kap_h);
             const SRad D = srad_of([&](int f) { return rdh[z + f * kWave]; });
             dh = stage_coef_da(R, D, G, sig, A.kap_h, kh);
-        }
-        {
-            const SRad R = srad_of([&](int f) { return rvi[z + f * kWave]; });
-            const Sig sig = ssigma(R, G);
-            ki = stage_coef(R, G, sig, A.kap_i);
-            const SRad D = srad_of([&](int f) { return rdi[z + f * kWave]; });
-            di = stage_coef_da(R, D, G, sig, A.kap_i, ki);
         }
         const cd p = b[0], q = b[1];
         if constexpr (V && CHECK) {
@@ -247,6 +245,10 @@ __device__ __forceinline__ void tangent_sweep(gin_t u_in, gin_t v_in, gout_t u_o
         const cd dU = csub(n.U, Um), dS = csub(n.S, Sm), tdS = csub(n.tS, tSm);
         cd tdU;
         if constexpr (V) tdU = csub(n.tU, tUm);
+        // row t up to its next-row terms
+        n.X = cadd(W, stage1_inc(kh, n.U, W, dp, dq, dU));
+        n.tX = stage1_inc(dh, n.U, W, dp, dq, dU);
+        if constexpr (V) n.tX = cadd(tW, cadd(n.tX, stage1_inc(kh, n.tU, tW, tdp, tdq, tdU)));
         if constexpr (CHECK != 2) {  // row t - 1
             const cd HQ = fma_real(s.k.wh, dU, s.X), HQl = from_left(HQ);
             const cd SQ = cadd(HQ, HQl), DQ = csub(HQ, HQl);
@@ -274,18 +276,22 @@ __device__ __forceinline__ void tangent_sweep(gin_t u_in, gin_t v_in, gout_t u_o
             st_row<kV>(row_rsrc(v_out + o, bytes), st_off, vp);
             st_row<kV>(row_rsrc(v_out + o + A.plane, bytes), st_off, vq);
         }
-        // row t up to its next-row terms
-        n.X = cadd(W, stage1_inc(kh, n.U, W, dp, dq, dU));
+        __builtin_amdgcn_sched_barrier(0);
+        Stage ki, di;
+        {
+            const SRad R = srad_of([&](int f) { return rvi[z + f * kWave]; });
+            const Sig sig = ssigma(R, G);
+            ki = stage_coef(R, G, sig, A.kap_i);
+            const SRad D = srad_of([&](int f) { return rdi[z + f * kWave]; });
+            di = stage_coef_da(R, D, G, sig, A.kap_i, ki);
+        }
         n.P = fma_real(-ki.b, D, p);
         n.Q = cadd(q, stage2_early(ki, n.S, D, dS));
-        const cd tx = stage1_inc(dh, n.U, W, dp, dq, dU);
         const cd tq = cadd(stage2_early(di, n.S, D, dS), stage2_early(ki, n.tS, tD, tdS));
         if constexpr (V) {
-            n.tX = cadd(tW, cadd(tx, stage1_inc(kh, n.tU, tW, tdp, tdq, tdU)));
             n.tP = fma_real(-di.b, D, fma_real(-ki.b, tD, b[2]));
             n.tQ = cadd(b[3], tq);
         } else {
-            n.tX = tx;
             n.tP = fma_real(-di.b, D, cd{-ki.b * tD.re, -ki.b * tD.im});
             n.tQ = tq;
         }

@@ -1,9 +1,6 @@
 // gfx950 forward-mode derivative of the Lax-Wendroff step (arXiv:1010.3816,
 // Eqs. (lw1)-(lw2) with the boundary conditions) with respect to the spin a:
 // the state and its a-derivative advance together, one pass per step.
-// Compiled on its own with the machine scheduler's occupancy-first strategy:
-// the two states' row data fit the registers of two wavefronts per SIMD only
-// when scheduled for occupancy (the default schedule spills).
 #include "adjoint_common.hpp"
 
 namespace teuk {

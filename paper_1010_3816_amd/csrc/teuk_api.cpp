@@ -396,7 +396,8 @@ void default_tile(int nr, int nth, int cus, int* rows, int* wpb) {
 // Tile height of a K-step sweep whose row loop is unrolled by G rows.  A
 // wavefront walks its tile's rows one after the other: K rows to fill the
 // steps, then the tile's rows and K more in groups of G, after a start (tables
-// and first rows) worth about three rows.  Two wavefronts fit a SIMD, where
+// and first rows) worth about three rows, or two where wavefronts overlap in
+// it.  Two wavefronts fit a SIMD, where
 // they share its issue: a row takes two units of time beside another wavefront
 // and `alone` units without.  Tiles beyond one round of wavefronts wait for a
 // slot; with several rounds the last, partly filled one counts for less.  The
@@ -405,8 +406,9 @@ void default_tile(int nr, int nth, int cus, int* rows, int* wpb) {
 // 12.2 / 12.3, at 14 rows (a second round) 14.7; 5003 x 197 at 9 / 10 / 13
 // rows 9.6 / 10.9 / 10.1; 1600 x 128 at 2 / 4 / 8 rows 7.0 / 5.1 / 5.9;
 // 25600 x 512 at 57 / 103 rows 68 / 86.  Step with its spin tangent (G = 2),
-// 6400 x 256 at 14 / 15 / 17 rows 46.4 / 43.4 / 44.9, 3200 x 128 at 4 / 7 / 9
-// rows 18.6 / 17.4 / 19.3.  Two-step adjoint (G = 2), 6400 x 256 at 14 / 15 /
+// 6400 x 256 at 15 / 17 / 29 rows 42.2 / 43.5 / 38.7, 3200 x 128 at 4 / 5 / 7
+// rows 17.0 / 17.6 / 16.4, 1200 x 100 at 1 / 2 / 3 rows 10.2 / 11.5 / 11.3.
+// Two-step adjoint (G = 2), 6400 x 256 at 14 / 15 /
 // 29 rows 15.0 / 16.5 / 22.4, 3200 x 128 at 4 / 5 / 8 rows 8.1 / 9.1 / 9.5.
 int sweep_rows(int nr, int nth, int cus, int K, int G, double alone, double* us = nullptr) {
     const int64_t strips = (nr + strip_cols(K) - 1) / strip_cols(K);
@@ -422,7 +424,7 @@ int sweep_rows(int nr, int nth, int cus, int K, int G, double alone, double* us 
             const double whole = 2.0 * (rounds - 1.0) + (over > 1.0 ? 2.0 : alone);
             f = x + (whole - x) / std::max(1.0, rounds - 1.0);
         }
-        const double t = 3.0 * rounds + its * f;
+        const double t = (x > 1.0 ? 2.0 : 3.0) * rounds + its * f;
         // equal times: fewer tiles where two share a SIMD, else shorter ones
         if (r == 1 || t < best || (t == best && x > 1.0)) {
             best = t;
@@ -668,7 +670,7 @@ int teuk_init_grid(const teuk_params* p, void* hip_stream, void* d_workspace, si
     // (the adjoint tile pass: 1.17 times the forward one's instructions)
     if (best_tile(nr, nth, cus, 1.17, &g->adj_tile, &g->adj_tile_steps) >= 0.95 * sweep_us) g->adj_tile_steps = 0;
     g->adj2_chunks = (nth + g->adj2_rows - 1) / g->adj2_rows;
-    g->tan_rows = sweep_rows(nr, nth, cus, 1, 2, 1.3);
+    g->tan_rows = sweep_rows(nr, nth, cus, 1, 2, 1.0);
     g->tan_chunks = (nth + g->tan_rows - 1) / g->tan_rows;
     g->adj_strips = ((int)p->nr + kStripCols - 1) / kStripCols;
     g->ext_r.assign(p->extract_rstar, p->extract_rstar + p->n_extract);
