@@ -218,8 +218,8 @@ int teuk_get_tile(const teuk_grid* g, int32_t* rows_per_tile, int32_t* waves_per
  * identical.  teuk_step_n_store takes two and keeps the intermediate state of
  * a pass in its window slot; its first step runs alone (it also copies its
  * input).  A pass whose extraction points share one of its tiles is not taken.
- * The tile rows of teuk_set_tile apply (until it is called, the three-step
- * pass takes a height of its own); at most 4 wavefronts per workgroup are
+ * The tile rows of teuk_set_tile apply (until it is called, the passes
+ * take heights of their own); at most 4 wavefronts per workgroup are
  * used.  Where the small-grid block pass is on (teuk_set_block_launch),
  * teuk_step_n takes it instead of these passes.  TEUK_E_INVALID_ARG for other
  * values. */

@@ -206,7 +206,8 @@ struct teuk_grid {
     int64_t steps = 0;
     int rows = 64;        // theta rows per wavefront tile
     int wpb = 4;          // wavefronts per workgroup
-    int rows3 = 64, wpb3 = 4;  // the same of the three-step pass (teuk_set_tile sets both)
+    // the same of the passes of 1, 2, 3 steps (teuk_set_tile sets them all)
+    int pass_rows[kMaxPassSteps] = {64, 64, 64}, pass_wpb[kMaxPassSteps] = {4, 4, 4};
     int steps_per_pass = 2;  // 2: several steps in one pass (temporal blocking)
     bool fused[kMaxPassSteps] = {true, true, true};  // extraction fusable with the strips of passes of 1, 2, 3 steps
     int block_steps = 0;     // teuk_set_block_launch: steps per launch of the block pass (0: off)
@@ -214,7 +215,8 @@ struct teuk_grid {
     TileShape tile_shape;    // the tile pass's shape and steps per launch (0: off)
     int tile_steps = 0;
     bool default_launch = true;  // tile and block launch as teuk_init_grid chose them
-    int default_tile[2] = {0, 0}, default_block[2] = {0, 0}, default_rows3 = 0, default_wpb3 = 0;
+    int default_tile[2] = {0, 0}, default_block[2] = {0, 0};
+    int default_rows[kMaxPassSteps] = {}, default_wpb[kMaxPassSteps] = {};
     int64_t check_every = 0;  // teuk_set_finite_check: steps between device checks of the state (0: off)
     char* sws = nullptr;      // source profile (teuk_set_source): [integer, half][nth][pitch] complex128
     bool coef_set = false;
@@ -295,7 +297,7 @@ bool fused_adjoint_ok(const teuk_grid* g) {
 
 void update_fusion(teuk_grid* g) {
     for (int k = 1; k <= kMaxPassSteps; ++k)
-        g->fused[k - 1] = fused_extraction_ok(g, strip_cols(k), k == 3 ? g->rows3 : g->rows, true);
+        g->fused[k - 1] = fused_extraction_ok(g, strip_cols(k), g->pass_rows[k - 1], true);
 }
 
 // Two states (a pass's input and output) up to this size stay in the
@@ -345,10 +347,8 @@ StepArgs step_args(const teuk_grid* g) {
 StepArgs pass_args(const teuk_grid* g, int steps) {
     StepArgs a = step_args(g);
     a.k.n_strips = (a.k.nr + strip_cols(steps) - 1) / strip_cols(steps);
-    if (steps == 3) {
-        a.k.rows = g->rows3;
-        a.k.n_chunks = (a.k.nth + g->rows3 - 1) / g->rows3;
-    }
+    a.k.rows = g->pass_rows[steps - 1];
+    a.k.n_chunks = (a.k.nth + a.k.rows - 1) / a.k.rows;
     a.k.n_ext = g->fused[steps - 1] ? g->p.n_extract : 0;
     a.k.order = steps > 1 && a.k.n_strips >= 64 ? kTileOrderXcdStrip : kTileOrderDispatch;
     return a;
@@ -624,9 +624,17 @@ int teuk_init_grid(const teuk_params* p, void* hip_stream, void* d_workspace, si
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
             cus = 256;
         default_tile(nr, nth, cus, &g->rows, &g->wpb);
+        // Each pass on a tile of its own: the strips of a pass of k steps are
+        // 64 - 2 k columns, and the rows that fill the chip once differ.  With
+        // the one-step pass's rows for all, source runs of 6400 x 256 (steps in
+        // pairs) took 18.8 us a step, with their own 16.8.
         // (four wavefronts a workgroup, or one, to spread few tiles over the CUs)
-        g->rows3 = sweep_rows(nr, nth, cus, 3, 4, 1.3, &sweep_us);
-        g->wpb3 = (nr + strip_cols(3) - 1) / strip_cols(3) * ((nth + g->rows3 - 1) / g->rows3) < cus * 4 ? 1 : 4;
+        for (int k = 1; k <= kMaxPassSteps; ++k) {
+            const int r = sweep_rows(nr, nth, cus, k, k + 1, 1.3, &sweep_us);
+            const int64_t tiles = (int64_t)((nr + strip_cols(k) - 1) / strip_cols(k)) * ((nth + r - 1) / r);
+            g->pass_rows[k - 1] = g->default_rows[k - 1] = r;
+            g->pass_wpb[k - 1] = g->default_wpb[k - 1] = tiles < cus * 4 ? 1 : 4;
+        }
     }
     // The block pass: one thread per point of (columns x all rows).  Default
     // launch: over workgroups of up to 256, 512 or 1024 threads (at most 64
@@ -659,8 +667,6 @@ int teuk_init_grid(const teuk_params* p, void* hip_stream, void* d_workspace, si
     g->default_tile[1] = g->wpb;
     g->default_block[0] = g->block_steps;
     g->default_block[1] = g->block_cols;
-    g->default_rows3 = g->rows3;
-    g->default_wpb3 = g->wpb3;
     // a device holds two adjoint wavefronts per SIMD (8 per CU).  The
     // one-step kernels leave one slot in eight to a recompute that runs
     // beside them.
@@ -901,7 +907,7 @@ int step_n_impl(teuk_grid* g, int64_t n, void* d_series, void* d_window, const d
         a.series_mid = sample ? series + k * ne : nullptr;
         if (h_f)
             for (int j = 0; j < 4 * m; ++j) a.k.sf[j] = g->p.dt * h_f[4 * k + j];
-        HIP_TRY(launch_pass(a, m, kerr, std::min(m == 3 ? g->wpb3 : g->wpb, 4), g->stream));
+        HIP_TRY(launch_pass(a, m, kerr, std::min(g->pass_wpb[m - 1], 4), g->stream));
         if (sample) sampled = k + m - 1;
         advance(out);
         k += m;
@@ -1084,19 +1090,16 @@ double teuk_get_dt(const teuk_grid* g) { return g ? g->p.dt : 0.0; }
 namespace {
 
 // After a change of the tile or the block launch: with both as teuk_init_grid
-// chose them the grid's own choice among the passes is back (the three-step
-// pass's tile and the tile pass); otherwise the sweeps take the tile given.
+// chose them the grid's own choice among the passes is back (the passes' own
+// tiles and the tile pass); otherwise the sweeps take the tile given.
 // off: the block pass was turned off, which leaves the sweeps.
 void select_launch(teuk_grid* g, bool off) {
     const bool tile = g->rows == g->default_tile[0] && g->wpb == g->default_tile[1];
     const bool block = g->block_steps == g->default_block[0] && g->block_cols == g->default_block[1];
     g->default_launch = tile && block && !off;
-    if (!tile) {
-        g->rows3 = g->rows;
-        g->wpb3 = g->wpb;
-    } else {
-        g->rows3 = g->default_rows3;
-        g->wpb3 = g->default_wpb3;
+    for (int k = 0; k < kMaxPassSteps; ++k) {
+        g->pass_rows[k] = tile ? g->default_rows[k] : g->rows;
+        g->pass_wpb[k] = tile ? g->default_wpb[k] : g->wpb;
     }
 }
 
