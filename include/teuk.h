@@ -211,8 +211,7 @@ int teuk_get_tile(const teuk_grid* g, int32_t* rows_per_tile, int32_t* waves_per
 
 /* Steps per pass over the state: 1, or 2 (default) for several.  With 2,
  * teuk_step_n takes three steps in one kernel pass, and two at a call's end,
- * with user coefficients, a source term, fewer than three rows or the in-loop
- * finite check (temporal blocking: the intermediate states stay in registers,
+ * with user coefficients, fewer than three rows or the in-loop finite check (temporal blocking: the intermediate states stay in registers,
  * so the state is read and written once per pass), and an odd last step
  * alone; the per-point arithmetic is that of single steps, so results are
  * identical.  teuk_step_n_store takes two and keeps the intermediate state of

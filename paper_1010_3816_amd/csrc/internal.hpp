@@ -183,7 +183,7 @@ hipError_t launch_tables_da(const TableArgs& a, const double* x_tab, double* da,
 
 // Launchers (lw_kernels.hip, adjoint_kernels.hip).  All return the
 // hipError_t of the launch.
-// 1, 2 or (Kerr coefficients, no source) 3 steps in one pass; k.n_strips
+// 1, 2 or (Kerr coefficients) 3 steps in one pass; k.n_strips
 // counted in strip_cols(steps)-column strips.
 hipError_t launch_pass(const StepArgs& a, int steps, bool kerr, int waves_per_block, hipStream_t s);
 // Small grids (ntheta <= kMaxBlockRows, Kerr coefficients): k.bsteps steps in

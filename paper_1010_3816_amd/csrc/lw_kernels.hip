@@ -366,9 +366,15 @@ __device__ __forceinline__ void pass_tile(const double2* __restrict__ u_in, doub
                               (gout_t)win, (lds_t)(rad_s + (threadIdx.x / kWave) * kSliceDoubles), A, strip, chunk, lane, (gin_t)src_i, (gin_t)src_h);
 }
 
+// Two wavefronts to a SIMD bar three steps with a source: its rows take 313
+// registers and would spill 60 at two.  One alone is as fast as two where
+// the grid has only that many tiles, and saves a third of the state's traffic
+// (us per step in pairs and in threes: 3200 x 128 7.65 and 7.0, 5003 x 197
+// 12.2 and 12.4, 6400 x 256 17.0 and 15.4, 12800 x 256 30.8 and 30.9,
+// 25600 x 512 129 and 111).
 #define TEUK_PASS_KERNEL(NAME, K)                                                                                     \
     template <bool KERR, bool SRC, int KEEP>                                                                          \
-    __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 4)))                                \
+    __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K == 3 && SRC ? 1 : 2, 4)))            \
         NAME(const double2* __restrict__ u_in, double2* __restrict__ u_out, const double* __restrict__ rad,           \
              const double* __restrict__ ang, const double* __restrict__ uci, const double* __restrict__ uch,          \
              const ExtPoint* __restrict__ ext, double2* __restrict__ series_in, double2* __restrict__ series_mid,     \
@@ -904,11 +910,11 @@ static hipError_t launch_pass_k(const StepArgs& a, bool kerr, int waves_per_bloc
     if constexpr (K == 1) return pick(lw_step_kernel<KERR, SRC, 0>, lw_step_kernel<KERR, SRC, 1>); \
     if constexpr (K == 2) return pick(lw_step2_kernel<KERR, SRC, 0>, lw_step2_kernel<KERR, SRC, 1>); \
     if constexpr (K == 3) return pick(lw_step3_kernel<KERR, SRC, 0>, lw_step3_kernel<KERR, SRC, 1>);
+    if (src && kerr) {
+        TEUK_PICK(true, true)
+    }
     if constexpr (K < 3) {
         if (src) {
-            if (kerr) {
-                TEUK_PICK(true, true)
-            }
             TEUK_PICK(false, true)
         }
         if (!kerr) {
@@ -920,7 +926,7 @@ static hipError_t launch_pass_k(const StepArgs& a, bool kerr, int waves_per_bloc
 }
 
 hipError_t launch_pass(const StepArgs& a, int steps, bool kerr, int waves_per_block, hipStream_t s) {
-    if (steps == 3 && kerr && a.src_i == nullptr) return launch_pass_k<3>(a, kerr, waves_per_block, s);
+    if (steps == 3 && kerr) return launch_pass_k<3>(a, kerr, waves_per_block, s);
     if (steps == 2) return launch_pass_k<2>(a, kerr, waves_per_block, s);
     if (steps == 1) return launch_pass_k<1>(a, kerr, waves_per_block, s);
     return hipErrorInvalidValue;

@@ -190,6 +190,13 @@ void* scratch_address(int device) {
     return (device >= 0 && (size_t)device < g_scratch_addr.size()) ? g_scratch_addr[device] : nullptr;
 }
 
+// The passes that have a tile height of their own: 1, 2, 3 steps, and 3 with a
+// source term (its kernel holds one wavefront on a SIMD, the others two).
+constexpr int kPassKinds = kMaxPassSteps + 1;
+constexpr int pass_kind(int steps, bool source) {
+    return steps == kMaxPassSteps && source ? kMaxPassSteps : steps - 1;
+}
+
 }  // namespace
 
 struct teuk_grid {
@@ -206,17 +213,18 @@ struct teuk_grid {
     int64_t steps = 0;
     int rows = 64;        // theta rows per wavefront tile
     int wpb = 4;          // wavefronts per workgroup
-    // the same of the passes of 1, 2, 3 steps (teuk_set_tile sets them all)
-    int pass_rows[kMaxPassSteps] = {64, 64, 64}, pass_wpb[kMaxPassSteps] = {4, 4, 4};
+    // the same of the passes of 1, 2, 3 steps and of 3 with a source
+    // (teuk_set_tile sets them all)
+    int pass_rows[kPassKinds] = {64, 64, 64, 64}, pass_wpb[kPassKinds] = {4, 4, 4, 4};
     int steps_per_pass = 2;  // 2: several steps in one pass (temporal blocking)
-    bool fused[kMaxPassSteps] = {true, true, true};  // extraction fusable with the strips of passes of 1, 2, 3 steps
+    bool fused[kPassKinds] = {true, true, true, true};  // extraction fusable with the tiles of each pass
     int block_steps = 0;     // teuk_set_block_launch: steps per launch of the block pass (0: off)
     int block_cols = 0;      // columns a block-pass workgroup holds (0: not set)
     TileShape tile_shape;    // the tile pass's shape and steps per launch (0: off)
     int tile_steps = 0;
     bool default_launch = true;  // tile and block launch as teuk_init_grid chose them
     int default_tile[2] = {0, 0}, default_block[2] = {0, 0};
-    int default_rows[kMaxPassSteps] = {}, default_wpb[kMaxPassSteps] = {};
+    int default_rows[kPassKinds] = {}, default_wpb[kPassKinds] = {};
     int64_t check_every = 0;  // teuk_set_finite_check: steps between device checks of the state (0: off)
     char* sws = nullptr;      // source profile (teuk_set_source): [integer, half][nth][pitch] complex128
     bool coef_set = false;
@@ -296,8 +304,8 @@ bool fused_adjoint_ok(const teuk_grid* g) {
 }
 
 void update_fusion(teuk_grid* g) {
-    for (int k = 1; k <= kMaxPassSteps; ++k)
-        g->fused[k - 1] = fused_extraction_ok(g, strip_cols(k), g->pass_rows[k - 1], true);
+    for (int i = 0; i < kPassKinds; ++i)
+        g->fused[i] = fused_extraction_ok(g, strip_cols(std::min(i + 1, kMaxPassSteps)), g->pass_rows[i], true);
 }
 
 // Two states (a pass's input and output) up to this size stay in the
@@ -344,12 +352,13 @@ StepArgs step_args(const teuk_grid* g) {
 // Launch arguments of a pass of `steps` steps.  XCD runs of strips where each
 // XCD gets at least 8 (measured: 0.6-0.8 % faster on 25600 x 512 at 32-64 row
 // tiles, neutral on 6400 x 256).
-StepArgs pass_args(const teuk_grid* g, int steps) {
+StepArgs pass_args(const teuk_grid* g, int steps, bool source) {
+    const int kind = pass_kind(steps, source);
     StepArgs a = step_args(g);
     a.k.n_strips = (a.k.nr + strip_cols(steps) - 1) / strip_cols(steps);
-    a.k.rows = g->pass_rows[steps - 1];
+    a.k.rows = g->pass_rows[kind];
     a.k.n_chunks = (a.k.nth + a.k.rows - 1) / a.k.rows;
-    a.k.n_ext = g->fused[steps - 1] ? g->p.n_extract : 0;
+    a.k.n_ext = g->fused[kind] ? g->p.n_extract : 0;
     a.k.order = steps > 1 && a.k.n_strips >= 64 ? kTileOrderXcdStrip : kTileOrderDispatch;
     return a;
 }
@@ -399,7 +408,7 @@ void default_tile(int nr, int nth, int cus, int* rows, int* wpb) {
 // and first rows) worth about three rows, or two where wavefronts overlap in
 // it.  Two wavefronts fit a SIMD, where
 // they share its issue: a row takes two units of time beside another wavefront
-// and `alone` units without.  Tiles beyond one round of wavefronts wait for a
+// and `alone` units without; waves = 1 for a kernel of which one fits.  Tiles beyond one round of wavefronts wait for a
 // slot; with several rounds the last, partly filled one counts for less.  The
 // height with the lowest such time is taken, at most 128 rows.  Measured (us
 // per step): three-step pass (G = 4), 6400 x 256 at 15 / 17 / 29 rows 13.3 /
@@ -410,7 +419,7 @@ void default_tile(int nr, int nth, int cus, int* rows, int* wpb) {
 // rows 17.0 / 17.6 / 16.4, 1200 x 100 at 1 / 2 / 3 rows 10.2 / 11.5 / 11.3.
 // Two-step adjoint (G = 2), 6400 x 256 at 14 / 15 /
 // 29 rows 15.0 / 16.5 / 22.4, 3200 x 128 at 4 / 5 / 8 rows 8.1 / 9.1 / 9.5.
-int sweep_rows(int nr, int nth, int cus, int K, int G, double alone, double* us = nullptr) {
+int sweep_rows(int nr, int nth, int cus, int K, int G, double alone, double* us = nullptr, int waves = 2) {
     const int64_t strips = (nr + strip_cols(K) - 1) / strip_cols(K);
     double best = 0.0;
     int rows = 1;
@@ -418,13 +427,16 @@ int sweep_rows(int nr, int nth, int cus, int K, int G, double alone, double* us 
         const double x = (double)(strips * ((nth + r - 1) / r)) / (4.0 * cus);  // tiles per SIMD
         const int its = K + (r + K + G - 1) / G * G;
         double f = alone, rounds = 1.0;
-        if (x > 1.0) {
+        if (x > 1.0 && waves == 1) {
+            rounds = std::ceil(x);
+            f = alone * (x + (rounds - x) / std::max(1.0, rounds - 1.0));
+        } else if (x > 1.0) {
             rounds = std::ceil(0.5 * x);
             const double over = x - 2.0 * (rounds - 1.0);
             const double whole = 2.0 * (rounds - 1.0) + (over > 1.0 ? 2.0 : alone);
             f = x + (whole - x) / std::max(1.0, rounds - 1.0);
         }
-        const double t = (x > 1.0 ? 2.0 : 3.0) * rounds + its * f;
+        const double t = (x > 1.0 && waves > 1 ? 2.0 : 3.0) * rounds + its * f;
         // equal times: fewer tiles where two share a SIMD, else shorter ones
         if (r == 1 || t < best || (t == best && x > 1.0)) {
             best = t;
@@ -627,13 +639,16 @@ int teuk_init_grid(const teuk_params* p, void* hip_stream, void* d_workspace, si
         // Each pass on a tile of its own: the strips of a pass of k steps are
         // 64 - 2 k columns, and the rows that fill the chip once differ.  With
         // the one-step pass's rows for all, source runs of 6400 x 256 (steps in
-        // pairs) took 18.8 us a step, with their own 16.8.
+        // pairs) took 18.8 us a step, with their own 16.8; three steps a pass
+        // with the rows of the pass without a source 18.7, with their own 15.4.
         // (four wavefronts a workgroup, or one, to spread few tiles over the CUs)
-        for (int k = 1; k <= kMaxPassSteps; ++k) {
-            const int r = sweep_rows(nr, nth, cus, k, k + 1, 1.3, &sweep_us);
+        for (int i = 0; i < kPassKinds; ++i) {
+            const int k = std::min(i + 1, kMaxPassSteps);
+            const int r = i < kMaxPassSteps ? sweep_rows(nr, nth, cus, k, k + 1, 1.3, &sweep_us)
+                                            : sweep_rows(nr, nth, cus, k, k + 1, 1.3, nullptr, 1);
             const int64_t tiles = (int64_t)((nr + strip_cols(k) - 1) / strip_cols(k)) * ((nth + r - 1) / r);
-            g->pass_rows[k - 1] = g->default_rows[k - 1] = r;
-            g->pass_wpb[k - 1] = g->default_wpb[k - 1] = tiles < cus * 4 ? 1 : 4;
+            g->pass_rows[i] = g->default_rows[i] = r;
+            g->pass_wpb[i] = g->default_wpb[i] = tiles < cus * 4 ? 1 : 4;
         }
     }
     // The block pass: one thread per point of (columns x all rows).  Default
@@ -798,7 +813,7 @@ int step_n_impl(teuk_grid* g, int64_t n, void* d_series, void* d_window, const d
     StepArgs args[kMaxPassSteps];
     for (int m = 1; m <= kMaxPassSteps; ++m) {
         StepArgs& a = args[m - 1];
-        a = pass_args(g, m);
+        a = pass_args(g, m, h_f != nullptr);
         if (h_f) {
             a.src_i = reinterpret_cast<const double2*>(g->sws);
             a.src_h = reinterpret_cast<const double2*>(g->sws + source_plane_bytes(g));
@@ -823,14 +838,14 @@ int step_n_impl(teuk_grid* g, int64_t n, void* d_series, void* d_window, const d
         in = out;
     };
     // Steps run several to a pass: three where the pass has a kernel for it
-    // (Kerr coefficients, no source, no window, three rows or more) and no
+    // (Kerr coefficients, no window, three rows or more) and no
     // check falls between them, two otherwise.  A call's last
     // four steps run as two and two rather than three and one, and the first
     // step of a window run, which also copies its input, runs alone.
     const bool multi = g->steps_per_pass == 2;
     const bool fuse2 = multi && (!series || g->fused[1]);
-    const bool fuse3 = fuse2 && kerr && !h_f && !win && g->p.ntheta >= 3 && g->check_every == 0 &&
-                       (!series || g->fused[2]);
+    const bool fuse3 = fuse2 && kerr && !win && g->p.ntheta >= 3 && g->check_every == 0 &&
+                       (!series || g->fused[pass_kind(3, h_f != nullptr)]);
     auto pass_steps = [&](int64_t k) -> int {
         const int64_t left = n - k;
         if (win && k == 0) return 1;
@@ -907,7 +922,7 @@ int step_n_impl(teuk_grid* g, int64_t n, void* d_series, void* d_window, const d
         a.series_mid = sample ? series + k * ne : nullptr;
         if (h_f)
             for (int j = 0; j < 4 * m; ++j) a.k.sf[j] = g->p.dt * h_f[4 * k + j];
-        HIP_TRY(launch_pass(a, m, kerr, std::min(g->pass_wpb[m - 1], 4), g->stream));
+        HIP_TRY(launch_pass(a, m, kerr, std::min(g->pass_wpb[pass_kind(m, h_f != nullptr)], 4), g->stream));
         if (sample) sampled = k + m - 1;
         advance(out);
         k += m;
@@ -1097,7 +1112,7 @@ void select_launch(teuk_grid* g, bool off) {
     const bool tile = g->rows == g->default_tile[0] && g->wpb == g->default_tile[1];
     const bool block = g->block_steps == g->default_block[0] && g->block_cols == g->default_block[1];
     g->default_launch = tile && block && !off;
-    for (int k = 0; k < kMaxPassSteps; ++k) {
+    for (int k = 0; k < kPassKinds; ++k) {
         g->pass_rows[k] = tile ? g->default_rows[k] : g->rows;
         g->pass_wpb[k] = tile ? g->default_wpb[k] : g->wpb;
     }

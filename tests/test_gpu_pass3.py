@@ -65,3 +65,43 @@ def test_three_step_pass(gpu, a, s, m, nr, nth, n, rows, waves):
     ref = o.evolve(p, q, n, w["er"], w["et"])
     for k in range(3):
         assert np.abs(three[k] - ref[k]).max() <= TOL * np.abs(ref[k]).max(), k
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("a,s,m,nr,nth,n,rows,waves", [CASES[0], CASES[2], CASES[4], CASES[6], CASES[7], CASES[8]])
+def test_three_step_pass_with_source(gpu, a, s, m, nr, nth, n, rows, waves):
+    """The same with a source term: bit for bit the single steps, on the given
+    tile and on the default one; the oracle's within the bar."""
+    import oracle
+    import torch
+
+    rng = np.random.default_rng(nr)
+    dr, dth = 200.0 / (nr - 1), math.pi / nth
+    er, et = [-60.0 + min(57.5, nr - 1.5) * dr], [(min(rows, nth - 1) + 0.1) * dth]
+    dt = inputs.stable_dt(dr, nth, m, s, 1000)
+    u = inputs.random_state(nr, nth, seed=nr + nth)
+    gi, gh = (rng.standard_normal((nth, c)) + 1j * rng.standard_normal((nth, c)) for c in (nr, nr - 1))
+    f = rng.standard_normal((n, 2)) + 1j * rng.standard_normal((n, 2))
+
+    def run(spp, tile):
+        g = gpu.TeukGrid(a, s, m, nr, nth, -60.0, 140.0, dt, extract_rstar=er, extract_theta=et)
+        if tile:
+            g.set_tile(min(rows, nth), waves)
+        g.set_steps_per_pass(spp)
+        g.set_source(torch.from_numpy(gi).cuda(), torch.from_numpy(gh).cuda())
+        g.set_initial_data(*(torch.from_numpy(x).cuda() for x in u))
+        series = g.step_source(f)
+        out = [t.cpu().numpy() for t in g.state()] + [series.cpu().numpy()]
+        g.close()
+        return out
+
+    one = run(1, True)
+    o = oracle.OracleGrid(a, s, m, nr, nth, -60.0, 140.0, dt)
+    o.set_source(gi, gh)
+    p, q = o.project(*u)
+    ref = o.evolve_source(p, q, f, er, et)
+    for tile in (True, False):
+        three = run(2, tile)
+        for k in range(3):
+            assert np.array_equal(three[k], one[k]), (tile, k)
+            assert np.abs(three[k] - ref[k]).max() <= TOL * np.abs(ref[k]).max(), (tile, k)
