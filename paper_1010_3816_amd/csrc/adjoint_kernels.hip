@@ -56,8 +56,8 @@ struct AdjRow {
     double bh;    // b at the half point
 };
 
-// LDS of a wavefront for the points of a row: two steps' weights per lane and gradients.
-constexpr int kHitDoubles = 2 * kRowHits * (kWave + 2);
+// LDS of a wavefront for the points of a row: two steps' weights and gradients per lane.
+constexpr int kHitDoubles = 2 * kRowHits * 3 * kWave;
 
 // What the adjoint's sweeps accumulate beside the cotangents: nothing, the
 // dot products with stored tangents, or the spin gradient from the states.
@@ -132,15 +132,15 @@ __device__ __forceinline__ double adjoint_sweep(const double2* __restrict__ nu_i
     // Transposed extraction of the sample of step j's output state: each
     // stencil point of an extraction point receives its bilinear weight times
     // the sample's gradient (gs, re/im interleaved).  The weights and
-    // gradients of the rows an iteration completes go to the wavefront's LDS
-    // beforehand (zeros where there are none), so that the row itself takes
-    // no branch; the host sees to it that a row of a tile has at most
-    // kRowHits points.
+    // gradients of the rows an iteration completes go to the lane's slots in
+    // the wavefront's LDS beforehand (zeros where there are none), so that the
+    // row itself takes no branch; the host sees to it that at most kRowHits
+    // points touch a grid point.
     lds_t hit_w = (lds_t)hits + lane;
-    cd_lds_t hit_g = (cd_lds_t)((lds_t)hits + K * kRowHits * kWave);
+    cd_lds_t hit_g = (cd_lds_t)((lds_t)hits + K * kRowHits * kWave) + lane;
     auto put_hit = [&](int slot, double w, double re, double im) {
         hit_w[slot * kWave] = w;
-        hit_g[slot] = v2d{re, im};
+        hit_g[slot * kWave] = v2d{re, im};
     };
     bool hit_set = true;  // slots to be cleared
     auto set_hits = [&](int r) {
@@ -157,11 +157,12 @@ __device__ __forceinline__ double adjoint_sweep(const double2* __restrict__ nu_i
             for (int e = 0; e < A.n_ext; ++e) {
                 if (!((emask >> e) & 1u)) continue;
                 const ExtPoint E = ext[e];
-                if ((t != E.rowa && t != E.rowb) || h >= kRowHits) continue;  // wavefront-uniform
-                const double wrow = (t == E.rowa) ? E.wa : E.wb;
-                const double w = (col == E.col) ? wrow * (1.0 - E.wr) : (col == E.col + 1) ? wrow * E.wr : 0.0;
-                put_hit(j * kRowHits + h, w, gs[j][2 * e], gs[j][2 * e + 1]);
+                if (t != E.rowa && t != E.rowb) continue;  // wavefront-uniform
                 hit_set = true;
+                if ((col != E.col && col != E.col + 1) || h >= kRowHits) continue;
+                const double wrow = (t == E.rowa) ? E.wa : E.wb;
+                const double w = (col == E.col) ? wrow * (1.0 - E.wr) : wrow * E.wr;
+                put_hit(j * kRowHits + h, w, gs[j][2 * e], gs[j][2 * e + 1]);
                 ++h;
             }
         }
@@ -297,7 +298,7 @@ __device__ __forceinline__ double adjoint_sweep(const double2* __restrict__ nu_i
 #pragma unroll
                 for (int h = 0; h < kRowHits; ++h) {
                     const double w = hit_w[(j * kRowHits + h) * kWave];
-                    const v2d g = hit_g[j * kRowHits + h];
+                    const v2d g = hit_g[(j * kRowHits + h) * kWave];
                     op.re = fma(w, g.x, op.re);
                     op.im = fma(w, g.y, op.im);
                 }

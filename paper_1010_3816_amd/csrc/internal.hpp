@@ -239,7 +239,7 @@ hipError_t launch_nonfinite_step(const double2* u, int nr, int nth, int pitch, l
 // read); with the spin gradient recomputed from u^m = u_in; with the spin
 // gradient as the dot product of nu with T_m = u_in, the stored tangent.
 enum class AdjMode { kCotangent, kSpin, kTangentDot };
-// Their fused transposed extraction takes at most kRowHits points on a row of a tile.
+// Their fused transposed extraction takes at most kRowHits points at a grid point.
 constexpr int kRowHits = 3;
 hipError_t launch_adjoint(const AdjArgs& a, int waves_per_block, AdjMode mode, hipStream_t s);
 // Two cotangent adjoint steps: nu_in = lambda^{m+2} -> lam_out = lambda^m

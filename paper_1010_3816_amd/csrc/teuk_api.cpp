@@ -287,8 +287,8 @@ bool fused_extraction_ok(const teuk_grid* g, int strip_cols, int rows, bool equa
     return true;
 }
 
-// The adjoint passes take up to kRowHits points on a row of a tile (of 64
-// columns): no point may share a row with more within that distance.
+// The adjoint passes take up to kRowHits points whose stencils touch a grid
+// point: no point may share a row with more at its column or a neighbouring one.
 bool fused_adjoint_ok(const teuk_grid* g) {
     const auto& E = g->ext;
     if ((int)E.size() > kMaxFusedAdjointExtract) return false;
@@ -296,7 +296,7 @@ bool fused_adjoint_ok(const teuk_grid* g) {
         int near = 0;
         for (const ExtPoint& b : E) {
             const bool row = a.rowa == b.rowa || a.rowa == b.rowb || (a.rowb >= 0 && (a.rowb == b.rowa || a.rowb == b.rowb));
-            if (row && std::abs(a.col - b.col) <= kWave) ++near;
+            if (row && std::abs(a.col - b.col) <= 1) ++near;
         }
         if (near > kRowHits) return false;
     }
