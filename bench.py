@@ -7,21 +7,21 @@ arXiv:1010.3816 with the boundary updates) of the whole grid, launched
 through the C ABI (teuk_step_n).  The default workload is the 25600 x 512
 Kerr a = 0.99 grid (13.1 M points, 419 MB per state copy): it does not fit
 in the 256 MB Infinity Cache, so HBM traffic is real.  The state is resident
-in HBM before the timed region starts.  The library advances pairs of steps
-in one pass (temporal blocking); the launch shape is autotuned first.
+in HBM before the timed region starts.  The library advances three steps in
+one pass (temporal blocking); the launch shape is autotuned first.
 
 Prints one JSON line.  `value` is grid-point updates per second (one update
 = one (r*, theta) point advanced one full step) over exactly the timed steps.
-`roofline` describes the dominant kernel, the two-step pass: it moves 64
+`roofline` describes the dominant kernel, the three-step pass: it moves 64
 algorithmic bytes per point per pass (Phi, Pi read and written once,
-complex128), i.e. 32 B per update, against HBM (`bound` "hbm", 8 TB/s), with
+complex128), i.e. 21.3 B per update, against HBM (`bound` "hbm", 8 TB/s), with
 its FP64 rate and vector-instruction issue rate beside it, and the rates of
 two plain copies (torch's and the library's own) for reference.  `repeats` are
 five more windows as long as the timed one, `sustained` a window of 2000
 steps (the device's steady state; short windows after an idle period run
 slower while the clocks come up).  `c1` and `c2` are the 400 x 32 and
 6400 x 256 workloads for all their steps with their extraction points, in
-the library's default launch (the small-grid block pass on 400 x 32);
+the library's default launch (the tile pass on 400 x 32);
 `batched` the 64-member uneven batch in one persistent launch per pass and
 its ratio to `value`; `waveform` nine modes of one problem and their sum;
 `adjoint` a waveform-loss gradient with respect to the initial data and the
@@ -29,7 +29,7 @@ spin on the 6400 x 256 grid: `ratio` = (forward + backward - plain
 forward) / plain forward by the default route (the spin derivative carried
 forward), and the checkpointed adjoint's routes beside it.  `source` is the
 inhomogeneous variant (a localised source f(t) g(r*, theta) in the Pi
-equation) on the default workload in the timed run's tile, 48 algorithmic
+equation) on the default workload in the timed run's tile, 32 algorithmic
 bytes per update, and its ratio to `value`.  `cpu_baseline` times
 the CPU oracle (test infrastructure, plain C + OpenMP) on a bounded number of
 steps of the same grid.
@@ -50,11 +50,15 @@ METRIC = "FP64 grid-point updates/s + % HBM roofline; adjoint/forward time ratio
 HBM_PEAK_GBS = 8000.0
 FP64_PEAK_TFLOPS = 78.6
 BYTES_PER_POINT_PASS = 64   # Phi, Pi read and written once per pass (complex128)
-# the inhomogeneous variant at two steps a pass: the state's 64 B and the
+STEPS_PER_LAUNCH = {1: 1, 2: 3}  # steps of a pass by teuk_set_steps_per_pass's value (2: several)
+# the inhomogeneous variant at three steps a pass: the state's 64 B and the
 # source profile's 32 B (g at the column and the half point) per point and pass
-SOURCE_BYTES_PER_UPDATE = (BYTES_PER_POINT_PASS + 32) / 2
-FLOPS_PER_UPDATE = {1: 230, 2: 192}  # FP64 flops per point and step, single-step and two-step kernels
-VALU_PER_UPDATE = {1: 217, 2: 180}   # vector ALU instructions per point and step (from the SQ counters)
+SOURCE_BYTES_PER_UPDATE = (BYTES_PER_POINT_PASS + 32) / 3
+# per point and step of a pass of 1 or 3 steps: FP64 flops of the steady row
+# loop, and vector ALU instructions of whole launches (SQ counters; halo
+# lanes and rows included)
+FLOPS_PER_UPDATE = {1: 178, 3: 131}
+VALU_PER_UPDATE = {1: 149, 3: 125}
 # vector instruction issue peak: 256 CUs x 4 SIMDs x 2.4 GHz, one wave64 instruction per 4 cycles per SIMD
 VALU_PEAK_T = 256 * 4 * 2.4e9 * 64 / 4 / 1e12
 KERNEL_SRCS = [os.path.join(ROOT, "paper_1010_3816_amd", "csrc", f)
@@ -303,7 +307,7 @@ def source_leg(name="kerr_a0.99_25600x512", steps=1000, tile=None):
     tile `tile` (rows, waves_per_block), timed with HIP events on the grid's
     stream.  Algorithmic bytes: the state's 64 B per point per pass of two
     steps and the profile's 32 B (g at the column and at the half point, read
-    once a pass), 48 B per update."""
+    once a pass), 32 B per update."""
     import torch
 
     from paper_1010_3816_amd import binding, inputs
@@ -524,25 +528,26 @@ def main():
     pts = w["nr"] * w["ntheta"]
     ms_step = ms / args.steps
     ups = pts / (ms_step * 1e-3)
-    # per launch of the dominant kernel (spp steps per launch)
-    launch_s = spp * ms_step * 1e-3
+    # per launch of the dominant kernel (spl steps per launch)
+    spl = STEPS_PER_LAUNCH[spp]
+    launch_s = spl * ms_step * 1e-3
     hbm_gbs = BYTES_PER_POINT_PASS * pts / launch_s / 1e9
-    tflops = FLOPS_PER_UPDATE[spp] * spp * pts / launch_s / 1e12
-    traffic = measured_traffic(args.workload, spp)
+    tflops = FLOPS_PER_UPDATE[spl] * spl * pts / launch_s / 1e12
+    traffic = measured_traffic(args.workload, spl)
     copy_torch = copy_bandwidth(torch)
     copy_lib = library_copy_bandwidth(torch, g, phi0, pi0)
     copy_gbs = max(copy_torch, copy_lib)
     traffic_gbs = traffic / launch_s / 1e9 if traffic else None
     rows, wpb = g.tile()
-    valu = VALU_PER_UPDATE[spp] * spp * pts / launch_s / 1e12
-    # Both passes are bound by HBM: the one-step pass streams its 64 B per
-    # update at a plain copy's rate; the two-step pass moves its measured
-    # traffic (halo rows and strip overlap on top of 32 B per update) at
-    # nearly that rate, with the vector ALUs busy about two thirds of the time.
+    valu = VALU_PER_UPDATE[spl] * spl * pts / launch_s / 1e12
+    # The one-step pass streams its 64 B per update at a plain copy's rate;
+    # the three-step pass moves its measured traffic (halo rows and strip
+    # overlap on top of 21.3 B per update) at four fifths of that rate, with
+    # the vector ALUs busy about two thirds of the time.
     roof = {"bound": "hbm", "achieved": hbm_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": hbm_gbs / HBM_PEAK_GBS, "traffic": traffic,
-            "kernel": "lw_step2_kernel" if spp == 2 else "lw_step_kernel", "steps_per_launch": spp,
-            "bytes_per_update": BYTES_PER_POINT_PASS / spp,
+            "kernel": "lw_step3_kernel" if spl == 3 else "lw_step_kernel", "steps_per_launch": spl,
+            "bytes_per_update": BYTES_PER_POINT_PASS / spl,
             # measured HBM traffic per launch over the launch time, and a plain copy's rate on this
             # device: the faster of torch's copy and the library's own import copy
             "traffic_achieved": traffic_gbs, "copy_achieved": copy_gbs,
@@ -553,9 +558,9 @@ def main():
             "one_step_bound_updates_per_s": HBM_PEAK_GBS * 1e9 / BYTES_PER_POINT_PASS,
             "value_over_one_step_bound": ups / (HBM_PEAK_GBS * 1e9 / BYTES_PER_POINT_PASS),
             "fp64": {"achieved": tflops, "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
-                     "frac": tflops / FP64_PEAK_TFLOPS, "flops_per_update": FLOPS_PER_UPDATE[spp]},
+                     "frac": tflops / FP64_PEAK_TFLOPS, "flops_per_update": FLOPS_PER_UPDATE[spl]},
             "valu_issue": {"achieved": valu, "peak": VALU_PEAK_T, "unit": "T lane-instructions/s",
-                           "frac": valu / VALU_PEAK_T, "instructions_per_update": VALU_PER_UPDATE[spp]}}
+                           "frac": valu / VALU_PEAK_T, "instructions_per_update": VALU_PER_UPDATE[spl]}}
 
     if args.calibrate:
         n = 1 << 27  # 1 GiB of float64
@@ -587,7 +592,7 @@ def main():
         "repeats": {"windows": 5, "steps_each": n_rep, "median": sorted(reps)[2], "min": min(reps), "max": max(reps)},
         "sustained": {"steps": 2000, "ms_per_step": ms_sus,
                       "value": w["nr"] * w["ntheta"] / (ms_sus * 1e-3),
-                      "roofline_frac": BYTES_PER_POINT_PASS * w["nr"] * w["ntheta"] / (spp * ms_sus * 1e-3) / 1e9
+                      "roofline_frac": BYTES_PER_POINT_PASS * w["nr"] * w["ntheta"] / (spl * ms_sus * 1e-3) / 1e9
                       / HBM_PEAK_GBS},
     }
     g.close()

@@ -482,7 +482,8 @@ int teuk_batch_set_launch(teuk_batch* b, int32_t rows_per_tile, int32_t waves_pe
 /* A batch writes its members' next states with cache-keeping stores (see
  * teuk_set_cache_policy) when all their states, two per member, take at most
  * 192 MiB; otherwise it streams them. */
-/* Steps per launch of the batch: 1 or 2 (default; see teuk_set_steps_per_pass).
+/* Steps per launch of the batch: 1, or 2 (default) for several: three, and two
+ * or one at a call's end (see teuk_set_steps_per_pass).
  * Member results do not depend on it.  Synchronises the batch's stream. */
 int teuk_batch_set_steps_per_pass(teuk_batch* b, int32_t steps_per_pass);
 int teuk_batch_get_launch(const teuk_batch* b, int32_t* rows_per_tile, int32_t* waves_per_block,

@@ -71,7 +71,7 @@ struct StepScalars {
     int32_t rows, n_strips, n_chunks, n_ext;
     int32_t zero;               // always 0 (an opaque row offset of LDS reads)
     int32_t keep;               // 1: the new state is written with ordinary stores (selects the kernel instance)
-    int32_t order;              // two-step pass: tile order (kTileOrder*)
+    int32_t order;              // passes of several steps: tile order (kTileOrder*)
     int32_t bsteps;             // block pass: steps per launch
     int32_t bcols;              // block pass: columns a workgroup holds (bsteps halo columns each side)
     int32_t pad_;

@@ -394,13 +394,12 @@ TEUK_PASS_KERNEL(lw_step3_kernel, 3)
 // per thread, and takes k steps there; each step consumes one column at each
 // edge (the stencil's radial reach), so after k steps its W middle columns
 // hold the new state, which it writes back.  Every point's coefficients are
-// built once per launch (the sweeps rebuild them every step), so a step is
+// built once per launch (the sweeps rebuild them every pass), so a step is
 // the stencil arithmetic alone, in two phases with a barrier after each:
 // stage 1 (the Pi half-step of row t needs the averages of rows t -/+ 1,
 // which each thread forms itself from the state) and stage 2.  The
-// expressions are those of
-// sweep_tile's fresh() and finish_row(), operand for operand, so the results
-// equal the sweeps' bit for bit; columns outside the grid read the clamped
+// expressions are those of the sweeps, operand for operand, so the results
+// equal theirs bit for bit; columns outside the grid read the clamped
 // edge column and, as in the sweeps, reach only the zeroed boundary columns.
 // Extraction: the samples of each step's input state, in the sweeps' order.
 // The points are read once per launch into LDS, each thread works out once

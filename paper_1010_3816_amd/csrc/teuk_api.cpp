@@ -376,7 +376,8 @@ size_t source_plane_bytes(const teuk_grid* g) { return align_up((size_t)g->p.nth
 // (0: none).
 long long* first_nonfinite(const teuk_grid* g) { return reinterpret_cast<long long*>(g->ws + g->L.off_flag + 8); }
 
-// Default tile of the two-step pass.  The device holds two of its wavefronts
+// Default tile as teuk_get_tile reports it (until teuk_set_tile, the passes
+// take their own heights), that of a two-step pass.  The device holds two of its wavefronts
 // per SIMD, so its tiles run in rounds of 8 x CUs; a last round that is only
 // partly filled leaves SIMDs idle, and a wavefront walks its tile's rows one
 // after the other, so on a grid that fits one round shorter tiles finish
