@@ -110,8 +110,9 @@ struct TanRow {
 // The state's expressions and row order are those of the forward passes, so
 // u^{m+1} equals theirs bit for bit; rows, poles and the two row loops are
 // theirs too (one step: a row is completed when the next arrives).
-// rvi, rvh, rdi, rdh: the lane's radial factors and their a-derivatives at
-// its column and half point, in LDS, read row by row.  smp: this wavefront's
+// rvi(f, z), rvh(f, z): factor f of the lane's radial factors at its column and
+// half point (z: zero, opaque to the compiler); rdi, rdh: their a-derivatives,
+// in LDS, read row by row.  smp: this wavefront's
 // sample slots.  T_m is streamed; the next states follow KEEP.
 //
 // What bounds it: 328 vector instructions per point and step with v (498
@@ -119,15 +120,18 @@ struct TanRow {
 // its 52 LDS reads a row and for memory (210 MB a step on 6400 x 256, 25 us at
 // the rate of a copy within the last-level cache).  Stage 1 is finished, and
 // the previous row completed and stored, before the column's coefficients are
-// read: 200 registers instead of 240 with v, 162 instead of 218 without, so the
-// default instruction schedule, which has more loads in flight than one for
-// occupancy, does not spill.  us per step, before and now: 6400 x 256 48.6 ->
-// 38.7 with v, 35.8 -> 33.4 without; 3200 x 128 19.4 -> 16.4, 13.7 -> 15.1.
+// read: 200 registers instead of 240 with v, so the default instruction
+// schedule, which has more loads in flight than one for occupancy, does not
+// spill.  Without v the factors themselves are in registers (214) and their
+// derivatives in the wavefront's own slice, which no other wavefront waits for.
+// us per step, before and now: 6400 x 256 48.6 -> 38.7 with v, 38.8 -> 33.5
+// without; 3200 x 128 19.4 -> 16.4, 14.3 -> 12.1 (15.1 from the workgroup's
+// tables in LDS); 1200 x 100 without v 9.8 -> 8.9 (9.7).
 // Three wavefronts per SIMD (168 registers) spill with v and take 51-60 us.
-template <bool V, int KEEP>
+template <bool V, int KEEP, class RadI, class RadH>
 __device__ __forceinline__ void tangent_sweep(gin_t u_in, gin_t v_in, gout_t u_out, gout_t v_out, ctab_t ang,
                                               const ExtPoint* __restrict__ ext, double2* __restrict__ series_u,
-                                              double2* __restrict__ series_v, lds_cptr rvi, lds_cptr rvh, lds_cptr rdi,
+                                              double2* __restrict__ series_v, RadI rvi, RadH rvh, lds_cptr rdi,
                                               lds_cptr rdh, __attribute__((address_space(3))) v2d* smp,
                                               const AdjScalars& A, int strip, int chunk, int lane) {
     constexpr int kN = V ? 4 : 2;  // planes read
@@ -195,7 +199,7 @@ __device__ __forceinline__ void tangent_sweep(gin_t u_in, gin_t v_in, gout_t u_o
         // the column's: both sets at once need more registers
         Stage kh, dh;
         {
-            const SRad R = srad_of([&](int f) { return rvh[z + f * kWave]; });
+            const SRad R = srad_of([&](int f) { return rvh(f, z); });
             const Sig sig = ssigma(R, G);
             kh = stage_coef(R, G, sig, A.kap_h);
             const SRad D = srad_of([&](int f) { return rdh[z + f * kWave]; });
@@ -279,7 +283,7 @@ __device__ __forceinline__ void tangent_sweep(gin_t u_in, gin_t v_in, gout_t u_o
         __builtin_amdgcn_sched_barrier(0);
         Stage ki, di;
         {
-            const SRad R = srad_of([&](int f) { return rvi[z + f * kWave]; });
+            const SRad R = srad_of([&](int f) { return rvi(f, z); });
             const Sig sig = ssigma(R, G);
             ki = stage_coef(R, G, sig, A.kap_i);
             const SRad D = srad_of([&](int f) { return rdi[z + f * kWave]; });
@@ -370,16 +374,42 @@ __device__ __forceinline__ void tangent_tile(const double2* u_in, const double2*
     const int lane = threadIdx.x & (kWave - 1);
     const int wpb = blockDim.x / kWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    typedef __attribute__((address_space(3))) v2d* slots_t;
     const TileOf T = tile_of(xcd_block(blockIdx.x, gridDim.x), wpb, wave, A.n_strips, A.n_chunks);
-    fill_tables<1, 2>(T, rad, rad_da, rad_s, A.nr, A.pitch, wave, wpb, lane);
-    if (!T.valid) return;  // wavefront-uniform
-    constexpr int kF = 4 * kNumSRad;
-    const double* slice = rad_s + T.slice * kF * kWave + lane;
-    const double* slots = rad_s + T.n_slices * kF * kWave + wave * 2 * kTanSlots;
-    tangent_sweep<V, KEEP>((gin_t)u_in, (gin_t)v_in, (gout_t)u_out, (gout_t)v_out, (ctab_t)ang, ext, series_u,
-                           series_v, (lds_cptr)slice, (lds_cptr)(slice + kNumSRad * kWave),
-                           (lds_cptr)(slice + 2 * kNumSRad * kWave), (lds_cptr)(slice + 3 * kNumSRad * kWave),
-                           (__attribute__((address_space(3))) v2d*)slots, A, T.strip, T.chunk, lane);
+    if constexpr (V) {
+        fill_tables<1, 2>(T, rad, rad_da, rad_s, A.nr, A.pitch, wave, wpb, lane);
+        if (!T.valid) return;  // wavefront-uniform
+        constexpr int kF = 4 * kNumSRad;
+        const double* slice = rad_s + T.slice * kF * kWave + lane;
+        const double* slots = rad_s + T.n_slices * kF * kWave + wave * 2 * kTanSlots;
+        const lds_cptr ri = (lds_cptr)slice, rh = (lds_cptr)(slice + kNumSRad * kWave);
+        tangent_sweep<V, KEEP>((gin_t)u_in, (gin_t)v_in, (gout_t)u_out, (gout_t)v_out, (ctab_t)ang, ext, series_u,
+                               series_v, [&](int f, int z) { return ri[z + f * kWave]; },
+                               [&](int f, int z) { return rh[z + f * kWave]; },
+                               (lds_cptr)(slice + 2 * kNumSRad * kWave), (lds_cptr)(slice + 3 * kNumSRad * kWave),
+                               (slots_t)slots, A, T.strip, T.chunk, lane);
+    } else {
+        // without v the lane's own factors fit its registers, and their
+        // derivatives its wavefront's own slice: no wait for the workgroup
+        if (!T.valid) return;  // wavefront-uniform
+        double* slice = rad_s + wave * 2 * kNumSRad * kWave + lane;
+        const int c = min(max(T.strip * kStripCols - 1 + lane, 0), A.nr - 1), ch = min(c, A.nr - 2);
+        double ri[kNumSRad], rh[kNumSRad], d[2 * kNumSRad];
+#pragma unroll
+        for (int f = 0; f < kNumSRad; ++f) {
+            const size_t o = (size_t)f * 2 * A.pitch;
+            ri[f] = rad[o + c];
+            rh[f] = rad[o + A.pitch + ch];
+            d[f] = rad_da[o + c];
+            d[kNumSRad + f] = rad_da[o + A.pitch + ch];
+        }
+#pragma unroll
+        for (int f = 0; f < 2 * kNumSRad; ++f) slice[f * kWave] = d[f];
+        tangent_sweep<V, KEEP>((gin_t)u_in, (gin_t)v_in, (gout_t)u_out, (gout_t)v_out, (ctab_t)ang, ext, series_u,
+                               series_v, [&](int f, int) { return ri[f]; }, [&](int f, int) { return rh[f]; },
+                               (lds_cptr)slice, (lds_cptr)(slice + kNumSRad * kWave), (slots_t)rad_s, A, T.strip,
+                               T.chunk, lane);
+    }
 }
 
 }  // namespace

@@ -695,7 +695,7 @@ hipError_t launch_tangent(const double2* u_in, double2* u_out, double2* t_out, c
                           hipStream_t s) {
     dim3 grid, block;
     size_t lds;
-    adjoint_launch_shape(a.k, waves_per_block, 4 * kNumSRad, &grid, &block, &lds, kTanSlots * sizeof(double2));
+    adjoint_launch_shape(a.k, waves_per_block, 0, &grid, &block, &lds, 2 * kNumSRad * kWave * sizeof(double));
     hipLaunchKernelGGL(a.k.keep ? lw_tangent_kernel<1> : lw_tangent_kernel<0>, grid, block, lds, s, u_in, u_out, t_out,
                        a.rad, a.rad_da, a.ang, a.k);
     return hipGetLastError();
