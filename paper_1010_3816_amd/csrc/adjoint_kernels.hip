@@ -56,8 +56,11 @@ struct AdjRow {
     double bh;    // b at the half point
 };
 
-// LDS of a wavefront for the points of a row: two steps' weights and gradients per lane.
-constexpr int kHitDoubles = 2 * kRowHits * 3 * kWave;
+// LDS of a wavefront for the points of a row: each step's weights and gradients
+// per lane.  No more than that: with two steps' slots the one-step kernel's
+// workgroups that span two strips came to 90 KB, one to a CU (5003 x 197 45 us
+// a step against 37).
+constexpr int hit_doubles(int steps) { return steps * kRowHits * 3 * kWave; }
 
 // What the adjoint's sweeps accumulate beside the cotangents: nothing, the
 // dot products with stored tangents, or the spin gradient from the states.
@@ -143,12 +146,18 @@ __device__ __forceinline__ double adjoint_sweep(const double2* __restrict__ nu_i
         hit_g[slot * kWave] = v2d{re, im};
     };
     bool hit_set = true;  // slots to be cleared
+    int e_lo = nth, e_hi = -1;  // rows that the tile's points touch
+    for (unsigned m = emask; m != 0; m &= m - 1) {
+        const ExtPoint E = ext[__builtin_ctz(m)];
+        e_lo = min(e_lo, E.rowb >= 0 ? min(E.rowa, E.rowb) : E.rowa);
+        e_hi = max(e_hi, max(E.rowa, E.rowb));
+    }
     auto set_hits = [&](int r) {
         if (hit_set) {
             for (int k = 0; k < K * kRowHits; ++k) put_hit(k, 0.0, 0.0, 0.0);
             hit_set = false;
         }
-        if (emask == 0) return;
+        if (r - 1 < e_lo || r - K > e_hi) return;
 #pragma unroll
         for (int j = 0; j < K; ++j) {
             if (gs[j] == nullptr) continue;
@@ -366,7 +375,7 @@ __device__ __forceinline__ void adjoint_tile(const double2* __restrict__ nu_in, 
                                             (lds_cptr)(slice + kNumSRad * kWave), (lds_cptr)da,
                                             (lds_cptr)(da + kNumSRad * kWave),
                                             (lds_t)(rad_s + T.n_slices * kTables * 2 * kNumSRad * kWave +
-                                                    wave * kHitDoubles),
+                                                    wave * hit_doubles(K)),
                                             A, T.strip, T.chunk, lane);
     if constexpr (SP != kNone) {
         for (int off = kWave / 2; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, kWave);
@@ -637,7 +646,7 @@ hipError_t launch_adjoint(const AdjArgs& a, int waves_per_block, AdjMode mode, h
     dim3 grid, block;
     size_t lds;
     const bool spin = mode == AdjMode::kSpin;
-    adjoint_launch_shape(a.k, waves_per_block, (spin ? 4 : 2) * kNumSRad, &grid, &block, &lds, kHitDoubles * sizeof(double));
+    adjoint_launch_shape(a.k, waves_per_block, (spin ? 4 : 2) * kNumSRad, &grid, &block, &lds, hit_doubles(1) * sizeof(double));
     const bool keep = a.k.keep != 0;
     auto pick = [&](auto k0, auto k1) { return keep ? k1 : k0; };
     auto kern = spin ? pick(lw_adjoint_kernel<true, false, 0>, lw_adjoint_kernel<true, false, 1>)
@@ -654,7 +663,7 @@ hipError_t launch_adjoint2(const AdjArgs& a, const double* gsample_b, const doub
                            hipStream_t s) {
     dim3 grid, block;
     size_t lds;
-    adjoint_launch_shape(a.k, waves_per_block, 2 * kNumSRad, &grid, &block, &lds, kHitDoubles * sizeof(double));
+    adjoint_launch_shape(a.k, waves_per_block, 2 * kNumSRad, &grid, &block, &lds, hit_doubles(2) * sizeof(double));
     const bool keep = a.k.keep != 0;
     auto kern = a.u_in ? (keep ? lw_adjoint2_kernel<true, 1> : lw_adjoint2_kernel<true, 0>)
                        : (keep ? lw_adjoint2_kernel<false, 1> : lw_adjoint2_kernel<false, 0>);
