@@ -686,7 +686,11 @@ int teuk_init_grid(const teuk_params* p, void* hip_stream, void* d_workspace, si
     // a device holds two adjoint wavefronts per SIMD (8 per CU).  The
     // one-step kernels leave one slot in eight to a recompute that runs
     // beside them.
+    // (tiles of one row only where there is one to a SIMD: 1600 x 64 11.9 us a
+    // step with the spin gradient from states, 10.5 with two rows; 400 x 32 9.0
+    // and 10.3)
     g->adj_rows = adjoint_rows(nr, nth, (int64_t)cus * 7, kStripCols);
+    if (g->adj_rows == 1 && (int64_t)((nr + kStripCols - 1) / kStripCols) * nth > 4 * cus) g->adj_rows = std::min<int>(2, nth);
     g->adj_chunks = (nth + g->adj_rows - 1) / g->adj_rows;
     g->adj2_rows = sweep_rows(nr, nth, cus, 2, 2, 1.8, &sweep_us);
     // (the adjoint tile pass: 1.17 times the forward one's instructions)
