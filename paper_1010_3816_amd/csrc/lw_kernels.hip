@@ -76,10 +76,12 @@ struct RowCoef {
 // at each edge of the wavefront and one row at each end of the tile.
 //
 // A row's coefficients are the same for all steps and are built once, when
-// its input row arrives (from the lane's radial factors in the wavefront's
-// LDS slice rs, [column/half][field][lane], and the angular row, scalar),
+// its input row arrives (from the lane's radial factors, in the wavefront's
+// LDS slice rs, [column/half][field][lane], or for K = 1 in its registers, and
+// the angular row, scalar),
 // and kept in registers until the last step has passed it: a ring of K + 1
-// rows.  The row loop is unrolled over the ring, so nothing is copied.
+// rows (K + 2 of user coefficients, which come a row ahead).  The row loop is
+// unrolled over the ring, so nothing is copied.
 //
 // Poles: the ghost rows are sigma times the first and last row, in the input
 // and in the stage-1 values alike, so at row 0 the difference to the
@@ -99,7 +101,12 @@ __device__ __forceinline__ void sweep(gin_t __restrict__ u_in, gout_t __restrict
                                       double2* series2, gout_t __restrict__ win, lds_t rs,
                                       const StepScalars& A, int strip, int chunk, int lane,
                                       gin_t __restrict__ src_i, gin_t __restrict__ src_h) {
-    constexpr int kRing = K + 1;               // coefficient rows held
+    // User coefficients, which come from memory, are loaded a row ahead where
+    // the registers allow it: in a short tile nothing else covers their latency
+    // (us per step: 400 x 32 3.8 and 3.5; with a source in single steps 1600 x
+    // 128 17.3 and 13.8).
+    constexpr bool kFetch = !KERR && !(K == 2 && SRC);
+    constexpr int kRing = kFetch ? K + 2 : K + 1;  // coefficient rows held
     constexpr int kAhead = (K == 3) ? 2 : kRing;  // input rows in flight (divides the unrolled rows)
     constexpr int kCols = strip_cols(K);
     const int nr = A.nr, nth = A.nth, P = A.pitch;
@@ -132,9 +139,12 @@ __device__ __forceinline__ void sweep(gin_t __restrict__ u_in, gout_t __restrict
         st_row<decltype(keep)::value>(row_rsrc(b + A.plane, bytes), st_off, vq);
     };
 
-    // the radial factors of this lane's column and half point, loaded
-    // with the first rows (so that the latencies overlap) and then written to the wavefront's slice
-    // (lane-private: written and read by the same lane, no barrier)
+    // The radial factors of this lane's column and half point, loaded with
+    // the first rows so that the latencies overlap.  Passes of several steps
+    // write them to the wavefront's slice (lane-private: written and read by
+    // the same lane, no barrier); one step leaves them in its registers, where
+    // a row does not wait for LDS (us per step from LDS and from registers:
+    // 1200 x 100 7.6 and 6.9, 3200 x 128 9.8 and 8.1, 6400 x 256 21.2 and 19.2).
     double tv[2 * kNumSRad];
     if constexpr (KERR) {
 #pragma unroll
@@ -146,7 +156,7 @@ __device__ __forceinline__ void sweep(gin_t __restrict__ u_in, gout_t __restrict
     cd bp[kAhead], bq[kAhead];
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) load_row(rs0 + u, bp[u], bq[u]);
-    if constexpr (KERR) {
+    if constexpr (KERR && K > 1) {
 #pragma unroll
         for (int f = 0; f < 2 * kNumSRad; ++f) rs[f * kWave + lane] = tv[f];
     }
@@ -160,9 +170,9 @@ __device__ __forceinline__ void sweep(gin_t __restrict__ u_in, gout_t __restrict
     auto coefs = [&](int t, const Ang& G, RowCoef& c) {
         if constexpr (KERR) {
             const __attribute__((address_space(3))) double* r = rs + lane + (t & A.zero);
-            const SRad Ri = srad_of([&](int f) { return r[f * kWave]; });
+            const SRad Ri = srad_of([&](int f) { return K == 1 ? tv[f] : r[f * kWave]; });
             c.i = stage_coef(Ri, G, ssigma(Ri, G), A.kap_i);
-            const SRad Rh = srad_of([&](int f) { return r[(kNumSRad + f) * kWave]; });
+            const SRad Rh = srad_of([&](int f) { return K == 1 ? tv[kNumSRad + f] : r[(kNumSRad + f) * kWave]; });
             c.h = stage_coef(Rh, G, ssigma(Rh, G), A.kap_h);
         } else {
             const int tc = min(t, nth - 1);
@@ -213,6 +223,7 @@ __device__ __forceinline__ void sweep(gin_t __restrict__ u_in, gout_t __restrict
         gh[slot] = ld_row(row_rsrc(src_h + o, row_bytes), half_off);
     };
     if constexpr (SRC) load_source(rs0, 0);
+    if constexpr (kFetch) coefs(rs0, g_next, C[0]);
 
     // Iteration r.  PH: the ring slot of row r's coefficients; STEPS: the
     // steps that take a row (fewer while a tile starts); CHECK: the row may
@@ -221,7 +232,10 @@ __device__ __forceinline__ void sweep(gin_t __restrict__ u_in, gout_t __restrict
         constexpr int PH = decltype(ph)::value, STEPS = decltype(steps)::value;
         constexpr bool CHECK = decltype(check)::value != 0, FIRST = decltype(check)::value == 2;
         const Ang G = g_next;
-        coefs(r, G, C[PH]);
+        if constexpr (kFetch)
+            coefs(r + 1, G, C[(PH + 1) % kRing]);
+        else
+            coefs(r, G, C[PH]);
         if constexpr (SRC) load_source(r + 1, (PH + 1) % kRing);
         if constexpr (CHECK) __builtin_amdgcn_sched_barrier(0);
         cd p = rp, q = rq;
@@ -314,7 +328,27 @@ __device__ __forceinline__ void sweep(gin_t __restrict__ u_in, gout_t __restrict
         }
     };
     while (r + kRing - 1 <= rM) rows(rows, Const<0>{}, Const<0>{});
-    while (r <= rE) rows(rows, Const<0>{}, Const<1>{});
+    // The last rows: one by one after the last whole group where a pass takes
+    // one or two steps, whose tiles are often as short as one row (store runs,
+    // us per step in groups and one by one: 1600 x 64 5.0 and 4.1, 3200 x 128 7.3
+    // and 6.9).  In whole groups (rows past rE are dropped) where the registers
+    // leave no room for more code: three steps (36 spilled), and two with user
+    // coefficients and a source (6400 x 256 54 and 63 us).
+    if constexpr (K == kMaxPassSteps || (K == 2 && SRC && !KERR)) {
+        while (r <= rE) rows(rows, Const<0>{}, Const<1>{});
+    } else {
+        while (r + kRing - 1 <= rE) rows(rows, Const<0>{}, Const<1>{});
+        auto tail = [&](auto self, auto u) {
+            constexpr int I = decltype(u)::value + K;
+            if constexpr (I < K + kRing - 1) {
+                if (r > rE) return;
+                iteration(r, bp[I % kAhead], bq[I % kAhead], Const<I % kRing>{}, Const<K>{}, Const<1>{});
+                ++r;
+                self(self, Const<I - K + 1>{});
+            }
+        };
+        tail(tail, Const<0>{});
+    }
 
     if (e_id >= 0 && lane < K) {
         // lane j: the sample of step j's input

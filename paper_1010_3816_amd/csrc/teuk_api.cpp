@@ -403,46 +403,63 @@ void default_tile(int nr, int nth, int cus, int* rows, int* wpb) {
     *wpb = tiles < (int64_t)cus * 4 ? 1 : 4;
 }
 
-// Tile height of a K-step sweep whose row loop is unrolled by G rows.  A
-// wavefront walks its tile's rows one after the other: K rows to fill the
-// steps, then the tile's rows and K more in groups of G, after a start (tables
-// and first rows) worth about three rows, or two where wavefronts overlap in
-// it.  Two wavefronts fit a SIMD, where
-// they share its issue: a row takes two units of time beside another wavefront
-// and `alone` units without; waves = 1 for a kernel of which one fits.  Tiles beyond one round of wavefronts wait for a
-// slot; with several rounds the last, partly filled one counts for less.  The
-// height with the lowest such time is taken, at most 128 rows.  Measured (us
-// per step): three-step pass (G = 4), 6400 x 256 at 15 / 17 / 29 rows 13.3 /
-// 12.2 / 12.3, at 14 rows (a second round) 14.7; 5003 x 197 at 9 / 10 / 13
-// rows 9.6 / 10.9 / 10.1; 1600 x 128 at 2 / 4 / 8 rows 7.0 / 5.1 / 5.9;
-// 25600 x 512 at 57 / 103 rows 68 / 86.  Step with its spin tangent (G = 2),
-// 6400 x 256 at 15 / 17 / 29 rows 42.2 / 43.5 / 38.7, 3200 x 128 at 4 / 5 / 7
-// rows 17.0 / 17.6 / 16.4, 1200 x 100 at 1 / 2 / 3 rows 10.2 / 11.5 / 11.3.
-// Two-step adjoint (G = 2), 6400 x 256 at 14 / 15 /
-// 29 rows 15.0 / 16.5 / 22.4, 3200 x 128 at 4 / 5 / 8 rows 8.1 / 9.1 / 9.5.
-int sweep_rows(int nr, int nth, int cus, int K, int G, double alone, double* us = nullptr, int waves = 2) {
-    const int64_t strips = (nr + strip_cols(K) - 1) / strip_cols(K);
+// What a sweep's tile height is chosen from, by kernel.  A wavefront walks its
+// tile's rows one after the other: `steps` rows to fill the steps, then the
+// tile's rows and `steps` more, in groups of `group`, after a start (tables and
+// first rows) worth about three rows, `start2` where wavefronts overlap in it.
+struct SweepCost {
+    int steps, group;
+    int waves;         // wavefronts a SIMD holds; two share its issue:
+    double alone;      // a row takes 2 units of time beside another one, `alone` units without
+    double start2;
+    bool longer;       // of heights that cost the same the longer (fewer tiles); otherwise
+                       // the shorter where the tiles have a SIMD each
+    double us0, us;    // us of a pass: us0 + us for each unit of time
+    double us_alone;   // (the same where the tiles have a SIMD each)
+};
+
+// Forward passes: of one and two steps; of three steps; with a source.
+// Measured, us per step by rows: one step, 1600 x 128 at 2 / 4 / 5 rows 9.5 /
+// 7.5 / 8.2, 6400 x 256 at 8 / 15 / 27 rows 21.8 / 19.8 / 19.2; two steps (store
+// runs), 3200 x 128 at 4 / 7 / 9 rows 7.7 / 6.9 / 7.4; three steps, 6400 x 256
+// at 15 / 17 / 29 rows 13.3 / 12.2 / 12.3, 5003 x 197 at 9 / 10 / 13 rows 9.6 /
+// 10.9 / 10.1, 25600 x 512 at 57 / 103 rows 68 / 86.
+constexpr SweepCost kForward[kPassKinds] = {{1, 1, 2, 1.2, 3.0, true, 4.1, 0.36, 0.38},
+                                            {2, 1, 2, 1.2, 3.0, true, 2.8, 0.75, 0.75},
+                                            {3, 4, 2, 1.3, 2.0, false, 8.4, 0.65, 0.5},
+                                            {3, 4, 1, 1.3, 2.0, false, 3.2, 0.81, 0.91}};
+// The step with its spin tangent, at 15 / 17 / 29 rows on 6400 x 256 42.2 / 43.5
+// / 38.7, at 4 / 5 / 7 on 3200 x 128 17.0 / 17.6 / 16.4; the two-step adjoint, at
+// 14 / 15 / 29 rows on 6400 x 256 15.0 / 16.5 / 22.4.
+constexpr SweepCost kTangentCost = {1, 2, 2, 1.0, 2.0, false, 8.4, 0.65, 0.5};
+constexpr SweepCost kAdjointCost = {2, 2, 2, 1.8, 2.0, false, 8.4, 0.65, 0.5};
+
+// The tile height of the lowest cost, at most 128 rows; us: the estimated time
+// of a step.  Tiles beyond one round of wavefronts wait for a slot; with
+// several rounds the last, partly filled one counts for less.
+int sweep_rows(int nr, int nth, int cus, const SweepCost& c, double* us = nullptr) {
+    const int cols = strip_cols(c.steps);
+    const int64_t strips = (nr + cols - 1) / cols;
     double best = 0.0;
     int rows = 1;
     for (int r = 1; r <= std::min(nth, 128); ++r) {
         const double x = (double)(strips * ((nth + r - 1) / r)) / (4.0 * cus);  // tiles per SIMD
-        const int its = K + (r + K + G - 1) / G * G;
-        double f = alone, rounds = 1.0;
-        if (x > 1.0 && waves == 1) {
+        const int its = c.steps + (r + c.steps + c.group - 1) / c.group * c.group;
+        double f = c.alone, rounds = 1.0;
+        if (x > 1.0 && c.waves == 1) {
             rounds = std::ceil(x);
-            f = alone * (x + (rounds - x) / std::max(1.0, rounds - 1.0));
+            f = c.alone * (x + (rounds - x) / std::max(1.0, rounds - 1.0));
         } else if (x > 1.0) {
             rounds = std::ceil(0.5 * x);
             const double over = x - 2.0 * (rounds - 1.0);
-            const double whole = 2.0 * (rounds - 1.0) + (over > 1.0 ? 2.0 : alone);
+            const double whole = 2.0 * (rounds - 1.0) + (over > 1.0 ? 2.0 : c.alone);
             f = x + (whole - x) / std::max(1.0, rounds - 1.0);
         }
-        const double t = (x > 1.0 && waves > 1 ? 2.0 : 3.0) * rounds + its * f;
-        // equal times: fewer tiles where two share a SIMD, else shorter ones
-        if (r == 1 || t < best || (t == best && x > 1.0)) {
+        const double t = (x > 1.0 && c.waves > 1 ? c.start2 : 3.0) * rounds + its * f;
+        if (r == 1 || t < best || (t == best && (x > 1.0 || c.longer))) {
             best = t;
             rows = r;
-            if (us) *us = (8.4 + (x > 1.0 ? 0.65 : 0.5) * its * f) / K;
+            if (us) *us = (c.us0 + (x > 1.0 ? c.us : c.us_alone) * its * f) / c.steps;
         }
     }
     return rows;
@@ -645,8 +662,7 @@ int teuk_init_grid(const teuk_params* p, void* hip_stream, void* d_workspace, si
         // (four wavefronts a workgroup, or one, to spread few tiles over the CUs)
         for (int i = 0; i < kPassKinds; ++i) {
             const int k = std::min(i + 1, kMaxPassSteps);
-            const int r = i < kMaxPassSteps ? sweep_rows(nr, nth, cus, k, k + 1, 1.3, &sweep_us)
-                                            : sweep_rows(nr, nth, cus, k, k + 1, 1.3, nullptr, 1);
+            const int r = sweep_rows(nr, nth, cus, kForward[i], k == i + 1 ? &sweep_us : nullptr);
             const int64_t tiles = (int64_t)((nr + strip_cols(k) - 1) / strip_cols(k)) * ((nth + r - 1) / r);
             g->pass_rows[i] = g->default_rows[i] = r;
             g->pass_wpb[i] = g->default_wpb[i] = tiles < cus * 4 ? 1 : 4;
@@ -692,11 +708,11 @@ int teuk_init_grid(const teuk_params* p, void* hip_stream, void* d_workspace, si
     g->adj_rows = adjoint_rows(nr, nth, (int64_t)cus * 7, kStripCols);
     if (g->adj_rows == 1 && (int64_t)((nr + kStripCols - 1) / kStripCols) * nth > 4 * cus) g->adj_rows = std::min<int>(2, nth);
     g->adj_chunks = (nth + g->adj_rows - 1) / g->adj_rows;
-    g->adj2_rows = sweep_rows(nr, nth, cus, 2, 2, 1.8, &sweep_us);
+    g->adj2_rows = sweep_rows(nr, nth, cus, kAdjointCost, &sweep_us);
     // (the adjoint tile pass: 1.17 times the forward one's instructions)
     if (best_tile(nr, nth, cus, 1.17, &g->adj_tile, &g->adj_tile_steps) >= 0.95 * sweep_us) g->adj_tile_steps = 0;
     g->adj2_chunks = (nth + g->adj2_rows - 1) / g->adj2_rows;
-    g->tan_rows = sweep_rows(nr, nth, cus, 1, 2, 1.0);
+    g->tan_rows = sweep_rows(nr, nth, cus, kTangentCost);
     g->tan_chunks = (nth + g->tan_rows - 1) / g->tan_rows;
     g->adj_strips = ((int)p->nr + kStripCols - 1) / kStripCols;
     g->ext_r.assign(p->extract_rstar, p->extract_rstar + p->n_extract);
