@@ -20,9 +20,9 @@
 // once per row and pass, a two-step sweep issues 133 vector instructions per
 // point and step (195 before); on 6400 x 256 (states in the last-level cache)
 // it is bound by the latency and issue of one round of wavefronts, two per
-// SIMD: us per step, before and now, cotangents 16.9 -> 15.0, with the dot
-// products 22.4 -> 23.0, spin gradient from states 48 -> 46; 3200 x 128 8.3 ->
-// 7.8, 10.0 -> 9.7, 20.3 -> 18.9.
+// SIMD, or one with the dot products: us per step, before and now, cotangents
+// 16.9 -> 14.9, with the dot products 22.4 -> 21.0, spin gradient from states 48
+// -> 43; 3200 x 128 8.3 -> 7.7, 10.0 -> 9.1, 20.3 -> 18.5.
 #include "adjoint_common.hpp"
 
 namespace teuk {
@@ -66,6 +66,13 @@ constexpr int hit_doubles(int steps) { return steps * kRowHits * 3 * kWave; }
 // dot products with stored tangents, or the spin gradient from the states.
 enum SpinPart { kNone, kDot, kStates };
 
+// Sweeps whose lanes hold their own radial factors: one step without the spin
+// gradient from states, which leaves the registers for it (us per step from the
+// workgroup's tables in LDS and from registers, one step a pass: cotangents,
+// 1600 x 128 8.0 and 6.8, 6400 x 256 22.8 and 20.9; dot products 9.7 and 8.4,
+// 31.9 and 31.6).
+constexpr bool own_factors(int steps, SpinPart sp) { return steps == 1 && sp != kStates; }
+
 // K adjoint steps in one pass over a tile of 64 - 2K columns: step j takes
 // row r - j in iteration r and completes row r - j - 1, as in the forward
 // passes (sweep in the forward kernels' source), with the same row loops: the
@@ -75,12 +82,14 @@ enum SpinPart { kNone, kDot, kStates };
 //   kDot:    tan[j] holds T = (dA/da) u of step j; Re <n, T> is summed over the owned points;
 //   kStates: (K = 1) tan[0] holds u^m; T_m is formed on the way (tangent_sweep's
 //            expressions) and its dot product with n summed.
-// Returns this lane's sum.
-template <int K, SpinPart SP, int KEEP>
+// rvi(f, z), rvh(f, z): factor f of the lane's radial factors at its column
+// and half point (z: zero, opaque to the compiler); rdi, rdh: their
+// a-derivatives in LDS (kStates).  Returns this lane's sum.
+template <int K, SpinPart SP, int KEEP, class RadI, class RadH>
 __device__ __forceinline__ double adjoint_sweep(const double2* __restrict__ nu_in, double2* __restrict__ lam_out,
                                                 const double* __restrict__ ang, const ExtPoint* __restrict__ ext,
                                                 const double* const (&gs)[K], const double2* const (&tan)[K],
-                                                lds_cptr rvi, lds_cptr rvh, lds_cptr rdi, lds_cptr rdh, lds_t hits,
+                                                RadI rvi, RadH rvh, lds_cptr rdi, lds_cptr rdh, lds_t hits,
                                                 const AdjScalars& A, int strip, int chunk, int lane) {
     static_assert(SP != kStates || K == 1, "the spin gradient from states is a one-step sweep");
     // rows in flight (and rows the loop is unrolled by); coefficient rows: K
@@ -184,7 +193,7 @@ __device__ __forceinline__ double adjoint_sweep(const double2* __restrict__ nu_i
         const int z = r & A.zero;
         Stage dh, di;
         {
-            const SRad R = srad_of([&](int f) { return rvi[z + f * kWave]; });
+            const SRad R = srad_of([&](int f) { return rvi(f, z); });
             const Sig s = ssigma(R, G);
             Ci[PH] = stage_coef(R, G, s, A.kap_i);
             if constexpr (SP == kStates) {
@@ -193,7 +202,7 @@ __device__ __forceinline__ double adjoint_sweep(const double2* __restrict__ nu_i
             }
         }
         {
-            const SRad R = srad_of([&](int f) { return rvh[z + f * kWave]; });
+            const SRad R = srad_of([&](int f) { return rvh(f, z); });
             const Sig s = ssigma(R, G);
             Ch[PH] = stage_coef(R, G, s, A.kap_h);
             if constexpr (SP == kStates) {
@@ -349,13 +358,20 @@ __device__ __forceinline__ double adjoint_sweep(const double2* __restrict__ nu_i
         }
     };
     while (r + kRing - 1 <= rM) rows(rows, Const<0>{}, Const<0>{});
-    while (r <= rE) rows(rows, Const<0>{}, Const<1>{});
+    // The last rows: one that is left after the whole groups goes alone (in
+    // pairs, a two-step tile of one row swept six rows where it has five: with
+    // dot products, 400 x 32 5.4 and 4.7 us a step).
+    while (r + kRing - 1 <= rE) rows(rows, Const<0>{}, Const<1>{});
+    if constexpr (kRing > 1)
+        if (r <= rE) iteration(r, bp[K % kRing], bq[K % kRing], Const<K>{}, Const<K>{}, Const<1>{});
     return acc;
 }
 
-// The workgroup's radial tables (with their a-derivatives for kStates) in
-// LDS, and its wavefront's tile of a K-step adjoint sweep; the sums of the
-// lanes go to the tile's slot, in a fixed order.
+// A wavefront's tile of a K-step adjoint sweep; the sums of the lanes go to
+// the tile's slot, in a fixed order.  Where the registers allow it (one step,
+// without the spin gradient from states) the lane holds its own radial factors
+// and no wavefront waits for another; otherwise the workgroup's radial tables
+// (with their a-derivatives for kStates) are in LDS.
 template <int K, SpinPart SP, int KEEP>
 __device__ __forceinline__ void adjoint_tile(const double2* __restrict__ nu_in, double2* __restrict__ lam_out,
                                              const double* __restrict__ rad, const double* __restrict__ rad_da,
@@ -367,16 +383,33 @@ __device__ __forceinline__ void adjoint_tile(const double2* __restrict__ nu_in, 
     const int wpb = blockDim.x / kWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const TileOf T = tile_of(xcd_block(blockIdx.x, gridDim.x), wpb, wave, A.n_strips, A.n_chunks);
-    fill_tables<K, kTables>(T, rad, rad_da, rad_s, A.nr, A.pitch, wave, wpb, lane);
-    if (!T.valid) return;  // wavefront-uniform
-    const double* slice = rad_s + T.slice * kTables * 2 * kNumSRad * kWave + lane;
-    const double* da = slice + (kTables - 1) * 2 * kNumSRad * kWave;
-    double acc = adjoint_sweep<K, SP, KEEP>(nu_in, lam_out, ang, ext, gs, tan, (lds_cptr)slice,
-                                            (lds_cptr)(slice + kNumSRad * kWave), (lds_cptr)da,
-                                            (lds_cptr)(da + kNumSRad * kWave),
-                                            (lds_t)(rad_s + T.n_slices * kTables * 2 * kNumSRad * kWave +
-                                                    wave * hit_doubles(K)),
-                                            A, T.strip, T.chunk, lane);
+    double acc;
+    if constexpr (own_factors(K, SP)) {
+        if (!T.valid) return;  // wavefront-uniform
+        const int c = min(max(T.strip * strip_cols(K) - K + lane, 0), A.nr - 1), ch = min(c, A.nr - 2);
+        double ri[kNumSRad], rh[kNumSRad];
+#pragma unroll
+        for (int f = 0; f < kNumSRad; ++f) {
+            ri[f] = rad[(size_t)f * 2 * A.pitch + c];
+            rh[f] = rad[((size_t)f * 2 + 1) * A.pitch + ch];
+        }
+        acc = adjoint_sweep<K, SP, KEEP>(nu_in, lam_out, ang, ext, gs, tan, [&](int f, int) { return ri[f]; },
+                                         [&](int f, int) { return rh[f]; }, nullptr, nullptr,
+                                         (lds_t)(rad_s + wave * hit_doubles(K)), A, T.strip, T.chunk, lane);
+    } else {
+        fill_tables<K, kTables>(T, rad, rad_da, rad_s, A.nr, A.pitch, wave, wpb, lane);
+        if (!T.valid) return;  // wavefront-uniform
+        const double* slice = rad_s + T.slice * kTables * 2 * kNumSRad * kWave + lane;
+        const double* da = slice + (kTables - 1) * 2 * kNumSRad * kWave;
+        const lds_cptr ri = (lds_cptr)slice, rh = (lds_cptr)(slice + kNumSRad * kWave);
+        acc = adjoint_sweep<K, SP, KEEP>(nu_in, lam_out, ang, ext, gs, tan,
+                                         [&](int f, int z) { return ri[z + f * kWave]; },
+                                         [&](int f, int z) { return rh[z + f * kWave]; }, (lds_cptr)da,
+                                         (lds_cptr)(da + kNumSRad * kWave),
+                                         (lds_t)(rad_s + T.n_slices * kTables * 2 * kNumSRad * kWave +
+                                                 wave * hit_doubles(K)),
+                                         A, T.strip, T.chunk, lane);
+    }
     if constexpr (SP != kNone) {
         for (int off = kWave / 2; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, kWave);
         if (lane == 0) dlda_slots[(size_t)T.chunk * A.n_strips + T.strip] += acc;
@@ -646,7 +679,8 @@ hipError_t launch_adjoint(const AdjArgs& a, int waves_per_block, AdjMode mode, h
     dim3 grid, block;
     size_t lds;
     const bool spin = mode == AdjMode::kSpin;
-    adjoint_launch_shape(a.k, waves_per_block, (spin ? 4 : 2) * kNumSRad, &grid, &block, &lds, hit_doubles(1) * sizeof(double));
+    adjoint_launch_shape(a.k, waves_per_block, spin ? 4 * kNumSRad : 0, &grid, &block, &lds,
+                         hit_doubles(1) * sizeof(double));
     const bool keep = a.k.keep != 0;
     auto pick = [&](auto k0, auto k1) { return keep ? k1 : k0; };
     auto kern = spin ? pick(lw_adjoint_kernel<true, false, 0>, lw_adjoint_kernel<true, false, 1>)

@@ -197,6 +197,12 @@ constexpr int pass_kind(int steps, bool source) {
     return steps == kMaxPassSteps && source ? kMaxPassSteps : steps - 1;
 }
 
+// The adjoint-side kernels, each with a tile height of its own: one adjoint
+// step with the spin gradient from states; one step otherwise; two steps; two
+// with the tangents' dot products; the step that stores its tangent; the step
+// with its spin derivative.
+enum AdjKind { kAdjStates, kAdjOne, kAdjTwo, kAdjTwoDot, kAdjTangent, kAdjSpinTangent, kAdjKinds };
+
 }  // namespace
 
 struct teuk_grid {
@@ -231,13 +237,12 @@ struct teuk_grid {
     // adjoint (teuk_enable_adjoint)
     char* aws = nullptr;      // adjoint workspace
     size_t aoff_lam[2]{}, aoff_da = 0, aoff_slots = 0, aoff_sum = 0;
-    int adj_rows = 32, adj_wpb = 4, adj_chunks = 0, adj_strips = 0;  // spin-gradient and one-step kernels
-    int adj2_rows = 32, adj2_chunks = 0;                              // two-step cotangent kernel
+    int adj_rows = 32, adj_wpb = 4, adj_strips = 0;  // the tile as teuk_get_adjoint_tile reports it
+    int adj_pass_rows[kAdjKinds] = {};               // the kernels' own heights (teuk_set_adjoint_tile sets them all)
     TileShape adj_tile;       // adjoint tile pass: shape and steps per launch (0: off)
     int adj_tile_steps = 0;
     bool adj_default = true;  // teuk_set_adjoint_tile has not been called
-    int tan_rows = 32, tan_chunks = 0;                                // step-with-tangent kernel
-    int cache_policy = TEUK_CACHE_AUTO;                               // teuk_set_cache_policy
+    int cache_policy = TEUK_CACHE_AUTO;  // teuk_set_cache_policy
     // forward-mode spin derivative (teuk_enable_spin_tangent): v = du/da in two buffers
     char* tws = nullptr;
     int vcur = 0;
@@ -414,7 +419,7 @@ struct SweepCost {
     double start2;
     bool longer;       // of heights that cost the same the longer (fewer tiles); otherwise
                        // the shorter where the tiles have a SIMD each
-    double us0, us;    // us of a pass: us0 + us for each unit of time
+    double us0, us;    // us of a pass: us0 + us for each unit of time (0: not used)
     double us_alone;   // (the same where the tiles have a SIMD each)
 };
 
@@ -428,11 +433,18 @@ constexpr SweepCost kForward[kPassKinds] = {{1, 1, 2, 1.2, 3.0, true, 4.1, 0.36,
                                             {2, 1, 2, 1.2, 3.0, true, 2.8, 0.75, 0.75},
                                             {3, 4, 2, 1.3, 2.0, false, 8.4, 0.65, 0.5},
                                             {3, 4, 1, 1.3, 2.0, false, 3.2, 0.81, 0.91}};
-// The step with its spin tangent, at 15 / 17 / 29 rows on 6400 x 256 42.2 / 43.5
-// / 38.7, at 4 / 5 / 7 on 3200 x 128 17.0 / 17.6 / 16.4; the two-step adjoint, at
-// 14 / 15 / 29 rows on 6400 x 256 15.0 / 16.5 / 22.4.
-constexpr SweepCost kTangentCost = {1, 2, 2, 1.0, 2.0, false, 8.4, 0.65, 0.5};
-constexpr SweepCost kAdjointCost = {2, 2, 2, 1.8, 2.0, false, 8.4, 0.65, 0.5};
+// Adjoint-side kernels (one-step cotangents from states first, see AdjKind).
+// Measured, us per step by rows: from states, 3200 x 128 at 4 / 5 / 7 rows 18.5 /
+// 21.4 / 20.6, 1600 x 64 at 1 / 2 / 3 rows 11.8 / 10.2 / 12.3; one step, 1600 x
+// 128 at 2 / 4 / 8 rows 8.2 / 6.8 / 8.2; two steps, 6400 x 256 at 9 / 14 / 29
+// rows 16.0 / 14.9 / 18.2; with dot products 28.3 / 22.7 / 21.0; the step with
+// its spin tangent, 6400 x 256 at 15 / 17 / 29 rows 42.2 / 43.5 / 38.7.
+constexpr SweepCost kAdjoint[kAdjKinds] = {{1, 1, 2, 1.4, 3.0, true, 0.0, 0.0, 0.0},
+                                           {1, 1, 2, 1.3, 3.0, true, 0.0, 0.0, 0.0},
+                                           {2, 1, 2, 1.3, 3.0, true, 3.4, 0.725, 0.725},
+                                           {2, 1, 2, 1.0, 3.0, true, 0.0, 0.0, 0.0},
+                                           {1, 2, 2, 1.0, 2.0, false, 0.0, 0.0, 0.0},
+                                           {1, 2, 2, 1.0, 2.0, false, 0.0, 0.0, 0.0}};
 
 // The tile height of the lowest cost, at most 128 rows; us: the estimated time
 // of a step.  Tiles beyond one round of wavefronts wait for a slot; with
@@ -699,21 +711,15 @@ int teuk_init_grid(const teuk_params* p, void* hip_stream, void* d_workspace, si
     g->default_tile[1] = g->wpb;
     g->default_block[0] = g->block_steps;
     g->default_block[1] = g->block_cols;
-    // a device holds two adjoint wavefronts per SIMD (8 per CU).  The
-    // one-step kernels leave one slot in eight to a recompute that runs
-    // beside them.
-    // (tiles of one row only where there is one to a SIMD: 1600 x 64 11.9 us a
-    // step with the spin gradient from states, 10.5 with two rows; 400 x 32 9.0
-    // and 10.3)
+    // The adjoint tile as it is reported; the kernels take heights of their own
+    // until teuk_set_adjoint_tile.
     g->adj_rows = adjoint_rows(nr, nth, (int64_t)cus * 7, kStripCols);
-    if (g->adj_rows == 1 && (int64_t)((nr + kStripCols - 1) / kStripCols) * nth > 4 * cus) g->adj_rows = std::min<int>(2, nth);
-    g->adj_chunks = (nth + g->adj_rows - 1) / g->adj_rows;
-    g->adj2_rows = sweep_rows(nr, nth, cus, kAdjointCost, &sweep_us);
-    // (the adjoint tile pass: 1.17 times the forward one's instructions)
+    for (int i = 0; i < kAdjKinds; ++i)
+        g->adj_pass_rows[i] = sweep_rows(nr, nth, cus, kAdjoint[i], i == kAdjTwo ? &sweep_us : nullptr);
+    // (the adjoint tile pass: 1.17 times the forward one's instructions.  us per
+    // step, tile pass and sweeps: 2000 x 256 7.2 and 8.1, 12000 x 64 10.3 and 9.9,
+    // 4000 x 200 10.4 and 9.8, 5003 x 197 12.9 and 11.1)
     if (best_tile(nr, nth, cus, 1.17, &g->adj_tile, &g->adj_tile_steps) >= 0.95 * sweep_us) g->adj_tile_steps = 0;
-    g->adj2_chunks = (nth + g->adj2_rows - 1) / g->adj2_rows;
-    g->tan_rows = sweep_rows(nr, nth, cus, kTangentCost);
-    g->tan_chunks = (nth + g->tan_rows - 1) / g->tan_rows;
     g->adj_strips = ((int)p->nr + kStripCols - 1) / kStripCols;
     g->ext_r.assign(p->extract_rstar, p->extract_rstar + p->n_extract);
     g->ext_t.assign(p->extract_theta, p->extract_theta + p->n_extract);
@@ -1224,8 +1230,8 @@ int teuk_set_adjoint_tile(teuk_grid* g, int32_t rows_per_tile, int32_t waves_per
         return fail(TEUK_E_INVALID_ARG, "rows_per_tile=%d outside [1, ntheta]", rows_per_tile);
     if (waves_per_block != 1 && waves_per_block != 2 && waves_per_block != 4)
         return fail(TEUK_E_INVALID_ARG, "waves_per_block=%d not in {1, 2, 4}", waves_per_block);
-    g->adj_rows = g->adj2_rows = g->tan_rows = rows_per_tile;
-    g->adj_chunks = g->adj2_chunks = g->tan_chunks = (int)((g->p.ntheta + rows_per_tile - 1) / rows_per_tile);
+    g->adj_rows = rows_per_tile;
+    for (int& r : g->adj_pass_rows) r = rows_per_tile;
     g->adj_wpb = waves_per_block;
     g->adj_default = false;
     return TEUK_OK;
@@ -1293,18 +1299,18 @@ int teuk_enable_adjoint(teuk_grid* g, void* d_adj_workspace, size_t bytes) {
 
 namespace {
 
-// Launch arguments of the adjoint-side kernels (tiles of the one-step
-// adjoint kernel; callers adjust rows, strips and chunks for the others).
-AdjArgs adjoint_args(const teuk_grid* g) {
+// Launch arguments of an adjoint-side kernel.
+AdjArgs adjoint_args(const teuk_grid* g, AdjKind kind) {
     AdjArgs a{};
     const int nth = (int)g->p.ntheta;
     a.k.nr = (int)g->p.nr;
     a.k.nth = nth;
     a.k.pitch = g->L.pitch;
     a.k.sigma = g->sigma;
-    a.k.rows = g->adj_rows;
-    a.k.n_strips = g->adj_strips;
-    a.k.n_chunks = g->adj_chunks;
+    const int cols = strip_cols(kAdjoint[kind].steps);
+    a.k.rows = g->adj_pass_rows[kind];
+    a.k.n_strips = (a.k.nr + cols - 1) / cols;
+    a.k.n_chunks = (nth + a.k.rows - 1) / a.k.rows;
     a.k.zero = 0;
     a.k.keep = keeps_states(g) ? 1 : 0;
     a.k.plane = (int64_t)nth * g->L.pitch;
@@ -1333,9 +1339,7 @@ int teuk_step_n_tangent(teuk_grid* g, int64_t n, void* d_window) {
         return fail(TEUK_E_WORKSPACE, "window not %zu-byte aligned", kAlign);
     if (n == 0) return TEUK_OK;
     if (int rc = set_device(g)) return rc;
-    AdjArgs a = adjoint_args(g);
-    a.k.rows = g->tan_rows;
-    a.k.n_chunks = g->tan_chunks;
+    const AdjArgs a = adjoint_args(g, kAdjTangent);
     char* win = static_cast<char*>(d_window);
     for (int64_t k = 0; k < n; ++k) {
         double2* t_out = reinterpret_cast<double2*>(win + (size_t)k * g->L.state);
@@ -1374,8 +1378,9 @@ int adjoint_impl(teuk_grid* g, int64_t n, void* d_lam_phi, void* d_lam_pi, const
     auto lam = [&](int k) { return reinterpret_cast<double2*>(g->aws + g->aoff_lam[k]); };
     double* slots = reinterpret_cast<double*>(g->aws + g->aoff_slots);
     double* sum = reinterpret_cast<double*>(g->aws + g->aoff_sum);
-    const int strips2 = (nr + kStripCols2 - 1) / kStripCols2;
-    const int nslots = std::max(g->adj_strips * g->adj_chunks, strips2 * g->adj2_chunks);
+    AdjArgs a = adjoint_args(g, spin && !tangent ? kAdjStates : kAdjOne);
+    AdjArgs a2 = adjoint_args(g, tangent ? kAdjTwoDot : kAdjTwo);
+    const int nslots = std::max(a.k.n_strips * a.k.n_chunks, a2.k.n_strips * a2.k.n_chunks);
 
     int c = 0;
     HIP_TRY(launch_import(static_cast<const double2*>(d_lam_phi), static_cast<const double2*>(d_lam_pi), lam(c),
@@ -1386,12 +1391,11 @@ int adjoint_impl(teuk_grid* g, int64_t n, void* d_lam_phi, void* d_lam_pi, const
     }
     // the sample of the segment's last state
     if (gs && n > 0) HIP_TRY(launch_extract_adjoint(lam(c), P, ext, ne, gs + (n - 1) * ne, s));
-    AdjArgs a = adjoint_args(g);
-    a.slots = slots;
+    a.slots = a2.slots = slots;
     // the sample of the state an adjoint step produces is added by the
     // adjoint kernel itself for a few points, by a separate pass otherwise
     const bool fused = fused_adjoint_ok(g);
-    a.k.n_ext = fused ? ne : 0;
+    a.k.n_ext = a2.k.n_ext = fused ? ne : 0;
     const char* win = static_cast<const char*>(d_window);
     auto slot = [&](int64_t k) { return reinterpret_cast<const double2*>(win + (size_t)k * g->L.state); };
     int64_t k = n - 1;
@@ -1412,10 +1416,6 @@ int adjoint_impl(teuk_grid* g, int64_t n, void* d_lam_phi, void* d_lam_pi, const
     if ((!spin || tangent) && fused && g->steps_per_pass == 2) {
         // cotangents (and the tangents' dot products): two adjoint steps
         // (k, then k-1) per pass
-        AdjArgs a2 = a;
-        a2.k.n_strips = strips2;
-        a2.k.rows = g->adj2_rows;
-        a2.k.n_chunks = g->adj2_chunks;
         for (; k >= 1; k -= 2) {
             a2.nu_in = lam(c);
             a2.lam_out = lam(1 - c);
@@ -1521,19 +1521,15 @@ int teuk_step_n_spin_tangent(teuk_grid* g, int64_t n, void* d_series, void* d_ts
     if (n < 0) return fail(TEUK_E_INVALID_ARG, "n=%lld < 0", (long long)n);
     if (n == 0) return TEUK_OK;
     if (int rc = set_device(g)) return rc;
-    const int nr = (int)g->p.nr;
     const int ne = g->p.n_extract;
     double2* series = (ne > 0) ? static_cast<double2*>(d_series) : nullptr;
     double2* tseries = (ne > 0) ? static_cast<double2*>(d_tseries) : nullptr;
     const ExtPoint* ext = g->at<ExtPoint>(g->L.off_ext);
-    AdjArgs a = adjoint_args(g);
-    a.k.rows = g->tan_rows;
-    a.k.n_strips = (nr + kStripCols - 1) / kStripCols;
-    a.k.n_chunks = g->tan_chunks;
+    AdjArgs a = adjoint_args(g, kAdjSpinTangent);
     // the launches sample their input (row k-1 of a series: the state after
     // step k); the call's last state, or every state when two extraction
     // points share a tile, by a separate pass
-    const bool fused = fused_extraction_ok(g, kStripCols, g->tan_rows, false);
+    const bool fused = fused_extraction_ok(g, kStripCols, a.k.rows, false);
     a.k.n_ext = fused ? ne : 0;
     auto extract = [&](int64_t j) -> int {
         if (series) HIP_TRY(launch_extract(g->u(g->cur), g->L.pitch, ext, ne, series + (j - 1) * ne, g->stream));

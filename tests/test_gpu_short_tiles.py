@@ -78,3 +78,43 @@ def test_forward(gpu, kind, m):
     for a, b in zip(ref[:3], exp):
         assert rel_err(a, b) <= TOL
     g.close()
+
+
+DLDA_TOL = 1e-10  # of the spin gradient, relative (a sum over all points and steps)
+
+
+@pytest.mark.parametrize("m", [1, 2])
+@pytest.mark.parametrize("spp", [1, 2])
+@pytest.mark.parametrize("kind", ["cotangents", "tangents", "states"])
+def test_adjoint(gpu, kind, spp, m):
+    n = 5
+    g, o, er, et = _grid(gpu, m)
+    u = inputs.random_state(NR, NTH, seed=10 + m)
+    rng = np.random.default_rng(10 + m)
+    gser = rng.standard_normal((n, 2)) + 1j * rng.standard_normal((n, 2))
+    g.enable_adjoint()
+    g.set_steps_per_pass(spp)
+    g.set_initial_data(*_cuda(u))
+    win = g.new_window(n)
+    if kind == "tangents":
+        g.step_tangent(n, win)
+    else:
+        g.step_store(n, win, series=False)
+    zero = np.zeros((NTH, NR), dtype=np.complex128)
+    exp = o.adjoint_evolve(*o.project(*u), n, er, et, gser)
+    ref = None
+    for rows in reversed(HEIGHTS):
+        g.set_adjoint_tile(rows, 4 if rows % 2 else 2)
+        lam = _cuda((zero, zero))
+        dlda = g.adjoint(n, *lam, _cuda([gser])[0], win, project_initial=True, spin=kind != "cotangents",
+                         tangent=kind == "tangents")
+        torch.cuda.synchronize()
+        out = [t.cpu().numpy() for t in lam]
+        if ref is None:
+            ref = out
+        assert np.array_equal(out[0], ref[0]) and np.array_equal(out[1], ref[1]), rows
+        if kind != "cotangents":
+            assert abs(dlda - exp[2]) <= DLDA_TOL * abs(exp[2]), (rows, dlda, exp[2])
+    p, q = o.project(exp[0], exp[1])
+    assert rel_err(ref[0], p) <= TOL and rel_err(ref[1], q) <= TOL
+    g.close()
