@@ -120,13 +120,14 @@ struct TanRow {
 // its 52 LDS reads a row and for memory (210 MB a step on 6400 x 256, 25 us at
 // the rate of a copy within the last-level cache).  Stage 1 is finished, and
 // the previous row completed and stored, before the column's coefficients are
-// read: 200 registers instead of 240 with v, so the default instruction
+// read: 226 registers with v, so the default instruction
 // schedule, which has more loads in flight than one for occupancy, does not
-// spill.  Without v the factors themselves are in registers (214) and their
+// spill.  Without v the factors themselves are in registers (220) and their
 // derivatives in the wavefront's own slice, which no other wavefront waits for.
-// us per step, before and now: 6400 x 256 48.6 -> 38.7 with v, 38.8 -> 33.5
-// without; 3200 x 128 19.4 -> 16.4, 14.3 -> 12.1 (15.1 from the workgroup's
-// tables in LDS); 1200 x 100 without v 9.8 -> 8.9 (9.7).
+// us per step, before and now: 6400 x 256 48.6 -> 39.5 with v, 38.8 -> 31.0
+// without; 3200 x 128 19.4 -> 16.1, 14.3 -> 11.6 (15.1 from the workgroup's
+// tables in LDS); 1600 x 64 8.9 -> 8.4, 9.7 -> 7.0; 1200 x 100 9.1 -> 9.7, 9.8 ->
+// 7.1.
 // Three wavefronts per SIMD (168 registers) spill with v and take 51-60 us.
 template <bool V, int KEEP, class RadI, class RadH>
 __device__ __forceinline__ void tangent_sweep(gin_t u_in, gin_t v_in, gout_t u_out, gout_t v_out, ctab_t ang,
@@ -281,26 +282,39 @@ __device__ __forceinline__ void tangent_sweep(gin_t u_in, gin_t v_in, gout_t u_o
             st_row<kV>(row_rsrc(v_out + o + A.plane, bytes), st_off, vq);
         }
         __builtin_amdgcn_sched_barrier(0);
-        Stage ki, di;
-        {
-            const SRad R = srad_of([&](int f) { return rvi(f, z); });
-            const Sig sig = ssigma(R, G);
-            ki = stage_coef(R, G, sig, A.kap_i);
-            const SRad D = srad_of([&](int f) { return rdi[z + f * kWave]; });
-            di = stage_coef_da(R, D, G, sig, A.kap_i, ki);
+        // Stage 2 of row t, but for the rows at the tile's ends that are only
+        // neighbours: in tiles of a few rows they are most of the rows (with v,
+        // 1600 x 64: 10.3 us a step with one-row tiles and all of it, 9.6
+        // without, 8.3 with two rows).  What such a row leaves is not used;
+        // the values are there for the registers' sake.
+        n.P = p;
+        n.Q = q;
+        n.tP = n.tS;
+        n.tQ = n.tS;
+        n.k = s.k;
+        n.d = s.d;
+        if (CHECK == 0 || (CHECK == 1 ? t < rE : rs0 == j0)) {
+            Stage ki, di;
+            {
+                const SRad R = srad_of([&](int f) { return rvi(f, z); });
+                const Sig sig = ssigma(R, G);
+                ki = stage_coef(R, G, sig, A.kap_i);
+                const SRad D = srad_of([&](int f) { return rdi[z + f * kWave]; });
+                di = stage_coef_da(R, D, G, sig, A.kap_i, ki);
+            }
+            n.P = fma_real(-ki.b, D, p);
+            n.Q = cadd(q, stage2_early(ki, n.S, D, dS));
+            const cd tq = cadd(stage2_early(di, n.S, D, dS), stage2_early(ki, n.tS, tD, tdS));
+            if constexpr (V) {
+                n.tP = fma_real(-di.b, D, fma_real(-ki.b, tD, b[2]));
+                n.tQ = cadd(b[3], tq);
+            } else {
+                n.tP = fma_real(-di.b, D, cd{-ki.b * tD.re, -ki.b * tD.im});
+                n.tQ = tq;
+            }
+            n.k = late_of(kh, ki);
+            n.d = late_of(dh, di);
         }
-        n.P = fma_real(-ki.b, D, p);
-        n.Q = cadd(q, stage2_early(ki, n.S, D, dS));
-        const cd tq = cadd(stage2_early(di, n.S, D, dS), stage2_early(ki, n.tS, tD, tdS));
-        if constexpr (V) {
-            n.tP = fma_real(-di.b, D, fma_real(-ki.b, tD, b[2]));
-            n.tQ = cadd(b[3], tq);
-        } else {
-            n.tP = fma_real(-di.b, D, cd{-ki.b * tD.re, -ki.b * tD.im});
-            n.tQ = tq;
-        }
-        n.k = late_of(kh, ki);
-        n.d = late_of(dh, di);
         g_next = load_ang(ang, nth, min(t + 1, nth - 1));
         load_row(t + 2, b);
         __builtin_amdgcn_sched_barrier(0);
@@ -313,9 +327,11 @@ __device__ __forceinline__ void tangent_sweep(gin_t u_in, gin_t v_in, gout_t u_o
         iteration(t, buf[1], row[0], row[1], Const<0>{});
         iteration(t + 1, buf[0], row[1], row[0], Const<0>{});
     }
-    for (; t <= rE; t += 2) {
+    while (t <= rE) {
         iteration(t, buf[1], row[0], row[1], Const<1>{});
-        iteration(t + 1, buf[0], row[1], row[0], Const<1>{});
+        if (++t > rE) break;
+        iteration(t, buf[0], row[1], row[0], Const<1>{});
+        ++t;
     }
     if constexpr (V) {
         if (e_id >= 0 && lane < 2) {  // lane 0: the sample of u, lane 1: of v

@@ -433,18 +433,20 @@ constexpr SweepCost kForward[kPassKinds] = {{1, 1, 2, 1.2, 3.0, true, 4.1, 0.36,
                                             {2, 1, 2, 1.2, 3.0, true, 2.8, 0.75, 0.75},
                                             {3, 4, 2, 1.3, 2.0, false, 8.4, 0.65, 0.5},
                                             {3, 4, 1, 1.3, 2.0, false, 3.2, 0.81, 0.91}};
-// Adjoint-side kernels (one-step cotangents from states first, see AdjKind).
+// Adjoint-side kernels, in the order of AdjKind.
 // Measured, us per step by rows: from states, 3200 x 128 at 4 / 5 / 7 rows 18.5 /
 // 21.4 / 20.6, 1600 x 64 at 1 / 2 / 3 rows 11.8 / 10.2 / 12.3; one step, 1600 x
 // 128 at 2 / 4 / 8 rows 8.2 / 6.8 / 8.2; two steps, 6400 x 256 at 9 / 14 / 29
-// rows 16.0 / 14.9 / 18.2; with dot products 28.3 / 22.7 / 21.0; the step with
-// its spin tangent, 6400 x 256 at 15 / 17 / 29 rows 42.2 / 43.5 / 38.7.
+// rows 16.0 / 14.9 / 18.2; with dot products 28.3 / 22.7 / 21.0; the step that
+// stores its tangent, 1600 x 64 at 1 / 2 / 3 rows 8.6 / 7.1 / 7.8; the step with
+// its spin derivative, 1600 x 64 9.6 / 8.3 / 10.5, 6400 x 256 at 15 / 17 / 29 rows
+// 42.2 / 43.5 / 38.7.
 constexpr SweepCost kAdjoint[kAdjKinds] = {{1, 1, 2, 1.4, 3.0, true, 0.0, 0.0, 0.0},
                                            {1, 1, 2, 1.3, 3.0, true, 0.0, 0.0, 0.0},
                                            {2, 1, 2, 1.3, 3.0, true, 3.4, 0.725, 0.725},
                                            {2, 1, 2, 1.0, 3.0, true, 0.0, 0.0, 0.0},
-                                           {1, 2, 2, 1.0, 2.0, false, 0.0, 0.0, 0.0},
-                                           {1, 2, 2, 1.0, 2.0, false, 0.0, 0.0, 0.0}};
+                                           {1, 1, 2, 1.2, 3.0, true, 0.0, 0.0, 0.0},
+                                           {1, 1, 2, 1.0, 3.0, true, 0.0, 0.0, 0.0}};
 
 // The tile height of the lowest cost, at most 128 rows; us: the estimated time
 // of a step.  Tiles beyond one round of wavefronts wait for a slot; with

@@ -118,3 +118,36 @@ def test_adjoint(gpu, kind, spp, m):
     p, q = o.project(exp[0], exp[1])
     assert rel_err(ref[0], p) <= TOL and rel_err(ref[1], q) <= TOL
     g.close()
+
+
+@pytest.mark.parametrize("m", [1, 2])
+def test_tangents(gpu, m):
+    """The step with its spin derivative and the step that stores its tangent."""
+    n = 4
+    g, o, er, et = _grid(gpu, m)
+    u, v = inputs.random_state(NR, NTH, seed=20 + m), inputs.random_state(NR, NTH, seed=30 + m)
+    g.enable_spin_tangent()
+    win = g.new_window(n)
+    ref = None
+    for rows in reversed(HEIGHTS):
+        g.set_adjoint_tile(rows, 4 if rows % 2 else 2)
+        g.set_initial_data(*_cuda(u))
+        g.set_spin_tangent(*_cuda(v))
+        out = [*g.step_spin_tangent(n)]
+        out = [*g.state(), *g.spin_tangent(), *out]
+        g.set_initial_data(*_cuda(u))
+        g.step_tangent(n, win)
+        out = [t.cpu().numpy() for t in (*out, *g.state(), *(f for k in range(n) for f in g.window_slot(win, k)))]
+        if ref is None:
+            ref = out
+        for k, (a, b) in enumerate(zip(out, ref)):
+            assert np.array_equal(a, b), (rows, k)
+    p, q = o.project(*u)
+    exp = o.evolve_spin_tangent(p, q, *o.project(*v), n, er, et)
+    for a, b in zip(ref[:6], exp):
+        assert rel_err(a, b) <= TOL
+    for k in range(n):
+        for a, b in zip(ref[8 + 2 * k:10 + 2 * k], o.tangent_a(p, q)):
+            assert rel_err(a, b) <= TOL
+        p, q = o.step(p, q)
+    g.close()
