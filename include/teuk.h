@@ -334,6 +334,26 @@ int teuk_enable_adjoint(teuk_grid* g, void* d_adj_workspace, size_t bytes);
 int teuk_set_adjoint_tile(teuk_grid* g, int32_t rows_per_tile, int32_t waves_per_block);
 int teuk_get_adjoint_tile(const teuk_grid* g, int32_t* rows_per_tile, int32_t* waves_per_block);
 
+/* How the launches of a long run of a kind go on this grid as it is set now.
+ * Sweep: `steps` a launch, tiles of `cols` columns x `rows` theta rows that a
+ * wavefront writes.  Tile pass: tiles of `cols` columns, `rows` rows a lane.
+ * Block pass: blocks of `cols` columns x all rows.  `waves` wavefronts a
+ * workgroup; samples = 1 if the launches sample the extraction points, 0 if
+ * launches of their own do.  TEUK_E_INVALID_ARG for another `run`. */
+enum {
+    TEUK_RUN_STEPS = 0,         /* teuk_step_n without a series */
+    TEUK_RUN_SERIES = 1,        /* ... with one */
+    TEUK_RUN_SOURCE = 2,        /* teuk_step_n_source without a series */
+    TEUK_RUN_SOURCE_SERIES = 3, /* ... with one */
+    TEUK_RUN_COTANGENTS = 4,    /* teuk_adjoint_step_n without a dL/da accumulator */
+    TEUK_RUN_SPIN_TANGENT = 5   /* teuk_step_n_spin_tangent with series */
+};
+enum { TEUK_PASS_SWEEP = 0, TEUK_PASS_TILE = 1, TEUK_PASS_BLOCK = 2 };
+typedef struct teuk_pass {
+    int32_t kind, steps, cols, rows, waves, samples;
+} teuk_pass;
+int teuk_get_pass(const teuk_grid* g, int32_t run, teuk_pass* out);
+
 /* Copy window slot k (a state of teuk_step_n_store, or a tangent of
  * teuk_step_n_tangent) into caller arrays (complex128 [ntheta][nr]).  The
  * caller keeps k below the window's slot count; the call cannot check it. */

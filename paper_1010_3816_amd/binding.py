@@ -84,6 +84,7 @@ def _load():
         "teuk_set_finite_check": (ctypes.c_int, [V, I64]),
         "teuk_set_adjoint_tile": (ctypes.c_int, [V, I32, I32]),
         "teuk_get_adjoint_tile": (ctypes.c_int, [V, ctypes.POINTER(I32), ctypes.POINTER(I32)]),
+        "teuk_get_pass": (ctypes.c_int, [V, I32, ctypes.POINTER(I32)]),
         "teuk_suggest_dt": (ctypes.c_int, [P, I64, D, D, ctypes.POINTER(D)]),
         "teuk_free": (ctypes.c_int, [V]),
         "teuk_last_error": (ctypes.c_char_p, []),
@@ -128,6 +129,7 @@ EXPORTED = ("teuk_workspace_bytes", "teuk_init_grid", "teuk_set_coefficients", "
             "teuk_get_dt", "teuk_set_tile", "teuk_get_tile", "teuk_suggest_dt", "teuk_free",
             "teuk_last_error", "teuk_window_bytes", "teuk_step_n_store", "teuk_adjoint_workspace_bytes",
             "teuk_enable_adjoint", "teuk_adjoint_step_n", "teuk_set_adjoint_tile", "teuk_get_adjoint_tile",
+            "teuk_get_pass",
             "teuk_set_steps_per_pass", "teuk_get_steps_per_pass", "teuk_set_block_launch", "teuk_get_block_launch",
             "teuk_set_cache_policy", "teuk_get_cache_policy",
             "teuk_batch_workspace_bytes", "teuk_batch_init",
@@ -297,6 +299,18 @@ def teuk_get_adjoint_tile(h):
     r, w = ctypes.c_int32(), ctypes.c_int32()
     _check(_lib.teuk_get_adjoint_tile(h, ctypes.byref(r), ctypes.byref(w)))
     return r.value, w.value
+
+
+RUNS = ("steps", "series", "source", "source_series", "cotangents", "spin_tangent")
+PASSES = ("sweep", "tile", "block")
+
+
+def teuk_get_pass(h, run):
+    """How the launches of a run (one of RUNS) go: {"kind": one of PASSES, "steps", "cols", "rows", "waves", "samples"}."""
+    v = (ctypes.c_int32 * 6)()
+    _check(_lib.teuk_get_pass(h, RUNS.index(run), v))
+    out = dict(zip(("kind", "steps", "cols", "rows", "waves", "samples"), v))
+    return dict(out, kind=PASSES[out["kind"]], samples=bool(out["samples"]))
 
 
 def teuk_free(h):
@@ -638,6 +652,10 @@ class TeukGrid:
 
     def adjoint_tile(self):
         return teuk_get_adjoint_tile(self.handle)
+
+    def get_pass(self, run):
+        """How the launches of a run go on this grid (teuk_get_pass)."""
+        return teuk_get_pass(self.handle, run)
 
     def close(self):
         if getattr(self, "handle", None) is not None:

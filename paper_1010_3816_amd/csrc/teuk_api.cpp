@@ -826,6 +826,37 @@ struct InLoopCheck {
     }
 };
 
+// How the steps of a run go: launches of the tile pass, or of the block pass, or
+// sweeps.
+struct RunPlan {
+    bool tile, block;
+    bool three, two;  // sweeps take three, two steps a pass (single ones always)
+    bool fused1;      // a single step samples its input
+};
+
+// The tile pass is for Kerr coefficients, neither a window, a source nor a
+// check between steps, and a series of no more points than it samples; so is
+// the block pass, which may check.  Sweeps run several steps to a pass: three
+// where the pass has a kernel for it (Kerr coefficients, no window, three rows
+// or more) and no check falls between them.
+RunPlan run_plan(const teuk_grid* g, bool series, bool source, bool window) {
+    const bool kerr = g->p.coef_mode == TEUK_COEF_KERR, multi = g->steps_per_pass == 2;
+    const bool in_launch = kerr && !window && !source && (!series || g->p.n_extract <= kMaxBlockExt);
+    RunPlan p{};
+    p.tile = in_launch && multi && g->tile_steps > 0 && g->default_launch && g->check_every == 0;
+    p.block = in_launch && g->block_steps > 0;
+    p.two = multi && (!series || g->fused[1]);
+    p.three = p.two && kerr && !window && g->p.ntheta >= 3 && g->check_every == 0 &&
+              (!series || g->fused[pass_kind(3, source)]);
+    p.fused1 = g->fused[0];
+    return p;
+}
+
+// Whether cotangents go by the adjoint tile pass.
+bool adjoint_on_tiles(const teuk_grid* g) {
+    return g->adj_tile_steps > 0 && g->adj_default && g->steps_per_pass == 2 && g->p.n_extract <= kMaxBlockExt;
+}
+
 // n steps; optional extraction series and optional window of input states
 // (slot k = the state before step k, stride L.state bytes); h_f: the time
 // factors of the source term for the n steps (4 doubles per step), or
@@ -866,25 +897,19 @@ int step_n_impl(teuk_grid* g, int64_t n, void* d_series, void* d_window, const d
         if (!win) cur = 1 - cur;
         in = out;
     };
-    // Steps run several to a pass: three where the pass has a kernel for it
-    // (Kerr coefficients, no window, three rows or more) and no
-    // check falls between them, two otherwise.  A call's last
-    // four steps run as two and two rather than three and one, and the first
-    // step of a window run, which also copies its input, runs alone.
-    const bool multi = g->steps_per_pass == 2;
-    const bool fuse2 = multi && (!series || g->fused[1]);
-    const bool fuse3 = fuse2 && kerr && !win && g->p.ntheta >= 3 && g->check_every == 0 &&
-                       (!series || g->fused[pass_kind(3, h_f != nullptr)]);
+    // A call's last four steps run as two and two rather than three and one,
+    // and the first step of a window run, which also copies its input, alone.
+    const RunPlan plan = run_plan(g, series != nullptr, h_f != nullptr, win != nullptr);
     auto pass_steps = [&](int64_t k) -> int {
         const int64_t left = n - k;
         if (win && k == 0) return 1;
-        if (fuse3 && left >= 3 && left != 4) return 3;
-        return fuse2 && left >= 2 ? 2 : 1;
+        if (plan.three && left >= 3 && (left != 4 || !plan.two)) return 3;
+        return plan.two && left >= 2 ? 2 : 1;
     };
     // Sample of state j (after step j) goes to series row j-1.  Launches
     // with fused extraction sample their input and a pass its intermediate
     // states; otherwise a separate pass samples each new state.
-    const bool fused = g->fused[0];
+    const bool fused = plan.fused1;
     int64_t sampled = 0;
     InLoopCheck chk(g);
     auto extract_state = [&](const double2* u, int64_t j) -> int {
@@ -892,14 +917,8 @@ int step_n_impl(teuk_grid* g, int64_t n, void* d_series, void* d_window, const d
         sampled = j;
         return TEUK_OK;
     };
-    // Small grids: launches of the block pass (not with a window, a source
-    // term or a series of more extraction points than it samples).
-    const bool block = g->block_steps > 0 && kerr && !win && !h_f && (!series || ne <= kMaxBlockExt);
-    // The tile pass, in launches of about equal steps.
-    const bool tile = g->tile_steps > 0 && g->default_launch && g->steps_per_pass == 2 && kerr && !win && !h_f &&
-                      g->check_every == 0 && (!series || ne <= kMaxBlockExt);
     for (int64_t k = 0; k < n;) {
-        if (tile) {
+        if (plan.tile) {  // in launches of about equal steps
             const int64_t left = n - k, launches = (left + g->tile_steps - 1) / g->tile_steps;
             const int m = (int)((left + launches - 1) / launches);
             double2* out = next_buffer(k + m);
@@ -917,7 +936,7 @@ int step_n_impl(teuk_grid* g, int64_t n, void* d_series, void* d_window, const d
             g->steps += m;
             continue;
         }
-        if (block) {
+        if (plan.block) {
             const int m = (int)std::min<int64_t>(g->block_steps, n - k);
             double2* out = next_buffer(k + m);
             StepArgs ab = step_args(g);
@@ -1246,6 +1265,42 @@ int teuk_get_adjoint_tile(const teuk_grid* g, int32_t* rows_per_tile, int32_t* w
     return TEUK_OK;
 }
 
+int teuk_get_pass(const teuk_grid* g, int32_t run, teuk_pass* out) {
+    if (int rc = check_grid(g)) return rc;
+    if (!out) return fail(TEUK_E_INVALID_ARG, "output pointer is NULL");
+    if (run < TEUK_RUN_STEPS || run > TEUK_RUN_SPIN_TANGENT) return fail(TEUK_E_INVALID_ARG, "run=%d unknown", run);
+    auto tile = [&](const TileShape& t, int steps) {
+        *out = {TEUK_PASS_TILE, steps, t.cols, t.rows, t.waves, 1};
+        return TEUK_OK;
+    };
+    if (run == TEUK_RUN_COTANGENTS) {
+        if (adjoint_on_tiles(g)) return tile(g->adj_tile, g->adj_tile_steps);
+        const bool two = fused_adjoint_ok(g) && g->steps_per_pass == 2;
+        const int steps = two ? 2 : 1;
+        *out = {TEUK_PASS_SWEEP, steps, strip_cols(steps), g->adj_pass_rows[two ? kAdjTwo : kAdjOne], g->adj_wpb,
+                fused_adjoint_ok(g)};
+        return TEUK_OK;
+    }
+    if (run == TEUK_RUN_SPIN_TANGENT) {
+        const int rows = g->adj_pass_rows[kAdjSpinTangent];
+        *out = {TEUK_PASS_SWEEP, 1, kStripCols, rows, g->adj_wpb, fused_extraction_ok(g, kStripCols, rows, false)};
+        return TEUK_OK;
+    }
+    const bool series = run == TEUK_RUN_SERIES || run == TEUK_RUN_SOURCE_SERIES;
+    const bool source = run == TEUK_RUN_SOURCE || run == TEUK_RUN_SOURCE_SERIES;
+    const RunPlan p = run_plan(g, series, source, false);
+    if (p.tile) return tile(g->tile_shape, g->tile_steps);
+    if (p.block) {
+        *out = {TEUK_PASS_BLOCK, g->block_steps, g->block_cols, (int32_t)g->p.ntheta,
+                (int32_t)(g->block_cols * g->p.ntheta + kWave - 1) / kWave, 1};
+        return TEUK_OK;
+    }
+    const int steps = p.three ? 3 : p.two ? 2 : 1, kind = pass_kind(steps, source);
+    *out = {TEUK_PASS_SWEEP, steps, strip_cols(steps), g->pass_rows[kind], std::min(g->pass_wpb[kind], 4),
+            steps > 1 || p.fused1};
+    return TEUK_OK;
+}
+
 namespace {
 
 void adjoint_layout(teuk_grid* g, size_t* total) {
@@ -1401,7 +1456,7 @@ int adjoint_impl(teuk_grid* g, int64_t n, void* d_lam_phi, void* d_lam_pi, const
     const char* win = static_cast<const char*>(d_window);
     auto slot = [&](int64_t k) { return reinterpret_cast<const double2*>(win + (size_t)k * g->L.state); };
     int64_t k = n - 1;
-    if (!spin && g->adj_tile_steps > 0 && g->adj_default && g->steps_per_pass == 2 && ne <= kMaxBlockExt) {
+    if (!spin && adjoint_on_tiles(g)) {
         // cotangents on register tiles, in launches of about equal steps
         AdjArgs at = a;
         at.k.n_ext = ne;
