@@ -42,6 +42,12 @@ int fail(int code, const char* fmt, ...) {
 constexpr size_t kAlign = 256;
 constexpr int kMaxExtract = 4096;
 constexpr int kMaxFusedAdjointExtract = 16;  // extraction points handled inside the adjoint kernel
+// Most points of a grid whose equal ones count as one in a tile.  Every
+// wavefront looks through all points at its start, 80 ns each: with samples
+// inside the three-step pass and in launches of their own after single steps,
+// us per step, 64 equal points on 1600 x 128 8.8 and 10.3, on 6400 x 256 17.5 and
+// 21.6; 256 points 20.8 and 30.6 inside; 4096 points 320 and 435.
+constexpr int kMaxEqualExtract = 64;
 constexpr int64_t kMaxNr = int64_t(1) << 24;
 constexpr int64_t kMaxNth = int64_t(1) << 20;
 constexpr int kMinDefaultBlockSteps = 4;  // the default block pass takes at least this many steps a launch
@@ -278,9 +284,11 @@ TableArgs table_args(const teuk_grid* g) {
 
 // Fused extraction handles at most one point per tile (its state is held
 // in scalar registers of the tile's wavefront); the forward passes also any
-// number of points equal to it (observers that differ in azimuth alone).
+// number of points equal to it (observers that differ in azimuth alone), of
+// kMaxEqualExtract points in all.
 bool fused_extraction_ok(const teuk_grid* g, int strip_cols, int rows, bool equal_ok) {
     const auto& E = g->ext;
+    equal_ok = equal_ok && (int)E.size() <= kMaxEqualExtract;
     auto same = [](const ExtPoint& a, const ExtPoint& b) {
         return a.col == b.col && a.rowa == b.rowa && a.rowb == b.rowb && a.wr == b.wr && a.wa == b.wa && a.wb == b.wb;
     };
@@ -1698,6 +1706,7 @@ int batch_upload(teuk_batch* b) {
         points += g->p.n_extract;
         M.k.n_ext = g->p.n_extract;
         M.k.keep = keep;
+        b->fused = b->fused && g->p.n_extract <= kMaxEqualExtract;
         for (int m = 1; m <= kMaxPassSteps; ++m)
             b->fused = b->fused && fused_extraction_ok(g, strip_cols(m), g->rows, true);
         for (int m = 0; m < kMaxPassSteps; ++m) {
