@@ -11,6 +11,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <tuple>
 #include <vector>
 
 #include "../../include/teuk.h"
@@ -229,7 +230,14 @@ struct teuk_grid {
     // (teuk_set_tile sets them all)
     int pass_rows[kPassKinds] = {64, 64, 64, 64}, pass_wpb[kPassKinds] = {4, 4, 4, 4};
     int steps_per_pass = 2;  // 2: several steps in one pass (temporal blocking)
-    bool fused[kPassKinds] = {true, true, true, true};  // extraction fusable with the tiles of each pass
+    // runs with samples: the passes' tiles, whether they hold a point apiece, and
+    // the most steps a pass takes, without and with a source
+    int sample_rows[kPassKinds] = {64, 64, 64, 64}, sample_wpb[kPassKinds] = {4, 4, 4, 4};
+    bool fused[kPassKinds] = {true, true, true, true};
+    int sample_steps[2] = {3, 3};
+    int tan_sample_rows = 32;  // the same of the step with its spin derivative
+    bool tan_fused = true;
+    int cus = 256;
     int block_steps = 0;     // teuk_set_block_launch: steps per launch of the block pass (0: off)
     int block_cols = 0;      // columns a block-pass workgroup holds (0: not set)
     TileShape tile_shape;    // the tile pass's shape and steps per launch (0: off)
@@ -282,21 +290,32 @@ TableArgs table_args(const teuk_grid* g) {
     return a;
 }
 
+// The extraction points in the order of a sweep's tiles: by strip of `cols`
+// columns, row, and then so that equal ones are neighbours.
+std::vector<ExtPoint> tile_order(const teuk_grid* g, int cols) {
+    std::vector<std::pair<int64_t, int>> order(g->ext.size());
+    for (size_t i = 0; i < order.size(); ++i)
+        order[i] = {((int64_t)(g->ext[i].col / cols) << 32) + g->ext[i].rowa, (int)i};
+    auto rest = [](const ExtPoint& e) { return std::make_tuple(e.col, e.rowb, e.wr, e.wa, e.wb); };
+    std::sort(order.begin(), order.end(), [&](const auto& a, const auto& b) {
+        return a.first != b.first ? a.first < b.first : rest(g->ext[a.second]) < rest(g->ext[b.second]);
+    });
+    std::vector<ExtPoint> E;
+    for (const auto& o : order) E.push_back(g->ext[o.second]);
+    return E;
+}
+
 // Fused extraction handles at most one point per tile (its state is held
 // in scalar registers of the tile's wavefront); the forward passes also any
 // number of points equal to it (observers that differ in azimuth alone), of
-// kMaxEqualExtract points in all.
-bool fused_extraction_ok(const teuk_grid* g, int strip_cols, int rows, bool equal_ok) {
-    const auto& E = g->ext;
+// kMaxEqualExtract points in all.  E: tile_order(g, cols).
+bool one_point_a_tile(const std::vector<ExtPoint>& E, int cols, int rows, bool equal_ok) {
     equal_ok = equal_ok && (int)E.size() <= kMaxEqualExtract;
-    auto same = [](const ExtPoint& a, const ExtPoint& b) {
-        return a.col == b.col && a.rowa == b.rowa && a.rowb == b.rowb && a.wr == b.wr && a.wa == b.wa && a.wb == b.wb;
-    };
-    for (size_t i = 0; i < E.size(); ++i)
-        for (size_t k = i + 1; k < E.size(); ++k)
-            if (E[i].col / strip_cols == E[k].col / strip_cols && E[i].rowa / rows == E[k].rowa / rows &&
-                !(equal_ok && same(E[i], E[k])))
-                return false;
+    for (size_t i = 1; i < E.size(); ++i) {
+        const ExtPoint &a = E[i - 1], &b = E[i];
+        const bool same = a.col == b.col && a.rowa == b.rowa && a.rowb == b.rowb && a.wr == b.wr && a.wa == b.wa && a.wb == b.wb;
+        if (a.col / cols == b.col / cols && a.rowa / rows == b.rowa / rows && !(equal_ok && same)) return false;
+    }
     return true;
 }
 
@@ -314,11 +333,6 @@ bool fused_adjoint_ok(const teuk_grid* g) {
         if (near > kRowHits) return false;
     }
     return true;
-}
-
-void update_fusion(teuk_grid* g) {
-    for (int i = 0; i < kPassKinds; ++i)
-        g->fused[i] = fused_extraction_ok(g, strip_cols(std::min(i + 1, kMaxPassSteps)), g->pass_rows[i], true);
 }
 
 // Two states (a pass's input and output) up to this size stay in the
@@ -365,13 +379,13 @@ StepArgs step_args(const teuk_grid* g) {
 // Launch arguments of a pass of `steps` steps.  XCD runs of strips where each
 // XCD gets at least 8 (measured: 0.6-0.8 % faster on 25600 x 512 at 32-64 row
 // tiles, neutral on 6400 x 256).
-StepArgs pass_args(const teuk_grid* g, int steps, bool source) {
+StepArgs pass_args(const teuk_grid* g, int steps, bool source, bool sample) {
     const int kind = pass_kind(steps, source);
     StepArgs a = step_args(g);
     a.k.n_strips = (a.k.nr + strip_cols(steps) - 1) / strip_cols(steps);
-    a.k.rows = g->pass_rows[kind];
+    a.k.rows = sample ? g->sample_rows[kind] : g->pass_rows[kind];
     a.k.n_chunks = (a.k.nth + a.k.rows - 1) / a.k.rows;
-    a.k.n_ext = g->fused[kind] ? g->p.n_extract : 0;
+    a.k.n_ext = sample ? g->p.n_extract : 0;
     a.k.order = steps > 1 && a.k.n_strips >= 64 ? kTileOrderXcdStrip : kTileOrderDispatch;
     return a;
 }
@@ -454,17 +468,20 @@ constexpr SweepCost kAdjoint[kAdjKinds] = {{1, 1, 2, 1.4, 3.0, true, 0.0, 0.0, 0
                                            {2, 1, 2, 1.3, 3.0, true, 3.4, 0.725, 0.725},
                                            {2, 1, 2, 1.0, 3.0, true, 0.0, 0.0, 0.0},
                                            {1, 1, 2, 1.2, 3.0, true, 0.0, 0.0, 0.0},
-                                           {1, 1, 2, 1.0, 3.0, true, 0.0, 0.0, 0.0}};
+                                           {1, 1, 2, 1.0, 3.0, true, 4.9, 0.89, 1.08}};
 
-// The tile height of the lowest cost, at most 128 rows; us: the estimated time
-// of a step.  Tiles beyond one round of wavefronts wait for a slot; with
-// several rounds the last, partly filled one counts for less.
-int sweep_rows(int nr, int nth, int cus, const SweepCost& c, double* us = nullptr) {
+// The tile height of the lowest cost, at most 128 rows, of those that ok(rows)
+// allows (0 if none); us: the estimated time of a step.  Tiles beyond one round
+// of wavefronts wait for a slot; with several rounds the last, partly filled
+// one counts for less.
+template <class Ok>
+int sweep_rows(int nr, int nth, int cus, const SweepCost& c, double* us, Ok ok) {
     const int cols = strip_cols(c.steps);
     const int64_t strips = (nr + cols - 1) / cols;
     double best = 0.0;
-    int rows = 1;
+    int rows = 0;
     for (int r = 1; r <= std::min(nth, 128); ++r) {
+        if (!ok(r)) continue;
         const double x = (double)(strips * ((nth + r - 1) / r)) / (4.0 * cus);  // tiles per SIMD
         const int its = c.steps + (r + c.steps + c.group - 1) / c.group * c.group;
         double f = c.alone, rounds = 1.0;
@@ -478,13 +495,94 @@ int sweep_rows(int nr, int nth, int cus, const SweepCost& c, double* us = nullpt
             f = x + (whole - x) / std::max(1.0, rounds - 1.0);
         }
         const double t = (x > 1.0 && c.waves > 1 ? c.start2 : 3.0) * rounds + its * f;
-        if (r == 1 || t < best || (t == best && (x > 1.0 || c.longer))) {
+        if (rows == 0 || t < best || (t == best && (x > 1.0 || c.longer))) {
             best = t;
             rows = r;
             if (us) *us = (c.us0 + (x > 1.0 ? c.us : c.us_alone) * its * f) / c.steps;
         }
     }
     return rows;
+}
+
+int sweep_rows(int nr, int nth, int cus, const SweepCost& c, double* us = nullptr) {
+    return sweep_rows(nr, nth, cus, c, us, [](int) { return true; });
+}
+
+// Wavefronts a workgroup of a sweep: four, or one, to spread few tiles over the CUs.
+int sweep_waves(int nr, int nth, int cus, int steps, int rows) {
+    const int64_t tiles = (int64_t)((nr + strip_cols(steps) - 1) / strip_cols(steps)) * ((nth + rows - 1) / rows);
+    return tiles < (int64_t)cus * 4 ? 1 : 4;
+}
+
+// A launch that samples between passes, per state, besides the passes' own time.
+constexpr double kExtractUs = 2.5;
+
+// The tiles of runs with samples, after a change of the tiles: a pass's own
+// where each holds a point at most.  Otherwise, where the heights are the
+// grid's choice, the best ones among those that part the points, and as many
+// steps a pass as are estimated fastest with them, single steps with launches
+// that sample among the choices.  (Two observers of one strip at rows 12 and 14,
+// us per step in single steps, as their shared tile has it at the passes' own
+// heights, and with the points parted: 6400 x 256 24.0 and 14.4, 5003 x 197 17.8
+// and 10.5, 25600 x 512 172 and 87.)
+void update_fusion(teuk_grid* g) {
+    const int nr = (int)g->p.nr, nth = (int)g->p.ntheta;
+    const bool choose = g->rows == g->default_tile[0] && g->wpb == g->default_tile[1];
+    double us[kPassKinds] = {};
+    bool own[kPassKinds] = {};
+    for (int i = 0; i < kPassKinds; ++i) {
+        const int steps = kForward[i].steps, cols = strip_cols(steps);
+        const std::vector<ExtPoint> E = tile_order(g, cols);
+        g->sample_rows[i] = g->pass_rows[i];
+        g->sample_wpb[i] = g->pass_wpb[i];
+        own[i] = g->fused[i] = one_point_a_tile(E, cols, g->pass_rows[i], true);
+        if (own[i] || !choose) continue;
+        const int r = sweep_rows(nr, nth, g->cus, kForward[i], &us[i],
+                                 [&](int rows) { return one_point_a_tile(E, cols, rows, true); });
+        if (r == 0) continue;
+        g->fused[i] = true;
+        g->sample_rows[i] = r;
+        g->sample_wpb[i] = sweep_waves(nr, nth, g->cus, steps, r);
+    }
+    // single steps: sampling inside or not, whichever is estimated faster
+    double single_us = 0.0;
+    sweep_rows(nr, nth, g->cus, kForward[0], &single_us);
+    if (!own[0] && choose) {
+        single_us += kExtractUs;
+        if (g->fused[0] && us[0] < single_us) {
+            single_us = us[0];
+        } else {
+            g->fused[0] = false;
+        }
+    }
+    if (own[1]) sweep_rows(nr, nth, g->cus, kForward[1], &us[1]);
+    for (int source = 0; source < 2; ++source) {
+        const int three = pass_kind(3, source != 0);
+        int& steps = g->sample_steps[source];
+        steps = g->fused[three] ? 3 : g->fused[1] ? 2 : 1;
+        if (!choose || own[three]) continue;
+        // The estimates know no memory: passes of fewer steps, which move more of
+        // it, have to be estimated the faster by a margin.  (With a source one
+        // and two steps take 1.3 times their estimates: 6400 x 256 23.5 and 17.2.)
+        const double f = source ? 1.3 : 1.0;
+        if (steps == 3 && g->fused[1] && us[three] > 1.15 * f * us[1]) steps = 2;
+        if (steps > 1 && us[steps == 3 ? three : 1] * (steps == 3 ? 1.0 : f) > 1.5 * f * single_us) steps = 1;
+    }
+    // the step with its spin derivative, which samples two series
+    const SweepCost& c = kAdjoint[kAdjSpinTangent];
+    const int cols = strip_cols(c.steps);
+    const std::vector<ExtPoint> E = tile_order(g, cols);
+    g->tan_sample_rows = g->adj_pass_rows[kAdjSpinTangent];
+    g->tan_fused = one_point_a_tile(E, cols, g->tan_sample_rows, false);
+    if (!g->tan_fused && g->adj_default) {
+        double fused_us = 0.0, plain_us = 0.0;
+        sweep_rows(nr, nth, g->cus, c, &plain_us);
+        const int r = sweep_rows(nr, nth, g->cus, c, &fused_us, [&](int rows) { return one_point_a_tile(E, cols, rows, false); });
+        if (r > 0 && fused_us < plain_us + 2.0 * kExtractUs) {
+            g->tan_fused = true;
+            g->tan_sample_rows = r;
+        }
+    }
 }
 
 // Shape and steps per launch of the tile pass with the lowest estimated time
@@ -675,19 +773,18 @@ int teuk_init_grid(const teuk_params* p, void* hip_stream, void* d_workspace, si
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
             cus = 256;
+        g->cus = cus;
         default_tile(nr, nth, cus, &g->rows, &g->wpb);
         // Each pass on a tile of its own: the strips of a pass of k steps are
         // 64 - 2 k columns, and the rows that fill the chip once differ.  With
         // the one-step pass's rows for all, source runs of 6400 x 256 (steps in
         // pairs) took 18.8 us a step, with their own 16.8; three steps a pass
         // with the rows of the pass without a source 18.7, with their own 15.4.
-        // (four wavefronts a workgroup, or one, to spread few tiles over the CUs)
         for (int i = 0; i < kPassKinds; ++i) {
-            const int k = std::min(i + 1, kMaxPassSteps);
+            const int k = kForward[i].steps;
             const int r = sweep_rows(nr, nth, cus, kForward[i], k == i + 1 ? &sweep_us : nullptr);
-            const int64_t tiles = (int64_t)((nr + strip_cols(k) - 1) / strip_cols(k)) * ((nth + r - 1) / r);
             g->pass_rows[i] = g->default_rows[i] = r;
-            g->pass_wpb[i] = g->default_wpb[i] = tiles < cus * 4 ? 1 : 4;
+            g->pass_wpb[i] = g->default_wpb[i] = sweep_waves(nr, nth, cus, k, r);
         }
     }
     // The block pass: one thread per point of (columns x all rows).  Default
@@ -853,9 +950,9 @@ RunPlan run_plan(const teuk_grid* g, bool series, bool source, bool window) {
     RunPlan p{};
     p.tile = in_launch && multi && g->tile_steps > 0 && g->default_launch && g->check_every == 0;
     p.block = in_launch && g->block_steps > 0;
-    p.two = multi && (!series || g->fused[1]);
-    p.three = p.two && kerr && !window && g->p.ntheta >= 3 && g->check_every == 0 &&
-              (!series || g->fused[pass_kind(3, source)]);
+    const int most = series ? g->sample_steps[source] : kMaxPassSteps;
+    p.two = multi && most >= 2 && (!series || g->fused[1]);
+    p.three = multi && most == 3 && kerr && !window && g->p.ntheta >= 3 && g->check_every == 0;
     p.fused1 = g->fused[0];
     return p;
 }
@@ -881,7 +978,7 @@ int step_n_impl(teuk_grid* g, int64_t n, void* d_series, void* d_window, const d
     StepArgs args[kMaxPassSteps];
     for (int m = 1; m <= kMaxPassSteps; ++m) {
         StepArgs& a = args[m - 1];
-        a = pass_args(g, m, h_f != nullptr);
+        a = pass_args(g, m, h_f != nullptr, series && g->fused[pass_kind(m, h_f != nullptr)]);
         if (h_f) {
             a.src_i = reinterpret_cast<const double2*>(g->sws);
             a.src_h = reinterpret_cast<const double2*>(g->sws + source_plane_bytes(g));
@@ -978,7 +1075,8 @@ int step_n_impl(teuk_grid* g, int64_t n, void* d_series, void* d_window, const d
         a.series_mid = sample ? series + k * ne : nullptr;
         if (h_f)
             for (int j = 0; j < 4 * m; ++j) a.k.sf[j] = g->p.dt * h_f[4 * k + j];
-        HIP_TRY(launch_pass(a, m, kerr, std::min(g->pass_wpb[pass_kind(m, h_f != nullptr)], 4), g->stream));
+        const int kind = pass_kind(m, h_f != nullptr);
+        HIP_TRY(launch_pass(a, m, kerr, std::min(sample ? g->sample_wpb[kind] : g->pass_wpb[kind], 4), g->stream));
         if (sample) sampled = k + m - 1;
         advance(out);
         k += m;
@@ -1263,6 +1361,7 @@ int teuk_set_adjoint_tile(teuk_grid* g, int32_t rows_per_tile, int32_t waves_per
     for (int& r : g->adj_pass_rows) r = rows_per_tile;
     g->adj_wpb = waves_per_block;
     g->adj_default = false;
+    update_fusion(g);
     return TEUK_OK;
 }
 
@@ -1290,8 +1389,7 @@ int teuk_get_pass(const teuk_grid* g, int32_t run, teuk_pass* out) {
         return TEUK_OK;
     }
     if (run == TEUK_RUN_SPIN_TANGENT) {
-        const int rows = g->adj_pass_rows[kAdjSpinTangent];
-        *out = {TEUK_PASS_SWEEP, 1, kStripCols, rows, g->adj_wpb, fused_extraction_ok(g, kStripCols, rows, false)};
+        *out = {TEUK_PASS_SWEEP, 1, kStripCols, g->tan_sample_rows, g->adj_wpb, g->tan_fused};
         return TEUK_OK;
     }
     const bool series = run == TEUK_RUN_SERIES || run == TEUK_RUN_SOURCE_SERIES;
@@ -1304,8 +1402,9 @@ int teuk_get_pass(const teuk_grid* g, int32_t run, teuk_pass* out) {
         return TEUK_OK;
     }
     const int steps = p.three ? 3 : p.two ? 2 : 1, kind = pass_kind(steps, source);
-    *out = {TEUK_PASS_SWEEP, steps, strip_cols(steps), g->pass_rows[kind], std::min(g->pass_wpb[kind], 4),
-            steps > 1 || p.fused1};
+    const bool samples = steps > 1 || p.fused1, sample = series && samples;
+    *out = {TEUK_PASS_SWEEP, steps, strip_cols(steps), sample ? g->sample_rows[kind] : g->pass_rows[kind],
+            std::min(sample ? g->sample_wpb[kind] : g->pass_wpb[kind], 4), samples};
     return TEUK_OK;
 }
 
@@ -1594,7 +1693,11 @@ int teuk_step_n_spin_tangent(teuk_grid* g, int64_t n, void* d_series, void* d_ts
     // the launches sample their input (row k-1 of a series: the state after
     // step k); the call's last state, or every state when two extraction
     // points share a tile, by a separate pass
-    const bool fused = fused_extraction_ok(g, kStripCols, a.k.rows, false);
+    const bool fused = (series || tseries) && g->tan_fused;
+    if (fused) {
+        a.k.rows = g->tan_sample_rows;
+        a.k.n_chunks = (a.k.nth + a.k.rows - 1) / a.k.rows;
+    }
     a.k.n_ext = fused ? ne : 0;
     auto extract = [&](int64_t j) -> int {
         if (series) HIP_TRY(launch_extract(g->u(g->cur), g->L.pitch, ext, ne, series + (j - 1) * ne, g->stream));
@@ -1708,7 +1811,7 @@ int batch_upload(teuk_batch* b) {
         M.k.keep = keep;
         b->fused = b->fused && g->p.n_extract <= kMaxEqualExtract;
         for (int m = 1; m <= kMaxPassSteps; ++m)
-            b->fused = b->fused && fused_extraction_ok(g, strip_cols(m), g->rows, true);
+            b->fused = b->fused && one_point_a_tile(tile_order(g, strip_cols(m)), strip_cols(m), g->rows, true);
         for (int m = 0; m < kMaxPassSteps; ++m) {
             M.strips[m] = (a.k.nr + strip_cols(m + 1) - 1) / strip_cols(m + 1);
             M.tile_begin[m] = tiles[m];

@@ -68,3 +68,69 @@ def test_equal_points_of_a_batch(gpu, n_points):
         s.batch.step(2)
         assert np.array_equal(got[k].ravel(), s.batch.extract().cpu().numpy()), k
     s.close()
+
+
+NEAR = {  # (fractional) columns and rows; whether some height parts the points
+    "two": ([1203.2, 1210.4], [12.7, 14.9], True),
+    "four": ([1203.2, 1210.4, 1222.5, 1230.0], [3.7, 14.9, 24.5, 60.2], True),
+    "one row": ([1203.2, 1210.4], [14.7, 14.9], False),
+    "equal and near": ([1203.2, 1203.2, 1210.4], [12.7, 12.7, 14.9], True),
+}
+
+
+@pytest.mark.parametrize("source", [False, True])
+@pytest.mark.parametrize("grid", [(5003, 197), (6400, 256)])
+@pytest.mark.parametrize("name", list(NEAR))
+def test_near_points(gpu, name, grid, source):
+    """Observers that share a tile of the passes' own heights: the passes take
+    heights that part them, and only where there is none single steps."""
+    nr, nth = grid
+    cols, rows, parts = NEAR[name]
+    g = _grid(gpu, nr, nth, cols, rows)
+    p = g.get_pass("source_series" if source else "series")
+    assert p["kind"] == "sweep" and p["samples"] == parts and (p["steps"] > 1) == parts, p
+    rng = np.random.default_rng(7)
+    prof = [rng.standard_normal((nth, w)) + 1j * rng.standard_normal((nth, w)) for w in (nr, nr - 1)] if source else None
+    _check_series(g, 7, inputs.random_state(nr, nth, seed=2), prof)
+    g.close()
+
+
+@pytest.mark.parametrize("name", list(NEAR))
+def test_near_points_spin_derivative(gpu, name):
+    """The same of the step with its spin derivative: on 1600 x 128 its launches
+    sample two points of one strip at rows 12 and 14."""
+    cols, rows, parts = NEAR[name]
+    g = _grid(gpu, 1600, 128, cols, rows)
+    if name == "two":
+        assert g.get_pass("spin_tangent")["samples"]
+    u, v = inputs.random_state(1600, 128, seed=3), inputs.random_state(1600, 128, seed=4)
+    er = [g.params.extract_rstar[k] for k in range(g.n_extract)]
+    et = [g.params.extract_theta[k] for k in range(g.n_extract)]
+    out = []
+    for tile in (None, (1, 4)):
+        if tile:
+            g.set_adjoint_tile(*tile)
+        g.set_initial_data(*_cuda(u))
+        g.set_spin_tangent(*_cuda(v))
+        out.append([t.cpu().numpy() for t in g.step_spin_tangent(5)])
+        assert np.array_equal(out[-1][0][-1], g.extract(er, et).cpu().numpy())
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+    g.close()
+
+
+def test_tile_of_ones_own_keeps_its_height(gpu):
+    """A tile given by the caller is not changed for the points' sake: three
+    steps where its three-step tiles hold one point each, else two, else one."""
+    g = _grid(gpu, 5003, 197, [1203.2, 1210.4], [12.7, 14.9])
+    for rows, fused in ((13, True), (14, True), (16, False), (40, False), (7, True)):
+        g.set_tile(rows, 4)
+        p = g.get_pass("series")
+        assert p["rows"] == rows and p["samples"] == fused and p["steps"] == (3 if fused else 1), p
+    # two columns that share a strip of 60 columns and none of 58
+    g.close()
+    g = _grid(gpu, 5003, 197, [1201.2, 1219.4], [12.7, 13.9])
+    g.set_tile(40, 4)
+    assert (1201 // 58 != 1219 // 58) and (1201 // 60 == 1219 // 60)
+    assert g.get_pass("series")["steps"] == 3
+    _check_series(g, 7, inputs.random_state(5003, 197, seed=5))
+    g.close()
