@@ -247,9 +247,11 @@ int teuk_get_steps_per_pass(const teuk_grid* g, int32_t* steps_per_pass);
  * them, several steps per pass and no in-loop check, a grid with Kerr
  * coefficients may take the tile pass in their place (several steps per launch
  * on register tiles, where that is estimated to be fastest: grids up to about
- * 4 x 10^5 points), for series of up to 8 points; results are identical.  Any
+ * 8 x 10^5 points), for series of up to 8 points; results are identical.  Any
  * other tile or block launch set turns it off, as does steps = 0 here;
- * teuk_set_tile with the default tile brings it back. */
+ * teuk_set_tile with the default tile brings it back where the block launch is
+ * the default one too (steps = 0 where the default is off, whatever columns
+ * were set in between). */
 int teuk_set_block_launch(teuk_grid* g, int32_t steps, int32_t cols);
 int teuk_get_block_launch(const teuk_grid* g, int32_t* steps, int32_t* cols);
 

@@ -1264,7 +1264,8 @@ namespace {
 // off: the block pass was turned off, which leaves the sweeps.
 void select_launch(teuk_grid* g, bool off) {
     const bool tile = g->rows == g->default_tile[0] && g->wpb == g->default_tile[1];
-    const bool block = g->block_steps == g->default_block[0] && g->block_cols == g->default_block[1];
+    const bool block = g->block_steps == g->default_block[0] &&
+                       (g->block_steps == 0 || g->block_cols == g->default_block[1]);  // off: whatever its columns
     g->default_launch = tile && block && !off;
     for (int k = 0; k < kPassKinds; ++k) {
         g->pass_rows[k] = tile ? g->default_rows[k] : g->rows;
