@@ -326,11 +326,13 @@ int teuk_enable_adjoint(teuk_grid* g, void* d_adj_workspace, size_t bytes);
 /* Launch shape of the adjoint kernels: theta rows per wavefront tile (1 ..
  * ntheta) and wavefronts per workgroup (1, 2 or 4, default 4; a workgroup
  * takes consecutive tiles of the strip-major tile list, and at most
- * 1 + the chunks per strip of them).  Default rows, at most 16: for the
- * spin-gradient (and one-step) kernel the fewest whose tiles fit 7/8 of one
- * round of two wavefronts per SIMD, leaving the rest to a recompute running
- * beside it; for the two-step cotangent kernel the fewest that fit the whole
- * round.  Setting the tile sets both; get returns the spin-gradient kernel's.
+ * 1 + the chunks per strip of them).  The default that get reports has at most
+ * 16 rows: the fewest whose tiles fit 7/8 of one round of two wavefronts per
+ * SIMD.  While it is set, each of the kernels takes a height of its own (one
+ * and two steps, with the spin gradient from states or from tangents, the steps
+ * that carry a tangent), and cotangents may go by the adjoint tile pass; another
+ * tile applies to all of them and turns that pass off, and setting the default
+ * again brings the grid's own choice back.
  * The cotangents do not depend on it; dL/da is summed per tile, so its last
  * bits may.  TEUK_E_INVALID_ARG outside these ranges. */
 int teuk_set_adjoint_tile(teuk_grid* g, int32_t rows_per_tile, int32_t waves_per_block);

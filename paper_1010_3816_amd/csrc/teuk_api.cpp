@@ -208,6 +208,7 @@ constexpr int pass_kind(int steps, bool source) {
 // step with the spin gradient from states; one step otherwise; two steps; two
 // with the tangents' dot products; the step that stores its tangent; the step
 // with its spin derivative.
+constexpr int kAdjWaves = 4;  // wavefronts a workgroup until teuk_set_adjoint_tile
 enum AdjKind { kAdjStates, kAdjOne, kAdjTwo, kAdjTwoDot, kAdjTangent, kAdjSpinTangent, kAdjKinds };
 
 }  // namespace
@@ -251,11 +252,12 @@ struct teuk_grid {
     // adjoint (teuk_enable_adjoint)
     char* aws = nullptr;      // adjoint workspace
     size_t aoff_lam[2]{}, aoff_da = 0, aoff_slots = 0, aoff_sum = 0;
-    int adj_rows = 32, adj_wpb = 4, adj_strips = 0;  // the tile as teuk_get_adjoint_tile reports it
-    int adj_pass_rows[kAdjKinds] = {};               // the kernels' own heights (teuk_set_adjoint_tile sets them all)
+    int adj_rows = 32, adj_wpb = kAdjWaves, adj_strips = 0;  // the tile as teuk_get_adjoint_tile reports it
+    int adj_pass_rows[kAdjKinds] = {};               // the kernels' heights, and as teuk_init_grid chose them
+    int default_adj_rows = 0, default_adj_pass_rows[kAdjKinds] = {};
     TileShape adj_tile;       // adjoint tile pass: shape and steps per launch (0: off)
     int adj_tile_steps = 0;
-    bool adj_default = true;  // teuk_set_adjoint_tile has not been called
+    bool adj_default = true;  // the adjoint tile is as teuk_init_grid chose it
     int cache_policy = TEUK_CACHE_AUTO;  // teuk_set_cache_policy
     // forward-mode spin derivative (teuk_enable_spin_tangent): v = du/da in two buffers
     char* tws = nullptr;
@@ -822,7 +824,9 @@ int teuk_init_grid(const teuk_params* p, void* hip_stream, void* d_workspace, si
     // until teuk_set_adjoint_tile.
     g->adj_rows = adjoint_rows(nr, nth, (int64_t)cus * 7, kStripCols);
     for (int i = 0; i < kAdjKinds; ++i)
-        g->adj_pass_rows[i] = sweep_rows(nr, nth, cus, kAdjoint[i], i == kAdjTwo ? &sweep_us : nullptr);
+        g->adj_pass_rows[i] = g->default_adj_pass_rows[i] =
+            sweep_rows(nr, nth, cus, kAdjoint[i], i == kAdjTwo ? &sweep_us : nullptr);
+    g->default_adj_rows = g->adj_rows;
     // (the adjoint tile pass: 1.17 times the forward one's instructions.  us per
     // step, tile pass and sweeps: 2000 x 256 7.2 and 8.1, 12000 x 64 10.3 and 9.9,
     // 4000 x 200 10.4 and 9.8, 5003 x 197 12.9 and 11.1)
@@ -1359,9 +1363,10 @@ int teuk_set_adjoint_tile(teuk_grid* g, int32_t rows_per_tile, int32_t waves_per
     if (waves_per_block != 1 && waves_per_block != 2 && waves_per_block != 4)
         return fail(TEUK_E_INVALID_ARG, "waves_per_block=%d not in {1, 2, 4}", waves_per_block);
     g->adj_rows = rows_per_tile;
-    for (int& r : g->adj_pass_rows) r = rows_per_tile;
     g->adj_wpb = waves_per_block;
-    g->adj_default = false;
+    // the tile as teuk_init_grid chose it: the kernels' own heights and the tile pass again
+    g->adj_default = rows_per_tile == g->default_adj_rows && waves_per_block == kAdjWaves;
+    for (int i = 0; i < kAdjKinds; ++i) g->adj_pass_rows[i] = g->adj_default ? g->default_adj_pass_rows[i] : rows_per_tile;
     update_fusion(g);
     return TEUK_OK;
 }

@@ -46,3 +46,20 @@ def test_block_launch_default_again(gpu):
     g.set_block_launch(*block)
     assert _passes(g) == before
     g.close()
+
+
+@pytest.mark.parametrize("nr,nth", [(1600, 64), (6400, 256)])
+def test_adjoint_tile_set_as_it_was(gpu, nr, nth):
+    """The adjoint tile set to the values that the getter returned, and back to
+    them after others: the kernels' own heights and the tile pass."""
+    g = _grid(gpu, nr, nth)
+    tile, before = g.adjoint_tile(), _passes(g)
+    g.set_adjoint_tile(*tile)
+    assert _passes(g) == before
+    g.set_adjoint_tile(7, 2)
+    p = g.get_pass("cotangents")
+    assert (p["kind"], p["rows"], p["waves"]) == ("sweep", 7, 2)
+    assert g.get_pass("spin_tangent")["rows"] == 7
+    g.set_adjoint_tile(*tile)
+    assert _passes(g) == before
+    g.close()

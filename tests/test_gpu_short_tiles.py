@@ -104,7 +104,7 @@ def test_adjoint(gpu, kind, spp, m):
     exp = o.adjoint_evolve(*o.project(*u), n, er, et, gser)
     ref = None
     for rows in reversed(HEIGHTS):
-        g.set_adjoint_tile(rows, 4 if rows % 2 else 2)
+        g.set_adjoint_tile(rows, 4 if rows > 1 and rows % 2 else 2)
         lam = _cuda((zero, zero))
         dlda = g.adjoint(n, *lam, _cuda([gser])[0], win, project_initial=True, spin=kind != "cotangents",
                          tangent=kind == "tangents")
@@ -130,7 +130,7 @@ def test_tangents(gpu, m):
     win = g.new_window(n)
     ref = None
     for rows in reversed(HEIGHTS):
-        g.set_adjoint_tile(rows, 4 if rows % 2 else 2)
+        g.set_adjoint_tile(rows, 4 if rows > 1 and rows % 2 else 2)
         g.set_initial_data(*_cuda(u))
         g.set_spin_tangent(*_cuda(v))
         out = [*g.step_spin_tangent(n)]
