@@ -8,13 +8,16 @@ of the persistent launch.  Candidates are timed with HIP events on the
 grid's own stream (median of three windows), the fastest is applied (for a
 single grid only if it beats the library's default by a margin), and the
 choice is cached in a JSON
-file keyed by device and problem shape ($TEUK_TUNE_CACHE, default
-~/.cache/paper_1010_3816_amd/launch.json).  Results of the kernels do not
+file keyed by device, built library and problem shape ($TEUK_TUNE_CACHE, default
+~/.cache/paper_1010_3816_amd/launch.json): a launch that was fastest with other
+kernels says nothing about these.  Results of the kernels do not
 depend on the launch shape, only their speed does.
 
 Timing advances the state of the grid or batch: tune before setting the
 initial data, or set it again afterwards.
 """
+import functools
+import hashlib
 import json
 import os
 
@@ -53,9 +56,15 @@ def _store_cache(key, value):
         pass  # a read-only home only loses the cache
 
 
+@functools.lru_cache(maxsize=None)
+def _library_key(path):
+    with open(path, "rb") as f:
+        return hashlib.sha256(f.read()).hexdigest()[:16]
+
+
 def _device_key(torch, device):
     p = torch.cuda.get_device_properties(device)
-    return f"{getattr(p, 'gcnArchName', p.name)}/{p.multi_processor_count}cu"
+    return f"{getattr(p, 'gcnArchName', p.name)}/{p.multi_processor_count}cu|{_library_key(binding.LIB_PATH)}"
 
 
 def _time(torch, stream, fn, steps, reps=3):
@@ -122,7 +131,9 @@ def tune_grid(grid, rows=None, waves=GRID_WAVES, steps=20, use_cache=True, margi
             return dict(hit, cached=True)
     cus = torch.cuda.get_device_properties(grid.device).multi_processor_count
     if rows is None:
-        rows = tuple(GRID_ROWS) + tuple(round_rows(grid.nr, grid.ntheta, cus))
+        # strips of the pass that most steps go by: three steps, two with user coefficients
+        cols = 60 if grid.params.coef_mode == binding.TEUK_COEF_USER else 58
+        rows = tuple(GRID_ROWS) + tuple(round_rows(grid.nr, grid.ntheta, cus, cols))
     if blocks is None:
         blocks = block_candidates(grid.nr, grid.ntheta, cus)
     default = grid.tile() + grid.block_launch()
@@ -155,8 +166,6 @@ def tune_batch(batch, rows=BATCH_ROWS, waves=BATCH_WAVES, blocks_per_cu=(1, 2, 4
     """Pick (rows_per_tile, waves_per_block, n_blocks) for a TeukBatch."""
     torch = batch.torch
     shapes = ",".join(f"{m['nr']}x{m['ntheta']}" for m in batch.members)
-    import hashlib
-
     key = f"batch|{_device_key(torch, batch.device)}|{hashlib.sha256(shapes.encode()).hexdigest()[:16]}"
     if use_cache:
         hit = _load_cache().get(key)
