@@ -334,6 +334,7 @@ __device__ __forceinline__ void tangent_sweep(gin_t u_in, gin_t v_in, gout_t u_o
         ++t;
     }
     if constexpr (V) {
+        wave_lds_handover();
         if (e_id >= 0 && lane < 2) {  // lane 0: the sample of u, lane 1: of v
             double2* out = lane == 0 ? series_u : series_v;
             if (out != nullptr) {

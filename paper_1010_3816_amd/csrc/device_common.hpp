@@ -179,6 +179,15 @@ __device__ __forceinline__ void st_row(__amdgpu_buffer_rsrc_t r, uint32_t off, c
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, w), r, off, 0, KEEP ? 0 : 2);
 }
 
+// Before a lane reads what other lanes of its wavefront wrote to LDS.  LDS
+// operations of a wavefront are done in order, so nothing is waited for; it
+// keeps the compiler, which sees one lane, from moving the reads up.
+__device__ __forceinline__ void wave_lds_handover() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // sched_barrier mask: all classes the scheduler may move across, scalar
 // memory not among them.
 constexpr int kAllButScalarLoads = 0x3FF;

@@ -350,6 +350,7 @@ __device__ __forceinline__ void sweep(gin_t __restrict__ u_in, gout_t __restrict
         tail(tail, Const<0>{});
     }
 
+    wave_lds_handover();
     if (e_id >= 0 && lane < K) {
         // lane j: the sample of step j's input
         double2* out = lane == 0 ? series0 : lane == 1 ? series1 : series2;
