@@ -807,7 +807,7 @@ TEUK_BATCH_KERNEL(lw_batch3_kernel, 3)
 // ...: a launch's y dimension is capped (kMaxGridY) while ntheta may reach 2^20.
 constexpr int kMaxGridY = 65535;
 
-// Both planes of a state in one launch (blockIdx.z: Phi, Pi).
+// Both planes of a state in one launch (blockIdx.z: Phi, Pi; export: from f0 on).
 __global__ void import_kernel(const double2* __restrict__ phi, const double2* __restrict__ pi, double2* __restrict__ u,
                               int nr, int nth, int pitch) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x, f = blockIdx.z;
@@ -822,9 +822,9 @@ __global__ void import_kernel(const double2* __restrict__ phi, const double2* __
     }
 }
 
-__global__ void export_kernel(const double2* __restrict__ u, double2* __restrict__ phi, double2* __restrict__ pi,
-                              int nr, int nth, int pitch) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x, f = blockIdx.z;
+__global__ void export_kernel(const double2* __restrict__ u, double2* phi, double2* pi,
+                              int nr, int nth, int pitch, int f0) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x, f = f0 + blockIdx.z;
     double2* dst = f == 0 ? phi : pi;
     if (i >= nr) return;
     for (int j = blockIdx.y; j < nth; j += gridDim.y)
@@ -1045,8 +1045,13 @@ hipError_t launch_import(const double2* phi, const double2* pi, double2* u, int 
 }
 
 hipError_t launch_export(const double2* u, double2* phi, double2* pi, int nr, int nth, int pitch, hipStream_t s) {
-    const dim3 block(256), grid((nr + 255) / 256, std::min(nth, kMaxGridY), 2);
-    hipLaunchKernelGGL(export_kernel, grid, block, 0, s, u, phi, pi, nr, nth, pitch);
+    // outputs that overlap get Phi first, then Pi, as if copied one after the other
+    const uintptr_t a = reinterpret_cast<uintptr_t>(phi), b = reinterpret_cast<uintptr_t>(pi);
+    const uintptr_t bytes = (uintptr_t)nr * nth * sizeof(double2);
+    const int planes = a < b + bytes && b < a + bytes ? 1 : 2;
+    const dim3 block(256), grid((nr + 255) / 256, std::min(nth, kMaxGridY), planes);
+    for (int f = 0; f < 2; f += planes)
+        hipLaunchKernelGGL(export_kernel, grid, block, 0, s, u, phi, pi, nr, nth, pitch, f);
     return hipGetLastError();
 }
 
