@@ -9,6 +9,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <limits>
 #include <mutex>
 #include <string>
 #include <tuple>
@@ -348,6 +349,10 @@ bool keeps_states(const teuk_grid* g) {
     return 2 * g->L.state <= kKeepStatesBytes;
 }
 
+// 1 / x for the factor that undoes a step's own: the product with what a step of
+// 1e-310 leaves of a coefficient (zero) has to be zero, not 0 x infinity.
+double finite_inverse(double x) { return std::min(1.0 / x, std::numeric_limits<double>::max()); }
+
 StepArgs step_args(const teuk_grid* g) {
     StepArgs a{};
     StepScalars& k = a.k;
@@ -360,8 +365,8 @@ StepArgs step_args(const teuk_grid* g) {
     k.dt = g->p.dt;
     k.hdt = 0.5 * g->p.dt;
     k.qdt = 0.25 * g->p.dt;
-    k.kap_h = 1.0 / k.hdt;
-    k.kap_i = 1.0 / k.qdt;
+    k.kap_h = finite_inverse(k.hdt);
+    k.kap_i = finite_inverse(k.qdt);
     k.dt_dr = g->p.dt / g->dr;
     k.hdt_dr = 0.5 * g->p.dt / g->dr;
     k.inv_dth2 = 1.0 / (g->dth * g->dth);
@@ -1491,8 +1496,8 @@ AdjArgs adjoint_args(const teuk_grid* g, AdjKind kind) {
     a.rad = g->at<double>(g->L.off_rad);
     a.rad_da = reinterpret_cast<const double*>(g->aws + g->aoff_da);
     a.k.qdt = 0.25 * g->p.dt;
-    a.k.kap_h = 1.0 / (0.5 * g->p.dt);
-    a.k.kap_i = 1.0 / a.k.qdt;
+    a.k.kap_h = finite_inverse(a.k.hdt);
+    a.k.kap_i = finite_inverse(a.k.qdt);
     a.ang = g->at<double>(g->L.off_ang);
     a.ext = g->at<ExtPoint>(g->L.off_ext);
     return a;
