@@ -289,13 +289,10 @@ def workload_leg(name):
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1)
     assert g.check_finite(), "state became non-finite"
-    rows, wpb = g.tile()
     out = {"workload": name, "steps": n, "n_extract": g.n_extract, "ms_per_step": ms / n,
            "value": w["nr"] * w["ntheta"] * n / (ms * 1e-3), "unit": "grid-point updates/s",
-           "tile_rows": rows, "waves_per_block": wpb,
-           # small grids: steps per launch of the block pass (0: the sweeps, with the tile above)
-           # and the columns a workgroup holds
-           "block_steps": g.block_launch()[0], "block_cols": g.block_launch()[1]}
+           # how its launches go: sweep, tile pass or block pass, steps per launch, tile
+           "pass": g.get_pass("series" if g.n_extract else "steps")}
     g.close()
     return out
 
@@ -305,7 +302,7 @@ def source_leg(name="kerr_a0.99_25600x512", steps=1000, tile=None):
     localised source f(t) g(r*, theta) (a blob at r* = centre + 20 on the
     equator, f = 50 exp(0.4 i t)), `steps` steps of teuk_step_n_source in the
     tile `tile` (rows, waves_per_block), timed with HIP events on the grid's
-    stream.  Algorithmic bytes: the state's 64 B per point per pass of two
+    stream.  Algorithmic bytes: the state's 64 B per point per pass of three
     steps and the profile's 32 B (g at the column and at the half point, read
     once a pass), 32 B per update."""
     import torch
@@ -333,11 +330,12 @@ def source_leg(name="kerr_a0.99_25600x512", steps=1000, tile=None):
     ms = e0.elapsed_time(e1)
     assert g.check_finite(), "state became non-finite"
     ups = w["nr"] * w["ntheta"] * steps / (ms * 1e-3)
-    rows, wpb = g.tile()
+    p = g.get_pass("source")
     out = {"workload": name, "source": "localised blob at r* = centre + 20, theta = pi/2; f = 50 exp(0.4 i t)",
            "steps": steps, "ms_per_step": ms / steps, "value": ups, "unit": "grid-point updates/s",
-           "steps_per_pass": g.steps_per_pass(), "bytes_per_update": SOURCE_BYTES_PER_UPDATE,
-           "hbm_frac": SOURCE_BYTES_PER_UPDATE * ups / 1e9 / HBM_PEAK_GBS, "tile_rows": rows, "waves_per_block": wpb}
+           "steps_per_pass": p["steps"], "bytes_per_update": SOURCE_BYTES_PER_UPDATE,
+           "hbm_frac": SOURCE_BYTES_PER_UPDATE * ups / 1e9 / HBM_PEAK_GBS, "tile_rows": p["rows"],
+           "waves_per_block": p["waves"]}
     g.close()
     return out
 
@@ -538,7 +536,9 @@ def main():
     copy_lib = library_copy_bandwidth(torch, g, phi0, pi0)
     copy_gbs = max(copy_torch, copy_lib)
     traffic_gbs = traffic / launch_s / 1e9 if traffic else None
-    rows, wpb = g.tile()
+    dominant = g.get_pass("series" if g.n_extract else "steps")
+    rows, wpb = dominant["rows"], dominant["waves"]
+    tile = g.tile()
     valu = VALU_PER_UPDATE[spl] * spl * pts / launch_s / 1e12
     # The one-step pass streams its 64 B per update at a plain copy's rate;
     # the three-step pass moves its measured traffic (halo rows and strip
@@ -606,7 +606,7 @@ def main():
         wl["ratio_to_single"] = wl["value"] / ups
         out["waveform"] = wl
         out["adjoint"] = adjoint_leg()
-        sl = source_leg(args.workload, tile=(rows, wpb))
+        sl = source_leg(args.workload, tile=tile)
         sl["ratio_to_homogeneous"] = sl["value"] / ups
         out["source"] = sl
     if not args.no_cpu_baseline:

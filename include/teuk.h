@@ -210,13 +210,17 @@ int teuk_set_tile(teuk_grid* g, int32_t rows_per_tile, int32_t waves_per_block);
 int teuk_get_tile(const teuk_grid* g, int32_t* rows_per_tile, int32_t* waves_per_block);
 
 /* Steps per pass over the state: 1, or 2 (default) for several.  With 2,
- * teuk_step_n takes three steps in one kernel pass, and two at a call's end,
- * with user coefficients, fewer than three rows or the in-loop finite check (temporal blocking: the intermediate states stay in registers,
- * so the state is read and written once per pass), and an odd last step
- * alone; the per-point arithmetic is that of single steps, so results are
- * identical.  teuk_step_n_store takes two and keeps the intermediate state of
- * a pass in its window slot; its first step runs alone (it also copies its
- * input).  A pass whose extraction points share one of its tiles is not taken.
+ * teuk_step_n takes three steps in one kernel pass (temporal blocking: the
+ * intermediate states stay in registers, so the state is read and written once
+ * per pass), two at a call's end, with user coefficients, fewer than three rows
+ * or the in-loop finite check, and an odd last step alone; the per-point
+ * arithmetic is that of single steps, so results are identical.
+ * teuk_step_n_store takes two and keeps the intermediate state of a pass in its
+ * window slot; its first step runs alone (it also copies its input).  A tile
+ * holds one extraction point, and up to 64 in all count as one where they are
+ * equal: runs with a series take tile heights that part their points, and
+ * where none does, or with a tile of the caller's that does not, fewer steps a
+ * pass, down to single steps with launches of their own for the samples.
  * The tile rows of teuk_set_tile apply (until it is called, the passes
  * take heights of their own); at most 4 wavefronts per workgroup are
  * used.  Where the small-grid block pass is on (teuk_set_block_launch),
@@ -319,7 +323,7 @@ int teuk_step_n_store(teuk_grid* g, int64_t n, void* d_series, void* d_window);
 /* Device bytes for teuk_enable_adjoint (256-byte aligned, caller-allocated). */
 size_t teuk_adjoint_workspace_bytes(teuk_grid* g);
 
-/* Build the a-derivative tables (dual numbers on the host) and attach the
+/* Build the a-derivative tables (dual numbers, on the device) and attach the
  * adjoint workspace.  KERR mode only.  Synchronous. */
 int teuk_enable_adjoint(teuk_grid* g, void* d_adj_workspace, size_t bytes);
 

@@ -17,9 +17,6 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-ffp-contract=on",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
-# Per-source flags (none at present).
-SOURCE_FLAGS = {}
-
 
 def _run(cmd):
     print("+", " ".join(cmd), flush=True)
@@ -33,9 +30,9 @@ def _run(cmd):
 
 
 def build(extra=(), out=None, source_flags=None):
-    """Compile every source to an object (its own flags), link the library."""
+    """Compile every source to an object (source_flags: {source: its own flags}), link the library."""
     lib = out or LIB
-    per = SOURCE_FLAGS if source_flags is None else source_flags
+    per = source_flags or {}
     objs = []
     for s in SOURCES:
         obj = f"{lib}.{os.path.splitext(s)[0]}.o"

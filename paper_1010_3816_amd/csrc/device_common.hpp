@@ -80,7 +80,8 @@ struct Sig {
 // Workgroups are dispatched round-robin over the 8 XCDs; map them so that
 // each XCD (own L2) receives a contiguous range of tiles, i.e. neighbouring
 // strips whose halo columns overlap.  Used by the adjoint kernels (measured
-// slightly faster with it); the forward passes keep dispatch order.
+// slightly faster with it); the forward passes take dispatch order or, from 64
+// strips on, runs of strips (kTileOrder*).
 __device__ __forceinline__ int xcd_block(int b, int nb) {
     constexpr int X = 8;
     const int x = b % X, idx = b / X, per = nb / X, rem = nb % X;
@@ -347,7 +348,5 @@ __device__ __forceinline__ cd stage2_late(double b, double tr, double ti, double
     return {r, i};
 }
 
-// All pointers are distinct allocations (restrict): the uniform reads of
-// the angular tables and extraction descriptors become scalar loads.
 }  // namespace
 }  // namespace teuk

@@ -77,7 +77,7 @@ struct StepScalars {
     int32_t pad_;
     int64_t row0;               // block pass: series row of the launch's first input state (-1: not sampled)
     int64_t plane;              // nth * pitch: offset of the Pi plane in a state
-    double dt, hdt, dt_dr, hdt_dr;
+    double hdt, dt_dr, hdt_dr;
     double qdt;                 // dt / 4
     double kap_h, kap_i;        // 1 over the factor of ct: 2 / dt (half points), 4 / dt (columns)
     double inv_dth2, inv_2dth;  // USER mode scalings
@@ -153,8 +153,7 @@ struct AdjScalars {
     int32_t n_ext;                           // extraction points (fused transposed extraction)
     int32_t keep;                            // 1: lam_out and the tangent step's state with ordinary stores
                                              // (selects the kernel instance)
-    double dt, hdt, dt_dr, hdt_dr;
-    double qdt, kap_h, kap_i;                // as in StepScalars
+    double hdt, qdt, kap_h, kap_i;           // as in StepScalars
 };
 
 struct AdjArgs {
@@ -195,7 +194,7 @@ constexpr int kMaxBlockSteps = 31;  // (64 columns - 2) / 2
 hipError_t launch_block(const StepArgs& a, hipStream_t s);
 // Tile pass (Kerr coefficients): k.bsteps steps in one launch on register
 // tiles of `cols` (16, 32 or 64) columns, `rows` (1 to 3) rows a lane and
-// `waves` wavefronts a workgroup (at most 16, 12 or 8 for 1, 2 or 3 rows).  A
+// `waves` wavefronts a workgroup (at most 16 with one row a lane, 8 with more).  A
 // tile of one row a lane may hold all rows of the grid; otherwise the grid
 // has more rows than a tile and a tile more than 2 x bsteps.  a.series as for
 // launch_block, at most kMaxBlockExt points.

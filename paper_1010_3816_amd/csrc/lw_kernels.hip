@@ -401,8 +401,8 @@ __device__ __forceinline__ void pass_tile(const double2* __restrict__ u_in, doub
                               (gout_t)win, (lds_t)(rad_s + (threadIdx.x / kWave) * kSliceDoubles), A, strip, chunk, lane, (gin_t)src_i, (gin_t)src_h);
 }
 
-// Two wavefronts to a SIMD bar three steps with a source: its rows take 313
-// registers and would spill 60 at two.  One alone is as fast as two where
+// Two wavefronts to a SIMD bar three steps with a source: its rows take 317
+// registers (5 more spilled) and would spill 60 at two.  One alone is as fast as two where
 // the grid has only that many tiles, and saves a third of the state's traffic
 // (us per step in pairs and in threes: 3200 x 128 7.65 and 7.0, 5003 x 197
 // 12.2 and 12.4, 6400 x 256 17.0 and 15.4, 12800 x 256 30.8 and 30.9,
@@ -583,8 +583,8 @@ __global__ void __launch_bounds__(1024)
 // 6.9 -> 3.0, 1200 x 100 5.2 (sweeps of three steps) -> 2.0, 3200 x 128 5.9 ->
 // 5.2; 5003 x 197 would take 11 against the sweeps' 9.
 //
-// T: most threads a workgroup may have (registers: 128, 160, 256 a lane for
-// one, two, three rows).
+// T: most threads a workgroup may have: 1024 with one row a lane (at most 128
+// registers; 100 used), 512 with two (256; 174) or three (244).
 template <int C, int R, int T, int KEEP>
 __global__ void __launch_bounds__(T)
     lw_tile_kernel(const double2* __restrict__ u_in, double2* __restrict__ u_out, const double* __restrict__ rad,
@@ -755,7 +755,8 @@ __global__ void zero_ints_kernel(int* p, int n) {
 // wavefront walks the list with a grid-wide stride.  All tiles have the
 // same shape (64 - 2K columns x `rows` rows, ragged only at a member's edges),
 // so the static stride balances uneven members.  `parity` selects which of
-// each member's two state buffers is the input.
+// each member's two state buffers is the input.  Three steps take 247 registers;
+// 22 scalar registers, the member's pointers and scalars, are spilled into lanes.
 template <int K, int KEEP>
 __device__ __forceinline__ void batch_tiles(const BatchMember* __restrict__ members, int n_members, int total_tiles,
                                             int parity, const BatchSeries& S, double* rad_s) {

@@ -362,7 +362,6 @@ StepArgs step_args(const teuk_grid* g) {
     k.sigma = g->sigma;
     k.rows = g->rows;
     k.n_chunks = (k.nth + g->rows - 1) / g->rows;
-    k.dt = g->p.dt;
     k.hdt = 0.5 * g->p.dt;
     k.qdt = 0.25 * g->p.dt;
     k.kap_h = finite_inverse(k.hdt);
@@ -1489,10 +1488,7 @@ AdjArgs adjoint_args(const teuk_grid* g, AdjKind kind) {
     a.k.zero = 0;
     a.k.keep = keeps_states(g) ? 1 : 0;
     a.k.plane = (int64_t)nth * g->L.pitch;
-    a.k.dt = g->p.dt;
     a.k.hdt = 0.5 * g->p.dt;
-    a.k.dt_dr = g->p.dt / g->dr;
-    a.k.hdt_dr = 0.5 * g->p.dt / g->dr;
     a.rad = g->at<double>(g->L.off_rad);
     a.rad_da = reinterpret_cast<const double*>(g->aws + g->aoff_da);
     a.k.qdt = 0.25 * g->p.dt;
