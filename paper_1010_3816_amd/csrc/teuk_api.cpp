@@ -254,8 +254,8 @@ struct teuk_grid {
     char* aws = nullptr;      // adjoint workspace
     size_t aoff_lam[2]{}, aoff_da = 0, aoff_slots = 0, aoff_sum = 0;
     int adj_rows = 32, adj_wpb = kAdjWaves, adj_strips = 0;  // the tile as teuk_get_adjoint_tile reports it
-    int adj_pass_rows[kAdjKinds] = {};               // the kernels' heights, and as teuk_init_grid chose them
-    int default_adj_rows = 0, default_adj_pass_rows[kAdjKinds] = {};
+    int adj_pass_rows[kAdjKinds] = {}, adj_pass_wpb[kAdjKinds] = {};  // the kernels' tiles, and as teuk_init_grid chose them
+    int default_adj_rows = 0, default_adj_pass_rows[kAdjKinds] = {}, default_adj_pass_wpb[kAdjKinds] = {};
     TileShape adj_tile;       // adjoint tile pass: shape and steps per launch (0: off)
     int adj_tile_steps = 0;
     bool adj_default = true;  // the adjoint tile is as teuk_init_grid chose it
@@ -827,9 +827,17 @@ int teuk_init_grid(const teuk_params* p, void* hip_stream, void* d_workspace, si
     // The adjoint tile as it is reported; the kernels take heights of their own
     // until teuk_set_adjoint_tile.
     g->adj_rows = adjoint_rows(nr, nth, (int64_t)cus * 7, kStripCols);
-    for (int i = 0; i < kAdjKinds; ++i)
-        g->adj_pass_rows[i] = g->default_adj_pass_rows[i] =
-            sweep_rows(nr, nth, cus, kAdjoint[i], i == kAdjTwo ? &sweep_us : nullptr);
+    // (Wavefronts whose lanes hold their own factors go one to a workgroup while
+    // there are few, the others share the workgroup's tables: us per step with
+    // four and one, the step that stores its tangent 200 x 16 5.8 and 4.7, 400 x 32
+    // 6.0 and 4.9; one cotangent step 5.4 and 4.7; with the spin gradient from
+    // states 8.6 and 11.8.)
+    for (int i = 0; i < kAdjKinds; ++i) {
+        const int r = sweep_rows(nr, nth, cus, kAdjoint[i], i == kAdjTwo ? &sweep_us : nullptr);
+        const bool own = i == kAdjOne || i == kAdjTangent;
+        g->adj_pass_rows[i] = g->default_adj_pass_rows[i] = r;
+        g->adj_pass_wpb[i] = g->default_adj_pass_wpb[i] = own ? sweep_waves(nr, nth, cus, kAdjoint[i].steps, r) : kAdjWaves;
+    }
     g->default_adj_rows = g->adj_rows;
     // (the adjoint tile pass: 1.17 times the forward one's instructions.  us per
     // step, tile pass and sweeps: 2000 x 256 7.2 and 8.1, 12000 x 64 10.3 and 9.9,
@@ -1370,7 +1378,10 @@ int teuk_set_adjoint_tile(teuk_grid* g, int32_t rows_per_tile, int32_t waves_per
     g->adj_wpb = waves_per_block;
     // the tile as teuk_init_grid chose it: the kernels' own heights and the tile pass again
     g->adj_default = rows_per_tile == g->default_adj_rows && waves_per_block == kAdjWaves;
-    for (int i = 0; i < kAdjKinds; ++i) g->adj_pass_rows[i] = g->adj_default ? g->default_adj_pass_rows[i] : rows_per_tile;
+    for (int i = 0; i < kAdjKinds; ++i) {
+        g->adj_pass_rows[i] = g->adj_default ? g->default_adj_pass_rows[i] : rows_per_tile;
+        g->adj_pass_wpb[i] = g->adj_default ? g->default_adj_pass_wpb[i] : waves_per_block;
+    }
     update_fusion(g);
     return TEUK_OK;
 }
@@ -1393,13 +1404,14 @@ int teuk_get_pass(const teuk_grid* g, int32_t run, teuk_pass* out) {
     if (run == TEUK_RUN_COTANGENTS) {
         if (adjoint_on_tiles(g)) return tile(g->adj_tile, g->adj_tile_steps);
         const bool two = fused_adjoint_ok(g) && g->steps_per_pass == 2;
-        const int steps = two ? 2 : 1;
-        *out = {TEUK_PASS_SWEEP, steps, strip_cols(steps), g->adj_pass_rows[two ? kAdjTwo : kAdjOne], g->adj_wpb,
+        const AdjKind kind = two ? kAdjTwo : kAdjOne;
+        const int steps = kAdjoint[kind].steps;
+        *out = {TEUK_PASS_SWEEP, steps, strip_cols(steps), g->adj_pass_rows[kind], g->adj_pass_wpb[kind],
                 fused_adjoint_ok(g)};
         return TEUK_OK;
     }
     if (run == TEUK_RUN_SPIN_TANGENT) {
-        *out = {TEUK_PASS_SWEEP, 1, kStripCols, g->tan_sample_rows, g->adj_wpb, g->tan_fused};
+        *out = {TEUK_PASS_SWEEP, 1, kStripCols, g->tan_sample_rows, g->adj_pass_wpb[kAdjSpinTangent], g->tan_fused};
         return TEUK_OK;
     }
     const bool series = run == TEUK_RUN_SERIES || run == TEUK_RUN_SOURCE_SERIES;
@@ -1514,7 +1526,7 @@ int teuk_step_n_tangent(teuk_grid* g, int64_t n, void* d_window) {
     char* win = static_cast<char*>(d_window);
     for (int64_t k = 0; k < n; ++k) {
         double2* t_out = reinterpret_cast<double2*>(win + (size_t)k * g->L.state);
-        HIP_TRY(launch_tangent(g->u(g->cur), g->u(1 - g->cur), t_out, a, g->adj_wpb, g->stream));
+        HIP_TRY(launch_tangent(g->u(g->cur), g->u(1 - g->cur), t_out, a, g->adj_pass_wpb[kAdjTangent], g->stream));
         g->cur = 1 - g->cur;
         g->steps += 1;
     }
@@ -1549,8 +1561,8 @@ int adjoint_impl(teuk_grid* g, int64_t n, void* d_lam_phi, void* d_lam_pi, const
     auto lam = [&](int k) { return reinterpret_cast<double2*>(g->aws + g->aoff_lam[k]); };
     double* slots = reinterpret_cast<double*>(g->aws + g->aoff_slots);
     double* sum = reinterpret_cast<double*>(g->aws + g->aoff_sum);
-    AdjArgs a = adjoint_args(g, spin && !tangent ? kAdjStates : kAdjOne);
-    AdjArgs a2 = adjoint_args(g, tangent ? kAdjTwoDot : kAdjTwo);
+    const AdjKind one = spin && !tangent ? kAdjStates : kAdjOne, two = tangent ? kAdjTwoDot : kAdjTwo;
+    AdjArgs a = adjoint_args(g, one), a2 = adjoint_args(g, two);
     const int nslots = std::max(a.k.n_strips * a.k.n_chunks, a2.k.n_strips * a2.k.n_chunks);
 
     int c = 0;
@@ -1593,7 +1605,7 @@ int adjoint_impl(teuk_grid* g, int64_t n, void* d_lam_phi, void* d_lam_pi, const
             a2.u_in = tangent ? slot(k) : nullptr;
             a2.gsample = gs ? reinterpret_cast<const double*>(gs + (k - 1) * ne) : nullptr;
             const double* gb = (gs && k >= 2) ? reinterpret_cast<const double*>(gs + (k - 2) * ne) : nullptr;
-            HIP_TRY(launch_adjoint2(a2, gb, tangent ? slot(k - 1) : nullptr, g->adj_wpb, s));
+            HIP_TRY(launch_adjoint2(a2, gb, tangent ? slot(k - 1) : nullptr, g->adj_pass_wpb[two], s));
             c = 1 - c;
         }
     }
@@ -1603,7 +1615,7 @@ int adjoint_impl(teuk_grid* g, int64_t n, void* d_lam_phi, void* d_lam_pi, const
         a.u_in = spin ? slot(k) : nullptr;
         a.lam_out = lam(1 - c);
         a.gsample = (gs && k >= 1 && fused) ? reinterpret_cast<const double*>(gs + (k - 1) * ne) : nullptr;
-        HIP_TRY(launch_adjoint(a, g->adj_wpb, mode, s));
+        HIP_TRY(launch_adjoint(a, g->adj_pass_wpb[one], mode, s));
         c = 1 - c;
         if (gs && k >= 1 && !fused) HIP_TRY(launch_extract_adjoint(lam(c), P, ext, ne, gs + (k - 1) * ne, s));
     }
@@ -1718,7 +1730,7 @@ int teuk_step_n_spin_tangent(teuk_grid* g, int64_t n, void* d_series, void* d_ts
         double2* su = (series && fused && k > 0) ? series + (k - 1) * ne : nullptr;
         double2* sv = (tseries && fused && k > 0) ? tseries + (k - 1) * ne : nullptr;
         HIP_TRY(launch_spin_tangent(g->u(g->cur), g->v(g->vcur), g->u(1 - g->cur), g->v(1 - g->vcur), su, sv, a,
-                                    g->adj_wpb, g->stream));
+                                    g->adj_pass_wpb[kAdjSpinTangent], g->stream));
         g->cur = 1 - g->cur;
         g->vcur = 1 - g->vcur;
         g->steps += 1;
