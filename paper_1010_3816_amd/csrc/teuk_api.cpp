@@ -43,6 +43,7 @@ int fail(int code, const char* fmt, ...) {
 
 constexpr size_t kAlign = 256;
 constexpr int kMaxExtract = 4096;
+constexpr int64_t kMaxSingleUserSource = 300000;  // points of a grid with user coefficients and a source
 constexpr int kMaxFusedAdjointExtract = 16;  // extraction points handled inside the adjoint kernel
 // Most points of a grid whose equal ones count as one in a tile.  Every
 // wavefront looks through all points at its start, 80 ns each: with samples
@@ -967,7 +968,12 @@ RunPlan run_plan(const teuk_grid* g, bool series, bool source, bool window) {
     p.tile = in_launch && multi && g->tile_steps > 0 && g->default_launch && g->check_every == 0;
     p.block = in_launch && g->block_steps > 0;
     const int most = series ? g->sample_steps[source] : kMaxPassSteps;
-    p.two = multi && most >= 2 && (!series || g->fused[1]);
+    // user coefficients and a source at once leave the two-step pass no registers
+    // to load them ahead: single steps on small grids (us per step, pairs and
+    // single: 800 x 48 9.1 and 6.1, 1200 x 100 14.0 and 12.3, 1600 x 128 15.1 and
+    // 13.8, 3200 x 128 18.5 and 19.1, 6400 x 256 53 and 75)
+    const bool single = !kerr && source && g->p.nr * g->p.ntheta <= kMaxSingleUserSource;
+    p.two = multi && most >= 2 && !single && (!series || g->fused[1]);
     p.three = multi && most == 3 && kerr && !window && g->p.ntheta >= 3 && g->check_every == 0;
     p.fused1 = g->fused[0];
     return p;

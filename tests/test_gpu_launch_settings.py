@@ -63,3 +63,12 @@ def test_adjoint_tile_set_as_it_was(gpu, nr, nth):
     g.set_adjoint_tile(*tile)
     assert _passes(g) == before
     g.close()
+
+
+def test_user_coefficients_with_a_source(gpu):
+    """Both at once: single steps on small grids, where pairs wait for the
+    coefficients on every row; pairs on large ones and without a source."""
+    for nr, nth, steps in ((800, 48, 1), (6400, 256, 2)):
+        g = gpu.TeukGrid(0.5, -2, 2, nr, nth, -50.0, 150.0, 0.001, coef_mode=gpu.TEUK_COEF_USER)
+        assert g.get_pass("source")["steps"] == steps and g.get_pass("steps")["steps"] == 2
+        g.close()
