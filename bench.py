@@ -58,7 +58,7 @@ SOURCE_BYTES_PER_UPDATE = (BYTES_PER_POINT_PASS + 32) / 3
 # loop, and vector ALU instructions of whole launches (SQ counters; halo
 # lanes and rows included)
 FLOPS_PER_UPDATE = {1: 178, 3: 131}
-VALU_PER_UPDATE = {1: 149, 3: 125}
+VALU_PER_UPDATE = {1: 146, 3: 125}
 # vector instruction issue peak: 256 CUs x 4 SIMDs x 2.4 GHz, one wave64 instruction per 4 cycles per SIMD
 VALU_PEAK_T = 256 * 4 * 2.4e9 * 64 / 4 / 1e12
 KERNEL_SRCS = [os.path.join(ROOT, "paper_1010_3816_amd", "csrc", f)
