@@ -4,6 +4,7 @@ import json
 import types
 
 import pytest
+import torch  # noqa: F401  (before the library: both have to find one HIP runtime)
 
 from paper_1010_3816_amd import autotune, binding
 
